@@ -1,5 +1,6 @@
-"""The exact product at the edges of its kernel's tiles (16 or 32 targets per workgroup, source tiles of 1024 rows in
-runs of 32) against fp64 sums formed with numpy."""
+"""The exact products.  direct_kmvm at the edges of its kernel's tiles (16 or 32 targets per workgroup, source tiles of 1024 rows in
+runs of 32) against fp64 sums formed with numpy;
+direct_kmvm_xy_rows_f64 where its tiles (64, 128 or 256 rows, 256 sources), slices and exponentials end."""
 import numpy as np
 import pytest
 import torch
@@ -31,3 +32,32 @@ def test_direct_at_tile_edges(nx, ny, D):
     # of a running sum of 32 terms
     bound = 2.0 ** -24 * (((D + 3) * k * np.abs(e) + 35.0 * k) @ np.abs(bh)) + 1e-30
     assert np.all(np.abs(y[rows] - want) <= bound)
+
+
+@pytest.mark.parametrize("m,ny,D,gamma", [(1, 1, 3, 0.5), (63, 255, 1, 0.3), (65, 257, 2, 0.02), (256, 4095, 3, 0.4),
+                                          (257, 8193, 4, 0.6), (2048, 3000, 7, 1.0), (2049, 12289, 3, 0.3)])
+def test_fp64_rows_at_tile_edges(m, ny, D, gamma):
+    print("direct_kmvm_xy_rows_f64 m=%d ny=%d D=%d gamma=%g" % (m, ny, D, gamma), flush=True)
+    X = inputs.points_uniform(3000, D, 21, device=DEV)
+    Y = inputs.points_normal(ny, D, 22, device=DEV)
+    b = inputs.rhs_normal(ny, 23, device=DEV)
+    rows = inputs.sample_rows(3000, m, 24).to(DEV)
+    y = f3m.direct_kmvm_xy_rows_f64(X, Y, b, gamma, rows).cpu().numpy()
+    at = np.unique(np.concatenate([np.arange(min(m, 30)), np.arange(max(0, m - 30), m)]))
+    Xr = X[rows].cpu().numpy().astype(np.float64)[at]
+    Yh, bh = Y.cpu().numpy().astype(np.float64), b.cpu().numpy().astype(np.float64)
+    g = float(np.float32(gamma))
+    e = -((Xr[:, None, :] - Yh[None, :, :]) ** 2).sum(-1) / (2.0 * g * g)
+    k = np.exp(e)
+    # fp64 rounding of the exponent on both sides, of the exponential and of the sum (ny / slices terms in a row, at
+    # most 4096 + 64); denormal kernel values are exact to 2^-1074 each
+    bound = 2.0 ** -53 * ((2 * (D + 3) * k * np.abs(e) + 4200.0 * k) @ np.abs(bh)) + 2.0 ** -1073 * ny * np.abs(bh).max()
+    assert np.all(np.abs(y[at] - k @ bh) <= bound)
+
+
+def test_fp64_rows_of_far_points_are_exactly_zero():
+    # exponents far below the smallest fp64 number, and beyond what a 32-bit power of two can hold
+    X = torch.tensor([[0.0, 0.0, 0.0], [1e18, 0.0, 0.0]], device=DEV)
+    Y = torch.tensor([[50.0, 0.0, 0.0], [1e15, 1e15, 0.0]], device=DEV)
+    y = f3m.direct_kmvm_xy_rows_f64(X, Y, torch.ones(2, device=DEV), 1e-3, torch.arange(2)).cpu().numpy()
+    assert np.all(y == 0.0)
