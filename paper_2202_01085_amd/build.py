@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libf3m.so")
 RATES = os.path.join(HERE, "f3m_rates")
-SOURCES = ["api.hip", "plan.hip", "kmvm.hip", "m2l.hip", "solve.hip", "pool.hip", "route.hip"]
+SOURCES = ["api.hip", "plan.hip", "kmvm.hip", "m2l.hip", "solve.hip", "pool.hip", "route.hip", "points.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed FP32 instructions are not to be generated on the test machines
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -343,7 +343,7 @@ f3m_status f3m_plan_get_list(const f3m_plan_t *plan, int level, int kind, uint64
             return;
         }
         copy_to_host(row_ptr_host, kind ? lv.far_ptr.p : lv.near_ptr.p, (size_t)lv.nb + 1);
-        if (kind && lv.far_implicit) {
+        if (kind && (lv.far_implicit || lv.far_points)) {
             // this depth keeps only the lengths of its far rows
             f3m::DevBuf<uint32_t> cols;
             cols.alloc((size_t)lv.far_sz);

@@ -2310,7 +2310,7 @@ static KronShape kron_shape(const f3m_plan_s &P, int level) {
 void build_far_orders(f3m_plan_s &P, hipStream_t st) {
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
-        if (lv.far_sz == 0 || lv.p == 0 || lv.far_implicit || lv.r / lv.p <= 32) continue;
+        if (lv.far_sz == 0 || lv.p == 0 || lv.far_implicit || lv.far_points || lv.r / lv.p <= 32) continue;
         lv.far_ord.alloc((size_t)lv.far_sz, &P.bytes);
         far_order_kernel<<<grid_for(lv.nb), dim3(FO_NT), 0, st>>>(lv.far_ptr.p, lv.far_col.p, P.slev(l).cell.p, P.D, l, lv.nb,
                                                                 lv.far_ord.p);
@@ -2337,7 +2337,7 @@ void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
             lv.gtab_omax = 3;
         }
         const int ndim = lv.far_implicit ? 1 : P.D;
-        if (!lv.far_implicit && lv.r / p <= 32) {
+        if (!lv.far_implicit && !lv.far_points && lv.r / p <= 32) {
             // m2l_kron_small_kernel stages the factor tables of the depth in LDS beside its far-pair buffers
             const size_t lds = (size_t)((64 / (lv.r / p)) * lv.r + P.D * S.no * p * p) * sizeof(float);
             if (lds > 64 * 1024)
@@ -2626,6 +2626,14 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         hipEvent_t *ev = level_events(l);
         const CentreArg C = make_centre(P, l);          // target grid
         F3M_HIP(hipEventRecord(ev[0], st));
+        if (lv.far_points) {   // from point to point: no node weights or potentials
+            const KronShape KS = kron_shape(P, l);
+            F3M_HIP(hipEventRecord(ev[1], st));
+            F3M_HIP(hipEventRecord(ev[2], st));
+            run_far_points(P, l, bs, P.ys.p, KS.omin[0], KS.no, st);
+            for (int k = 3; k < 6; ++k) F3M_HIP(hipEventRecord(ev[k], st));
+            continue;
+        }
         p2m_depth(l);
         F3M_HIP(hipEventRecord(ev[1], st));
         F3M_HIP(hipEventRecord(ev[2], st));

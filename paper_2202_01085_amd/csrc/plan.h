@@ -37,6 +37,12 @@ struct f3m_level {
     // ... and, without a small field, per box of the depth ABOVE: the rank of the candidate at each of the 216
     // positions of the grid around it and its child of each parity (~0: none)
     f3m::DevBuf<uint32_t> st_cand, st_child;
+    // boxes with few points, more than three dimensions: the far field of the depth goes from point to point
+    // (points.hip), by runs of targets of the boxes of the depth ABOVE; far_col stays empty
+    bool far_points = false;
+    f3m::DevBuf<float> fp_loc;                         // [n][8] local coordinates and child bits of every point
+    int64_t fp_ntiles = 0;
+    f3m::DevBuf<uint32_t> fp_tile_box, fp_tile_first;
     // Sec. 4.3: nodes per dimension used at this depth (interp_nodes, 3 under the adaptive rule, or 0 =
     // the far pairs of the depth are dropped), r = p^D, and whether every pair of the depth is interpolated
     int p = 0, r = 0;
@@ -201,6 +207,12 @@ void build_far_orders(f3m_plan_s &P, hipStream_t st);           // far rows in r
 // solve.hip: conjugate gradients for (K + lambda I) x = b on a one-set plan (synchronises)
 void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter, float tol, int *iters_host,
             float *history_host, hipStream_t st);
+// points.hip: the far field of a depth between points
+constexpr int FP_TT = 16;                                                        // targets of a workgroup
+bool far_points_allowed(const f3m_plan_s &P, int level);
+bool far_points_pays(const f3m_plan_s &P, int level, int64_t point_pairs);       // point pairs of the near boxes one depth up
+void far_points_prepare(f3m_plan_s &P, int level, hipStream_t st);
+void run_far_points(f3m_plan_s &P, int level, const float *bs, float *ys, int omin, int no, hipStream_t st);
 // m2l.hip
 bool m2l_stencil_applies(const f3m_plan_s &P);
 void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);

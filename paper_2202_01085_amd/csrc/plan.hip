@@ -1127,6 +1127,11 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                 // parent): only the row lengths are kept
                 lv.far_implicit = true;
                 lv.far_col.alloc(0, tally);
+            } else if (tf > 0 && far_points_allowed(P, l)) {
+                ScanState S;
+                scan_prepare(NearPairsIn{up.start.p, up.start.p, up.near_ptr.p, up.near_col.p}, up.nb, S, true, st);
+                lv.far_points = far_points_pays(P, l, (int64_t)S.total);
+                lv.far_col.alloc(lv.far_points ? 0 : (size_t)tf, tally);
             } else {
                 lv.far_col.alloc((size_t)tf, tally);
             }
@@ -1134,7 +1139,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             A.far_ptr = lv.far_ptr.p;
             A.small_ptr = lv.small_ptr.p;
             A.near_col = lv.near_col.p;
-            A.far_col = lv.far_implicit ? nullptr : lv.far_col.p;
+            A.far_col = lv.far_implicit || lv.far_points ? nullptr : lv.far_col.p;
             A.small_col = lv.small_col.p;
             if constexpr (D == 3) {
                 // the tables of the candidate-grid M2L come out of the same enumeration
@@ -1192,6 +1197,12 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     for (int k = 1; k <= P.L; ++k) {
         f3m_level &lv = P.lev[k];
         if (lv.far_sz == 0 || lv.p == 0) continue;   // nothing to interpolate, or dropped
+        if (lv.far_points) {
+            far_points_prepare(P, k, st);
+            const f3m_level &up = P.lev[k - 1];
+            build_chunks(up.start.p, up.nb, FP_TT, lv.fp_tile_first, lv.fp_tile_box, lv.fp_ntiles, tally, st);
+            continue;
+        }
         const bool tree = P.tree_lmin > 0 && k >= P.tree_lmin && k <= P.tree_lmax;
         f3m_level &sv = P.slev(k);
         if (tree) {
@@ -1338,7 +1349,7 @@ void compute_far_point_pairs(f3m_plan_s &P) {
         }
         lv.far_point_pairs = 0;
         if (lv.far_sz == 0) continue;
-        if (lv.far_implicit) {
+        if (lv.far_implicit || lv.far_points) {
             DevBuf<uint32_t> cols;
             cols.alloc((size_t)lv.far_sz);
             materialize_far(P, l, cols.p, nullptr);
