@@ -248,12 +248,18 @@ def main():
     level_runs.append({l: plan.level_times(l) for l in range(1, L + 1)})
     st = {key: median([run[key] for run in stage_runs]) for key in stage_runs[0]}
     level_ms = {l: tuple(median([run[l][j] for run in level_runs]) for j in range(3)) for l in range(1, L + 1)}
-    far_L = int(inf.far_pairs[L])
-    r = inf.nodes_per_box
-    m2l_ms = level_ms[L][1] if L >= 1 else 0.0
-    D = cfg["D"]
+    # the last depth the product worked at: above the last depth of the tree where the pairs left at it are all
+    # interpolated to within fp32 rounding (then there is no near field)
+    Lw = max([l for l in range(1, L + 1) if level_ms[l][1] > 0 and int(inf.far_pairs[l]) > 0], default=L)
     pairs = int(inf.near_point_pairs)
-    nb_L = int(inf.nboxes[L])
+    if pairs > 2e13 * st["p2p"] * 1e-3:     # more than one exponential per pair allows: the pairs were interpolated
+        pairs = 0
+    near_interpolated = pairs == 0 and L >= 1 and int(inf.near_pairs[L]) > 0
+    far_L = int(inf.far_pairs[Lw]) + (int(inf.near_pairs[Lw]) if near_interpolated else 0)
+    r = inf.nodes_per_box
+    m2l_ms = level_ms[Lw][1] if L >= 1 else 0.0
+    D = cfg["D"]
+    nb_L = int(inf.nboxes[Lw])
     tag = ("xy_n%d" % n) if args.xy else "config%d_n%d" % (k, n)
     traffic, issue, counters_note = load_counters(tag)
     rates = None
@@ -282,12 +288,12 @@ def main():
         hbm_stage("gather_x", "gather of the points into box order: 4 + 8D B/pt", (4.0 + 8.0 * D) * n, st["gather"])
         hbm_stage("permute_in", "right-hand side into box order: 12 B/pt", 12.0 * ns, st["permute_in"])
         hbm_stage("permute_out", "result back to the caller's order: 12 B/pt", 12.0 * n, st["permute_out"])
-        if L >= 1 and level_ms[L][0] > 0:
-            hbm_stage("p2m_leaf", "P2M at depth %d: 4(D+1) B/pt + 4r B/box" % L, 4.0 * (D + 1) * ns + 4.0 * r * nb_L,
-                      level_ms[L][0])
-        if L >= 1 and level_ms[L][2] > 0:
-            hbm_stage("l2p_leaf", "L2P at depth %d: (4D+8) B/pt + 4r B/box" % L, (4.0 * D + 8) * n + 4.0 * r * nb_L,
-                      level_ms[L][2])
+        if L >= 1 and level_ms[Lw][0] > 0:
+            hbm_stage("p2m_leaf", "P2M at depth %d: 4(D+1) B/pt + 4r B/box" % Lw, 4.0 * (D + 1) * ns + 4.0 * r * nb_L,
+                      level_ms[Lw][0])
+        if L >= 1 and level_ms[Lw][2] > 0:
+            hbm_stage("l2p_leaf", "L2P at depth %d: (4D+8) B/pt + 4r B/box" % Lw, (4.0 * D + 8) * n + 4.0 * r * nb_L,
+                      level_ms[Lw][2])
     if far_L > 0 and m2l_ms > 0:
         # algorithmic: 2 r^2 flop per far pair (the dense node-to-node product).  For D = 3 with 4 nodes per
         # dimension the kernel applies the Kronecker factors per candidate / line / plane of the 6x6x6 grid around
@@ -297,7 +303,8 @@ def main():
         # `achieved` counts the multiply-adds it executes; `algorithmic_tflops` the dense equivalent.
         t = m2l_ms * 1e-3
         if D == 3 and cfg["p"] == 4 and cfg["theta"] == 2.0 and not args.xy:
-            executed = 2.0 * 117 * 256 * nb_L
+            # (78 where the near pairs of the depth are interpolated too: nothing is taken off the sum over all candidates)
+            executed = 2.0 * (78 if near_interpolated else 117) * 256 * nb_L
             kernel = "m2l_stencil_shared_kernel"
         else:
             executed = 2.0 * D * r * cfg["p"] * far_L
@@ -305,7 +312,7 @@ def main():
                 "m2l_kron_grouped_kernel (shares partial sums between far partners, so it executes fewer than the " \
                 "2 D r p flop per far pair counted here)"
         ach = executed / t / 1e12
-        rooflines["m2l"] = {"kernel": "%s, leaf depth %d, %d far pairs, %d target boxes" % (kernel, L, far_L, nb_L),
+        rooflines["m2l"] = {"kernel": "%s, depth %d, %d pairs of boxes, %d target boxes" % (kernel, Lw, far_L, nb_L),
                             "bound": "alu", "achieved": ach, "peak": PEAK_VALU_F32_TFLOPS, "unit": "TFLOP/s",
                             "frac": ach / PEAK_VALU_F32_TFLOPS, "traffic": traffic.get("m2l"), "launch_ms": m2l_ms,
                             "frac_of_unpacked_fp32_peak": ach / UNPACKED_F32_TFLOPS,
@@ -376,8 +383,10 @@ def main():
                                 % (n, n, cfg["lengthscale"], cfg["p"], cfg["theta"])) if args.xy else
                                "config %d: n=%d D=%d %s, Gaussian lengthscale %g, b~N(0,1), %d nodes/dim, far ratio %g"
                                % (k, n, cfg["D"], cfg["dist"], cfg["lengthscale"], cfg["p"], cfg["theta"]),
-                   "depth": L, "leaf_max": 128, "boxes_leaf": nb_L, "near_pairs_leaf": int(inf.near_pairs[L]),
-                   "far_pairs_leaf": far_L, "device_bytes": int(inf.device_bytes),
+                   "depth": L, "leaf_max": 128, "boxes_leaf": int(inf.nboxes[L]),
+                   "near_pairs_leaf": int(inf.near_pairs[L]), "far_pairs_leaf": int(inf.far_pairs[L]),
+                   "product_depth": Lw, "near_field": "interpolated at depth %d to within fp32 rounding (truncation bound "
+                   "2^-24 of a kernel value)" % Lw if near_interpolated else "exact sums", "device_bytes": int(inf.device_bytes),
                    "eta_smooth": args.eta_smooth, "adaptive_far": bool(args.adaptive_far),
                    "smooth_depth": int(inf.smooth_depth),
                    "arithmetic": "fp32 throughout; the near-field exponents -|x-y|^2/(2 gamma^2) come from one fp16 MFMA on "

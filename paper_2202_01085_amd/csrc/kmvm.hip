@@ -92,12 +92,12 @@ __global__ __launch_bounds__(256) void gather_kernel(const float *__restrict__ b
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k < n) bs[k] = b[perm[k]];
 }
-// y = far-field part + near-field part, back in the caller's order
+// y = far-field part + near-field part (if there is one), back in the caller's order
 __global__ __launch_bounds__(256) void scatter_kernel(const float *__restrict__ ys, const float *__restrict__ yn,
                                                       const uint32_t *__restrict__ perm, int64_t n,
                                                       float *__restrict__ y) {
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k < n) y[perm[k]] = ys[k] + yn[k];
+    if (k < n) y[perm[k]] = yn ? ys[k] + yn[k] : ys[k];
 }
 // the same two steps for a caller that keeps its vectors in box order (the solver)
 __global__ __launch_bounds__(256) void copy_kernel(const float *__restrict__ b, int64_t n, float *__restrict__ bs) {
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void copy_kernel(const float *__restrict__ b, 
 __global__ __launch_bounds__(256) void add_kernel(const float *__restrict__ ys, const float *__restrict__ yn, int64_t n,
                                                   float *__restrict__ y) {
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k < n) y[k] = ys[k] + yn[k];
+    if (k < n) y[k] = yn ? ys[k] + yn[k] : ys[k];
 }
 __global__ __launch_bounds__(256) void zero_kernel(float *__restrict__ p, int64_t n) {
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -2323,7 +2323,7 @@ void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
     std::vector<std::vector<float>> host_tabs;
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
-        if (lv.far_sz == 0 || lv.p == 0) continue;
+        if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && l > P.near_depth)) continue;
         const int p = lv.p;
         std::vector<double> s(p);
         for (int k = 0; k < p; ++k) s[k] = p > 1 ? std::cos(M_PI * (double)k / (double)(p - 1)) : 0.0;
@@ -2422,7 +2422,9 @@ template <int D>
 static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, bool box_order,
                        const float *bs_in = nullptr, const float *yn_in = nullptr) {
     const float *bs = bs_in ? bs_in : P.bs.p;
-    const float *yn = yn_in ? yn_in : P.yn.p;
+    // no near field: every pair is interpolated (smooth field, or the products stop above the last depth)
+    const bool no_near = !yn_in && P.rho == 0 && (P.lev[P.L].near_sz == 0 || P.near_depth);
+    const float *yn = yn_in ? yn_in : no_near ? nullptr : P.yn.p;
     const int64_t n = P.n;
     const float nc2 = (float)(-1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma));
     const int nev = 4 + 3 * (P.L + 1);
@@ -2488,8 +2490,8 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                                                                 tile_box, tile_first, ntiles, nc2, P.yn.p, accumulate);
         F3M_HIP(hipGetLastError());
     };
-    if (yn_in) {
-        // computed by the caller
+    if (yn_in || no_near) {
+        // computed by the caller, or nothing to compute
     } else if (leaf.near_sz == 0) {
         // every pair was interpolated (smooth field, Sec. 4.3) or summed at its own depth (small field)
         zero_kernel<<<dim3(gn), dim3(256), 0, sn>>>(P.yn.p, n);
@@ -2620,7 +2622,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
         // no far pairs, dropped by the adaptive rule (Sec. 4.3), or part of the band below
-        if (lv.far_sz == 0 || lv.p == 0 || (tree && l >= P.tree_lmin && l <= P.tree_lmax)) continue;
+        if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && l > P.near_depth) || (tree && l >= P.tree_lmin && l <= P.tree_lmax)) continue;
         const int p = lv.p, r = lv.r;
         const NodeArg N = make_nodes(p);
         hipEvent_t *ev = level_events(l);
@@ -2766,7 +2768,7 @@ void run_kmvm_multi(f3m_plan_s &P, const float *B, int64_t ldb, float *Y, int64_
     const double gl = 1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma) * CL.edge * CL.edge;
     // the conditions under which the single product uses the plain D = 3 Gram kernel for its near field
     const bool fused = m > 1 && P.D == 3 && gl * 3.0 <= 6.0 && gl > 1e-30 && !P.force_all_near && P.T <= 1024 &&
-                       !(P.src && P.L == 0) && P.rho == 0 && leaf.near_sz > 0 && P.ntiles >= 8192;
+                       !(P.src && P.L == 0) && P.rho == 0 && leaf.near_sz > 0 && !P.near_depth && P.ntiles >= 8192;
     if (!fused) {
         for (int j = 0; j < m; ++j) run_kmvm(P, B + (int64_t)j * ldb, Y + (int64_t)j * ldy, st);
         return;

@@ -442,7 +442,7 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
 // candidate and child tables of a depth whose M2L runs on the candidate grid without a small field
 // the tables of a depth, preset to "none"; false: the depth does not use them
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st) {
-    if (!m2l_stencil_applies(P) || level < 1 || P.rho != 0) return false;
+    if (!m2l_stencil_applies(P) || level < 1 || P.rho != 0 || (P.near_depth && level > P.near_depth)) return false;
     f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
     if (!lv.far_implicit || lv.far_sz == 0 || lv.p == 0) return false;
     lv.st_cand.alloc((size_t)up.nb * ST_CAND, &P.bytes);
@@ -466,19 +466,20 @@ bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStre
     f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
     if (lv.gtab.p == nullptr || lv.gtab_omax != 3) return false;
     const int64_t per_xcd = cdiv(up.nb, 8);
+    const int all_far = lv.smooth || level == P.near_depth ? 1 : 0;
     if (lv.st_cand.p) {   // no small field: the variant that shares the line and plane sums between the children
         if (zero_row)   // W carries a row of zeros at index nb
             m2l_stencil_shared_kernel<true><<<grid2(per_xcd * 8), dim3(512), 0, st>>>(
-                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, lv.smooth ? 1 : 0, (uint32_t)lv.nb, W, V);
+                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, all_far, (uint32_t)lv.nb, W, V);
         else
             m2l_stencil_shared_kernel<false><<<grid2(per_xcd * 8), dim3(512), 0, st>>>(
-                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, lv.smooth ? 1 : 0, 0u, W, V);
+                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, all_far, 0u, W, V);
         F3M_HIP(hipGetLastError());
         return true;
     }
     m2l_stencil_kernel<<<grid2(per_xcd * 8), dim3(512), 0, st>>>(up.near_ptr.p, up.near_col.p, up.cstart.p, up.cell.p,
                                                                 lv.cell.p, lv.key.p, up.nb, per_xcd, lv.gtab.p,
-                                                                lv.smooth ? 1 : 0, lv.start.p, (uint32_t)P.rho, W, V);
+                                                                all_far, lv.start.p, (uint32_t)P.rho, W, V);
     F3M_HIP(hipGetLastError());
     return true;
 }

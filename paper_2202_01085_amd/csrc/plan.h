@@ -142,6 +142,8 @@ struct f3m_plan_s {
             u[d] = q * (double)(1ull << level);
         }
     }
+    int near_depth = 0;                 // > 0: the products work down to this depth only, whose adjacent pairs are
+                                        // interpolated too, to within fp32 rounding (near_interp_error)
     int tree_lmin = 0, tree_lmax = 0;   // tree_lmin > 0: node weights/potentials are passed between depths
                                         // tree_lmin..tree_lmax (D = 3, 4 nodes/dim); other depths work
                                         // straight from the points
@@ -173,6 +175,8 @@ constexpr int MAX_NODES = 4096;
 int quant_depth(int D);
 bool smooth_rule(double E, int depth, int D, double gamma, double eta_smooth);   // Sec. 4.3 smoothness criterion
 int adaptive_nodes(double E, int depth, double gamma, int p);                   // Sec. 4.3 node rule (0: dropped)
+
+double near_interp_error(double E, int depth, double gamma);                    // D = 3, 4 nodes per dimension
 
 // plan.hip
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
