@@ -105,7 +105,10 @@ static f3m_status make_plan(const float *X, int64_t n, const float *Y, int64_t n
             P->src->n = ny;
         }
         // with no targets there is nothing to compute, with no sources the product is zero
-        if (n > 0 && (!two_sets || ny > 0)) f3m::build_plan(*P, X, two_sets ? Y : nullptr, (hipStream_t)stream);
+        if (n > 0 && (!two_sets || ny > 0)) {
+            f3m::ReleaseScope scope((hipStream_t)stream);
+            f3m::build_plan(*P, X, two_sets ? Y : nullptr, (hipStream_t)stream);
+        }
     });
     if (st != F3M_OK) {
         delete P;
@@ -240,6 +243,7 @@ int64_t f3m_trim_memory(void) {
 void f3m_destroy(f3m_plan_t *plan) {
     if (!plan) return;
     (void)hipDeviceSynchronize();
+    f3m::ReleaseScope idle;   // one wait for all of its buffers
     delete plan;
 }
 

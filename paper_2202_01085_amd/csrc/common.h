@@ -35,6 +35,25 @@ void *pool_alloc(size_t bytes);
 void pool_free(void *p, size_t bytes);
 size_t pool_trim();
 
+// While a scope is open on a thread, the blocks that the thread releases are not waited for one by one.  A scope of a
+// stream keeps them for the thread's next requests (all work on them is on that stream, so its order protects them)
+// and gives them to the pool after one wait at its end; an idle scope (the device has just been waited for, and the
+// thread launches nothing inside) passes them on at once.  words() of a stream's scope is a small array in pinned
+// host memory that kernels write counts to; the host reads it after a wait for the stream.
+class ReleaseScope {
+public:
+    explicit ReleaseScope(hipStream_t st);   // for work on one stream
+    ReleaseScope() noexcept;                 // idle (no effect inside another scope)
+    ~ReleaseScope();
+    ReleaseScope(const ReleaseScope &) = delete;
+    ReleaseScope &operator=(const ReleaseScope &) = delete;
+
+private:
+    bool owner = false;
+};
+constexpr int HOST_WORDS = 512;
+uint64_t *scope_words();   // of the thread's open scope of a stream
+
 // A device allocation that releases itself; the byte count is added to *tally if given.
 template <class T>
 struct DevBuf {
@@ -158,21 +177,60 @@ __global__ __launch_bounds__(SCAN_NT) void scan_reduce_kernel(In in, int64_t n, 
     if (threadIdx.x == 0) block_sums[blockIdx.x] = tot;
 }
 
+// total (if not null): sum of all inputs, written by the last block
 template <class In, class Out>
-__global__ __launch_bounds__(SCAN_NT) void scan_apply_kernel(In in, int64_t n, const uint64_t *block_offsets, Out out) {
+__global__ __launch_bounds__(SCAN_NT) void scan_apply_kernel(In in, int64_t n, const uint64_t *block_offsets, Out out,
+                                                             uint64_t *total) {
     int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT;
     uint64_t v[SCAN_IPT];
     scan_load(in, base, n, v);
     uint64_t s = 0;
 #pragma unroll
     for (int k = 0; k < SCAN_IPT; ++k) s += v[k];
+    const uint64_t ofs = block_offsets ? block_offsets[blockIdx.x] : 0;
     uint64_t tot;
-    uint64_t ex = block_excl_scan_u64(s, &tot) + (block_offsets ? block_offsets[blockIdx.x] : 0);
+    uint64_t ex = block_excl_scan_u64(s, &tot) + ofs;
+    if (total && blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *total = ofs + tot;
 #pragma unroll
     for (int k = 0; k < SCAN_IPT; ++k) {
         if (base + k < n) out(base + k, ex, v[k]);
         ex += v[k];
     }
+}
+
+// exclusive prefix sum of a short array in place, by one block of 1024 threads with four values each per round
+constexpr int SCAN_SUMS_NT = 1024;
+constexpr int64_t SCAN_SUMS_MAX = 16384;
+static __global__ __launch_bounds__(SCAN_SUMS_NT) void scan_sums_kernel(uint64_t *sums, int64_t n, uint64_t *total) {
+    __shared__ uint64_t wsum[SCAN_SUMS_NT / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t carry = 0;
+    for (int64_t r = 0; r < n; r += 4 * SCAN_SUMS_NT) {
+        const int64_t base = r + 4 * (int64_t)threadIdx.x;
+        uint64_t v[4], s = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = base + k < n ? sums[base + k] : 0;
+            s += v[k];
+        }
+        const uint64_t incl = wave_incl_scan_u64(s, lane);
+        __syncthreads();   // the last round has read wsum
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        uint64_t ex = carry + incl - s;
+#pragma unroll
+        for (int k = 0; k < SCAN_SUMS_NT / 64; ++k) {
+            const uint64_t t = wsum[k];
+            if (k < w) ex += t;
+            carry += t;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (base + k < n) sums[base + k] = ex;
+            ex += v[k];
+        }
+    }
+    if (total && threadIdx.x == 0) *total = carry;
 }
 
 struct ArrayInU64 {
@@ -184,56 +242,73 @@ struct ArrayOutU64 {
     __device__ void operator()(int64_t i, uint64_t ex, uint64_t) const { p[i] = ex; }
 };
 
+// exclusive scan of the block sums in place: one launch while they are few (a plan is a chain of scans of some
+// thousand boxes: it waits for launches, not for memory), else by blocks again
+inline void scan_block_sums(uint64_t *sums, int64_t nblk, uint64_t *total, hipStream_t st) {
+    if (nblk <= SCAN_SUMS_MAX) {
+        scan_sums_kernel<<<dim3(1), dim3(SCAN_SUMS_NT), 0, st>>>(sums, nblk, total);
+    } else {
+        DevBuf<uint64_t> inner;
+        const int64_t nb2 = cdiv(nblk, SCAN_TILE);
+        inner.alloc((size_t)nb2);
+        const ArrayInU64 in{sums};
+        scan_reduce_kernel<<<dim3((unsigned)nb2), dim3(SCAN_NT), 0, st>>>(in, nblk, inner.p);
+        scan_block_sums(inner.p, nb2, nullptr, st);
+        scan_apply_kernel<<<dim3((unsigned)nb2), dim3(SCAN_NT), 0, st>>>(in, nblk, (const uint64_t *)inner.p,
+                                                                        ArrayOutU64{sums}, total);
+    }
+    F3M_HIP(hipGetLastError());
+}
+
 // Exclusive scan of n elements in two host steps, so that the caller can size the output
 // from the grand total before the values are written.
 struct ScanState {
-    DevBuf<uint64_t> sums;  // scanned block sums
+    DevBuf<uint64_t> sums;  // scanned block sums (more than one block)
     int64_t nblk = 0;
     uint64_t total = 0;
 };
 
+// waits for the total (the thread has an open scope of the stream; word 0 of its array is used)
 template <class In>
-void scan_prepare(In in, int64_t n, ScanState &S, bool want_total, hipStream_t st);
+void scan_prepare(In in, int64_t n, ScanState &S, hipStream_t st) {
+    S.total = 0;
+    S.nblk = 0;
+    if (n <= 0) return;
+    uint64_t *total = scope_words();
+    S.nblk = cdiv(n, SCAN_TILE);
+    if (S.nblk == 1) {
+        scan_reduce_kernel<<<dim3(1), dim3(SCAN_NT), 0, st>>>(in, n, total);
+    } else {
+        S.sums.alloc((size_t)S.nblk);
+        scan_reduce_kernel<<<dim3((unsigned)S.nblk), dim3(SCAN_NT), 0, st>>>(in, n, S.sums.p);
+        scan_block_sums(S.sums.p, S.nblk, total, st);
+    }
+    F3M_HIP(hipGetLastError());
+    F3M_HIP(hipStreamSynchronize(st));
+    S.total = *total;
+}
 
 template <class In, class Out>
 void scan_finish(In in, int64_t n, ScanState &S, Out out, hipStream_t st) {
     if (n <= 0) return;
-    scan_apply_kernel<<<dim3((unsigned)S.nblk), dim3(SCAN_NT), 0, st>>>(in, n, (const uint64_t *)S.sums.p, out);
+    scan_apply_kernel<<<dim3((unsigned)S.nblk), dim3(SCAN_NT), 0, st>>>(in, n, (const uint64_t *)S.sums.p, out,
+                                                                       (uint64_t *)nullptr);
     F3M_HIP(hipGetLastError());
 }
 
-template <class In>
-void scan_prepare(In in, int64_t n, ScanState &S, bool want_total, hipStream_t st) {
-    S.total = 0;
-    S.nblk = 0;
-    if (n <= 0) return;
-    S.nblk = cdiv(n, SCAN_TILE);
-    S.sums.alloc((size_t)S.nblk + 1);
-    scan_reduce_kernel<<<dim3((unsigned)S.nblk), dim3(SCAN_NT), 0, st>>>(in, n, S.sums.p);
-    F3M_HIP(hipGetLastError());
-    if (S.nblk == 1) {
-        if (want_total) {
-            F3M_HIP(hipMemcpyAsync(&S.total, S.sums.p, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-            F3M_HIP(hipStreamSynchronize(st));
-        }
-        F3M_HIP(hipMemsetAsync(S.sums.p, 0, sizeof(uint64_t), st));
-        return;
-    }
-    // scan the block sums in place; the grand total of that scan is the grand total
-    ScanState inner;
-    scan_prepare(ArrayInU64{S.sums.p}, S.nblk, inner, want_total, st);
-    scan_finish(ArrayInU64{S.sums.p}, S.nblk, inner, ArrayOutU64{S.sums.p}, st);
-    S.total = inner.total;
-    F3M_HIP(hipStreamSynchronize(st));  // `inner` is released on return
-}
-
+// both steps at once; the grand total is left in *total (if not null: a word that the device can write)
 template <class In, class Out>
-void exclusive_scan(In in, int64_t n, Out out, uint64_t *total_host, hipStream_t st) {
-    ScanState S;
-    scan_prepare(in, n, S, total_host != nullptr, st);
-    scan_finish(in, n, S, out, st);
-    if (total_host) *total_host = S.total;
-    if (n > 0) F3M_HIP(hipStreamSynchronize(st));  // S.sums is released on return
+void exclusive_scan(In in, int64_t n, Out out, uint64_t *total, hipStream_t st) {
+    if (n <= 0) return;
+    DevBuf<uint64_t> sums;
+    const int64_t nblk = cdiv(n, SCAN_TILE);
+    if (nblk > 1) {
+        sums.alloc((size_t)nblk);
+        scan_reduce_kernel<<<dim3((unsigned)nblk), dim3(SCAN_NT), 0, st>>>(in, n, sums.p);
+        scan_block_sums(sums.p, nblk, nullptr, st);
+    }
+    scan_apply_kernel<<<dim3((unsigned)nblk), dim3(SCAN_NT), 0, st>>>(in, n, (const uint64_t *)sums.p, out, total);
+    F3M_HIP(hipGetLastError());
 }
 
 }  // namespace f3m

@@ -1819,8 +1819,8 @@ static TransferArg make_transfer() {
 void upload_transfer(f3m_plan_s &P, hipStream_t st) {
     const TransferArg T = make_transfer();
     P.transfer.alloc(32, &P.bytes);
-    F3M_HIP(hipMemcpyAsync(P.transfer.p, &T.t[0][0][0], 32 * sizeof(float), hipMemcpyHostToDevice, st));
-    F3M_HIP(hipStreamSynchronize(st));
+    P.host_tabs.emplace_back(&T.t[0][0][0], &T.t[0][0][0] + 32);
+    F3M_HIP(hipMemcpyAsync(P.transfer.p, P.host_tabs.back().data(), 32 * sizeof(float), hipMemcpyHostToDevice, st));
 }
 
 // Both transfers run one wavefront per PARENT with lane = node (ix + 4 iy + 16 iz) and apply the
@@ -2320,7 +2320,6 @@ void build_far_orders(f3m_plan_s &P, hipStream_t st) {
 
 // per depth with far pairs: the 1-D factor matrices of the node-to-node kernel matrix, built in fp64
 void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
-    std::vector<std::vector<float>> host_tabs;
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
         if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && l > P.near_depth)) continue;
@@ -2358,9 +2357,8 @@ void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
                     }
         lv.gtab.alloc(g.size(), &P.bytes);
         F3M_HIP(hipMemcpyAsync(lv.gtab.p, g.data(), g.size() * sizeof(float), hipMemcpyHostToDevice, st));
-        host_tabs.push_back(std::move(g));   // stays alive until the copies of all depths have been waited for
+        P.host_tabs.push_back(std::move(g));   // stays alive until the plan has been waited for
     }
-    if (!host_tabs.empty()) F3M_HIP(hipStreamSynchronize(st));
 }
 
 

@@ -156,6 +156,8 @@ struct f3m_plan_s {
     const f3m_route *sroute() const { return src ? src->route.get() : route.get(); }
 
     hipEvent_t ev[16] = {nullptr};
+    std::vector<hipEvent_t> plan_events;  // two per depth while the plan is built
+    std::vector<std::vector<float>> host_tabs;   // tables on their way to the device, until the plan is complete
     std::vector<hipEvent_t> far_events;   // 6 per depth, around the far-field kernels of that depth
     bool have_plan_times = false, have_kmvm_times = false, have_far_point_pairs = false;
     f3m_times times = {};
@@ -182,7 +184,7 @@ double near_interp_error(double E, int depth, double gamma);                    
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
 void compute_far_point_pairs(f3m_plan_s &P);   // near_point_pairs and lev[].far_point_pairs, once (synchronises)
 // route.hip: permutations of large vectors as three streaming passes with tables built once per plan
-void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, hipStream_t st);   // synchronises
+void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, hipStream_t st);
 void route_scatter(const f3m_route &R, const float *in, const float *in2, float *out, float *tmp_a, float *tmp_b,
                    hipStream_t st);                                   // out[perm[k]] = in[k] (+ in2[k])
 void route_gather(const f3m_route &R, const float *in, float *out, float *tmp_a, float *tmp_b, hipStream_t st);

@@ -10,6 +10,8 @@
 f3m_plan_s::~f3m_plan_s() {
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
+    for (auto &e : plan_events)
+        if (e) (void)hipEventDestroy(e);
     for (auto &e : far_events)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {ev_fork, ev_join, ev_p2p0, ev_p2p1})
@@ -328,7 +330,6 @@ static bool radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uin
         in_b = !in_b;
         first = false;
     }
-    F3M_HIP(hipStreamSynchronize(st));
     return in_b;
 }
 
@@ -368,22 +369,28 @@ struct HeadIn {
         if (base == 0) v[0] = 1;
     }
 };
+// (the last element also writes the entry behind the last box, in the same way in the outputs below)
 struct HeadOut {
     const uint32_t *keys;
     int shift;
     uint32_t *start, *bkey;
+    int64_t n;
     __device__ void operator()(int64_t i, uint64_t ex, uint64_t v) const {
         if (v) {
             start[ex] = (uint32_t)i;
             bkey[ex] = (uint32_t)((uint64_t)keys[i] >> shift);
         }
+        if (i == n - 1) start[ex + v] = (uint32_t)n;
     }
 };
+// nup: boxes of the depth above (there is one head per box; a count that disagrees is reported by the host)
 struct ParentOut {
     uint32_t *parent, *cstart_up;
+    int64_t nb, nup;
     __device__ void operator()(int64_t a, uint64_t ex, uint64_t v) const {
         parent[a] = (uint32_t)(ex + v - 1);
-        if (v) cstart_up[ex] = (uint32_t)a;
+        if (v && (int64_t)ex < nup) cstart_up[ex] = (uint32_t)a;
+        if (a == nb - 1) cstart_up[nup] = (uint32_t)nb;
     }
 };
 
@@ -393,7 +400,8 @@ struct ParentOut {
 template <int D>
 __global__ __launch_bounds__(256) void child_bounds_kernel(const uint32_t *__restrict__ keys, int shift,
                                                            const uint32_t *__restrict__ up_start, int64_t nslots,
-                                                           const uint32_t *__restrict__ up_key, uint32_t *__restrict__ lb) {
+                                                           const uint32_t *__restrict__ up_key, uint32_t *__restrict__ lb,
+                                                           uint32_t n) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= nslots) return;
     const int64_t P = idx >> D;
@@ -408,6 +416,7 @@ __global__ __launch_bounds__(256) void child_bounds_kernel(const uint32_t *__res
         }
     }
     lb[idx] = lo;
+    if (idx == nslots - 1) lb[nslots] = n;
 }
 struct ChildIn {
     const uint32_t *lb;   // [nslots + 1]
@@ -417,6 +426,7 @@ template <int D>
 struct ChildOut {
     const uint32_t *lb, *up_key;
     uint32_t *start, *bkey, *parent, *cstart_up;
+    int64_t nslots;
     __device__ void operator()(int64_t i, uint64_t ex, uint64_t v) const {
         const int64_t P = i >> D;
         const uint32_t c = (uint32_t)(i & ((1 << D) - 1));
@@ -426,17 +436,36 @@ struct ChildOut {
             bkey[ex] = (uint32_t)(((uint64_t)up_key[P] << D) | c);
             parent[ex] = (uint32_t)P;
         }
+        if (i == nslots - 1) {
+            start[ex + v] = lb[nslots];
+            cstart_up[P + 1] = (uint32_t)(ex + v);
+        }
     }
 };
 
-__global__ void set_u32_kernel(uint32_t *p, uint32_t v) { *p = v; }
-__global__ void set_u64_kernel(uint64_t *p, uint64_t v) { *p = v; }
+// depth 0: one box, near itself
+__global__ void root_kernel(uint32_t n, int D, uint32_t *key, uint32_t *start, uint32_t *parent, int32_t *cell) {
+    key[0] = 0;
+    start[0] = 0;
+    start[1] = n;
+    parent[0] = 0;
+    for (int d = 0; d < D; ++d) cell[d] = 0;
+}
+__global__ void root_lists_kernel(uint64_t *near_ptr, uint64_t *far_ptr, uint32_t *near_col) {
+    near_ptr[0] = 0;
+    near_ptr[1] = 1;
+    far_ptr[0] = 0;
+    far_ptr[1] = 0;
+    near_col[0] = 0;
+}
 
+// largest box: a partial maximum per block, then one block over the partial maxima (which then are the "sizes")
+template <bool SIZES>
 __global__ __launch_bounds__(256) void max_count_kernel(const uint32_t *__restrict__ start, int64_t nb,
-                                                        uint32_t *__restrict__ part) {
+                                                        uint32_t *__restrict__ part, uint64_t *__restrict__ result) {
     uint32_t m = 0;
     for (int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x; a < nb; a += (int64_t)gridDim.x * 256)
-        m = max(m, start[a + 1] - start[a]);
+        m = max(m, SIZES ? start[a] : start[a + 1] - start[a]);
     __shared__ uint32_t sm[256];
     sm[threadIdx.x] = m;
     __syncthreads();
@@ -444,7 +473,10 @@ __global__ __launch_bounds__(256) void max_count_kernel(const uint32_t *__restri
         if (threadIdx.x < s) sm[threadIdx.x] = max(sm[threadIdx.x], sm[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sm[0];
+    if (threadIdx.x == 0) {
+        if (gridDim.x == 1) *result = sm[0];
+        else part[blockIdx.x] = sm[0];
+    }
 }
 
 template <int D>
@@ -703,9 +735,22 @@ struct NearPairsIn {
     }
 };
 
+// offsets of n items, and the total behind them
 struct PtrOut {
     uint64_t *p;
-    __device__ void operator()(int64_t i, uint64_t ex, uint64_t) const { p[i] = ex; }
+    int64_t n;
+    __device__ void operator()(int64_t i, uint64_t ex, uint64_t v) const {
+        p[i] = ex;
+        if (i == n - 1) p[n] = ex + v;
+    }
+};
+struct FirstOut {
+    uint32_t *p;
+    int64_t n;
+    __device__ void operator()(int64_t i, uint64_t ex, uint64_t v) const {
+        p[i] = (uint32_t)ex;
+        if (i == n - 1) p[n] = (uint32_t)(ex + v);
+    }
 };
 
 // ------------------------------------------------------------------------------------
@@ -825,39 +870,50 @@ __global__ __launch_bounds__(256) void mark_cols_kernel(const uint32_t *__restri
         flag[cols[e]] = 1u;
 }
 
-// work items counted per box by `count`: first[nb+1] (exclusive scan) and the box of every item
-template <class CountIn>
-static void build_items(CountIn count, int64_t nb, DevBuf<uint32_t> &first, DevBuf<uint32_t> &cbox, int64_t &nitems,
-                        int64_t *tally, hipStream_t st) {
-    first.alloc((size_t)nb + 1, tally);
-    uint64_t total = 0;
-    exclusive_scan(count, nb, U32Out{first.p}, &total, st);
-    nitems = (int64_t)total;
-    set_u32_kernel<<<1, 1, 0, st>>>(first.p + nb, (uint32_t)total);
-    cbox.alloc((size_t)nitems, tally);
-    if (nitems > 0)
-        chunk_box_kernel<<<dim3((unsigned)cdiv(nitems, 256)), dim3(256), 0, st>>>(first.p, nb, nitems, cbox.p);
-    F3M_HIP(hipGetLastError());
-}
+// Lists of work items counted per box: first[nb+1] (exclusive scan) and the box of every item.  The counts of all the
+// lists that are asked for are waited for together (build).
+struct ItemLists {
+    struct List {
+        int64_t nb;
+        const uint32_t *first;
+        DevBuf<uint32_t> *box;
+        int64_t *nitems;
+    };
+    int64_t *tally;
+    hipStream_t st;
+    std::vector<List> lists;
+    ItemLists(int64_t *tally_, hipStream_t st_) : tally(tally_), st(st_) {}
 
-static void build_chunks(const uint32_t *start, int64_t nb, uint32_t chunk, DevBuf<uint32_t> &first,
-                         DevBuf<uint32_t> &cbox, int64_t &nchunks, int64_t *tally, hipStream_t st,
-                         const uint64_t *only_rows = nullptr, const uint32_t *only_flagged = nullptr) {
-    first.alloc((size_t)nb + 1, tally);
-    uint64_t total = 0;
-    if (only_flagged)
-        exclusive_scan(ChunkCountFlagIn{start, only_flagged, chunk}, nb, U32Out{first.p}, &total, st);
-    else if (only_rows)
-        exclusive_scan(ChunkCountIfIn{start, only_rows, chunk}, nb, U32Out{first.p}, &total, st);
-    else
-        exclusive_scan(ChunkCountIn{start, chunk}, nb, U32Out{first.p}, &total, st);
-    nchunks = (int64_t)total;
-    set_u32_kernel<<<1, 1, 0, st>>>(first.p + nb, (uint32_t)total);
-    cbox.alloc((size_t)nchunks, tally);
-    if (nchunks > 0)
-        chunk_box_kernel<<<dim3((unsigned)cdiv(nchunks, 256)), dim3(256), 0, st>>>(first.p, nb, nchunks, cbox.p);
-    F3M_HIP(hipGetLastError());
-}
+    template <class CountIn>
+    void add(CountIn count, int64_t nb, DevBuf<uint32_t> &first, DevBuf<uint32_t> &box, int64_t &nitems) {
+        if ((int)lists.size() >= HOST_WORDS) fail(F3M_ERR_HIP, "internal: too many lists of work items");
+        first.alloc((size_t)nb + 1, tally);
+        exclusive_scan(count, nb, FirstOut{first.p, nb}, scope_words() + lists.size(), st);
+        lists.push_back(List{nb, first.p, &box, &nitems});
+    }
+    // runs of at most `chunk` points, in every box or in those with a row / a flag
+    void chunks(const uint32_t *start, int64_t nb, uint32_t chunk, DevBuf<uint32_t> &first, DevBuf<uint32_t> &box,
+                int64_t &nitems, const uint64_t *only_rows = nullptr, const uint32_t *only_flagged = nullptr) {
+        if (only_flagged) add(ChunkCountFlagIn{start, only_flagged, chunk}, nb, first, box, nitems);
+        else if (only_rows) add(ChunkCountIfIn{start, only_rows, chunk}, nb, first, box, nitems);
+        else add(ChunkCountIn{start, chunk}, nb, first, box, nitems);
+    }
+    void build() {
+        if (lists.empty()) return;
+        F3M_HIP(hipStreamSynchronize(st));
+        const uint64_t *totals = scope_words();
+        for (size_t k = 0; k < lists.size(); ++k) {
+            const List &W = lists[k];
+            const int64_t items = (int64_t)totals[k];
+            *W.nitems = items;
+            W.box->alloc((size_t)items, tally);
+            if (items > 0)
+                chunk_box_kernel<<<dim3((unsigned)cdiv(items, 256)), dim3(256), 0, st>>>(W.first, W.nb, items, W.box->p);
+            F3M_HIP(hipGetLastError());
+        }
+        lists.clear();
+    }
+};
 
 // ------------------------------------------------------------------------------------
 // a point set while it is partitioned: the targets X of the plan, or the sources Y of a two-set plan
@@ -900,75 +956,76 @@ static float set_bounds(const SetRef &S, const char *name, hipStream_t st) {
     return E;
 }
 
+// words of the scope's array that a depth leaves its counts in (word 0: scan_prepare)
+enum { HW_NEAR = 1, HW_FAR = 2, HW_SMALL = 3, HW_SET = 4 };   // HW_SET + 2 k: largest box of set k, heads counted
+
 // Divide (Algorithm 1): the box table of depth l of one set -- heads of runs of equal depth-l keys,
 // from the points or, once the boxes of the depth above are few against the points, from their
-// intervals -- with parent ranks, child intervals of the depth above, cells and the largest box.
+// intervals -- with parent ranks, child intervals of the depth above and cells.  The size of the largest box arrives
+// in `words` with the next wait for the stream (divide_finish).
 template <int D>
-static void divide_set(f3m_plan_s &P, const SetRef &S, int l, DevBuf<uint32_t> &part, hipStream_t st) {
+static void divide_set(f3m_plan_s &P, const SetRef &S, int l, DevBuf<uint32_t> &part, uint64_t *words, hipStream_t st) {
     int64_t *tally = &P.bytes;
     const int64_t n = S.n;
     f3m_level &lv = S.lev[l];
     const uint32_t *keys = S.keys->p;
-    int shift = D * (P.Lq - l);
-    const bool from_parents = l > 0 && (S.lev[l - 1].nb << D) <= n / 4;
-    if (from_parents) {
-        f3m_level &up = S.lev[l - 1];
+    if (l == 0) {
+        lv.nb = 1;
+        lv.key.alloc(1, tally);
+        lv.start.alloc(2, tally);
+        lv.parent.alloc(1, tally);
+        lv.cell.alloc(D, tally);
+        root_kernel<<<1, 1, 0, st>>>((uint32_t)n, D, lv.key.p, lv.start.p, lv.parent.p, lv.cell.p);
+        F3M_HIP(hipGetLastError());
+        lv.max_box = n;
+        return;
+    }
+    const int shift = D * (P.Lq - l);
+    f3m_level &up = S.lev[l - 1];
+    up.cstart.alloc((size_t)up.nb + 1, tally);
+    words[1] = (uint64_t)up.nb;
+    if ((up.nb << D) <= n / 4) {
         const int64_t nslots = up.nb << D;
         DevBuf<uint32_t> lb;
         lb.alloc((size_t)nslots + 1);
         child_bounds_kernel<D><<<dim3((unsigned)cdiv(nslots, 256)), dim3(256), 0, st>>>(keys, shift, up.start.p, nslots,
-                                                                                      up.key.p, lb.p);
+                                                                                      up.key.p, lb.p, (uint32_t)n);
         F3M_HIP(hipGetLastError());
-        set_u32_kernel<<<1, 1, 0, st>>>(lb.p + nslots, (uint32_t)n);
         ChildIn cin{lb.p};
         ScanState SS;
-        scan_prepare(cin, nslots, SS, true, st);
+        scan_prepare(cin, nslots, SS, st);
         lv.nb = (int64_t)SS.total;
         lv.key.alloc((size_t)lv.nb, tally);
         lv.start.alloc((size_t)lv.nb + 1, tally);
         lv.parent.alloc((size_t)lv.nb, tally);
-        up.cstart.alloc((size_t)up.nb + 1, tally);
-        scan_finish(cin, nslots, SS, ChildOut<D>{lb.p, up.key.p, lv.start.p, lv.key.p, lv.parent.p, up.cstart.p}, st);
-        set_u32_kernel<<<1, 1, 0, st>>>(lv.start.p + lv.nb, (uint32_t)n);
-        set_u32_kernel<<<1, 1, 0, st>>>(up.cstart.p + up.nb, (uint32_t)lv.nb);
-        F3M_HIP(hipStreamSynchronize(st));   // lb is released on leaving the scope
+        scan_finish(cin, nslots, SS,
+                    ChildOut<D>{lb.p, up.key.p, lv.start.p, lv.key.p, lv.parent.p, up.cstart.p, nslots}, st);
     } else {
         HeadIn hin{keys, shift};
         ScanState SS;
-        scan_prepare(hin, n, SS, true, st);
+        scan_prepare(hin, n, SS, st);
         lv.nb = (int64_t)SS.total;
         lv.key.alloc((size_t)lv.nb, tally);
         lv.start.alloc((size_t)lv.nb + 1, tally);
-        scan_finish(hin, n, SS, HeadOut{keys, shift, lv.start.p, lv.key.p}, st);
-        set_u32_kernel<<<1, 1, 0, st>>>(lv.start.p + lv.nb, (uint32_t)n);
+        lv.parent.alloc((size_t)lv.nb, tally);
+        scan_finish(hin, n, SS, HeadOut{keys, shift, lv.start.p, lv.key.p, n}, st);
+        exclusive_scan(HeadIn{lv.key.p, D}, lv.nb, ParentOut{lv.parent.p, up.cstart.p, lv.nb, up.nb}, words + 1, st);
     }
     {
-        int grid = (int)std::min<int64_t>(1024, cdiv(lv.nb, 256));
-        max_count_kernel<<<dim3(grid), dim3(256), 0, st>>>(lv.start.p, lv.nb, part.p);
+        const int grid = lv.nb <= 16384 ? 1 : (int)std::min<int64_t>(1024, cdiv(lv.nb, 256));
+        max_count_kernel<false><<<dim3(grid), dim3(256), 0, st>>>(lv.start.p, lv.nb, part.p, words);
+        if (grid > 1) max_count_kernel<true><<<dim3(1), dim3(256), 0, st>>>(part.p, grid, part.p, words);
         F3M_HIP(hipGetLastError());
-        std::vector<uint32_t> hp(grid);
-        F3M_HIP(hipMemcpyAsync(hp.data(), part.p, grid * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        F3M_HIP(hipStreamSynchronize(st));
-        lv.max_box = *std::max_element(hp.begin(), hp.end());
     }
     lv.cell.alloc((size_t)lv.nb * D, tally);
     cells_kernel<D><<<dim3((unsigned)cdiv(lv.nb, 256)), dim3(256), 0, st>>>(lv.key.p, lv.nb, l, lv.cell.p);
     F3M_HIP(hipGetLastError());
-    if (from_parents) {
-        // parent ranks and child intervals came with the division
-    } else if (l > 0) {
-        lv.parent.alloc((size_t)lv.nb, tally);
-        f3m_level &up = S.lev[l - 1];
-        up.cstart.alloc((size_t)up.nb + 1, tally);
-        HeadIn pin{lv.key.p, D};
-        uint64_t tot = 0;
-        exclusive_scan(pin, lv.nb, ParentOut{lv.parent.p, up.cstart.p}, &tot, st);
-        if ((int64_t)tot != up.nb) fail(F3M_ERR_HIP, "internal: parent count mismatch");
-        set_u32_kernel<<<1, 1, 0, st>>>(up.cstart.p + up.nb, (uint32_t)lv.nb);
-    } else {
-        lv.parent.alloc((size_t)lv.nb, tally);
-        F3M_HIP(hipMemsetAsync(lv.parent.p, 0, sizeof(uint32_t), st));
-    }
+}
+
+// after a wait for the stream
+static void divide_finish(const SetRef &S, int l, const uint64_t *words) {
+    S.lev[l].max_box = (int64_t)words[0];
+    if ((int64_t)words[1] != S.lev[l - 1].nb) fail(F3M_ERR_HIP, "internal: parent count mismatch");
 }
 
 template <int D>
@@ -1020,7 +1077,6 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             std::swap(S.keys->p, keys_b.p);
             std::swap(S.perm->p, perm_b.p);
         }
-        F3M_HIP(hipStreamSynchronize(st));   // the second buffers are released on leaving the scope
     }
     F3M_HIP(hipEventRecord(P.ev[2], st));
     for (size_t k = 0; k < sets.size(); ++k) {
@@ -1039,14 +1095,12 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             DevBuf<float> tmp;
             tmp.alloc((size_t)S.n * 3);
             route_gather_rows3(*route, S.X, S.Xs->p, tmp.p, st);
-            F3M_HIP(hipStreamSynchronize(st));   // `tmp` is released on leaving the scope
         } else {
             gather_rows_kernel<D><<<dim3((unsigned)cdiv(S.n, 256)), dim3(256), 0, st>>>(S.X, S.perm->p, S.n, S.Xs->p);
             F3M_HIP(hipGetLastError());
         }
     }
     F3M_HIP(hipEventRecord(P.ev[3], st));
-    F3M_HIP(hipStreamSynchronize(st));
 
     // ---- Algorithm 1 loop: divide, new interactions, partition
     int cap = P.Lq;
@@ -1055,15 +1109,17 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     if (!(P.E > 0.f)) cap = 0;
     DevBuf<uint32_t> part;
     part.alloc(1024);
-    float t_boxes = 0.f, t_lists = 0.f;
-    hipEvent_t ea = P.ev[4], eb = P.ev[5], ec = P.ev[6];
+    hipEvent_t ea = P.ev[4], eb = P.ev[5];
+    // per depth: after the division, after the lists
+    P.plan_events.resize(2 * (size_t)(cap + 1), nullptr);
+    uint64_t *words = scope_words();
     int l = 0;
     for (;; ++l) {
         f3m_level &lv = P.lev[l];
-        F3M_HIP(hipEventRecord(ea, st));
-        for (const SetRef &S : sets) divide_set<D>(P, S, l, part, st);
+        for (size_t k = 0; k < sets.size(); ++k) divide_set<D>(P, sets[k], l, part, words + HW_SET + 2 * k, st);
         const f3m_level &sv = P.slev(l);
-        F3M_HIP(hipEventRecord(eb, st));
+        for (int k = 0; k < 2; ++k) F3M_HIP(hipEventCreate(&P.plan_events[2 * (size_t)l + k]));
+        F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l], st));
 
         // new interactions + partition
         lv.near_ptr.alloc((size_t)lv.nb + 1, tally);
@@ -1071,10 +1127,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         if (l == 0) {
             lv.near_col.alloc(1, tally);
             lv.far_col.alloc(1, tally);
-            F3M_HIP(hipMemsetAsync(lv.near_ptr.p, 0, 2 * sizeof(uint64_t), st));
-            F3M_HIP(hipMemsetAsync(lv.far_ptr.p, 0, 2 * sizeof(uint64_t), st));
-            F3M_HIP(hipMemsetAsync(lv.near_col.p, 0, sizeof(uint32_t), st));
-            set_u64_kernel<<<1, 1, 0, st>>>(lv.near_ptr.p + 1, 1ull);
+            root_lists_kernel<<<1, 1, 0, st>>>(lv.near_ptr.p, lv.far_ptr.p, lv.near_col.p);
+            F3M_HIP(hipGetLastError());
             lv.near_sz = 1;
             lv.far_sz = 0;
         } else {
@@ -1104,17 +1158,17 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                                                                  up.near_col.p, sup.cstart.p, A);
             }
             F3M_HIP(hipGetLastError());
-            uint64_t tn = 0, tf = 0, ts = 0;
-            exclusive_scan(U32In{cn.p}, lv.nb, PtrOut{lv.near_ptr.p}, &tn, st);
-            exclusive_scan(U32In{cf.p}, lv.nb, PtrOut{lv.far_ptr.p}, &tf, st);
-            set_u64_kernel<<<1, 1, 0, st>>>(lv.near_ptr.p + lv.nb, tn);
-            set_u64_kernel<<<1, 1, 0, st>>>(lv.far_ptr.p + lv.nb, tf);
+            words[HW_SMALL] = 0;
+            exclusive_scan(U32In{cn.p}, lv.nb, PtrOut{lv.near_ptr.p, lv.nb}, words + HW_NEAR, st);
+            exclusive_scan(U32In{cf.p}, lv.nb, PtrOut{lv.far_ptr.p, lv.nb}, words + HW_FAR, st);
             if (P.rho > 0) {
                 lv.small_ptr.alloc((size_t)lv.nb + 1, tally);
-                exclusive_scan(U32In{cs.p}, lv.nb, PtrOut{lv.small_ptr.p}, &ts, st);
-                set_u64_kernel<<<1, 1, 0, st>>>(lv.small_ptr.p + lv.nb, ts);
-                lv.small_col.alloc((size_t)ts, tally);
+                exclusive_scan(U32In{cs.p}, lv.nb, PtrOut{lv.small_ptr.p, lv.nb}, words + HW_SMALL, st);
             }
+            F3M_HIP(hipStreamSynchronize(st));
+            for (size_t k = 0; k < sets.size(); ++k) divide_finish(sets[k], l, words + HW_SET + 2 * k);
+            const uint64_t tn = words[HW_NEAR], tf = words[HW_FAR], ts = words[HW_SMALL];
+            if (P.rho > 0) lv.small_col.alloc((size_t)ts, tally);
             lv.near_sz = (int64_t)tn;
             lv.far_sz = (int64_t)tf;
             lv.small_sz = (int64_t)ts;
@@ -1136,7 +1190,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                     P.near_depth = l;
             } else if (tf > 0 && far_points_allowed(P, l)) {
                 ScanState S;
-                scan_prepare(NearPairsIn{up.start.p, up.start.p, up.near_ptr.p, up.near_col.p}, up.nb, S, true, st);
+                scan_prepare(NearPairsIn{up.start.p, up.start.p, up.near_ptr.p, up.near_col.p}, up.nb, S, st);
                 lv.far_points = far_points_pays(P, l, (int64_t)S.total);
                 lv.far_col.alloc(lv.far_points ? 0 : (size_t)tf, tally);
             } else {
@@ -1167,15 +1221,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                                                                  up.near_col.p, sup.cstart.p, A);
             }
             F3M_HIP(hipGetLastError());
-            F3M_HIP(hipStreamSynchronize(st));
         }
-        F3M_HIP(hipEventRecord(ec, st));
-        F3M_HIP(hipStreamSynchronize(st));
-        float ms = 0.f;
-        F3M_HIP(hipEventElapsedTime(&ms, ea, eb));
-        t_boxes += ms;
-        F3M_HIP(hipEventElapsedTime(&ms, eb, ec));
-        t_lists += ms;
+        F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l + 1], st));
         // while interactions remain and the largest box of either tree is above zeta (Algorithm 1)
         if (!(lv.near_sz > 0 && lv.max_box > P.leaf_max && sv.max_box > P.leaf_max && l < cap)) break;
     }
@@ -1202,14 +1249,15 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     upload_kron_tables(P, st);
     build_far_orders(P, st);
     for (int k = 1; k <= P.L; ++k) build_stencil_tables(P, k, st);
-    int64_t max_w = 0, max_v = 0, max_part = 0, max_slice = 0;
+    ItemLists items(tally, st);
+    int64_t max_w = 0, max_v = 0;
     for (int k = 1; k <= P.L; ++k) {
         f3m_level &lv = P.lev[k];
         if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && k > P.near_depth)) continue;   // nothing to interpolate, or dropped
         if (lv.far_points) {
             far_points_prepare(P, k, st);
             const f3m_level &up = P.lev[k - 1];
-            build_chunks(up.start.p, up.nb, FP_TT, lv.fp_tile_first, lv.fp_tile_box, lv.fp_ntiles, tally, st);
+            items.chunks(up.start.p, up.nb, FP_TT, lv.fp_tile_first, lv.fp_tile_box, lv.fp_ntiles);
             continue;
         }
         const bool tree = P.tree_lmin > 0 && k >= P.tree_lmin && k <= P.tree_lmax;
@@ -1228,7 +1276,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         // runs of points for the L2P (targets: in the band only its last depth) and the P2M (sources: the
         // same runs for one point set)
         if (!tree || k == P.tree_lmax)
-            build_chunks(lv.start.p, lv.nb, P2M_CHUNK, lv.chunk_first, lv.chunk_box, lv.nchunks, tally, st);
+            items.chunks(lv.start.p, lv.nb, P2M_CHUNK, lv.chunk_first, lv.chunk_box, lv.nchunks);
         if (P.src) {
             // Only the source boxes that occur in a far row of this depth need node weights (the two sets
             // may overlap in a small part of the sources' cube only).
@@ -1238,26 +1286,39 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             mark_cols_kernel<<<dim3((unsigned)std::min<int64_t>(cdiv(lv.far_sz, 256), 1 << 20)), dim3(256), 0, st>>>(
                 lv.far_col.p, lv.far_sz, used.p);
             F3M_HIP(hipGetLastError());
-            build_chunks(sv.start.p, sv.nb, P2M_CHUNK, sv.chunk_first, sv.chunk_box, sv.nchunks, tally, st, nullptr,
-                         used.p);
-            F3M_HIP(hipStreamSynchronize(st));   // `used` is released on leaving the scope
+            items.chunks(sv.start.p, sv.nb, P2M_CHUNK, sv.chunk_first, sv.chunk_box, sv.nchunks, nullptr, used.p);
         }
         if (sv.max_box > (int64_t)P2M_CHUNK * P2M_SLICE * 2) {
             // a box with more than a thousand chunks: its partial node weights are summed in two stages
-            build_chunks(sv.chunk_first.p, sv.nb, P2M_SLICE, sv.slice_first, sv.slice_box, sv.nslices, tally, st);
-            max_slice = std::max(max_slice, sv.nslices * (int64_t)lv.r);
+            items.chunks(sv.chunk_first.p, sv.nb, P2M_SLICE, sv.slice_first, sv.slice_box, sv.nslices);
         }
         if (!tree || P.src) max_w = std::max(max_w, sv.nb * (int64_t)lv.r);
         if (!tree) max_v = std::max(max_v, lv.nb * (int64_t)lv.r);
-        max_part = std::max(max_part, sv.nchunks * (int64_t)lv.r);
     }
     if (P.near_depth == 0) {
         const f3m_level &lf = P.lev[P.L];
         // Few boxes: rows are long, and the near field splits every tile over several wavefronts; an overflow
         // tile would leave its whole row to one wavefront, so there are none (every run is a tile of its own).
         const uint32_t ts = lf.nb < 8192 ? 0u : (uint32_t)overflow_targets(D);
-        build_items(BigTileCountIn{lf.start.p, ts}, lf.nb, P.tile_first, P.tile_box, P.ntiles, tally, st);
-        build_items(OverflowTileCountIn{lf.start.p, ts}, lf.nb, P.otile_first, P.otile_box, P.notiles, tally, st);
+        items.add(BigTileCountIn{lf.start.p, ts}, lf.nb, P.tile_first, P.tile_box, P.ntiles);
+        items.add(OverflowTileCountIn{lf.start.p, ts}, lf.nb, P.otile_first, P.otile_box, P.notiles);
+    }
+    // target tiles of the small-field rows of every depth (Sec. 4.2)
+    for (int k = 1; k <= P.L; ++k) {
+        f3m_level &lv = P.lev[k];
+        if (lv.small_sz > 0)   // runs of targets as p2p_small_kernel takes them
+            items.chunks(lv.start.p, lv.nb, D <= 4 ? 16 : 8, lv.sm_tile_first, lv.sm_tile_box, lv.sm_ntiles, lv.small_ptr.p);
+    }
+    items.build();
+    int64_t max_part = 0, max_slice = 0;
+    for (int k = 1; k <= P.L; ++k) {
+        const f3m_level &sv = P.slev(k);
+        max_part = std::max(max_part, sv.nchunks * (int64_t)P.lev[k].r);
+        max_slice = std::max(max_slice, sv.nslices * (int64_t)P.lev[k].r);
+    }
+    if (P.near_depth == 0) {
+        const f3m_level &lf = P.lev[P.L];
+        const uint32_t ts = lf.nb < 8192 ? 0u : (uint32_t)overflow_targets(D);
         // tiles worked in pairs (the rows must come from the plain far rule: the kernel tells the shared near
         // boxes of a pair by it)
         if (P.L >= 1 && ts > 0 && lf.near_sz > 0 && !lf.smooth && P.rho == 0 && p2p_pairs_allowed(P)) {
@@ -1266,16 +1327,10 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             pair_flag_kernel<<<dim3((unsigned)cdiv(up.nb, 256)), dim3(256), 0, st>>>(
                 up.nb, up.cstart.p, lf.cell.p, lf.start.p, lf.near_ptr.p, ts, P.paired.p);
             F3M_HIP(hipGetLastError());
-            build_items(PairCountIn{P.paired.p}, lf.nb, P.pair_first, P.pair_box, P.npairs, tally, st);
-            build_items(RestTileCountIn{lf.start.p, ts, P.paired.p}, lf.nb, P.rtile_first, P.rtile_box, P.nrtiles, tally, st);
+            items.add(PairCountIn{P.paired.p}, lf.nb, P.pair_first, P.pair_box, P.npairs);
+            items.add(RestTileCountIn{lf.start.p, ts, P.paired.p}, lf.nb, P.rtile_first, P.rtile_box, P.nrtiles);
+            items.build();
         }
-    }
-    // target tiles of the small-field rows of every depth (Sec. 4.2)
-    for (int k = 1; k <= P.L; ++k) {
-        f3m_level &lv = P.lev[k];
-        if (lv.small_sz > 0)
-            build_chunks(lv.start.p, lv.nb, D <= 4 ? 16 : 8, lv.sm_tile_first, lv.sm_tile_box, lv.sm_ntiles, tally, st,
-                         lv.small_ptr.p);   // runs of targets as p2p_small_kernel takes them
     }
     {
         // partial sums of a near field whose tiles are split over several wavefronts (few targets, long rows)
@@ -1304,8 +1359,16 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     F3M_HIP(hipEventElapsedTime(&P.times.bbox_keys, P.ev[0], P.ev[1]));
     F3M_HIP(hipEventElapsedTime(&P.times.sort, P.ev[1], P.ev[2]));
     F3M_HIP(hipEventElapsedTime(&P.times.gather, P.ev[2], P.ev[3]));
-    P.times.boxes = t_boxes;
-    P.times.lists = t_lists;
+    P.host_tabs.clear();
+    P.times.boxes = P.times.lists = 0.f;
+    for (int k = 0; k <= P.L; ++k) {
+        const hipEvent_t before = k ? P.plan_events[2 * (size_t)k - 1] : P.ev[3];
+        const hipEvent_t mid = P.plan_events[2 * (size_t)k], after = P.plan_events[2 * (size_t)k + 1];
+        F3M_HIP(hipEventElapsedTime(&ms, before, mid));
+        P.times.boxes += ms;
+        F3M_HIP(hipEventElapsedTime(&ms, mid, after));
+        P.times.lists += ms;
+    }
     F3M_HIP(hipEventElapsedTime(&P.times.tables, ea, eb));
     F3M_HIP(hipEventElapsedTime(&ms, P.ev[0], eb));
     P.times.plan_total = ms;
@@ -1342,10 +1405,11 @@ void materialize_far(const f3m_plan_s &P, int level, uint32_t *cols_dev, hipStre
 // re-reads every list.
 void compute_far_point_pairs(f3m_plan_s &P) {
     if (P.have_far_point_pairs) return;
+    ReleaseScope scope((hipStream_t) nullptr);
     {
         ScanState S;
         const f3m_level &lf = P.lev[P.L];
-        scan_prepare(NearPairsIn{lf.start.p, P.slev(P.L).start.p, lf.near_ptr.p, lf.near_col.p}, lf.nb, S, true, nullptr);
+        scan_prepare(NearPairsIn{lf.start.p, P.slev(P.L).start.p, lf.near_ptr.p, lf.near_col.p}, lf.nb, S, nullptr);
         P.near_point_pairs = (int64_t)S.total;
     }
     for (int l = 1; l <= P.L; ++l) {
@@ -1353,7 +1417,7 @@ void compute_far_point_pairs(f3m_plan_s &P) {
         lv.small_point_pairs = 0;
         if (lv.small_sz > 0) {
             ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.small_ptr.p, lv.small_col.p}, lv.nb, S, true, nullptr);
+            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.small_ptr.p, lv.small_col.p}, lv.nb, S, nullptr);
             lv.small_point_pairs = (int64_t)S.total;
         }
         lv.far_point_pairs = 0;
@@ -1363,11 +1427,11 @@ void compute_far_point_pairs(f3m_plan_s &P) {
             cols.alloc((size_t)lv.far_sz);
             materialize_far(P, l, cols.p, nullptr);
             ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, cols.p}, lv.nb, S, true, nullptr);
+            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, cols.p}, lv.nb, S, nullptr);
             lv.far_point_pairs = (int64_t)S.total;
         } else {
             ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, lv.far_col.p}, lv.nb, S, true, nullptr);
+            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, lv.far_col.p}, lv.nb, S, nullptr);
             lv.far_point_pairs = (int64_t)S.total;
         }
     }

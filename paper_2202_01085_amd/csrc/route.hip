@@ -458,7 +458,6 @@ void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, 
                                                              pass == 1 ? R.gofs1.p : R.gofs2.p);
         F3M_HIP(hipGetLastError());
     }
-    F3M_HIP(hipStreamSynchronize(st));   // the work arrays are released on return
 }
 
 // out[perm[k]] = in[k] (+ in2[k]); tmp_a, tmp_b: n floats each

@@ -1,0 +1,71 @@
+"""Plans at the edges of their scans and lists: the box tables and every list equal the oracle's, bit for bit, also when
+plans are built and destroyed in turn (released buffers are used again by the next plan)."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2202_01085_amd import f3m, inputs
+from parity_util import TOL_F3M, assert_close, say
+from test_gpu_parity import check_plan_bit_exact
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+# a scan is one block up to 2048 elements (256 counts per sort tile of 8192 keys: 65 536 keys); the largest box comes
+# from one block up to 16 384 boxes; lists of more than three dimensions have rows of 1 to thousands of candidates,
+# 64 at a time
+@pytest.mark.parametrize("n,D,p,zeta,more", [
+    (65_536, 3, 4, 16, {}), (65_537, 3, 4, 16, {}), (2_048, 1, 3, 1, {}), (2_049, 2, 3, 1, {}),
+    (40_000, 2, 3, 2, {}),                                   # more than 16 384 leaf boxes
+    (3_000, 4, 3, 8, {}), (5_000, 5, 2, 4, {}), (6_000, 6, 2, 16, {}), (4_001, 7, 2, 8, {}),
+    (4_001, 4, 3, 16, dict(small_field=40)),
+    (3_001, 3, 4, 16, dict(small_field=60)),
+    (3_001, 4, 3, 16, dict(force_all_near=True, max_depth=2)),
+])
+def test_plan_tables(n, D, p, zeta, more):
+    say("plan edges n=%d D=%d zeta=%d %r" % (n, D, zeta, more))
+    X = inputs.points_normal(n, D, 91 + D)
+    T = oracle.Tree(X.numpy(), theta=2.0, zeta=zeta, **more)
+    plan = f3m.Plan(X.to(DEV), 1.0, p, 2.0, leaf_max=zeta, **more)
+    check_plan_bit_exact(plan, T)
+    plan.close()
+
+
+def test_plans_in_turn_and_from_two_threads():
+    """Buffers of a plan that is gone serve the next one, on other streams and threads too: the same bits every time."""
+    sizes = [30_000, 3_000, 70_001]
+    Xs = [inputs.points_uniform(n, 3, 95).to(DEV) for n in sizes]
+    bs = [inputs.rhs_normal(n, 96).to(DEV) for n in sizes]
+
+    def one(k):
+        plan = f3m.Plan(Xs[k], 0.4, 4, 2.0)
+        y = plan.kmvm(bs[k])
+        plan.close()
+        return y
+
+    want = [one(k) for k in range(3)]
+    torch.cuda.synchronize()
+    T = oracle.Tree(Xs[1].cpu().numpy(), theta=2.0, zeta=128)
+    assert_close(want[1].cpu().numpy(), T.apply(bs[1].cpu().numpy(), float(np.float32(0.4)), 4), TOL_F3M, "vs CPU F3M")
+    bad = []
+
+    def work():
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for i in range(6):
+                y = one(i % 3)
+                s.synchronize()
+                if not torch.equal(y, want[i % 3]):
+                    bad.append(i)
+
+    threads = [threading.Thread(target=work) for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
