@@ -44,6 +44,12 @@ f3m_status check_problem(const float *X, int64_t n, int D, float lengthscale) {
 // false for a plan with no targets or no sources: it holds no tables
 bool built(const f3m_plan_t *plan) { return plan->n > 0 && plan->ns() > 0; }
 
+// milliseconds between two marks of a product (stages without a launch share one)
+hipError_t elapsed(float *ms, hipEvent_t from, hipEvent_t to) {
+    *ms = 0.f;
+    return from == to ? hipSuccess : hipEventElapsedTime(ms, from, to);
+}
+
 template <class T>
 void copy_to_host(T *dst, const T *src, size_t count) {
     if (count == 0) return;
@@ -364,21 +370,21 @@ f3m_status f3m_stage_times(f3m_plan_t *plan, f3m_times *out) {
     return guarded([&] {
         f3m_times t = plan->times;
         if (plan->have_kmvm_times) {
-            F3M_HIP(hipEventSynchronize(plan->ev[12]));
-            F3M_HIP(hipEventElapsedTime(&t.permute_in, plan->ev[8], plan->ev[9]));
-            F3M_HIP(hipEventSynchronize(plan->ev_p2p1));
-            F3M_HIP(hipEventElapsedTime(&t.p2p, plan->ev_p2p0, plan->ev_p2p1));
-            F3M_HIP(hipEventElapsedTime(&t.permute_out, plan->ev[11], plan->ev[12]));
-            F3M_HIP(hipEventElapsedTime(&t.kmvm_total, plan->ev[8], plan->ev[12]));
+            F3M_HIP(hipEventSynchronize(plan->t_end));
+            F3M_HIP(elapsed(&t.permute_in, plan->t_begin, plan->t_in));
+            F3M_HIP(hipEventSynchronize(plan->t_p2p1));
+            F3M_HIP(elapsed(&t.p2p, plan->t_p2p0, plan->t_p2p1));
+            F3M_HIP(elapsed(&t.permute_out, plan->t_out, plan->t_end));
+            F3M_HIP(elapsed(&t.kmvm_total, plan->t_begin, plan->t_end));
             t.p2m = t.m2l = t.l2p = 0.f;
             for (int l = 1; l <= plan->L; ++l) {
                 if (plan->lev[l].far_sz == 0 || plan->far_events.size() < (size_t)(l + 1) * 6) continue;
                 hipEvent_t *ev = &plan->far_events[(size_t)l * 6];
                 if (!ev[5]) continue;
                 float ms = 0.f;
-                F3M_HIP(hipEventElapsedTime(&ms, ev[0], ev[1])); t.p2m += ms;
-                F3M_HIP(hipEventElapsedTime(&ms, ev[2], ev[3])); t.m2l += ms;
-                F3M_HIP(hipEventElapsedTime(&ms, ev[4], ev[5])); t.l2p += ms;
+                F3M_HIP(elapsed(&ms, ev[0], ev[1])); t.p2m += ms;
+                F3M_HIP(elapsed(&ms, ev[2], ev[3])); t.m2l += ms;
+                F3M_HIP(elapsed(&ms, ev[4], ev[5])); t.l2p += ms;
             }
         }
         *out = t;
@@ -394,8 +400,8 @@ f3m_status f3m_level_times(f3m_plan_t *plan, int level, float *ms_host) {
             return;
         hipEvent_t *ev = &plan->far_events[(size_t)level * 6];
         if (!ev[5]) return;
-        F3M_HIP(hipEventSynchronize(plan->ev[12]));
-        for (int k = 0; k < 3; ++k) F3M_HIP(hipEventElapsedTime(&ms_host[k], ev[2 * k], ev[2 * k + 1]));
+        F3M_HIP(hipEventSynchronize(plan->t_end));
+        for (int k = 0; k < 3; ++k) F3M_HIP(elapsed(&ms_host[k], ev[2 * k], ev[2 * k + 1]));
     });
 }
 

@@ -99,11 +99,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const float *__restrict__ 
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k < n) y[perm[k]] = yn ? ys[k] + yn[k] : ys[k];
 }
-// the same two steps for a caller that keeps its vectors in box order (the solver)
-__global__ __launch_bounds__(256) void copy_kernel(const float *__restrict__ b, int64_t n, float *__restrict__ bs) {
-    int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k < n) bs[k] = b[k];
-}
+// the last step for a caller that keeps its vectors in box order (the solver)
 __global__ __launch_bounds__(256) void add_kernel(const float *__restrict__ ys, const float *__restrict__ yn, int64_t n,
                                                   float *__restrict__ y) {
     int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1696,7 +1692,9 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
                                                    const uint64_t *__restrict__ far_ptr,
                                                    const uint32_t *__restrict__ chunk_box,
                                                    const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
-                                                   const float *__restrict__ V, float *__restrict__ ys, int one_chunk) {
+                                                   const float *__restrict__ V, const float *base, float *out,
+                                                   int one_chunk) {
+    // out = base (nullptr: zero) + far field
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ __attribute__((aligned(16))) float vbuf[L2P_NCH][64];
     const int64_t c0 = block_index() * L2P_NCH;
@@ -1751,7 +1749,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
             }
             y = fmaf(Lz[i3], sy, y);
         }
-        if (live) ys[k] = yold + y;
+        if (live) out[k] = yold + y;
     };
     // Loads are unconditional with the index of a lane beyond the chunk clamped to the chunk's first
     // point (a branch around them would make the compiler wait for every load on its own); the first
@@ -1766,7 +1764,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
         kk[j] = live[j] ? k : k0[j];
 #pragma unroll
         for (int d = 0; d < 3; ++d) x[j][d] = Xs[(int64_t)kk[j] * 3 + d];
-        yold[j] = ys[kk[j]];
+        yold[j] = base ? base[kk[j]] : 0.f;
     }
 #pragma unroll
     for (int j = 0; j < L2P_NCH; ++j) run(j, live[j], kk[j], x[j], yold[j]);
@@ -1779,7 +1777,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
             float xr[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) xr[d] = Xs[(int64_t)kc * 3 + d];
-            run(j, lv, kc, xr, ys[kc]);
+            run(j, lv, kc, xr, base ? base[kc] : 0.f);
         }
     }
 }
@@ -2412,48 +2410,53 @@ int p2p_nsplit(const f3m_plan_s &P, int l, int64_t ntiles) {
     return nsplit < 2 ? 1 : nsplit;
 }
 
-// box_order: b and y are in the plan's box order (one-set plans), so both permutations are plain passes.
+// box_order: b and y are in the plan's box order (one-set plans; b padded), so there are no permutations.
 // bs_in / yn_in (both or neither): the right-hand side already gathered into box order (padded like
 // the plan's own buffer) and the near-field result already computed for it; used by the products with
 // several right-hand sides, whose near field is evaluated for a group of columns at once.
 template <int D>
 static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, bool box_order,
                        const float *bs_in = nullptr, const float *yn_in = nullptr) {
+    if (box_order) bs_in = b;
     const float *bs = bs_in ? bs_in : P.bs.p;
     // no near field: every pair is interpolated (smooth field, or the products stop above the last depth)
     const bool no_near = !yn_in && P.rho == 0 && (P.lev[P.L].near_sz == 0 || P.near_depth);
     const float *yn = yn_in ? yn_in : no_near ? nullptr : P.yn.p;
     const int64_t n = P.n;
     const float nc2 = (float)(-1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma));
-    const int nev = 4 + 3 * (P.L + 1);
-    if (!P.ev[8]) {
-        // events of the kmvm stages live in ev[8..15] plus a per-depth set created lazily
-        for (int k = 8; k < 12; ++k) F3M_HIP(hipEventCreate(&P.ev[k]));
-    }
-    (void)nev;
+    // A mark at every boundary between two stages with launches.  An event record is a packet of its own on the stream:
+    // one event per boundary, where stages used to record their begin and end each, and no pass that only fills or
+    // copies (below), take the product of 2e4 points from 134 us to 85 us.
+    size_t nmarks = 0;
+    auto mark = [&] {
+        if (nmarks == P.marks.size()) {
+            P.marks.push_back(nullptr);
+            F3M_HIP(hipEventCreate(&P.marks.back()));
+        }
+        F3M_HIP(hipEventRecord(P.marks[nmarks], st));
+        return P.marks[nmarks++];
+    };
     const unsigned gn = (unsigned)cdiv(n, 256);
     f3m_level &leaf = P.lev[P.L];
     const float *Ys = P.Ys();   // sources in box order (the targets themselves for one point set)
 
-    F3M_HIP(hipEventRecord(P.ev[8], st));
-    if (bs_in) {
-        // gathered by the caller
-    } else if (box_order)
-        copy_kernel<<<dim3((unsigned)cdiv(P.ns(), 256)), dim3(256), 0, st>>>(b, P.ns(), P.bs.p);
-    else
+    hipEvent_t now = P.t_begin = mark();   // the last mark: nothing has been launched on the stream since
+    if (!bs_in) {   // else gathered by the caller
         if (P.sroute())
             route_gather(*P.sroute(), b, P.bs.p, P.route_a.p, P.route_b.p, st);
         else
             gather_kernel<<<dim3((unsigned)cdiv(P.ns(), 256)), dim3(256), 0, st>>>(b, P.sperm(), P.ns(), P.bs.p);
-    F3M_HIP(hipEventRecord(P.ev[9], st));
+        now = mark();
+    }
+    P.t_in = now;
     // The near field goes to the plan's second stream (vector ALU work) and overlaps the
     // far field (matrix-core work) on the caller's stream; with no_overlap it runs in line.
     hipStream_t sn = P.side ? P.side : st;
     if (P.side) {
         F3M_HIP(hipEventRecord(P.ev_fork, st));
         F3M_HIP(hipStreamWaitEvent(P.side, P.ev_fork, 0));
+        F3M_HIP(hipEventRecord(P.ev_p2p0, sn));
     }
-    F3M_HIP(hipEventRecord(P.ev_p2p0, sn));
     // exact sums over a CSR list of box pairs of one depth (target tiles given), into yn
     auto direct_pairs = [&](int l, const uint64_t *row_ptr, const uint32_t *cols, const uint32_t *tile_box,
                             const uint32_t *tile_first, int64_t ntiles, int accumulate,
@@ -2523,20 +2526,36 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         }
     }
     F3M_HIP(hipGetLastError());
-    F3M_HIP(hipEventRecord(P.ev_p2p1, sn));
-    if (P.side) F3M_HIP(hipEventRecord(P.ev_join, P.side));
-    zero_kernel<<<dim3(gn), dim3(256), 0, st>>>(P.ys.p, n);
-    F3M_HIP(hipEventRecord(P.ev[10], st));
-    // six events per depth: [0,1] bracket the upward pass (P2M or M2M), [2,3] the M2L, [4,5] the
+    if (P.side) {
+        F3M_HIP(hipEventRecord(P.ev_p2p1, P.side));
+        F3M_HIP(hipEventRecord(P.ev_join, P.side));
+        P.t_p2p0 = P.ev_p2p0;
+        P.t_p2p1 = P.ev_p2p1;
+    } else {
+        P.t_p2p0 = now;
+        if (!yn_in && !no_near) now = mark();
+        P.t_p2p1 = now;
+    }
+    // six marks per depth: [0,1] bracket the upward pass (P2M or M2M), [2,3] the M2L, [4,5] the
     // downward pass (L2L and/or L2P) of that depth
-    P.far_events.resize((size_t)(P.L + 1) * 6, nullptr);
-    auto level_events = [&](int l) {
-        hipEvent_t *ev = &P.far_events[(size_t)l * 6];
-        for (int k = 0; k < 6; ++k)
-            if (!ev[k]) F3M_HIP(hipEventCreate(&ev[k]));
-        return ev;
-    };
+    P.far_events.assign((size_t)(P.L + 1) * 6, nullptr);
+    auto level_events = [&](int l) { return &P.far_events[(size_t)l * 6]; };
     const bool tree = P.tree_lmin > 0;   // D = 3, 4 nodes per dimension on depths tree_lmin..tree_lmax
+    // no far pairs, dropped by the adaptive rule (Sec. 4.3), or part of the band of the tree
+    auto on_its_own = [&](int l) {
+        const f3m_level &lv = P.lev[l];
+        return lv.far_sz > 0 && lv.p > 0 && !(P.near_depth && l > P.near_depth) && !(tree && l >= P.tree_lmin && l <= P.tree_lmax);
+    };
+    // Where the band holds every far depth its one L2P writes the far field of every point: nothing to preset, and in box
+    // order it adds the near field and writes the result.
+    bool one_l2p = tree;
+    for (int l = 1; l <= P.L; ++l) one_l2p = one_l2p && !on_its_own(l);
+    const bool direct_out = one_l2p && box_order;
+    if (!one_l2p) {
+        zero_kernel<<<dim3(gn), dim3(256), 0, st>>>(P.ys.p, n);
+        F3M_HIP(hipGetLastError());
+        now = mark();
+    }
     // node weights of the source boxes of a depth, from the points, into P.W (the boxes its chunk list names)
     auto p2m_depth = [&](int l) {
         f3m_level &lv = P.lev[l];
@@ -2619,40 +2638,36 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     // ---- depths that are handled on their own, straight from the points (Fig. 4 steps 1-3)
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
-        // no far pairs, dropped by the adaptive rule (Sec. 4.3), or part of the band below
-        if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && l > P.near_depth) || (tree && l >= P.tree_lmin && l <= P.tree_lmax)) continue;
+        if (!on_its_own(l)) continue;
         const int p = lv.p, r = lv.r;
         const NodeArg N = make_nodes(p);
         hipEvent_t *ev = level_events(l);
         const CentreArg C = make_centre(P, l);          // target grid
-        F3M_HIP(hipEventRecord(ev[0], st));
+        ev[0] = now;
         if (lv.far_points) {   // from point to point: no node weights or potentials
             const KronShape KS = kron_shape(P, l);
-            F3M_HIP(hipEventRecord(ev[1], st));
-            F3M_HIP(hipEventRecord(ev[2], st));
+            ev[1] = ev[2] = now;
             run_far_points(P, l, bs, P.ys.p, KS.omin[0], KS.no, st);
-            for (int k = 3; k < 6; ++k) F3M_HIP(hipEventRecord(ev[k], st));
+            ev[3] = ev[4] = ev[5] = now = mark();
             continue;
         }
         p2m_depth(l);
-        F3M_HIP(hipEventRecord(ev[1], st));
-        F3M_HIP(hipEventRecord(ev[2], st));
+        ev[1] = ev[2] = now = mark();
         if (!(lv.far_implicit && run_m2l_stencil(P, l, P.W.p, P.V.p, st))) kron_m2l(l, P.W.p, P.V.p);
-        F3M_HIP(hipEventRecord(ev[3], st));
-        F3M_HIP(hipEventRecord(ev[4], st));
+        ev[3] = ev[4] = now = mark();
         {
             size_t sh = (size_t)(r + P2M_CHUNK * (D * p + 1)) * sizeof(float);
             if (D == 3 && p == 4)
                 l2p34_kernel<<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p,
                                                                       lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C,
-                                                                      P.V.p, P.ys.p, single_chunks(lv));
+                                                                      P.V.p, P.ys.p, P.ys.p, single_chunks(lv));
             else
                 l2p_kernel<D><<<grid_for(lv.nchunks), dim3(P2M_CHUNK), sh, st>>>(
                     P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, p, r, C, N,
                     P.V.p, P.ys.p);
             F3M_HIP(hipGetLastError());
         }
-        F3M_HIP(hipEventRecord(ev[5], st));
+        ev[5] = now = mark();
     }
     // ---- depths tree_lmin..tree_lmax: P2M at the last depth of the band, weights passed upward,
     //      M2L per depth, potentials passed downward, one L2P at the last depth of the band
@@ -2667,7 +2682,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (!P.src) {
             {
                 hipEvent_t *ev = level_events(L);
-                F3M_HIP(hipEventRecord(ev[0], st));
+                ev[0] = now;
                 if (single_chunks(lf))
                     p2m34_pair_kernel<<<grid_for(cdiv(lf.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p,
                                                                                                 lf.nb, make_centre(P, L), lf.Wl.p);
@@ -2679,26 +2694,26 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 if (lf.max_box > P2M_CHUNK)   // some box has several chunks
                     reduce_partials(P, lf, r, lf.Wl.p, st);
                 F3M_HIP(hipGetLastError());
-                F3M_HIP(hipEventRecord(ev[1], st));
+                ev[1] = now = mark();
             }
             for (int l = L - 1; l >= P.tree_lmin; --l) {
                 f3m_level &lv = P.lev[l], &dn = P.lev[l + 1];
                 hipEvent_t *ev = level_events(l);
-                F3M_HIP(hipEventRecord(ev[0], st));
+                ev[0] = now;
                 m2m34_kernel<<<grid_for(lv.nb), dim3(64), 0, st>>>(lv.cstart.p, dn.key.p, lv.nb, P.transfer.p, dn.Wl.p, lv.Wl.p);
                 F3M_HIP(hipGetLastError());
-                F3M_HIP(hipEventRecord(ev[1], st));
+                ev[1] = now = mark();
             }
         }
         for (int l = P.tree_lmin; l <= L; ++l) {
             f3m_level &lv = P.lev[l];
             hipEvent_t *ev = level_events(l);
             if (P.src) {
-                F3M_HIP(hipEventRecord(ev[0], st));
+                ev[0] = now;
                 p2m_depth(l);
-                F3M_HIP(hipEventRecord(ev[1], st));
+                ev[1] = now = mark();
             }
-            F3M_HIP(hipEventRecord(ev[2], st));
+            ev[2] = now;
             if (lv.far_implicit) {
                 if (!run_m2l_stencil(P, l, lv.Wl.p, lv.Vl.p, st, true))   // Wl ends with a row of zeros
                     fail(F3M_ERR_HIP, "internal: depth outside the candidate-grid M2L");
@@ -2707,37 +2722,41 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 zero_kernel<<<dim3((unsigned)cdiv(lv.nb * (int64_t)r, 256)), dim3(256), 0, st>>>(lv.Vl.p, lv.nb * (int64_t)r);
                 kron_m2l(l, P.src ? P.W.p : lv.Wl.p, lv.Vl.p);
             }
-            F3M_HIP(hipEventRecord(ev[3], st));
+            ev[3] = now = mark();
         }
         for (int l = P.tree_lmin + 1; l <= L; ++l) {
             f3m_level &lv = P.lev[l], &up = P.lev[l - 1];
             hipEvent_t *ev = level_events(l);
-            F3M_HIP(hipEventRecord(ev[4], st));
+            ev[4] = now;
             l2l34_kernel<<<grid_for(up.nb), dim3(64), 0, st>>>(up.cstart.p, lv.key.p, up.nb, P.transfer.p, up.Vl.p, lv.Vl.p);
             F3M_HIP(hipGetLastError());
-            if (l < L) F3M_HIP(hipEventRecord(ev[5], st));
+            if (l < L) ev[5] = now = mark();
         }
         {
             hipEvent_t *ev = level_events(L);
-            if (P.tree_lmin == L) F3M_HIP(hipEventRecord(ev[4], st));
+            if (P.tree_lmin == L) ev[4] = now;
+            if (P.side && direct_out) F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
+            const float *base = direct_out ? yn : one_l2p ? nullptr : P.ys.p;
             l2p34_kernel<<<grid_for(cdiv(lf.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p,
                                                                   lf.chunk_first.p, lf.nchunks, make_centre(P, L),
-                                                                  lf.Vl.p, P.ys.p, single_chunks(lf));
+                                                                  lf.Vl.p, base, direct_out ? y : P.ys.p, single_chunks(lf));
             F3M_HIP(hipGetLastError());
-            F3M_HIP(hipEventRecord(ev[5], st));
+            ev[5] = now = mark();
         }
         // the lowest tree depth has no downward pass of its own
-        {
+        if (P.tree_lmin < L) {
             hipEvent_t *ev = level_events(P.tree_lmin);
-            if (P.tree_lmin < L) {
-                F3M_HIP(hipEventRecord(ev[4], st));
-                F3M_HIP(hipEventRecord(ev[5], st));
-            }
+            ev[4] = ev[5] = now;
         }
     }
-    if (P.side) F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
-    F3M_HIP(hipEventRecord(P.ev[11], st));
-    if (box_order) {
+    if (P.side && !direct_out) {
+        F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
+        now = mark();
+    }
+    P.t_out = now;
+    if (direct_out) {
+        // written by the L2P
+    } else if (box_order) {
         add_kernel<<<dim3(gn), dim3(256), 0, st>>>(P.ys.p, yn, n, y);
         F3M_HIP(hipGetLastError());
     } else if (P.route) {
@@ -2746,8 +2765,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         scatter_kernel<<<dim3(gn), dim3(256), 0, st>>>(P.ys.p, yn, P.perm.p, n, y);
         F3M_HIP(hipGetLastError());
     }
-    if (!P.ev[12]) F3M_HIP(hipEventCreate(&P.ev[12]));
-    F3M_HIP(hipEventRecord(P.ev[12], st));
+    P.t_end = direct_out ? now : mark();
     // A product that is being captured into a graph has no times: its event records are nodes of the graph, not
     // time stamps the host can read (f3m_stage_times then reports the stages of the plan only).
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;

@@ -158,7 +158,10 @@ struct f3m_plan_s {
     hipEvent_t ev[16] = {nullptr};
     std::vector<hipEvent_t> plan_events;  // two per depth while the plan is built
     std::vector<std::vector<float>> host_tabs;   // tables on their way to the device, until the plan is complete
-    std::vector<hipEvent_t> far_events;   // 6 per depth, around the far-field kernels of that depth
+    // Times of a product: an event at every boundary between its stages, in order (marks); the others name them.
+    // far_events: 6 per depth, around the far-field kernels of that depth.
+    std::vector<hipEvent_t> marks, far_events;
+    hipEvent_t t_begin = nullptr, t_in = nullptr, t_p2p0 = nullptr, t_p2p1 = nullptr, t_out = nullptr, t_end = nullptr;
     bool have_plan_times = false, have_kmvm_times = false, have_far_point_pairs = false;
     f3m_times times = {};
     ~f3m_plan_s();
@@ -193,7 +196,8 @@ void route_gather_rows3(const f3m_route &R, const float *in, float *out, float *
                                                                       // rows of 3 floats; tmp: 3 n floats
 void materialize_far(const f3m_plan_s &P, int level, uint32_t *cols_dev, hipStream_t st);   // far rows of an implicit depth
 // kmvm.hip
-// box_order: b and y are already in the plan's box order (one-set plans only; used by the solver)
+// box_order: b and y are already in the plan's box order, b with PAD_POINTS zeros behind it (one-set plans only; used by
+// the solver)
 void run_kmvm(f3m_plan_s &P, const float *b, float *y, hipStream_t st, bool box_order = false);
 void run_kmvm_multi(f3m_plan_s &P, const float *B, int64_t ldb, float *Y, int64_t ldy, int m, hipStream_t st);
 int p2p_nsplit(const f3m_plan_s &P, int l, int64_t ntiles);   // source slices per target tile of the near field (1: none)

@@ -12,7 +12,7 @@ f3m_plan_s::~f3m_plan_s() {
         if (e) (void)hipEventDestroy(e);
     for (auto &e : plan_events)
         if (e) (void)hipEventDestroy(e);
-    for (auto &e : far_events)
+    for (auto &e : marks)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {ev_fork, ev_join, ev_p2p0, ev_p2p1})
         if (e) (void)hipEventDestroy(e);

@@ -127,7 +127,8 @@ void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter,
     DevBuf<double> part, scal;
     xs.alloc((size_t)n);
     r.alloc((size_t)n);
-    p.alloc((size_t)n);
+    p.alloc((size_t)n + PAD_POINTS);
+    F3M_HIP(hipMemsetAsync(p.p + n, 0, PAD_POINTS * sizeof(float), st));
     q.alloc((size_t)n);
     const int blocks = (int)std::min<int64_t>(CG_BLOCKS, cdiv(n, CG_NT));
     part.alloc((size_t)blocks);

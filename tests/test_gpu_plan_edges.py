@@ -69,3 +69,21 @@ def test_plans_in_turn_and_from_two_threads():
     for t in threads:
         t.join()
     assert not bad
+
+
+# overlap and the solver: the far field's last pass adds the near field, which another stream may have computed
+@pytest.mark.parametrize("n,zeta,gamma", [(20_000, 128, 0.5), (30_001, 12, 1.7), (400, 128, 0.5)])
+def test_solver_with_and_without_overlap(n, zeta, gamma):
+    X = inputs.points_uniform(n, 3, 97).to(DEV)
+    b = inputs.rhs_normal(n, 98).to(DEV)
+    got = []
+    for overlap in (False, True):
+        plan = f3m.Plan(X, gamma, 4, 2.0, leaf_max=zeta, overlap=overlap)
+        x, it, hist = plan.cg_solve(b, 0.1 * n, tol=0.0, max_iter=4)
+        t = plan.stage_times()
+        assert all(np.isfinite(v) and v >= 0.0 for v in t.values())
+        got.append(x)
+        res = float((plan.kmvm(x) + 0.1 * n * x - b).norm() / b.norm())
+        assert abs(res - float(hist[-1])) <= 1e-5
+        plan.close()
+    assert torch.equal(got[0], got[1])
