@@ -701,6 +701,92 @@ __global__ __launch_bounds__(64) void lists_parent_kernel(int pass, int64_t npar
     }
 }
 
+// The same with a wavefront per target box: 64 candidates at a time, a lane each, ballots keep the entries in candidate
+// order.  lists_kernel waits for one dependent read of a cell after the other; with few or long rows (few boxes; up to
+// 2^D children of up to 3^D near boxes) there are not enough threads to hide that.
+template <int D>
+__global__ __launch_bounds__(64) void lists_wave_kernel(int pass, int64_t nb, const uint32_t *__restrict__ parent,
+                                                        const int32_t *__restrict__ cell,
+                                                        const uint64_t *__restrict__ up_near_ptr,
+                                                        const uint32_t *__restrict__ up_near_col,
+                                                        const uint32_t *__restrict__ up_cstart, ListArg A) {
+    __shared__ uint32_t cend[64], cdelta[64];   // near boxes of the parent: end in the sequence, position -> box rank
+    const int64_t a = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (a >= nb) return;
+    const int lane = threadIdx.x;
+    int32_t ca[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) ca[d] = cell[a * D + d];
+    const uint32_t P = parent[a];
+    uint64_t nbase = pass && A.near_ptr ? A.near_ptr[a] : 0, fbase = pass && A.far_ptr ? A.far_ptr[a] : 0,
+             sbase = pass && A.small_ptr ? A.small_ptr[a] : 0;
+    uint32_t nn = 0, nf = 0, ns = 0;
+    const uint32_t cnt_a = A.rho ? A.start[a + 1] - A.start[a] : 0u;
+    const uint64_t e0 = up_near_ptr[P], e1 = up_near_ptr[P + 1];
+    for (uint64_t er = e0; er < e1; er += 64) {
+        const int m = (int)(e1 - er < 64 ? e1 - er : 64);
+        uint32_t b0 = 0, nq = 0;
+        if (lane < m) {
+            const uint32_t Q = up_near_col[er + lane];
+            b0 = up_cstart[Q];
+            nq = up_cstart[Q + 1] - b0;
+        }
+        const uint32_t end = wave_incl_scan_u32(nq);
+        const uint32_t S = __builtin_amdgcn_readlane(end, 63);   // candidates of this round
+        __syncthreads();   // the previous round has been read
+        cend[lane] = end;
+        cdelta[lane] = b0 - (end - nq);
+        __syncthreads();
+        for (uint32_t w0 = 0; w0 < S; w0 += 64) {
+            const bool live = w0 + lane < S;
+            const uint32_t p = min(w0 + (uint32_t)lane, S - 1u);
+            int lo = 0;   // first entry with cend > p (the last one has S > p)
+#pragma unroll
+            for (int s = 32; s > 0; s >>= 1) lo += cend[lo + s - 1] <= p ? s : 0;
+            const uint32_t bq = p + cdelta[lo];
+            int d2 = 0;
+            int o[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                o[d] = A.cell_src[(int64_t)bq * D + d] - ca[d];
+                d2 += o[d] * o[d];
+            }
+            bool far_rule = d2 >= A.T;
+            if (A.shifted) {
+                double s = 0.0;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const double t = __dadd_rn((double)o[d], A.u[d]);
+                    s = __dadd_rn(s, __dmul_rn(t, t));
+                }
+                far_rule = s >= A.theta2;
+            }
+            const bool is_small = live && A.rho && A.mode != 1 && cnt_a + (A.start_src[bq + 1] - A.start_src[bq]) <= A.rho;
+            const bool is_far = live && !is_small && (A.mode == 2 || (A.mode == 0 && far_rule));
+            const bool is_near = live && !is_small && !is_far;
+            const uint64_t mn = __ballot(is_near), mf = __ballot(is_far), ms = __ballot(is_small);
+            if (pass) {
+                const uint64_t below = (1ull << lane) - 1ull;
+                if (A.near_col && is_near) A.near_col[nbase + (uint32_t)__popcll(mn & below)] = bq;
+                if (A.far_col && is_far) A.far_col[fbase + (uint32_t)__popcll(mf & below)] = bq;
+                if (A.small_col && is_small) A.small_col[sbase + (uint32_t)__popcll(ms & below)] = bq;
+                nbase += (uint32_t)__popcll(mn);
+                fbase += (uint32_t)__popcll(mf);
+                sbase += (uint32_t)__popcll(ms);
+            } else {
+                nn += (uint32_t)__popcll(mn);
+                nf += (uint32_t)__popcll(mf);
+                ns += (uint32_t)__popcll(ms);
+            }
+        }
+    }
+    if (!pass && lane == 0) {
+        A.cnt_near[a] = nn;
+        A.cnt_far[a] = nf;
+        if (A.cnt_small) A.cnt_small[a] = ns;
+    }
+}
+
 // the rule of the depth is the plain far rule on one point set: the lists can be built by parent
 static bool lists_by_parent(const ListArg &A, int D) { return D <= 3 && !A.shifted && A.rho == 0 && A.mode == 0; }
 
@@ -720,20 +806,73 @@ static ListArg list_rules(const f3m_plan_s &P, int level) {
     return A;
 }
 
-// point pairs of a CSR interaction list: |p| * sum of |q| over the row of p
-struct NearPairsIn {
-    const uint32_t *start, *start_src;   // point intervals of the target boxes / of the source boxes
-    const uint64_t *near_ptr;
-    const uint32_t *near_col;
-    __device__ uint64_t operator()(int64_t a) const {
+// One pass over the candidates of a depth.  By parent where the rule allows it; else a wavefront per box above three
+// dimensions, where rows are long (n = 3e5, D = 7: plan and product 48.8 -> 37.2 ms), and for fewer than 2^17 boxes, whose threads would not fill the chip (two
+// sets, 1e7 x 1e5: 3.14 -> 2.84 ms);
+// with more boxes of at most 216 candidates each the thread per box issues a quarter of the instructions.
+template <int D>
+static void launch_lists(int pass, const f3m_plan_s &P, int level, const ListArg &A, bool by_parent, hipStream_t st) {
+    const f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
+    const uint32_t *up_cstart = P.slev(level - 1).cstart.p;
+    bool done = false;
+    if constexpr (D <= 3) {
+        if (by_parent) {
+            lists_parent_kernel<D><<<dim3((unsigned)((up.nb + 7) / 8 * 8)), dim3(64), 0, st>>>(
+                pass, up.nb, up.cstart.p, lv.cell.p, up.near_ptr.p, up.near_col.p, A);
+            done = true;
+        } else if (lv.nb >= (1 << 17)) {
+            lists_kernel<D><<<dim3((unsigned)cdiv(lv.nb, 128)), dim3(128), 0, st>>>(
+                pass, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p, up.near_col.p, up_cstart, A);
+            done = true;
+        }
+    }
+    if (!done) {
+        const int64_t gx = std::min<int64_t>(lv.nb, 1 << 20);
+        lists_wave_kernel<D><<<dim3((unsigned)gx, (unsigned)cdiv(lv.nb, gx)), dim3(64), 0, st>>>(
+            pass, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p, up.near_col.p, up_cstart, A);
+    }
+    F3M_HIP(hipGetLastError());
+}
+
+// Point pairs of a CSR interaction list, |p| * sum of |q| over the row of p: a wavefront per row, a partial sum per
+// workgroup.
+__global__ __launch_bounds__(256) void point_pairs_kernel(const uint32_t *__restrict__ start,
+                                                          const uint32_t *__restrict__ start_src,
+                                                          const uint64_t *__restrict__ row_ptr,
+                                                          const uint32_t *__restrict__ cols, int64_t nb,
+                                                          uint64_t *__restrict__ part) {
+    __shared__ uint64_t wsum[4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t total = 0;
+    for (int64_t a = (int64_t)blockIdx.x * 4 + w; a < nb; a += (int64_t)gridDim.x * 4) {
         uint64_t s = 0;
-        for (uint64_t e = near_ptr[a]; e < near_ptr[a + 1]; ++e) {
-            uint32_t q = near_col[e];
+        for (uint64_t e = row_ptr[a] + lane; e < row_ptr[a + 1]; e += 64) {
+            const uint32_t q = cols[e];
             s += start_src[q + 1] - start_src[q];
         }
-        return s * (uint64_t)(start[a + 1] - start[a]);
+        total += s * (uint64_t)(start[a + 1] - start[a]);
     }
-};
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+    if (lane == 0) wsum[w] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+}
+
+// waits for the stream (the thread has an open scope of it)
+static int64_t point_pairs(const uint32_t *start, const uint32_t *start_src, const uint64_t *row_ptr, const uint32_t *cols,
+                           int64_t nb, hipStream_t st) {
+    if (nb <= 0) return 0;
+    const int64_t grid = std::min<int64_t>(4096, cdiv(nb, 4));
+    DevBuf<uint64_t> part;
+    part.alloc((size_t)grid);
+    uint64_t *total = scope_words();
+    point_pairs_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(start, start_src, row_ptr, cols, nb, part.p);
+    scan_block_sums(part.p, grid, total, st);
+    F3M_HIP(hipGetLastError());
+    F3M_HIP(hipStreamSynchronize(st));
+    return (int64_t)*total;
+}
 
 // offsets of n items, and the total behind them
 struct PtrOut {
@@ -1133,12 +1272,10 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             lv.far_sz = 0;
         } else {
             f3m_level &up = P.lev[l - 1];
-            const f3m_level &sup = P.slev(l - 1);
             DevBuf<uint32_t> cn, cf, cs;
             cn.alloc((size_t)lv.nb);
             cf.alloc((size_t)lv.nb);
             if (P.rho > 0) cs.alloc((size_t)lv.nb);
-            unsigned grid = (unsigned)cdiv(lv.nb, 128);
             // Sec. 4.3: once the boxes pass the smoothness criterion every pair left is interpolated
             lv.smooth = !P.force_all_near && smooth_rule((double)P.E, l, D, (double)P.gamma, (double)P.eta_smooth);
             if (lv.smooth) P.smooth_depth = l;
@@ -1146,18 +1283,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             A.cnt_near = cn.p;
             A.cnt_far = cf.p;
             A.cnt_small = cs.p;
-            if constexpr (D <= 3) {
-                if (lists_by_parent(A, D))
-                    lists_parent_kernel<D><<<dim3((unsigned)((up.nb + 7) / 8 * 8)), dim3(64), 0, st>>>(0, up.nb, up.cstart.p, lv.cell.p,
-                                                                                       up.near_ptr.p, up.near_col.p, A);
-                else
-                    lists_kernel<D><<<dim3(grid), dim3(128), 0, st>>>(0, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p,
-                                                                     up.near_col.p, sup.cstart.p, A);
-            } else {
-                lists_kernel<D><<<dim3(grid), dim3(128), 0, st>>>(0, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p,
-                                                                 up.near_col.p, sup.cstart.p, A);
-            }
-            F3M_HIP(hipGetLastError());
+            launch_lists<D>(0, P, l, A, lists_by_parent(A, D), st);
             words[HW_SMALL] = 0;
             exclusive_scan(U32In{cn.p}, lv.nb, PtrOut{lv.near_ptr.p, lv.nb}, words + HW_NEAR, st);
             exclusive_scan(U32In{cf.p}, lv.nb, PtrOut{lv.far_ptr.p, lv.nb}, words + HW_FAR, st);
@@ -1189,9 +1315,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                     near_interp_error((double)P.E, l, (double)P.gamma) <= 0x1p-24)
                     P.near_depth = l;
             } else if (tf > 0 && far_points_allowed(P, l)) {
-                ScanState S;
-                scan_prepare(NearPairsIn{up.start.p, up.start.p, up.near_ptr.p, up.near_col.p}, up.nb, S, st);
-                lv.far_points = far_points_pays(P, l, (int64_t)S.total);
+                lv.far_points = far_points_pays(P, l, point_pairs(up.start.p, up.start.p, up.near_ptr.p, up.near_col.p, up.nb, st));
                 lv.far_col.alloc(lv.far_points ? 0 : (size_t)tf, tally);
             } else {
                 lv.far_col.alloc((size_t)tf, tally);
@@ -1209,18 +1333,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                     A.st_child = lv.st_child.p;
                 }
             }
-            if constexpr (D <= 3) {
-                if (lists_by_parent(A, D))
-                    lists_parent_kernel<D><<<dim3((unsigned)((up.nb + 7) / 8 * 8)), dim3(64), 0, st>>>(1, up.nb, up.cstart.p, lv.cell.p,
-                                                                                       up.near_ptr.p, up.near_col.p, A);
-                else
-                    lists_kernel<D><<<dim3(grid), dim3(128), 0, st>>>(1, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p,
-                                                                     up.near_col.p, sup.cstart.p, A);
-            } else {
-                lists_kernel<D><<<dim3(grid), dim3(128), 0, st>>>(1, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p,
-                                                                 up.near_col.p, sup.cstart.p, A);
-            }
-            F3M_HIP(hipGetLastError());
+            launch_lists<D>(1, P, l, A, lists_by_parent(A, D), st);
         }
         F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l + 1], st));
         // while interactions remain and the largest box of either tree is above zeta (Algorithm 1)
@@ -1378,25 +1491,19 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
 // Far rows (CSR columns, ascending) of a depth that keeps only their lengths: the fill pass of
 // the list kernel with the near side switched off.  cols_dev holds far_sz entries.
 void materialize_far(const f3m_plan_s &P, int level, uint32_t *cols_dev, hipStream_t st) {
-    const f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
-    const unsigned grid = (unsigned)cdiv(lv.nb, 128);
+    const f3m_level &lv = P.lev[level];
     ListArg A = list_rules(P, level);
     A.far_ptr = lv.far_ptr.p;
     A.far_col = cols_dev;
-    auto launch = [&](auto kern) {
-        kern<<<dim3(grid), dim3(128), 0, st>>>(1, lv.nb, lv.parent.p, lv.cell.p, up.near_ptr.p, up.near_col.p,
-                                               P.slev(level - 1).cstart.p, A);
-    };
     switch (P.D) {
-        case 1: launch(lists_kernel<1>); break;
-        case 2: launch(lists_kernel<2>); break;
-        case 3: launch(lists_kernel<3>); break;
-        case 4: launch(lists_kernel<4>); break;
-        case 5: launch(lists_kernel<5>); break;
-        case 6: launch(lists_kernel<6>); break;
-        default: launch(lists_kernel<7>); break;
+        case 1: launch_lists<1>(1, P, level, A, false, st); break;
+        case 2: launch_lists<2>(1, P, level, A, false, st); break;
+        case 3: launch_lists<3>(1, P, level, A, false, st); break;
+        case 4: launch_lists<4>(1, P, level, A, false, st); break;
+        case 5: launch_lists<5>(1, P, level, A, false, st); break;
+        case 6: launch_lists<6>(1, P, level, A, false, st); break;
+        default: launch_lists<7>(1, P, level, A, false, st); break;
     }
-    F3M_HIP(hipGetLastError());
     F3M_HIP(hipStreamSynchronize(st));
 }
 
@@ -1406,33 +1513,22 @@ void materialize_far(const f3m_plan_s &P, int level, uint32_t *cols_dev, hipStre
 void compute_far_point_pairs(f3m_plan_s &P) {
     if (P.have_far_point_pairs) return;
     ReleaseScope scope((hipStream_t) nullptr);
-    {
-        ScanState S;
-        const f3m_level &lf = P.lev[P.L];
-        scan_prepare(NearPairsIn{lf.start.p, P.slev(P.L).start.p, lf.near_ptr.p, lf.near_col.p}, lf.nb, S, nullptr);
-        P.near_point_pairs = (int64_t)S.total;
-    }
+    auto pairs = [&](int l, const uint64_t *row_ptr, const uint32_t *cols) {
+        return point_pairs(P.lev[l].start.p, P.slev(l).start.p, row_ptr, cols, P.lev[l].nb, nullptr);
+    };
+    P.near_point_pairs = pairs(P.L, P.lev[P.L].near_ptr.p, P.lev[P.L].near_col.p);
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
-        lv.small_point_pairs = 0;
-        if (lv.small_sz > 0) {
-            ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.small_ptr.p, lv.small_col.p}, lv.nb, S, nullptr);
-            lv.small_point_pairs = (int64_t)S.total;
-        }
+        lv.small_point_pairs = lv.small_sz > 0 ? pairs(l, lv.small_ptr.p, lv.small_col.p) : 0;
         lv.far_point_pairs = 0;
         if (lv.far_sz == 0) continue;
         if (lv.far_implicit || lv.far_points) {
             DevBuf<uint32_t> cols;
             cols.alloc((size_t)lv.far_sz);
             materialize_far(P, l, cols.p, nullptr);
-            ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, cols.p}, lv.nb, S, nullptr);
-            lv.far_point_pairs = (int64_t)S.total;
+            lv.far_point_pairs = pairs(l, lv.far_ptr.p, cols.p);
         } else {
-            ScanState S;
-            scan_prepare(NearPairsIn{lv.start.p, P.slev(l).start.p, lv.far_ptr.p, lv.far_col.p}, lv.nb, S, nullptr);
-            lv.far_point_pairs = (int64_t)S.total;
+            lv.far_point_pairs = pairs(l, lv.far_ptr.p, lv.far_col.p);
         }
     }
     P.have_far_point_pairs = true;
