@@ -934,7 +934,7 @@ __global__ __launch_bounds__(256) void p2p_split_sum_kernel(const float *__restr
 template <int D>
 constexpr int small_tt() { return D <= 4 ? 16 : 8; }
 
-template <int D, int TT>
+template <int D, int TT, int MB = 1>
 __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict__ Xt,
                                                         const uint32_t *__restrict__ startT,
                                                         const float *__restrict__ Xs, const float *__restrict__ bs,
@@ -943,7 +943,8 @@ __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict_
                                                         const uint32_t *__restrict__ cols,
                                                         const uint32_t *__restrict__ tile_box,
                                                         const uint32_t *__restrict__ tile_first, int64_t ntiles,
-                                                        float nc2, float *__restrict__ ys, int overflow, int accumulate) {
+                                                        float nc2, float *__restrict__ ys, int overflow, int accumulate,
+                                                         MultiArg MA) {
     const int lane = threadIdx.x & 63;
     const int64_t t = block_index() * 4 + (threadIdx.x >> 6);
     if (t >= ntiles) return;
@@ -959,9 +960,12 @@ __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict_
 #pragma unroll
         for (int d = 0; d < D; ++d) xt[tt][d] = Xt[(int64_t)kt * D + d];
     }
-    float acc[TT];
+    float acc[TT][MB];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) acc[tt] = 0.f;
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) acc[tt][j] = 0.f;
+    auto rhs = [&](int j, uint32_t src) { return MB == 1 ? bs[src] : MA.bs[j][src]; };
 
     const uint64_t e0 = row_ptr[a], e1 = row_ptr[a + 1];
     for (uint64_t er = e0; er < e1; er += 64) {   // rounds of up to 64 boxes of the row
@@ -992,28 +996,33 @@ __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict_
             }
             return src;
         };
-        float xn[D], bn;
+        float xn[D], bn[MB];
         {
             const uint32_t src = locate(0);
 #pragma unroll
             for (int d = 0; d < D; ++d) xn[d] = Xs[(int64_t)src * D + d];
-            bn = bs[src];
+#pragma unroll
+            for (int j = 0; j < MB; ++j) bn[j] = rhs(j, src);
         }
         for (uint32_t w0 = 0; w0 < S; w0 += 64) {
             float x[D];
 #pragma unroll
             for (int d = 0; d < D; ++d) x[d] = xn[d];
-            float bv = bn;
+            float bv[MB];
+#pragma unroll
+            for (int j = 0; j < MB; ++j) bv[j] = bn[j];
             if (w0 + 64 > S) {      // last step only: positions behind the sequence contribute nothing
                 asm volatile("");   // keeps this a branch (as a select it costs every step three instructions)
-                bv = w0 + lane < S ? bv : 0.f;
+#pragma unroll
+                for (int j = 0; j < MB; ++j) bv[j] = w0 + lane < S ? bv[j] : 0.f;
             }
             // the loads of the next step are in flight during this one (the last step loads its own
             // sources again, so the number of loads in flight is fixed)
             const uint32_t nsrc = locate(w0 + 64 < S ? w0 + 64 : w0);
 #pragma unroll
             for (int d = 0; d < D; ++d) xn[d] = Xs[(int64_t)nsrc * D + d];
-            bn = bs[nsrc];
+#pragma unroll
+            for (int j = 0; j < MB; ++j) bn[j] = rhs(j, nsrc);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
                 if (tt < nt) {
@@ -1023,23 +1032,29 @@ __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict_
                         const float df = x[d] - xt[tt][d];
                         r2 = fmaf(df, df, r2);
                     }
-                    acc[tt] = fmaf(__builtin_amdgcn_exp2f(r2 * nc2), bv, acc[tt]);
+                    const float e = __builtin_amdgcn_exp2f(r2 * nc2);
+#pragma unroll
+                    for (int j = 0; j < MB; ++j) acc[tt][j] = fmaf(e, bv[j], acc[tt][j]);
                 }
             }
         }
     }
     // sums over the lanes; lane tt keeps the total of target tt
-    float res = 0.f;
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (tt < nt) {
-            float v = acc[tt];
+    for (int j = 0; j < MB; ++j) {
+        float res = 0.f;
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-            if (lane == tt) res = v;
+        for (int tt = 0; tt < TT; ++tt) {
+            if (tt < nt) {
+                float v = acc[tt][j];
+#pragma unroll
+                for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+                if (lane == tt) res = v;
+            }
         }
+        float *out = MB == 1 ? ys : MA.ys[j];
+        if (lane < nt) out[k0 + lane] = accumulate ? out[k0 + lane] + res : res;
     }
-    if (lane < nt) ys[k0 + lane] = accumulate ? ys[k0 + lane] + res : res;
 }
 
 // exact product, all pairs (Sec. 2, KeOps paragraph): targets are the rows of X (nx of them), sources the rows of Y
@@ -2513,7 +2528,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (P.notiles > 0)
             p2p_small_kernel<D, overflow_targets(D)><<<grid_for(cdiv(P.notiles, 4)), dim3(256), 0, sn>>>(
                 P.Xs.p, leaf.start.p, Ys, bs, P.slev(P.L).start.p, leaf.near_ptr.p, leaf.near_col.p, P.otile_box.p,
-                P.otile_first.p, P.notiles, nc2, P.yn.p, 1, 0);
+                P.otile_first.p, P.notiles, nc2, P.yn.p, 1, 0, MultiArg{});
     }
     // small-field pairs of every depth (Sec. 4.2), added on top
     for (int l = 1; l <= P.L && !yn_in; ++l) {
@@ -2521,7 +2536,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (lv.small_sz > 0) {
             p2p_small_kernel<D, small_tt<D>()><<<grid_for(cdiv(lv.sm_ntiles, 4)), dim3(256), 0, sn>>>(
                 P.Xs.p, lv.start.p, Ys, bs, P.slev(l).start.p, lv.small_ptr.p, lv.small_col.p, lv.sm_tile_box.p,
-                lv.sm_tile_first.p, lv.sm_ntiles, nc2, P.yn.p, 0, 1);
+                lv.sm_tile_first.p, lv.sm_ntiles, nc2, P.yn.p, 0, 1, MultiArg{});
             F3M_HIP(hipGetLastError());
         }
     }
@@ -2824,10 +2839,14 @@ void run_kmvm_multi(f3m_plan_s &P, const float *B, int64_t ldb, float *Y, int64_
         F3M_HIP(hipGetLastError());
         if (P.notiles > 0) {
             const float nc2 = (float)(-1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma));
-            for (int j = 0; j < mb; ++j)
-                p2p_small_kernel<3, overflow_targets(3)><<<grid_for(cdiv(P.notiles, 4)), dim3(256), 0, st>>>(
-                    P.Xs.p, leaf.start.p, P.Ys(), MA.bs[j], P.slev(P.L).start.p, leaf.near_ptr.p, leaf.near_col.p,
-                    P.otile_box.p, P.otile_first.p, P.notiles, nc2, MA.ys[j], 1, 0);
+            auto overflow = [&](auto kern) {
+                kern<<<grid_for(cdiv(P.notiles, 4)), dim3(256), 0, st>>>(
+                    P.Xs.p, leaf.start.p, P.Ys(), nullptr, P.slev(P.L).start.p, leaf.near_ptr.p, leaf.near_col.p,
+                    P.otile_box.p, P.otile_first.p, P.notiles, nc2, nullptr, 1, 0, MA);
+            };
+            if (mb == 2) overflow(p2p_small_kernel<3, overflow_targets(3), 2>);
+            else if (mb == 3) overflow(p2p_small_kernel<3, overflow_targets(3), 3>);
+            else overflow(p2p_small_kernel<3, overflow_targets(3), 4>);
             F3M_HIP(hipGetLastError());
         }
         for (int j = 0; j < mb; ++j)
