@@ -807,9 +807,9 @@ static ListArg list_rules(const f3m_plan_s &P, int level) {
 }
 
 // One pass over the candidates of a depth.  By parent where the rule allows it; else a wavefront per box above three
-// dimensions, where rows are long (n = 3e5, D = 7: plan and product 48.8 -> 37.2 ms), and for fewer than 2^17 boxes, whose threads would not fill the chip (two
-// sets, 1e7 x 1e5: 3.14 -> 2.84 ms);
-// with more boxes of at most 216 candidates each the thread per box issues a quarter of the instructions.
+// dimensions, where rows are long (n = 3e5, D = 7: plan and product 48.8 -> 37.2 ms), and for fewer than 2^17 boxes,
+// whose threads would not fill the chip (two sets, 1e7 x 1e5: 3.14 -> 2.84 ms); with more boxes of at most 216
+// candidates each the thread per box issues a quarter of the instructions.
 template <int D>
 static void launch_lists(int pass, const f3m_plan_s &P, int level, const ListArg &A, bool by_parent, hipStream_t st) {
     const f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
