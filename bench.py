@@ -297,14 +297,14 @@ def main():
     if far_L > 0 and m2l_ms > 0:
         # algorithmic: 2 r^2 flop per far pair (the dense node-to-node product).  For D = 3 with 4 nodes per
         # dimension the kernel applies the Kronecker factors per candidate / line / plane of the 6x6x6 grid around
-        # the parent, and shares the line and plane sums between the eight children: 936 factor applications of 256
-        # multiply-adds per parent (117 per target box) instead of 189 x 4096 per target, on the vector ALU.
+        # the parent, and shares the line and plane sums between the eight children: 672 factor applications of 256
+        # multiply-adds per parent (84 per target box) instead of 189 x 4096 per target, on the vector ALU.
         # Every other shape applies D one-dimensional factors per far pair: 2 D r p flop.
         # `achieved` counts the multiply-adds it executes; `algorithmic_tflops` the dense equivalent.
         t = m2l_ms * 1e-3
         if D == 3 and cfg["p"] == 4 and cfg["theta"] == 2.0 and not args.xy:
             # (78 where the near pairs of the depth are interpolated too: nothing is taken off the sum over all candidates)
-            executed = 2.0 * (78 if near_interpolated else 117) * 256 * nb_L
+            executed = 2.0 * (78 if near_interpolated else 84) * 256 * nb_L
             kernel = "m2l_stencil_shared_kernel"
         else:
             executed = 2.0 * D * r * cfg["p"] * far_L

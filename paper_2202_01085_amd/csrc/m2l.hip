@@ -209,9 +209,13 @@ __global__ __launch_bounds__(512) void m2l_stencil_kernel(const uint64_t *__rest
 //   Y_{tx,ty}(cz) = sum_cy G_{cy-2-ty} X_tx(cy, cz)             4 x 6 planes, 6 applications each
 // serve two, and a target needs only
 //   V_all = sum_cz G_{cz-2-tz} Y_{tx,ty}(cz)                    6 applications
-//   V_t   = V_all - sum over the near block, again by lines and planes: 27 + 9 + 3 applications.
-// Per parent 432 + 144 + 8 x (6 + 39) = 936 applications of a 4 x 4 factor to a 64-vector instead
-// of 8 x 231.  Rows of absent candidates are zero in LDS, so no masks are needed.  The
+// from which the same sums over the near block are taken plane by plane.  The near candidates of a line are the first
+// three applications of its sum, so they cost nothing; their 4 x 4 plane sums take 3 applications each.
+// Per parent 432 + 144 + 48 + 48 = 672 applications of a 4 x 4 factor to a 64-vector instead of 8 x 231.  The rows of
+// the candidates go from memory into the registers of the wavefront that sums their line, zeros for absent ones: no
+// masks, and with 37 KB of LDS three workgroups share a compute unit (with the rows in LDS, 80 KB, it was two, and
+// the kernel waits at its barriers: plan and product of 1e6 normal points
+// 2.63 -> 2.35 ms, of 1e7 points the product 2.63 -> 2.45, four columns of 3e6 points 4.51 -> 3.78).  The
 // subtraction costs no accuracy that matters: |near part| / |far part| is of order one for wide
 // kernels, and for narrow ones both are part of a result dominated by the near field itself.
 // all_far (the smooth depth of Sec. 4.3, every candidate interpolated): no subtraction.
@@ -262,54 +266,78 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
                                                                  const float *__restrict__ G, int all_far,
                                                                  uint32_t zero_row,
                                                                  const float *__restrict__ W, float *__restrict__ V) {
-    __shared__ float rows[ST_CAND * 64];
     __shared__ float xl[2 * 36 * 64];       // X_tx(cy, cz) at [(tx * 36 + cy + 6 cz) * 64 + node]
+    __shared__ float xn[2 * 16 * 64];       // the same over the near candidates only, 1 <= cy, cz <= 4
     __shared__ float yp[4 * 6 * 64];        // Y_{tx,ty}(cz) at [((tx + 2 ty) * 6 + cz) * 64 + node]
-    // the candidate ranks are needed only while the rows are loaded and live in the memory of xl
-    // (two workgroups per compute unit fit only below 80 KB each)
-    uint32_t *cand = reinterpret_cast<uint32_t *>(xl);
+    __shared__ float yn[4 * 4 * 64];        // near, 1 <= cz <= 4
     __shared__ float gs[7 * 16];            // the factor table
-    // (the wavefront's number in a scalar register: the row addresses are then formed by scalar instructions)
+    // (the wavefront's number in a scalar register: ranks and row addresses are then scalar work)
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive parents (neighbours in space) on the same XCD, so that its L2 serves the overlap
     const int64_t bi = block_index2();
     const int64_t pb = (bi & 7) * per_xcd + (bi >> 3);
     if ((bi >> 3) >= per_xcd || pb >= nparents) return;
-    if (tid < ST_CAND) cand[tid] = cand_tab[pb * ST_CAND + tid];
-    if (tid >= 256 && tid < 256 + 7 * 16) gs[tid - 256] = G[tid - 256];
+    if (tid < 7 * 16) gs[tid] = G[tid];
     const uint32_t t = child_tab[pb * 8 + w];   // the child with parity w (wave-uniform), or ~0
-    __syncthreads();
-    // node weights of the candidates into LDS at their grid position, zeros for absent ones: 27 rows
-    // per wavefront, all loads in flight together
-    {
-        float tmp[27];
-        if constexpr (ZROW) {
+    // lines w + 8 i of six candidates each, i = 0..4: node weights straight into registers (zeros for absent
+    // candidates), all loads in flight together
+    constexpr int NL = 5;
+    float v[NL][6];
 #pragma unroll
-            for (int i = 0; i < 27; ++i) tmp[i] = W[(int64_t)min(cand[w + 8 * i], zero_row) * 64 + lane];
+    for (int i = 0; i < NL; ++i) {
+        const int ln = min(w + 8 * i, 35);   // (wavefronts 4 to 7 have four lines: the fifth is not used)
+        const uint32_t *cand = cand_tab + pb * ST_CAND + 6 * ln;
 #pragma unroll
-            for (int i = 0; i < 27; ++i) rows[(w + 8 * i) * 64 + lane] = tmp[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 27; ++i) {
-                const uint32_t c = cand[w + 8 * i];
-                tmp[i] = W[(int64_t)(c == 0xFFFFFFFFu ? 0u : c) * 64 + lane];
+        for (int cx = 0; cx < 6; ++cx) {
+            const uint32_t c = cand[cx];
+            if constexpr (ZROW) v[i][cx] = W[(int64_t)min(c, zero_row) * 64 + lane];
+            else {
+                const float val = W[(int64_t)(c == 0xFFFFFFFFu ? 0u : c) * 64 + lane];
+                v[i][cx] = c == 0xFFFFFFFFu ? 0.f : val;
             }
-#pragma unroll
-            for (int i = 0; i < 27; ++i) rows[(w + 8 * i) * 64 + lane] = cand[w + 8 * i] == 0xFFFFFFFFu ? 0.f : tmp[i];
         }
     }
     __syncthreads();
     const int tx = w & 1, ty = (w >> 1) & 1, tz = w >> 2;
     const int ix = lane & 3, iy = (lane >> 2) & 3, iz = lane >> 4;
-    // out += sum_k f[k] * (entry k places further on in the lane's quad / row of 16 / wavefront);
-    // the input always comes straight from an LDS read (no vector-ALU write precedes the DPP reads)
-    auto xapply = [&](float &out, float v, const float (&f)[4]) {
-        asm("v_fmac_f32 %0, %2, %1\n\t"
-            "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "+v"(out)
-            : "v"(v), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]));
+    // out += sum_k f[k] * (entry k places further on in the lane's quad / row of 16 / wavefront).  A DPP operand must not
+    // have been written by one of the last two vector instructions: the x factors of both parities are applied in one
+    // block that starts with two ordinary multiply-adds, the y factor waits.
+    auto xfirst2 = [&](float &out0, float &out1, float v0, float v1, const float (&f)[4]) {   // the same factor, two inputs
+        asm("v_mul_f32 %0, %4, %2\n\t"
+            "v_mul_f32 %1, %4, %3\n\t"
+            "v_fmac_f32_dpp %0, %2, %5 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %5 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %7 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %7 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "=&v"(out0), "=&v"(out1)
+            : "v"(v0), "v"(v1), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]));
+    };
+    auto xapply2 = [&](float &out0, float &out1, float v0, float v1, const float (&f)[4]) {
+        asm("v_fmac_f32 %0, %4, %2\n\t"
+            "v_fmac_f32 %1, %4, %3\n\t"
+            "v_fmac_f32_dpp %0, %2, %5 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %5 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %7 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %7 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "+&v"(out0), "+&v"(out1)
+            : "v"(v0), "v"(v1), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]));
+    };
+    auto xapply2d = [&](float &out0, float &out1, float v0, float v1, const float (&f)[4], const float (&h)[4]) {
+        asm("v_fmac_f32 %0, %4, %2\n\t"
+            "v_fmac_f32 %1, %8, %3\n\t"
+            "v_fmac_f32_dpp %0, %2, %5 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %9 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %0, %2, %7 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %11 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "+&v"(out0), "+&v"(out1)
+            : "v"(v0), "v"(v1), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]));
     };
     auto yapply = [&](float &out, float v, const float (&f)[4]) {
         asm("v_fmac_f32 %0, %2, %1\n\t"
@@ -321,14 +349,6 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
             : "v"(v), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]));
     };
     // the first application of a sum: out = ..., no zeroed accumulator to start from
-    auto xfirst = [&](float &out, float v, const float (&f)[4]) {
-        asm("v_mul_f32 %0, %2, %1\n\t"
-            "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,0,1,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "=&v"(out)
-            : "v"(v), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]));
-    };
     auto yfirst = [&](float &out, float v, const float (&f)[4]) {
         asm("v_mul_f32 %0, %2, %1\n\t"
             "s_nop 0\n\t"
@@ -352,22 +372,32 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
         for (int k = 0; k < 4; ++k) f[k] = gs[(c + 1 - t) * 16 + i * 4 + ((i + k) & 3)];
     };
 
-    // ---- line sums over x: wavefront w takes x parity w & 1 and the lines (w >> 1) + 4 i, i = 0..8
+    // ---- line sums over x for both parities.  Parity 0 has offset c - 2 from candidate c, parity 1 c - 3: table
+    // entries c + 1 and c, so candidate c of parity 0 and c + 1 of parity 1 share a factor.  The near candidates
+    // (c = 1..3 and 2..4, entries 2, 3, 4) come first, and their sum is kept where the line is near in y and z.
     {
-        float fx[6][4];
+        float fx[7][4];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) factor(c, tx, ix, fx[c]);
+        for (int e = 0; e < 7; ++e) factor(e, 1, ix, fx[e]);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const int ln = (w >> 1) + 4 * i;
-            float v[6];
-#pragma unroll
-            for (int cx = 0; cx < 6; ++cx) v[cx] = rows[(cx + 6 * ln) * 64 + lane];
-            float line;
-            xfirst(line, v[0], fx[0]);
-#pragma unroll
-            for (int cx = 1; cx < 6; ++cx) xapply(line, v[cx], fx[cx]);
-            xl[(tx * 36 + ln) * 64 + lane] = line;
+        for (int i = 0; i < NL; ++i) {
+            const int ln = w + 8 * i;
+            if (ln < 36) {   // wave-uniform
+                float l0, l1;
+                xfirst2(l0, l1, v[i][1], v[i][2], fx[2]);
+                xapply2(l0, l1, v[i][2], v[i][3], fx[3]);
+                xapply2(l0, l1, v[i][3], v[i][4], fx[4]);
+                const int cy = ln % 6, cz = ln / 6;
+                if (!all_far && cy >= 1 && cy <= 4 && cz >= 1 && cz <= 4) {
+                    xn[(cy - 1 + 4 * (cz - 1)) * 64 + lane] = l0;
+                    xn[(16 + cy - 1 + 4 * (cz - 1)) * 64 + lane] = l1;
+                }
+                xapply2(l0, l1, v[i][0], v[i][1], fx[1]);
+                xapply2(l0, l1, v[i][4], v[i][5], fx[5]);
+                xapply2d(l0, l1, v[i][5], v[i][0], fx[6], fx[0]);
+                xl[ln * 64 + lane] = l0;
+                xl[(36 + ln) * 64 + lane] = l1;
+            }
         }
     }
     __syncthreads();
@@ -379,62 +409,55 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const int cz = 3 * (w >> 2) + i;
-            float v[6];
+            float u[6];
 #pragma unroll
-            for (int cy = 0; cy < 6; ++cy) v[cy] = xl[(tx * 36 + cy + 6 * cz) * 64 + lane];
+            for (int cy = 0; cy < 6; ++cy) u[cy] = xl[(tx * 36 + cy + 6 * cz) * 64 + lane];
             float plane;
-            yfirst(plane, v[0], fy[0]);
+            yfirst(plane, u[0], fy[0]);
 #pragma unroll
-            for (int cy = 1; cy < 6; ++cy) yapply(plane, v[cy], fy[cy]);
+            for (int cy = 1; cy < 6; ++cy) yapply(plane, u[cy], fy[cy]);
             yp[((w & 3) * 6 + cz) * 64 + lane] = plane;
+        }
+        if (!all_far) {
+            // near candidates t_d + 1 .. t_d + 3, offsets -1, 0, 1: entries 2, 3, 4 whatever the parity
+            float fn[3][4];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) factor(k + 1, 0, iy, fn[k]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int cz = 2 * (w >> 2) + i;   // counted from the first near plane
+                float u[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) u[k] = xn[(16 * tx + ty + k + 4 * cz) * 64 + lane];
+                float plane;
+                yfirst(plane, u[0], fn[0]);
+#pragma unroll
+                for (int k = 1; k < 3; ++k) yapply(plane, u[k], fn[k]);
+                yn[((w & 3) * 4 + cz) * 64 + lane] = plane;
+            }
         }
     }
     __syncthreads();
-    // ---- the child with parity w, if it exists (no barrier below this point)
+    // ---- the child with parity w, if it exists (no barrier below this point): far = all - near, plane by plane
     if (t == 0xFFFFFFFFu) return;
     float acc = 0.f;
     {
-        float v[6];
+        float u[6];
 #pragma unroll
-        for (int cz = 0; cz < 6; ++cz) v[cz] = yp[((w & 3) * 6 + cz) * 64 + lane];
+        for (int cz = 0; cz < 6; ++cz) u[cz] = yp[((w & 3) * 6 + cz) * 64 + lane];
+        if (!all_far) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {   // near planes tz + 1 .. tz + 3
+                const float near = yn[((w & 3) * 4 + k) * 64 + lane];
+                if (k >= tz && k <= tz + 2) u[k + 1] -= near;
+            }
+        }
 #pragma unroll
         for (int cz = 0; cz < 6; ++cz) {
             float fz[4];
             factor(cz, tz, iz, fz);
-            zapply(acc, v[cz], fz);
+            zapply(acc, u[cz], fz);
         }
-    }
-    if (!all_far) {
-        // minus the near block: candidates t_d + 1 .. t_d + 3 in every dimension, offsets -1, 0, 1,
-        // whose factors G_{-1}, G_0, G_1 sit at table entries 2, 3, 4 whatever the parity
-        float nfx[3][4], nfy[3][4], nfz[3][4];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                nfx[i][k] = gs[(i + 2) * 16 + ix * 4 + ((ix + k) & 3)];
-                nfy[i][k] = gs[(i + 2) * 16 + iy * 4 + ((iy + k) & 3)];
-                nfz[i][k] = gs[(i + 2) * 16 + iz * 4 + ((iz + k) & 3)];
-            }
-        float near = 0.f;
-#pragma unroll
-        for (int k3 = 0; k3 < 3; ++k3) {
-            float plane = 0.f;
-#pragma unroll
-            for (int k2 = 0; k2 < 3; ++k2) {
-                const int base = (tx + 1) + 6 * (ty + 1 + k2) + 36 * (tz + 1 + k3);
-                float v[3];
-#pragma unroll
-                for (int k1 = 0; k1 < 3; ++k1) v[k1] = rows[(base + k1) * 64 + lane];
-                float line;
-                xfirst(line, v[0], nfx[0]);
-#pragma unroll
-                for (int k1 = 1; k1 < 3; ++k1) xapply(line, v[k1], nfx[k1]);
-                yapply(plane, line, nfy[k2]);
-            }
-            zapply(near, plane, nfz[k3]);
-        }
-        acc -= near;
     }
     V[(int64_t)t * 64 + lane] = acc;
 }
