@@ -1192,7 +1192,8 @@ __global__ __launch_bounds__(DT_NT) void direct_kernel(const float *__restrict__
 // (the classic shift by 1.5 2^52 leaves it in the low word of the sum), f = exponent - k with |f| <= 1/2 in one fused
 // operation, 2^f by 1 + f q(f) with q the polynomial of degree 10 that interpolates (2^f - 1) / f at the Chebyshev
 // points of [-1/2, 1/2] (relative error 8.5e-18, formed with 60 digits), and v_ldexp_f64, which also does the
-// denormal results.  r2 is cut at `cap`, where the result has long been zero, so that k fits the low word.
+// denormal results.  r2 is cut at `cap`, where the result has long been zero, so that k fits the low word; the minimum
+// also turns a NaN into `cap`, so the caller has to see to coordinates that are not numbers.
 // The library's exp needs some ten instructions more for arguments of either sign and its special cases.
 __device__ inline double exp2_scaled(double r2, double nc2, double cap) {
     constexpr double SHIFT = 6755399441055744.0;
@@ -1219,6 +1220,9 @@ __device__ inline double exp2_scaled(double r2, double nc2, double cap) {
 // Bound: the fp64 vector ALU (some 25 operations per 3-D pair).  The sources are turned into fp64 once per workgroup
 // on their way into LDS (as scalar operands they cost every wavefront D + 1 conversions per source).
 // Measured (3-D, 1e4 rows x 1e6 sources): 9.66 -> 7.1 ms, 1.40e12 pairs/s at 23 fp64 instructions each.
+// A squared distance that is not a number (a NaN coordinate, or equal infinities) makes the sum NaN, without an
+// instruction in the inner loop: a source with a NaN coordinate gets the weight NaN, and a wavefront with a row whose
+// coordinates are not all finite goes through its sources a second time.
 constexpr int ROWS_TILE = 256;
 template <int D, int R>
 __global__ __launch_bounds__(256) void rows_f64_kernel(const float *__restrict__ X, const float *__restrict__ Y,
@@ -1244,9 +1248,13 @@ __global__ __launch_bounds__(256) void rows_f64_kernel(const float *__restrict__
         __syncthreads();   // the previous tile has been read
         {
             const int64_t j = min(jt + tid, j1 - 1);   // behind the slice: its last source with weight zero
-            const float bj = b[j];
+            float bj = b[j];
 #pragma unroll
-            for (int d = 0; d < D; ++d) src[tid * RS + d] = (double)Y[j * D + d];
+            for (int d = 0; d < D; ++d) {
+                const float yj = Y[j * D + d];
+                src[tid * RS + d] = (double)yj;
+                bj = yj == yj ? bj : yj;
+            }
             src[tid * RS + D] = jt + tid < j1 ? (double)bj : 0.0;
         }
         __syncthreads();
@@ -1270,6 +1278,25 @@ __global__ __launch_bounds__(256) void rows_f64_kernel(const float *__restrict__
         }
 #pragma unroll
         for (int t = 0; t < R; ++t) acc[t] += run[t];
+    }
+    bool finite = true;
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int d = 0; d < D; ++d) finite = finite && xi[t][d] - xi[t][d] == 0.0;
+    if (__any(!finite)) {
+        for (int64_t j = j0 + w; j < j1; j += 4) {
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                double r2 = 0.0;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const double diff = (double)Y[j * D + d] - xi[t][d];
+                    r2 = fma(diff, diff, r2);
+                }
+                acc[t] = r2 == r2 ? acc[t] : r2;
+            }
+        }
     }
 #pragma unroll
     for (int t = 0; t < R; ++t) sums[w][t * 64 + lane] = acc[t];

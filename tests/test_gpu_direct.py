@@ -61,3 +61,42 @@ def test_fp64_rows_of_far_points_are_exactly_zero():
     Y = torch.tensor([[50.0, 0.0, 0.0], [1e15, 1e15, 0.0]], device=DEV)
     y = f3m.direct_kmvm_xy_rows_f64(X, Y, torch.ones(2, device=DEV), 1e-3, torch.arange(2)).cpu().numpy()
     assert np.all(y == 0.0)
+
+
+def test_fp64_rows_of_points_that_are_not_numbers():
+    """A squared distance that is NaN makes the sum NaN, an infinite one contributes nothing, in every row kernel
+    (64, 128 and 256 rows per workgroup) and through every entry point."""
+    inf, nan = float("inf"), float("nan")
+    bad_src = [[nan, 0.2, 0.3], [0.1, inf, 0.3], [0.1, 0.2, -inf]]
+    bad_row = [[0.5, nan, 0.5], [0.5, inf, 0.5], [0.5, 0.5, -inf], [0.5, -inf, 0.5], [inf, inf, 0.5], [0.5, 0.5, inf]]
+    bh = inputs.rhs_normal(5000, 33)
+    for m in (40, 300, 3000):
+        for last in range(len(bad_src) + 1):
+            Yh = inputs.points_uniform(5000, 3, 31)
+            for k in range(last):                     # in the first and the last tile and in the middle
+                Yh[(0, 4999, 2500)[k]] = torch.tensor(bad_src[::-1][k])
+            Xh = inputs.points_uniform(m, 3, 32)
+            at = np.arange(len(bad_row)) * 6 + 1
+            Xh[at] = torch.tensor(bad_row)
+            rows = torch.arange(m, device=DEV)
+            y = f3m.direct_kmvm_xy_rows_f64(Xh.to(DEV), Yh.to(DEV), bh.to(DEV), 0.3, rows)[:400].cpu().numpy()
+            with np.errstate(invalid="ignore"):
+                diff = Xh[:400].numpy().astype(np.float64)[:, None, :] - Yh.numpy().astype(np.float64)[None, :, :]
+                g = float(np.float32(0.3))
+                k = np.exp(-(diff ** 2).sum(-1) / (2.0 * g * g))
+            want = np.where(np.isnan(k).any(1), np.nan, np.nan_to_num(k) @ bh.numpy().astype(np.float64))
+            assert np.isnan(want[1]) and (last == 3) == bool(np.isnan(want[0])) and np.isnan(want[13]) == (last >= 1)
+            assert np.array_equal(np.isnan(y), np.isnan(want))
+            ok = ~np.isnan(want)
+            assert np.allclose(y[ok], want[ok], rtol=1e-11, atol=1e-11)
+    # one point set, and the entry point that allocates nothing
+    X = inputs.points_uniform(5000, 3, 34)
+    X[77, 2] = nan
+    X, b, rows = X.to(DEV), bh.to(DEV), torch.arange(60, 90, device=DEV)
+    y64 = torch.empty(30, dtype=torch.float64, device=DEV)
+    f3m.direct_kmvm_rows_f64_static(X, b, 0.3, rows, y64)
+    assert bool(torch.isnan(f3m.direct_kmvm_rows_f64(X, b, 0.3, rows)).all()) and bool(torch.isnan(y64).all())
+    X[77, 2] = inf                                    # the row itself only
+    f3m.direct_kmvm_rows_f64_static(X, b, 0.3, rows, y64)
+    for v in (f3m.direct_kmvm_rows_f64(X, b, 0.3, rows), y64):
+        assert torch.isnan(v).nonzero().flatten().tolist() == [17]
