@@ -1307,9 +1307,9 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                 // parent): only the row lengths are kept
                 lv.far_implicit = true;
                 lv.far_col.alloc(0, tally);
-                // The first depth at which interpolating a pair of adjacent boxes is off by no more than half a unit in
-                // the last place of a kernel value is the last one the products need: all the pairs left there go
-                // through the M2L, and the tree below it only defines the lists that are reported.  Measured at n = 1e9,
+                // The first depth at which interpolating a pair of adjacent boxes is off by no more than 2^-24, the rounding
+                // unit of fp32 (kernel values are close to 1 there), is the last one the products need: all the pairs
+                // left there go through the M2L, and the tree below it only defines the lists that are reported.  Measured at n = 1e9,
                 // lengthscale 1 (depth 5 of 8): 314 -> 85 ms for plan and product, the error against the oracle unchanged.
                 if (P.near_depth == 0 && l >= 2 && lv.p == 4 && P.rho == 0 && !P.adaptive_far && !(P.eta_smooth > 0.f) &&
                     near_interp_error((double)P.E, l, (double)P.gamma) <= 0x1p-24)
@@ -1544,12 +1544,13 @@ bool smooth_rule(double E, int depth, int D, double gamma, double eta_smooth) {
 }
 
 // Bound on the error of a kernel value between points of two adjacent (or farther) boxes of a depth, in 3-D with
-// 4 Chebyshev nodes of the second kind per dimension: g^2 l^4 (12 / 4!) (9/64) / 16 for one dimension of one of the two
+// 4 Chebyshev nodes of the second kind per dimension: g^2 l^4 (12 / 4!) (1/4) / 16 for one dimension of one of the two
 // points (l the box edge, g = 1 / (2 gamma^2); the fourth derivative of the 1-D Gaussian is at most 12 g^2, the node
-// polynomial at most 9/64), times 1 + L + ... + L^5 for the six of them, L = 5/3 the Lebesgue constant of these nodes.
+// polynomial (t^2 - 1)(t^2 - 1/4) at most 1/4, at t = 0), times 1 + L + ... + L^5 for the six of them, L = 5/3 the
+// Lebesgue constant of these nodes: 0.2395 (l^2 / (2 gamma^2))^2, which is 2^-24 at l = 0.0316 gamma.
 double near_interp_error(double E, int depth, double gamma) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (2.0 * gamma * gamma), L = 5.0 / 3.0;
-    return q * q * (12.0 / 24.0) * (9.0 / 64.0) / 16.0 * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
+    return q * q * (12.0 / 24.0) * 0.25 / 16.0 * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
 }
 
 // Adaptive far-field rule of Sec. 4.3 on q = l^2 / (2 gamma^2): min(p, 3) nodes per dimension if

@@ -10,12 +10,15 @@ from parity_util import TOL_F3M, assert_close, say
 pytestmark = pytest.mark.gpu
 
 
-# the bound 0.1346 (l^2 / (2 gamma^2))^2 <= 2^-24 holds from l <= 0.0363 gamma on: n, dist, gamma, zeta put that depth at
+# the bound 0.2395 (l^2 / (2 gamma^2))^2 <= 2^-24 holds from l <= 0.0316 gamma on: n, dist, gamma, zeta put that depth at
 # the last depth, above it, at depth 2, and (the narrow kernels) nowhere
 @pytest.mark.parametrize("n,dist,gamma,zeta", [
-    (30_001, "uniform", 1.7, 12),    # l = 1/16 at depth 4 of 5
-    (20_000, "uniform", 3.5, 128),   # l = 1/8 at depth 3 of 3
-    (20_000, "uniform", 7.5, 64),    # depth 2
+    (30_001, "uniform", 2.0, 12),    # l = 1/16 at depth 4 of 5
+    (20_000, "uniform", 4.0, 128),   # l = 1/8 at depth 3 of 3
+    (20_000, "uniform", 8.0, 64),    # depth 2
+    (20_000, "uniform", 7.5, 64),    # depth 3
+    (30_001, "uniform", 1.7, 12),    # l = 1/32 at depth 5 of 5
+    (20_000, "uniform", 3.5, 128),   # nowhere: it would be depth 4 of 3
     (40_000, "normal", 60.0, 64),
     (20_000, "uniform", 1.0, 128),   # nowhere: exact near field
 ])
