@@ -1096,16 +1096,49 @@ __global__ __launch_bounds__(256) void p2p_small_kernel(const float *__restrict_
 }
 
 // exact product, all pairs (Sec. 2, KeOps paragraph): targets are the rows of X (nx of them), sources the rows of Y
-// (n of them, weights b); X == Y for one point set.
-// Bound: the vector ALU (ten issue slots per 3-D pair: three differences, four for the scaled square, two for the
-// half-rate exponential, one multiply-add).  A lane per target alone leaves the chip idle below some 1e5 targets
-// (n = 2e4: 313 wavefronts on 1024 SIMDs), so a wavefront is TL target lanes x 64 / TL source lanes, the eight
-// wavefronts of a workgroup share their targets and divide the sources, and the sums meet in a fixed order at
-// the end.  Sources pass through LDS in tiles of DT_TILE rows (D coordinates and the weight); a lane keeps
-// TPL targets, so that a row read from LDS serves TPL pairs.
-// Runs of 32 sources are summed in fp32 and the runs added in fp64.
-// Measured (3-D): n = 2e4 1005 -> 121 us, n = 3e5 24.6 -> 18.9 ms (4.76e12 pairs/s); 1e3 .. 5e3 points 9 .. 15 us, the
-// time of a launch.
+// (n of them, weights b); X == Y for one point set.  Two kernels (run_direct_d says which one takes a call); both add
+// runs of 32 sources in fp32 and the runs in fp64.
+//
+// Lane = target, the sources wave-uniform (scalar loads).  Bound: the vector ALU with many sources (3-D: 4.5e12 pairs/s),
+// the reads of X and writes of y with few (1e7 targets, 1 source, 3-D: 35 us).
+template <int D>
+__global__ __launch_bounds__(64) void direct_lane_kernel(const float *__restrict__ X, int64_t nx,
+                                                         const float *__restrict__ Y, const float *__restrict__ b,
+                                                         int64_t n, float nc2, float *__restrict__ y) {
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const bool active = i < nx;
+    float xi[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) xi[d] = active ? X[i * D + d] : 0.f;
+    double acc = 0.0;
+    for (int64_t j0 = 0; j0 < n; j0 += 32) {
+        const int64_t je = min(j0 + 32, n);
+        float run = 0.f;
+#pragma unroll 4
+        for (int64_t j = j0; j < je; ++j) {
+            float r2 = 0.f;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const float diff = Y[j * D + d] - xi[d];
+                r2 = fmaf(diff, diff, r2);
+            }
+            run = fmaf(__builtin_amdgcn_exp2f(r2 * nc2), b[j], run);
+        }
+        acc += (double)run;
+    }
+    if (active) y[i] = (float)acc;
+}
+
+// A lane per target alone leaves the chip idle below some 1e5 targets (n = 2e4: 313 wavefronts on 1024 SIMDs), so here a
+// wavefront is TL target lanes x 64 / TL source lanes, the eight wavefronts of a workgroup share their targets and divide
+// the sources, and the sums meet in a fixed order at the end.  Sources pass through LDS in tiles of DT_TILE rows (D
+// coordinates and the weight); a lane keeps TPL targets, so that a row read from LDS serves TPL pairs.
+// Bound: the vector ALU, nine instructions per 3-D pair (three differences, four for the scaled square, the exponential,
+// one multiply-add): 32 cycles of a SIMD for the eight at full rate, and the exponential overlaps with them (33 cycles
+// measured: 4.76e12 pairs/s at n = 3e5).
+// Measured (3-D): n = 2e4 1003 -> 102 us (1250 workgroups, 1024 of which are resident at once: the second round leaves
+// most of the chip idle; 84 us at the rate of n = 3e5), n = 3e5 24.6 -> 18.9 ms; 1e3 .. 5e3 points 9 .. 15 us, the time
+// of a launch.
 constexpr int DT_NT = 512;
 constexpr int DT_TILE = 1024;
 template <int D, int TL, int TPL>
@@ -2941,8 +2974,21 @@ template <int D>
 static void run_direct_d(const float *X, int64_t nx, const float *Y, int64_t ny, float gamma, const float *b, float *y,
                          hipStream_t st) {
     const float nc2 = (float)(-1.4426950408889634 / (2.0 * (double)gamma * (double)gamma));
-    // Two targets per lane halve the LDS reads (4.76e12 against 4.35e12 pairs/s at n = 3e5, 3-D); below 2^16 targets
-    // the smaller tiles fill the compute units more evenly (n = 2e4: 121 against 129 us; at 5e4 both take 630 us).
+    // A workgroup of direct_kernel has fixed costs (a whole tile of sources loaded, sums met across lanes and wavefronts), so
+    // with few sources for the number of targets the lane per target is faster: 1e7 targets x 10 sources 41 against 605
+    // us, x 200 438 against 817; 1e6 x 200 52 against 78, x 500 (even), x 1000 244 against 213; 1e5 x 100 even, x 200 13
+    // against 11 (3-D).  With all SIMDs full of target lanes it needs no LDS reads and no second sum: above three
+    // dimensions it then stays ahead with any number of sources (3e6 targets x 4000, 4-D to 7-D: 2 to 12 %), in fewer
+    // dimensions up to some 1100.
+    const bool many = nx >= (1 << 21);
+    const int64_t few = std::max<int64_t>(128, std::min<int64_t>(nx / 800, D >= 4 ? 700 : many ? 1100 : 400));
+    if (ny <= few || (many && D >= 4)) {
+        direct_lane_kernel<D><<<dim3((unsigned)cdiv(nx, 64)), dim3(64), 0, st>>>(X, nx, Y, b, ny, nc2, y);
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    // Two targets per lane halve the LDS reads (n = 3e5, 3-D: 4.76e12 against 4.41e12 pairs/s); below 2^16 targets the
+    // smaller tiles fill the compute units more evenly (n = 2e4: 8 % faster, at 5e4 1 %).
     if (nx <= 65536)
         direct_kernel<D, 16, 1><<<grid_for(cdiv(nx, 16)), dim3(DT_NT), 0, st>>>(X, nx, Y, b, ny, nc2, y);
     else

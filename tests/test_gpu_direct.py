@@ -1,5 +1,5 @@
-"""The exact products.  direct_kmvm at the edges of its kernel's tiles (16 or 32 targets per workgroup, source tiles of 1024 rows in
-runs of 32) against fp64 sums formed with numpy;
+"""The exact products.  direct_kmvm at the edges of its kernels (64 targets a wavefront, or 16 or 32 targets a workgroup and
+source tiles of 1024 rows; both in runs of 32) against fp64 sums formed with numpy;
 direct_kmvm_xy_rows_f64 where its tiles (64, 128 or 256 rows, 256 sources), slices and exponentials end."""
 import numpy as np
 import pytest
@@ -12,7 +12,11 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("nx,ny,D", [(1, 1, 3), (15, 33, 1), (16, 1023, 2), (17, 1024, 3), (33, 1025, 4), (64, 5000, 5),
-                                     (1000, 31, 6), (4097, 2049, 7), (65536, 1500, 3), (65537, 777, 2), (70001, 1056, 5)])
+                                     (1000, 31, 6), (4097, 2049, 7), (65536, 1500, 3), (65537, 777, 2), (70001, 1056, 5),
+                                     # both sides of the rule for few sources: a lane per target, or tiles of sources
+                                     (1, 129, 3), (17, 160, 7), (63, 128, 1), (65, 129, 2), (2_097_151, 400, 3),
+                                     (2_097_151, 401, 1), (2_097_151, 700, 5), (2_097_151, 701, 7), (2_097_153, 1100, 2),
+                                     (2_097_153, 1101, 3), (160_000, 200, 6), (159_999, 200, 4), (2_097_152, 3001, 4)])
 def test_direct_at_tile_edges(nx, ny, D):
     gamma = 0.4
     print("direct_kmvm_xy nx=%d ny=%d D=%d" % (nx, ny, D), flush=True)
@@ -32,6 +36,22 @@ def test_direct_at_tile_edges(nx, ny, D):
     # of a running sum of 32 terms
     bound = 2.0 ** -24 * (((D + 3) * k * np.abs(e) + 35.0 * k) @ np.abs(bh)) + 1e-30
     assert np.all(np.abs(y[rows] - want) <= bound)
+
+
+def test_direct_with_few_sources_is_bound_by_its_targets():
+    # 1e7 targets, ten sources: 160 MB in and out; a workgroup's share of a tile of sources for every few targets
+    # (600 us) would be several times what the traffic takes (40 us; 250 us are 0.64 TB/s)
+    X, Y = inputs.points_uniform(10_000_000, 3, 14, device=DEV), inputs.points_uniform(10, 3, 15, device=DEV)
+    b, y = inputs.rhs_normal(10, 16, device=DEV), torch.empty(10_000_000, device=DEV)
+    times = []
+    for _ in range(8):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        f3m.direct_kmvm_xy(X, Y, b, 0.5, y=y)
+        t1.record()
+        t1.synchronize()
+        times.append(t0.elapsed_time(t1))
+    assert min(times) <= 0.25
 
 
 @pytest.mark.parametrize("m,ny,D,gamma", [(1, 1, 3, 0.5), (63, 255, 1, 0.3), (65, 257, 2, 0.02), (256, 4095, 3, 0.4),
