@@ -248,13 +248,12 @@ def main():
     level_runs.append({l: plan.level_times(l) for l in range(1, L + 1)})
     st = {key: median([run[key] for run in stage_runs]) for key in stage_runs[0]}
     level_ms = {l: tuple(median([run[l][j] for run in level_runs]) for j in range(3)) for l in range(1, L + 1)}
-    # the last depth the product worked at: above the last depth of the tree where the pairs left at it are all
-    # interpolated to within fp32 rounding (then there is no near field)
-    Lw = max([l for l in range(1, L + 1) if level_ms[l][1] > 0 and int(inf.far_pairs[l]) > 0], default=L)
-    pairs = int(inf.near_point_pairs)
-    if pairs > 2e13 * st["p2p"] * 1e-3:     # more than one exponential per pair allows: the pairs were interpolated
-        pairs = 0
-    near_interpolated = pairs == 0 and L >= 1 and int(inf.near_pairs[L]) > 0
+    # The last depth the product worked at: above the last depth of the tree where the pairs left at it are all
+    # interpolated to within fp32 rounding (then there is no near field).
+    near_depth = int(plan.product_info().near_depth)
+    near_interpolated = near_depth > 0
+    Lw = near_depth or max([l for l in range(1, L + 1) if level_ms[l][1] > 0 and int(inf.far_pairs[l]) > 0], default=L)
+    pairs = 0 if near_interpolated else int(inf.near_point_pairs)
     far_L = int(inf.far_pairs[Lw]) + (int(inf.near_pairs[Lw]) if near_interpolated else 0)
     r = inf.nodes_per_box
     m2l_ms = level_ms[Lw][1] if L >= 1 else 0.0

@@ -86,7 +86,8 @@ typedef struct {
     int32_t D;
     int32_t interp_nodes;   /* p, nodes per dimension */
     int32_t nodes_per_box;  /* r = p^D */
-    int32_t depth;          /* L: divisions actually made (near field is evaluated at depth L) */
+    int32_t depth;          /* L: divisions actually made (the near pairs that are left are those of depth L; a
+                               product may stop above it, see f3m_plan_product_info) */
     int32_t quant_depth;    /* depth at which cells are quantised once (keys have D*quant_depth bits) */
     int32_t far_threshold;  /* T = ceil(eta^2): a pair is far iff the squared integer cell offset >= T */
     float edge;             /* E, edge of the enclosing cube */
@@ -98,8 +99,9 @@ typedef struct {
     int64_t far_pairs[F3M_MAX_LEVELS + 1];     /* ordered far pairs per depth */
     int64_t far_point_pairs[F3M_MAX_LEVELS + 1]; /* per depth: sum of |p||q| over the far pairs; with
                                                   near_point_pairs they add up to n*n */
-    int64_t near_point_pairs;                  /* point pairs evaluated exactly: sum of |p||q| over the
-                                                  near pairs of depth L */
+    int64_t near_point_pairs;                  /* sum of |p||q| over the near pairs of depth L: the point pairs
+                                                  a product sums exactly, unless it interpolates them
+                                                  (f3m_product_info.near_depth > 0) */
     int64_t device_bytes;                      /* device memory held by the plan */
     int32_t smooth_depth;                      /* depth whose adjacent pairs are interpolated (smooth
                                                   field), -1 if none */
@@ -149,6 +151,10 @@ f3m_status f3m_plan_ex(const float *X, int64_t n, int D, float lengthscale, int 
  * per depth the far-field product L_X^T (K (L_Y b)) of Sec. 3 "Interpolating
  * k(x,y)" (P2M, M2L, L2P), then the exact near-field sums of Sec. 3 eq. (1) at
  * the last depth, then the inverse permutation sigma.
+ *   Wide kernels: in 3-D with 4 nodes per dimension, one point set, eta = 2 and none of the options of
+ *   Sec. 4.2 and 4.3, the product ends at the first depth >= 2 whose adjacent pairs too are interpolated to
+ *   within 2^-24 (the rounding unit of fp32; boxes with an edge of at most 0.0316 lengthscales), and has no
+ *   exact sums then.  f3m_plan_product_info reports that depth.
  *   b, y   device fp32[n], caller's order; y is overwritten; they must not overlap.
  *   Asynchronous on `stream`: the call only enqueues kernels, it allocates nothing and never waits for
  *   the device (every workspace was sized by f3m_plan); one call in flight per plan (the plan holds the
@@ -284,6 +290,17 @@ const char *f3m_last_error(void);
  * product, so the first call on a plan computes them on the device, re-reading every
  * interaction list, and waits for that; later calls only copy.  Not thread-safe on one plan. */
 f3m_status f3m_plan_info(const f3m_plan_t *plan, f3m_info *out);
+
+/* How the products of a plan work, where that is not one M2L per depth and exact sums at depth L.  Chosen by
+ * f3m_plan; costs nothing to ask for. */
+typedef struct {
+    int32_t near_depth;                        /* 0: the near pairs of depth L are summed exactly.  k > 0: the
+                                                  products work down to depth k only and interpolate every pair
+                                                  left there (the tree and the lists of f3m_info still end at L) */
+    int32_t far_points[F3M_MAX_LEVELS + 1];    /* 1: the far pairs of the depth are interpolated from point to
+                                                  point, without node weights (its P2M and L2P times are 0) */
+} f3m_product_info;
+f3m_status f3m_plan_product_info(const f3m_plan_t *plan, f3m_product_info *out);
 
 /* perm[k] = caller's index of the k-th point in box order (n entries): the
  * permutation pi of Sec. 4.1; ascending (key, index). */

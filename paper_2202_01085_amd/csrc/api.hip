@@ -289,6 +289,14 @@ f3m_status f3m_plan_info(const f3m_plan_t *plan, f3m_info *out) {
     return F3M_OK;
 }
 
+f3m_status f3m_plan_product_info(const f3m_plan_t *plan, f3m_product_info *out) {
+    if (!plan || !out) return set_error(F3M_ERR_INVALID_ARG, "null argument");
+    std::memset(out, 0, sizeof(*out));
+    out->near_depth = plan->near_depth;
+    for (int l = 1; l <= plan->L && built(plan); ++l) out->far_points[l] = plan->lev[l].far_points ? 1 : 0;
+    return F3M_OK;
+}
+
 f3m_status f3m_plan_get_perm(const f3m_plan_t *plan, uint32_t *perm_host) {
     if (!plan || !perm_host) return set_error(F3M_ERR_INVALID_ARG, "null argument");
     return guarded([&] { copy_to_host(perm_host, plan->perm.p, built(plan) ? (size_t)plan->n : 0); });

@@ -52,6 +52,10 @@ class SourceInfo(ctypes.Structure):
                 ("nboxes", ctypes.c_int64 * (MAX_LEVELS + 1)), ("max_box", ctypes.c_int64 * (MAX_LEVELS + 1))]
 
 
+class ProductInfo(ctypes.Structure):
+    _fields_ = [("near_depth", ctypes.c_int32), ("far_points", ctypes.c_int32 * (MAX_LEVELS + 1))]
+
+
 class Times(ctypes.Structure):
     _fields_ = [(k, ctypes.c_float) for k in
                 ("bbox_keys", "sort", "gather", "boxes", "lists", "tables", "plan_total",
@@ -95,6 +99,7 @@ def lib():
         L.f3m_trim_memory.restype = ctypes.c_int64
         L.f3m_last_error.restype = ctypes.c_char_p
         L.f3m_plan_info.argtypes = [vp, ctypes.POINTER(Info)]
+        L.f3m_plan_product_info.argtypes = [vp, ctypes.POINTER(ProductInfo)]
         L.f3m_plan_get_perm.argtypes = [vp, vp]
         L.f3m_plan_get_point_keys.argtypes = [vp, vp]
         L.f3m_plan_get_boxes.argtypes = [vp, ci, vp, vp]
@@ -105,7 +110,7 @@ def lib():
                      "f3m_plan_get_perm", "f3m_plan_get_point_keys", "f3m_plan_get_boxes", "f3m_plan_get_list",
                      "f3m_stage_times", "f3m_level_times", "f3m_plan_xy", "direct_kmvm_xy", "direct_kmvm_xy_rows_f64",
                      "f3m_plan_source_info", "f3m_plan_get_source_perm", "f3m_plan_get_source_boxes",
-                     "direct_kmvm_rows_f64_static"):
+                     "direct_kmvm_rows_f64_static", "f3m_plan_product_info"):
             getattr(L, name).restype = ci
         _lib = L
     return _lib
@@ -221,6 +226,13 @@ class Plan:
     def info(self):
         out = Info()
         _check(lib().f3m_plan_info(self._h, ctypes.byref(out)))
+        return out
+
+    def product_info(self):
+        """f3m_plan_product_info: the depth at which products interpolate the near pairs (near_depth, 0: exact sums),
+        and the depths whose far field goes from point to point (far_points)"""
+        out = ProductInfo()
+        _check(lib().f3m_plan_product_info(self._h, ctypes.byref(out)))
         return out
 
     def perm(self):

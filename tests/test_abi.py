@@ -40,6 +40,7 @@ def test_struct_sizes_match_the_header():
     assert ctypes.sizeof(f3m.Options) == 4 * 4 + 4 + 4 + 4 + 4
     assert ctypes.sizeof(f3m.Info) == 8 + 6 * 4 + 2 * 4 + 7 * 4 + 4 + 5 * 21 * 8 + 8 + 8 + 4 + 21 * 4 + 2 * 21 * 8
     assert ctypes.sizeof(f3m.Times) == 14 * 4
+    assert ctypes.sizeof(f3m.ProductInfo) == 4 + 21 * 4
     assert ctypes.sizeof(f3m.SourceInfo) == 8 + 4 + 7 * 4 + 2 * 21 * 8
 
 
@@ -64,6 +65,7 @@ def test_argument_checks_need_no_device(lib):
     assert lib.f3m_plan(fake, 10, 7, 1.0, 4, 2.0, None, ctypes.byref(h)) == 3      # 4^7 nodes
     assert lib.f3m_plan(fake, 10, 3, 1.0, 4, 2.0, None, None) == 1                 # null plan_out
     assert lib.f3m_kmvm(None, fake, fake, None) == 1
+    assert lib.f3m_plan_product_info(None, ctypes.byref(f3m.ProductInfo())) == 1
     assert lib.direct_kmvm(fake, 10, 3, 1.0, None, fake, None) == 1
     assert lib.direct_kmvm(fake, 10, 3, 1.0, fake, fake, None) == 1                # b aliases y
     assert lib.direct_kmvm(None, 0, 3, 1.0, None, None, None) == 0                 # empty problem
