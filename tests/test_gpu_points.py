@@ -34,11 +34,25 @@ def test_far_field_between_points(n, D, dist, p, theta, zeta, eta_smooth, adapti
     T = oracle.Tree(X.numpy(), theta=theta, zeta=zeta, gamma=g, eta_smooth=float(np.float32(eta_smooth)))
     plan = f3m.Plan(X.to("cuda:0"), gamma, p, theta, leaf_max=zeta, eta_smooth=eta_smooth, adaptive_far=adaptive)
     assert plan.info().depth == T.L
+    # the depths that go from point to point: point pairs of the near boxes one depth up against nodes and far pairs
+    used, info = plan.product_info(), plan.info()
+    for l in range(1, T.L + 1):
+        size = np.diff(T.boxes(l - 1)[1].astype(np.int64))
+        ptr, cols = T.interactions(l - 1, 0)
+        near = np.add.reduceat(size[cols], ptr[:-1]) if cols.size else np.zeros(size.size, np.int64)
+        pairs, far, r = int((near * size).sum()), T.interactions(l, 1)[1].size, int(info.level_nodes[l]) ** D
+        pays = far > 0 and info.level_nodes[l] in (2, 3) and (1.0 if r > 512 else 0.5) * pairs <= far * r
+        assert bool(used.far_points[l]) == pays, l
+    assert any(used.far_points) and used.near_depth == 0
     y = plan.kmvm(b.to("cuda:0"))
     torch.cuda.synchronize()
     idx = np.arange(rows) * (n // rows)
     want = T.apply_rows(b.numpy(), g, p, idx, adaptive=adaptive)
     assert_close(y.cpu().numpy()[idx], want, TOL_F3M, "vs CPU F3M")
+    for l in range(1, T.L + 1):
+        if used.far_points[l]:
+            p2m, m2l, l2p = plan.level_times(l)
+            assert p2m == 0.0 and l2p == 0.0 and m2l > 0.0
     # the far rows are not kept at such a depth: they come out of the plan on request
     for l in range(1, T.L + 1):
         ptr, cols = plan.interactions(l, 1)
