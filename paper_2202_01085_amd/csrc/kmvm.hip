@@ -2542,9 +2542,11 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     // copies (below), take the product of 2e4 points from 134 us to 85 us.
     size_t nmarks = 0;
     auto mark = [&] {
-        if (nmarks == P.marks.size()) {
-            P.marks.push_back(nullptr);
-            F3M_HIP(hipEventCreate(&P.marks.back()));
+        if (nmarks == P.marks.size()) {   // (an event that cannot be made leaves the list as it is)
+            P.marks.reserve(nmarks + 1);
+            hipEvent_t e = nullptr;
+            F3M_HIP(hipEventCreate(&e));
+            P.marks.push_back(e);
         }
         F3M_HIP(hipEventRecord(P.marks[nmarks], st));
         return P.marks[nmarks++];
