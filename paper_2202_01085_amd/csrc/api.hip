@@ -1,4 +1,5 @@
 // extern "C" boundary of libf3m: argument checks, error translation, introspection.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -394,6 +395,9 @@ f3m_status f3m_stage_times(f3m_plan_t *plan, f3m_times *out) {
                 F3M_HIP(elapsed(&ms, ev[2], ev[3])); t.m2l += ms;
                 F3M_HIP(elapsed(&ms, ev[4], ev[5])); t.l2p += ms;
             }
+            float wait = 0.f;
+            F3M_HIP(elapsed(&wait, plan->t_wait0, plan->t_wait1));
+            t.l2p = std::max(0.f, t.l2p - wait);
         }
         *out = t;
     });
@@ -410,6 +414,11 @@ f3m_status f3m_level_times(f3m_plan_t *plan, int level, float *ms_host) {
         if (!ev[5]) return;
         F3M_HIP(hipEventSynchronize(plan->t_end));
         for (int k = 0; k < 3; ++k) F3M_HIP(elapsed(&ms_host[k], ev[2 * k], ev[2 * k + 1]));
+        if (level == plan->tree_lmax) {
+            float wait = 0.f;
+            F3M_HIP(elapsed(&wait, plan->t_wait0, plan->t_wait1));
+            ms_host[2] = std::max(0.f, ms_host[2] - wait);
+        }
     });
 }
 

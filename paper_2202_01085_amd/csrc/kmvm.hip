@@ -2654,6 +2654,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     // six marks per depth: [0,1] bracket the upward pass (P2M or M2M), [2,3] the M2L, [4,5] the
     // downward pass (L2L and/or L2P) of that depth
     P.far_events.assign((size_t)(P.L + 1) * 6, nullptr);
+    P.t_wait0 = P.t_wait1 = nullptr;
     auto level_events = [&](int l) { return &P.far_events[(size_t)l * 6]; };
     const bool tree = P.tree_lmin > 0;   // D = 3, 4 nodes per dimension on depths tree_lmin..tree_lmax
     // no far pairs, dropped by the adaptive rule (Sec. 4.3), or part of the band of the tree
@@ -2850,7 +2851,11 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         {
             hipEvent_t *ev = level_events(L);
             if (P.tree_lmin == L) ev[4] = now;
-            if (P.side && direct_out) F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
+            if (P.side && direct_out) {   // the near field may be what is waited for: not part of the downward pass
+                P.t_wait0 = mark();
+                F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
+                P.t_wait1 = mark();
+            }
             const float *base = direct_out ? yn : one_l2p ? nullptr : P.ys.p;
             l2p34_kernel<<<grid_for(cdiv(lf.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p,
                                                                   lf.chunk_first.p, lf.nchunks, make_centre(P, L),

@@ -159,9 +159,11 @@ struct f3m_plan_s {
     std::vector<hipEvent_t> plan_events;  // two per depth while the plan is built
     std::vector<std::vector<float>> host_tabs;   // tables on their way to the device, until the plan is complete
     // Times of a product: an event at every boundary between its stages, in order (marks); the others name them.
-    // far_events: 6 per depth, around the far-field kernels of that depth.
+    // far_events: 6 per depth, around the far-field kernels of that depth.  t_wait0 .. t_wait1 (if not null): a wait for
+    // the near field inside the downward pass of depth tree_lmax.
     std::vector<hipEvent_t> marks, far_events;
-    hipEvent_t t_begin = nullptr, t_in = nullptr, t_p2p0 = nullptr, t_p2p1 = nullptr, t_out = nullptr, t_end = nullptr;
+    hipEvent_t t_begin = nullptr, t_in = nullptr, t_p2p0 = nullptr, t_p2p1 = nullptr, t_out = nullptr, t_end = nullptr,
+               t_wait0 = nullptr, t_wait1 = nullptr;
     bool have_plan_times = false, have_kmvm_times = false, have_far_point_pairs = false;
     f3m_times times = {};
     ~f3m_plan_s();

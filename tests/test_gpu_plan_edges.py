@@ -87,3 +87,22 @@ def test_solver_with_and_without_overlap(n, zeta, gamma):
         assert abs(res - float(hist[-1])) <= 1e-5
         plan.close()
     assert torch.equal(got[0], got[1])
+
+
+def test_downward_time_leaves_out_the_wait_for_the_near_field():
+    """Large leaf boxes of depth 2: the near field takes some 5 ms and holds the chip, the far field gets through beside it
+    shortly before its end, and with overlap the solver's last pass waits for the rest (0.13 of 0.15 ms), which is not its
+    own time (0.02 ms)."""
+    X = inputs.points_uniform(500_000, 3, 99).to(DEV)
+    b = inputs.rhs_normal(500_000, 100).to(DEV)
+    times = []
+    for overlap in (False, True):
+        plan = f3m.Plan(X, 0.5, 4, 2.0, leaf_max=10_000, overlap=overlap)
+        for _ in range(2):
+            plan.cg_solve(b, 5e4, tol=0.0, max_iter=3)
+        t = plan.stage_times()
+        say("overlap %d: p2p %.3f l2p %.3f ms, depth 2 %r" % (overlap, t["p2p"], t["l2p"], plan.level_times(2)))
+        assert plan.info().depth == 2 and abs(plan.level_times(2)[2] - t["l2p"]) <= 1e-6
+        times.append(t)
+        plan.close()
+    assert times[1]["p2p"] > 2.0 and times[1]["l2p"] <= 2.0 * times[0]["l2p"] + 0.03
