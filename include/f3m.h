@@ -219,6 +219,7 @@ f3m_status direct_kmvm(const float *X, int64_t n, int D, float lengthscale,
  * reference the paper measures its relative error against (Sec. 5, first
  * paragraph: a subset of rows against the entire data set in double precision).
  *   rows  device int64[m], each in [0,n);  y64  device double[m].
+ * Coordinates are not checked: a row is NaN if one of its distances is (NaN coordinates, equal infinities).
  */
 f3m_status direct_kmvm_rows_f64(const float *X, int64_t n, int D, float lengthscale,
                                 const float *b, const int64_t *rows, int64_t m,

@@ -226,9 +226,9 @@ bool far_points_pays(const f3m_plan_s &P, int level, int64_t point_pairs);      
 void far_points_prepare(f3m_plan_s &P, int level, hipStream_t st);
 void run_far_points(f3m_plan_s &P, int level, const float *bs, float *ys, int omin, int no, hipStream_t st);
 // m2l.hip
-bool m2l_stencil_applies(const f3m_plan_s &P);
-void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);
-bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables   // after the lists of the depth exist                   // D = 3, 4 nodes/dim, far ratio 2
+bool m2l_stencil_applies(const f3m_plan_s &P);   // D = 3, 4 nodes per dimension, far ratio 2
+void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);   // after the lists of the depth exist
+bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables
 bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStream_t st, bool zero_row = false);  // false: does not apply
 
 }  // namespace f3m

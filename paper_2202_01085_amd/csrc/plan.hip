@@ -1310,7 +1310,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                 // The first depth at which interpolating a pair of adjacent boxes is off by no more than 2^-24, the rounding
                 // unit of fp32 (kernel values are close to 1 there), is the last one the products need: all the pairs
                 // left there go through the M2L, and the tree below it only defines the lists that are reported.  Measured at n = 1e9,
-                // lengthscale 1 (depth 5 of 8): 314 -> 85 ms for plan and product, the error against the oracle unchanged.
+                // lengthscale 1 (depth 5 of 8): 314 -> 82 ms for plan and product, the error against the oracle unchanged.
                 if (P.near_depth == 0 && l >= 2 && lv.p == 4 && P.rho == 0 && !P.adaptive_far && !(P.eta_smooth > 0.f) &&
                     near_interp_error((double)P.E, l, (double)P.gamma) <= 0x1p-24)
                     P.near_depth = l;
