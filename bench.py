@@ -254,6 +254,7 @@ def main():
     near_interpolated = near_depth > 0
     Lw = near_depth or max([l for l in range(1, L + 1) if level_ms[l][1] > 0 and int(inf.far_pairs[l]) > 0], default=L)
     pairs = 0 if near_interpolated else int(inf.near_point_pairs)
+    far_points = bool(plan.product_info().far_points[Lw])
     far_L = int(inf.far_pairs[Lw]) + (int(inf.near_pairs[Lw]) if near_interpolated else 0)
     r = inf.nodes_per_box
     m2l_ms = level_ms[Lw][1] if L >= 1 else 0.0
@@ -291,20 +292,26 @@ def main():
             hbm_stage("p2m_leaf", "P2M at depth %d: 4(D+1) B/pt + 4r B/box" % Lw, 4.0 * (D + 1) * ns + 4.0 * r * nb_L,
                       level_ms[Lw][0])
         if L >= 1 and level_ms[Lw][2] > 0:
-            hbm_stage("l2p_leaf", "L2P at depth %d: (4D+8) B/pt + 4r B/box" % Lw, (4.0 * D + 8) * n + 4.0 * r * nb_L,
+            hbm_stage("l2p_leaf", "L2P at depth %d: (4D+4) B/pt + 4r B/box" % Lw, (4.0 * D + 4) * n + 4.0 * r * nb_L,
                       level_ms[Lw][2])
     if far_L > 0 and m2l_ms > 0:
         # algorithmic: 2 r^2 flop per far pair (the dense node-to-node product).  For D = 3 with 4 nodes per
         # dimension the kernel applies the Kronecker factors per candidate / line / plane of the 6x6x6 grid around
         # the parent, and shares the line and plane sums between the eight children: 672 factor applications of 256
         # multiply-adds per parent (84 per target box) instead of 189 x 4096 per target, on the vector ALU.
-        # Every other shape applies D one-dimensional factors per far pair: 2 D r p flop.
+        # Depths whose far field goes from point to point need no node weights.  Every other shape applies D one-dimensional
+        # factors per far pair: 2 D r p flop.
         # `achieved` counts the multiply-adds it executes; `algorithmic_tflops` the dense equivalent.
         t = m2l_ms * 1e-3
         if D == 3 and cfg["p"] == 4 and cfg["theta"] == 2.0 and not args.xy:
             # (78 where the near pairs of the depth are interpolated too: nothing is taken off the sum over all candidates)
             executed = 2.0 * (78 if near_interpolated else 84) * 256 * nb_L
             kernel = "m2l_stencil_shared_kernel"
+        elif far_points:
+            # between points: per point pair of a box and the boxes near its parent D dot products of p terms, their product,
+            # the squared offset and the sum
+            executed = (2.0 * cfg["p"] + 1.0) * D * (int(inf.near_point_pairs) + sum(int(v) for v in inf.far_point_pairs[Lw:]))
+            kernel = "far_points_kernel"
         else:
             executed = 2.0 * D * r * cfg["p"] * far_L
             kernel = "m2l_kron_small_kernel" if r // cfg["p"] <= 32 else \

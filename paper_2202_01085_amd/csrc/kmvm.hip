@@ -1134,8 +1134,8 @@ __global__ __launch_bounds__(64) void direct_lane_kernel(const float *__restrict
 // the sources, and the sums meet in a fixed order at the end.  Sources pass through LDS in tiles of DT_TILE rows (D
 // coordinates and the weight); a lane keeps TPL targets, so that a row read from LDS serves TPL pairs.
 // Bound: the vector ALU, nine instructions per 3-D pair (three differences, four for the scaled square, the exponential,
-// one multiply-add): 32 cycles of a SIMD for the eight at full rate, and the exponential overlaps with them (33 cycles
-// measured: 4.76e12 pairs/s at n = 3e5).
+// one multiply-add).  As dependent chains they take 40 cycles of a SIMD (4 each, the exponential 8); the kernel takes 33
+// (4.76e12 pairs/s at n = 3e5 and 2.4 GHz): instructions of several wavefronts overlap.
 // Measured (3-D): n = 2e4 1003 -> 102 us (1250 workgroups, 1024 of which are resident at once: the second round leaves
 // most of the chip idle; 84 us at the rate of n = 3e5), n = 3e5 24.6 -> 18.9 ms; 1e3 .. 5e3 points 9 .. 15 us, the time
 // of a launch.

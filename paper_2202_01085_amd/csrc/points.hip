@@ -13,8 +13,9 @@
 //   A_d[c][j] = sum_i L_i(x_d) G_o[i][j],  c = 0..5 the source's cell relative to the parent's block of 6 per dimension
 // lie in LDS with o^2 as a fourth entry: a lane (= one source) reads the entry of its own c, 16 bytes per dimension,
 // multiplies it with its L_j(y_d), and the sum of the o^2 tells whether the pair of boxes is far.  Bound: the LDS reads,
-// D x 1 KB per 64 pairs (56 cycles of a compute unit at D = 7 at 128 bytes per cycle), and 40 vector instructions
-// (40 cycles on four SIMDs).  Measured at D = 7, 3 nodes: 1.0e12 pairs/s, some 37 cycles per 64 pairs.
+// D x 1 KB per 64 pairs (at D = 7 28 cycles of a compute unit at 256 bytes per cycle), beside 41 vector instructions.
+// Measured at n = 1e7, D = 7, 3 nodes: a 128-bit LDS read every 3.98 cycles of a compute unit, their full rate, at a clock
+// of 1.98 GHz; 1.0e12 pairs/s at n = 3e5.
 #include <algorithm>
 #include <cmath>
 
