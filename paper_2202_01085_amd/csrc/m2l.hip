@@ -462,6 +462,227 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
     V[(int64_t)t * 64 + lane] = acc;
 }
 
+// ------------------------------------------------------------------------------------
+// The same sums where parents are many.  A workgroup of twelve wavefronts takes four parents (neighbours in box order); a
+// wavefront takes one plane cy of their grids and one x parity of the targets, a quarter of its lanes one parent.  A lane
+// holds a fibre: the four entries of a row along x, read from memory as one float4, so the x factor is 16 multiply-adds on
+// registers with operands that are the same in every lane.  Two v_permlane32_swap and two v_permlane16_swap exchange the
+// register index (ix) with the two highest lane bits (iz), and the z factor is of the same kind; only the finished plane
+// sums go through LDS, where the y factor is applied.  The nodes are {1, 1/2, -1/2, -1}, so an entry of a factor depends on
+// |2 (2 o + s_j - s_i)| = 0 .. 16 only: 17 numbers, in registers.
+// What bounds it: vector issue, 4.1 cycles per instruction and SIMD.  A multiply-add on registers alone takes 3.1 cycles a wavefront
+// here, one with a DPP operand 4.4.  Leaf depth of 1e7 uniform points (32768 parents): 306 us by the kernel above, 192 by this
+// one; of 1e6 normal points (sparse grids: lines without a candidate are passed over): 397 and 270.  The
+// kernel above with a plane per wavefront and two barriers instead of three took 306 us as well; this one with both x
+// parities in a wavefront (96 registers, five wavefronts per SIMD) 220.
+// ------------------------------------------------------------------------------------
+// index into the 17 factor values of entry (i, j) of G_o
+__device__ constexpr int factor_index(int o, int i, int j) {
+    constexpr int h[4] = {2, 1, -1, -2};   // twice the nodes
+    const int k = 4 * o + h[j] - h[i];
+    return k < 0 ? -k : k;
+}
+// out[i] += sum_j G_o[i][j] in[j]
+template <int O>
+__device__ __forceinline__ void fibre_apply(float (&out)[4], const float (&in)[4], const float (&E)[17]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = fmaf(E[factor_index(O, i, j)], in[j], out[i]);
+}
+// register index <-> the two highest lane bits (a 4 x 4 transpose)
+__device__ __forceinline__ void fibre_swap(float (&r)[4]) {
+    uint32_t u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = __builtin_bit_cast(uint32_t, r[k]);
+    const auto a = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    r[0] = __builtin_bit_cast(float, (uint32_t)c[0]);
+    r[1] = __builtin_bit_cast(float, (uint32_t)c[1]);
+    r[2] = __builtin_bit_cast(float, (uint32_t)d[0]);
+    r[3] = __builtin_bit_cast(float, (uint32_t)d[1]);
+}
+
+// Plane sums of the finished planes in LDS: planes 1 and 4 are near for the lower / the upper children only, so they are
+// kept twice.  Row of plane cy for children of y parity ty: the four parities tx + 2 tz of the four parents.
+constexpr int PL_ROWS = 8;
+constexpr int PL_STRIDE = 80;   // floats a 64-vector takes (the four parents fall on different banks)
+constexpr int ST_PAR = 4;       // parents of a workgroup
+__device__ inline int plane_row(int cy, int ty) {
+    return cy == 0 ? 0 : cy == 1 ? 1 + ty : cy == 4 ? 5 + ty : cy == 5 ? 7 : cy + 1;   // 2 -> 3, 3 -> 4
+}
+
+// the children of one y parity: sum over the planes, in a lane the four entries of a y fibre
+template <int TY>
+__device__ __forceinline__ void planes_to_child(float (&acc)[4], const float *pl, int comb, int lane, const float (&E)[17]) {
+    const float *src = pl + comb * (ST_PAR * PL_STRIDE) + (lane >> 4) * PL_STRIDE + 4 * (lane & 15);
+    constexpr int ROW = 4 * ST_PAR * PL_STRIDE;
+    auto plane = [&](int cy, auto o) __attribute__((always_inline)) {
+        const float4 f = *reinterpret_cast<const float4 *>(src + plane_row(cy, TY) * ROW);
+        const float in[4] = {f.x, f.y, f.z, f.w};
+        fibre_apply<decltype(o)::value>(acc, in, E);
+    };
+    plane(0, std::integral_constant<int, -2 - TY>{});
+    plane(1, std::integral_constant<int, -1 - TY>{});
+    plane(2, std::integral_constant<int, 0 - TY>{});
+    plane(3, std::integral_constant<int, 1 - TY>{});
+    plane(4, std::integral_constant<int, 2 - TY>{});
+    plane(5, std::integral_constant<int, 3 - TY>{});
+}
+
+// the line and plane sums of one plane cy for children of x parity TX (see m2l_stencil_quad_kernel)
+template <bool ZROW, int TX>
+__device__ __forceinline__ void plane_sums(const uint32_t (*__restrict__ rank)[36], int w, int lane, int all_far, uint32_t zero_row,
+                                           const float *__restrict__ W, const float (&E)[17], float *pl) {
+    // lane = iy + 4 (parent) + 16 iz
+    const uint2 *cand = reinterpret_cast<const uint2 *>(rank[(lane >> 2) & 3]);
+    const float *Wl = W + 4 * ((lane & 3) + 4 * (lane >> 4));
+    float p0[4], p1[4], q0[4], q1[4];   // plane sums of the z parities, and the same over the near candidates
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p0[i] = p1[i] = q0[i] = q1[i] = 0.f;
+    const bool near_plane = !all_far && w >= 1 && w <= 4;
+    // The rows of a line are loaded while the line before it is worked: each into the registers that the row in the same
+    // place has just left.
+    float u[6][4];
+    uint32_t c[6];
+    auto rank_line = [&](int cz) __attribute__((always_inline)) {
+        const uint2 r0 = cand[3 * cz], r1 = cand[3 * cz + 1], r2 = cand[3 * cz + 2];
+        c[0] = r0.x; c[1] = r0.y; c[2] = r1.x; c[3] = r1.y; c[4] = r2.x; c[5] = r2.y;
+        // false: no candidate in the line of any of the parents: it adds nothing
+        return __ballot((c[0] & c[1] & c[2] & c[3] & c[4] & c[5]) != ~0u) != 0ull;
+    };
+    auto load_row = [&](int cx) __attribute__((always_inline)) {
+        const bool none = c[cx] == ~0u;
+        const uint32_t row = ZROW ? min(c[cx], zero_row) : none ? 0u : c[cx];
+        const float4 f = *reinterpret_cast<const float4 *>(Wl + (int64_t)row * 64);
+        u[cx][0] = ZROW || !none ? f.x : 0.f;
+        u[cx][1] = ZROW || !none ? f.y : 0.f;
+        u[cx][2] = ZROW || !none ? f.z : 0.f;
+        u[cx][3] = ZROW || !none ? f.w : 0.f;
+    };
+    bool some = rank_line(0);
+#pragma unroll
+    for (int cx = 0; cx < 6; ++cx) load_row(cx);
+    auto line = [&](auto CZ) __attribute__((always_inline)) {
+        constexpr int cz = decltype(CZ)::value;
+        bool next = false;
+        if constexpr (cz < 5) next = rank_line(cz + 1);
+        // offset c - 2 - TX from candidate c; the near candidates (c = TX + 1 .. TX + 3) come first, and their sum is
+        // kept where the line is near in y and z
+        float l[4] = {0.f, 0.f, 0.f, 0.f};
+        if (some) {
+            fibre_apply<-1>(l, u[TX + 1], E);
+            fibre_apply<0>(l, u[TX + 2], E);
+            fibre_apply<1>(l, u[TX + 3], E);
+        }
+        if constexpr (cz < 5) {
+            load_row(TX + 1);
+            load_row(TX + 2);
+            load_row(TX + 3);
+        }
+        if (some) {
+            if constexpr (cz >= 1 && cz <= 4) {
+                if (near_plane) {
+                    float n[4] = {l[0], l[1], l[2], l[3]};
+                    fibre_swap(n);
+                    if constexpr (cz <= 3) fibre_apply<cz - 2>(q0, n, E);   // near the children with tz = 0: cz = 1..3
+                    if constexpr (cz >= 2) fibre_apply<cz - 3>(q1, n, E);   // tz = 1: cz = 2..4
+                }
+            }
+            fibre_apply<-2 - TX>(l, u[0], E);
+            fibre_apply<3 - TX>(l, u[5], E);
+            fibre_apply<TX ? -2 : 2>(l, u[TX ? 1 : 4], E);
+        }
+        if constexpr (cz < 5) {
+            load_row(0);
+            load_row(5);
+            load_row(TX ? 1 : 4);
+        }
+        if (some) {
+            fibre_swap(l);
+            fibre_apply<cz - 2>(p0, l, E);
+            fibre_apply<cz - 3>(p1, l, E);
+        }
+        some = next;
+    };
+    line(std::integral_constant<int, 0>{});
+    line(std::integral_constant<int, 1>{});
+    line(std::integral_constant<int, 2>{});
+    line(std::integral_constant<int, 3>{});
+    line(std::integral_constant<int, 4>{});
+    line(std::integral_constant<int, 5>{});
+    // far = all - near, where the plane is near the child (planes ty + 1 .. ty + 3).  Now lane = iy + 4 (parent) + 16 ix;
+    // entry (ix, iy, iz) of a plane sum goes to place iy + 4 ix + 16 iz.
+    const int row0 = plane_row(w, 0), row1 = plane_row(w, 1);   // wave-uniform
+    const bool near0 = near_plane && w <= 3, near1 = near_plane && w >= 2;
+    float *dst = pl + TX * (ST_PAR * PL_STRIDE) + ((lane >> 2) & 3) * PL_STRIDE + (lane & 3) + 4 * (lane >> 4);
+    auto store = [&](int row, bool near) __attribute__((always_inline)) {
+        float *d = dst + row * (4 * ST_PAR * PL_STRIDE);
+#pragma unroll
+        for (int iz = 0; iz < 4; ++iz) {
+            d[16 * iz] = near ? p0[iz] - q0[iz] : p0[iz];
+            d[2 * ST_PAR * PL_STRIDE + 16 * iz] = near ? p1[iz] - q1[iz] : p1[iz];
+        }
+    };
+    store(row0, near0);
+    if (row1 != row0) store(row1, near1);
+}
+
+template <bool ZROW>
+__global__ __launch_bounds__(768) void m2l_stencil_quad_kernel(const uint32_t *__restrict__ cand_tab,
+                                                                 const uint32_t *__restrict__ child_tab,
+                                                                 int64_t nparents, int64_t per_xcd,
+                                                                 const float *__restrict__ G, int all_far,
+                                                                 uint32_t zero_row,
+                                                                 const float *__restrict__ W, float *__restrict__ V) {
+    __shared__ __attribute__((aligned(16))) float pl[PL_ROWS * 4 * ST_PAR * PL_STRIDE];
+    __shared__ float es[17];
+    __shared__ __attribute__((aligned(8))) uint32_t ranks[6][ST_PAR][36];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // consecutive parents (neighbours in space) on the same XCD, so that its L2 serves the overlap
+    const int64_t bi = block_index2();
+    const int64_t p0 = ((bi & 7) * per_xcd + (bi >> 3)) * ST_PAR;
+    if ((bi >> 3) >= per_xcd || p0 >= nparents) return;
+    if (tid < 17) {   // entry k of the factors: offset o and nodes (i, j) with 4 o + 2 s_j - 2 s_i = k
+        const int o = tid >= 12 ? 3 : tid >= 8 ? 2 : tid >= 4 ? 1 : 0, d = tid - 4 * o;   // d = 0 .. 4
+        const int i = d == 0 ? 0 : d == 1 ? 1 : d == 2 ? 2 : d == 3 ? 2 : 3;              // h = 2, 1, -1, -2
+        const int j = d == 0 ? 0 : d == 1 ? 0 : d == 2 ? 1 : d == 3 ? 0 : 0;
+        es[tid] = G[(o + 3) * 16 + i * 4 + j];
+    }
+    // candidate ranks by plane: place cx + 6 cy + 36 cz of a parent goes to [cy][parent][cx + 6 cz]; a parent behind the
+    // last one repeats it, and nothing of it is stored
+    for (int e = tid; e < ST_PAR * ST_CAND; e += 768) {
+        const int q = e / ST_CAND, k = e - q * ST_CAND;
+        const int cz = k / 36, cy = (k - 36 * cz) / 6, cx = k - 36 * cz - 6 * cy;
+        ranks[cy][q][cx + 6 * cz] = cand_tab[min(p0 + q, nparents - 1) * ST_CAND + k];
+    }
+    __syncthreads();
+    float E[17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) E[k] = es[k];
+    if (w < 6) plane_sums<ZROW, 0>(ranks[w], w, lane, all_far, zero_row, W, E, pl);
+    else plane_sums<ZROW, 1>(ranks[w - 6], w - 6, lane, all_far, zero_row, W, E, pl);
+    __syncthreads();
+    // ---- the child of parity w of the four parents, where it exists: lane = ix + 4 iz + 16 (parent)
+    if (w >= 8) return;
+    const int64_t pb = p0 + (lane >> 4);
+    const uint32_t t = pb < nparents ? child_tab[pb * 8 + w] : ~0u;
+    if (__ballot(t != ~0u) == 0ull) return;
+    const int comb = (w & 1) + 2 * (w >> 2);   // tx + 2 tz
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    if ((w >> 1) & 1) planes_to_child<1>(acc, pl, comb, lane, E);
+    else planes_to_child<0>(acc, pl, comb, lane, E);
+    if (t != ~0u) {
+        float *out = V + (int64_t)t * 64 + (lane & 3) + 16 * ((lane >> 2) & 3);
+#pragma unroll
+        for (int iy = 0; iy < 4; ++iy) out[4 * iy] = acc[iy];
+    }
+}
+
+constexpr int64_t M2L_QUAD_PARENTS = 1024;
+
 // candidate and child tables of a depth whose M2L runs on the candidate grid without a small field
 // the tables of a depth, preset to "none"; false: the depth does not use them
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st) {
@@ -490,13 +711,21 @@ bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStre
     if (lv.gtab.p == nullptr || lv.gtab_omax != 3) return false;
     const int64_t per_xcd = cdiv(up.nb, 8);
     const int all_far = lv.smooth || level == P.near_depth ? 1 : 0;
-    if (lv.st_cand.p) {   // no small field: the variant that shares the line and plane sums between the children
-        if (zero_row)   // W carries a row of zeros at index nb
-            m2l_stencil_shared_kernel<true><<<grid2(per_xcd * 8), dim3(512), 0, st>>>(
-                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, all_far, (uint32_t)lv.nb, W, V);
-        else
-            m2l_stencil_shared_kernel<false><<<grid2(per_xcd * 8), dim3(512), 0, st>>>(
-                lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, lv.gtab.p, all_far, 0u, W, V);
+    if (lv.st_cand.p) {   // no small field: the variants that share the line and plane sums between the children
+        // Four parents to a workgroup from M2L_QUAD_PARENTS on: below, the chip is not full and the longer chain of a workgroup
+        // shows (8, 64, 512, 4096 parents: 5.0, 5.1, 6 to 7, 42 us with one parent to a workgroup, 8.2, 9.3, 9.6, 28 with four).
+        const bool quad = up.nb >= M2L_QUAD_PARENTS;
+        const int64_t per = quad ? cdiv(cdiv(up.nb, ST_PAR), 8) : per_xcd;
+        auto launch = [&](auto kern, int threads, uint32_t zr) {
+            kern<<<grid2(per * 8), dim3(threads), 0, st>>>(lv.st_cand.p, lv.st_child.p, up.nb, per, lv.gtab.p, all_far, zr, W, V);
+        };
+        if (zero_row) {   // W carries a row of zeros at index nb
+            if (quad) launch(m2l_stencil_quad_kernel<true>, 768, (uint32_t)lv.nb);
+            else launch(m2l_stencil_shared_kernel<true>, 512, (uint32_t)lv.nb);
+        } else {
+            if (quad) launch(m2l_stencil_quad_kernel<false>, 768, 0u);
+            else launch(m2l_stencil_shared_kernel<false>, 512, 0u);
+        }
         F3M_HIP(hipGetLastError());
         return true;
     }
