@@ -1375,6 +1375,23 @@ __device__ inline void point_weights(const float *__restrict__ x, const int32_t 
     }
 }
 
+// The same with the number of nodes known when compiled, one dimension.
+template <int PN>
+__device__ inline void dim_weights(float x, int32_t cell, double alpha, const CentreArg &C, const NodeArg &N, float *out) {
+    const double centre = alpha + ((double)cell + 0.5) * C.edge;
+    const float t = (float)(((double)x - centre) * C.inv_half);
+#pragma unroll
+    for (int i = 0; i < PN; ++i) {
+        float num = 1.f;
+#pragma unroll
+        for (int j = 0; j < PN; ++j)
+            if (j != i) num *= t - N.s[j];
+        out[i] = num * N.invden[i];
+    }
+}
+
+constexpr int ipow(int p, int e) { return e <= 0 ? 1 : p * ipow(p, e - 1); }
+
 // node index -> packed digits (4 bits per dimension)
 template <int D>
 __device__ inline uint32_t node_code(int i, int p) {
@@ -1389,21 +1406,20 @@ __device__ inline uint32_t node_code(int i, int p) {
 
 // ------------------------------------------------------------------------------------
 // P2M, v1 = L_Y b (Fig. 4 step 1): W_q[i] = sum_{j in q} L_i(t_j) b_j.
-// One block per chunk (a run of <= P2M_CHUNK points of one box), one thread per node (or
-// several nodes per thread when r > NT); points are staged 64 at a time through LDS as
-// their 1-D basis values.  No atomics: a box with several chunks gets partial sums that
-// p2m_reduce_kernel adds in a fixed order.
+// One block per chunk (a run of <= P2M_CHUNK points of one box); points are staged through LDS as their 1-D basis
+// values.  No atomics: a box with several chunks gets partial sums that p2m_reduce_kernel adds in a fixed order.
+// At most 64 nodes: a wavefront per chunk, a lane per node; with at most 32 nodes the lanes form groups that share the
+// points (16 nodes, 256 points: 64 steps instead of 256).
 // ------------------------------------------------------------------------------------
 constexpr int FF_TP = 64;  // points staged per step
 
-template <int D, int NT>
-__global__ __launch_bounds__(NT) void p2m_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
+template <int D>
+__global__ __launch_bounds__(64) void p2m_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
                                                  const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
                                                  const uint32_t *__restrict__ chunk_box,
                                                  const uint32_t *__restrict__ chunk_first, int64_t nchunks, int p,
                                                  int r, CentreArg C, NodeArg N, float *__restrict__ W,
                                                  float *__restrict__ Wpart) {
-    constexpr int NPT_MAX = NT == 64 ? 1 : MAX_NODES / 256;
     extern __shared__ float lds[];
     const int DP = D * p;
     float *wts = lds;                 // [FF_TP][DP]
@@ -1415,43 +1431,154 @@ __global__ __launch_bounds__(NT) void p2m_kernel(const float *__restrict__ Xs, c
     const uint32_t nch = chunk_first[a + 1] - chunk_first[a];
     const uint32_t k0 = start[a] + ci * (uint32_t)P2M_CHUNK;
     const uint32_t k1 = min(k0 + (uint32_t)P2M_CHUNK, start[a + 1]);
-    const int npt = (r + NT - 1) / NT;
-    uint32_t code[NPT_MAX];
-    float acc[NPT_MAX];
-#pragma unroll
-    for (int m = 0; m < NPT_MAX; ++m) {
-        int i = threadIdx.x + m * NT;
-        code[m] = node_code<D>(i < r ? i : 0, p);
-        acc[m] = 0.f;
-    }
+    const int tid = threadIdx.x;
+    const int groups = 64 / r, g = tid / r, i = tid - g * r;   // lanes behind the last whole group have no points
+    const uint32_t code = node_code<D>(i, p);
+    float acc = 0.f;
     for (uint32_t kb = k0; kb < k1; kb += FF_TP) {
         const int cnt = (int)min((uint32_t)FF_TP, k1 - kb);
         __syncthreads();
-        if ((int)threadIdx.x < cnt) {
-            const int64_t k = (int64_t)kb + threadIdx.x;
-            point_weights<D>(Xs + k * D, cell + (int64_t)a * D, C, N, p, wts + threadIdx.x * DP);
-            bj[threadIdx.x] = bs[k];
+        if (tid < cnt) {
+            const int64_t k = (int64_t)kb + tid;
+            point_weights<D>(Xs + k * D, cell + (int64_t)a * D, C, N, p, wts + tid * DP);
+            bj[tid] = bs[k];
         }
         __syncthreads();
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float *wj = wts + jj * DP;
-            const float bv = bj[jj];
+        if (g < groups) {
+            for (int jj = g; jj < cnt; jj += groups) {
+                const float *wj = wts + jj * DP;
+                float prod = bj[jj];
 #pragma unroll
-            for (int m = 0; m < NPT_MAX; ++m) {
-                if (m < npt) {
-                    float prod = bv;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) prod *= wj[d * p + ((code[m] >> (4 * d)) & 15u)];
-                    acc[m] += prod;
-                }
+                for (int d = 0; d < D; ++d) prod *= wj[d * p + ((code >> (4 * d)) & 15u)];
+                acc += prod;
             }
         }
     }
-    float *dst = nch == 1 ? W + (int64_t)a * r : Wpart + c * r;
+    __syncthreads();
+    bj[tid] = acc;
+    __syncthreads();
+    if (tid < r) {
+        for (int q = 1; q < groups; ++q) acc += bj[q * r + tid];
+        float *dst = nch == 1 ? W + (int64_t)a * r : Wpart + c * r;
+        dst[tid] = acc;
+    }
+}
+
+// More than 64 nodes.  The nodes are a tensor grid, so W is a sum over points of outer products: the weights over the lower
+// dimensions (RA of them) times those over the upper ones (RB, times b), both made once per point in LDS.  A thread
+// owns PN x PN nodes -- the lowest dimension of either half -- so it reads 2 PN values for PN^2 multiply-adds, and where
+// that leaves threads over they form groups that share the points.  (A thread per node read D values and multiplied D
+// times for each: n = 3e5, D = 7, 3 nodes, both depths 6.1 ms.)
+template <int D, int PN>
+struct P2mHalves {
+    static constexpr int DA = (D + 1) / 2, DB = D - DA;
+    static constexpr int RA = ipow(PN, DA), RB = ipow(PN, DB), R = RA * RB;
+    static constexpr int TA = RA / PN, TB = RB / PN, ITEMS = TA * TB;
+    static constexpr int GROUPS = 256 / ITEMS;
+    static constexpr int TP = 32;   // points staged per step
+    static_assert(DB >= 1 && ITEMS <= 256, "a thread per PN x PN nodes");
+};
+template <int D, int PN>
+__global__ __launch_bounds__(256) void p2m_halves_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
+                                                         const uint32_t *__restrict__ start,
+                                                         const int32_t *__restrict__ cell,
+                                                         const uint32_t *__restrict__ chunk_box,
+                                                         const uint32_t *__restrict__ chunk_first, int64_t nchunks,
+                                                         CentreArg C, NodeArg N, float *__restrict__ W,
+                                                         float *__restrict__ Wpart) {
+    using H = P2mHalves<D, PN>;
+    constexpr int TP = H::TP;
+    __shared__ float wts[TP][D * PN];
+    __shared__ float half_a[TP][H::RA], half_b[TP][H::RB];
+    __shared__ float sums[H::GROUPS > 1 ? H::R : 1];
+    const int64_t c = block_index();
+    if (c >= nchunks) return;
+    const uint32_t a = chunk_box[c];
+    const uint32_t ci = (uint32_t)(c - chunk_first[a]);
+    const uint32_t nch = chunk_first[a + 1] - chunk_first[a];
+    const uint32_t k0 = start[a] + ci * (uint32_t)P2M_CHUNK;
+    const uint32_t k1 = min(k0 + (uint32_t)P2M_CHUNK, start[a + 1]);
+    const int tid = threadIdx.x;
+    const int g = tid / H::ITEMS, item = tid - g * H::ITEMS;
+    const int ia = (item % H::TA) * PN, ib = (item / H::TA) * PN;
+    float acc[PN][PN];
 #pragma unroll
-    for (int m = 0; m < NPT_MAX; ++m) {
-        int i = threadIdx.x + m * NT;
-        if (m < npt && i < r) dst[i] = acc[m];
+    for (int v = 0; v < PN; ++v)
+#pragma unroll
+        for (int u = 0; u < PN; ++u) acc[v][u] = 0.f;
+    for (uint32_t kb = k0; kb < k1; kb += TP) {
+        const int cnt = (int)min((uint32_t)TP, k1 - kb);
+        __syncthreads();
+        for (int e = tid; e < TP * D; e += 256) {
+            const int j = e / D, d = e - j * D;
+            if (j < cnt)
+                dim_weights<PN>(Xs[((int64_t)kb + j) * D + d], cell[(int64_t)a * D + d], C.alpha[d], C, N, &wts[j][d * PN]);
+        }
+        __syncthreads();
+        for (int e = tid; e < TP * H::RA; e += 256) {
+            const int j = e / H::RA;
+            int q = e - j * H::RA;
+            const int at = q;
+            float prod = 1.f;
+#pragma unroll
+            for (int d = 0; d < H::DA; ++d) {
+                prod *= wts[j][d * PN + q % PN];
+                q /= PN;
+            }
+            half_a[j][at] = prod;
+        }
+        for (int e = tid; e < TP * H::RB; e += 256) {
+            const int j = e / H::RB;
+            int q = e - j * H::RB;
+            const int at = q;
+            float prod = j < cnt ? bs[(int64_t)kb + j] : 0.f;
+#pragma unroll
+            for (int d = 0; d < H::DB; ++d) {
+                prod *= wts[j][(H::DA + d) * PN + q % PN];
+                q /= PN;
+            }
+            half_b[j][at] = prod;
+        }
+        __syncthreads();
+        if (g < H::GROUPS) {
+            for (int j = g; j < cnt; j += H::GROUPS) {
+                float A[PN], B[PN];
+#pragma unroll
+                for (int u = 0; u < PN; ++u) {
+                    A[u] = half_a[j][ia + u];
+                    B[u] = half_b[j][ib + u];
+                }
+#pragma unroll
+                for (int v = 0; v < PN; ++v)
+#pragma unroll
+                    for (int u = 0; u < PN; ++u) acc[v][u] = fmaf(A[u], B[v], acc[v][u]);
+            }
+        }
+    }
+    // the groups' sums one after the other, in ascending order
+    if constexpr (H::GROUPS > 1) {
+        for (int q = H::GROUPS - 1; q >= 1; --q) {
+            if (g == q) {
+#pragma unroll
+                for (int v = 0; v < PN; ++v)
+#pragma unroll
+                    for (int u = 0; u < PN; ++u) {
+                        float *at = &sums[(ia + u) + H::RA * (ib + v)];
+                        *at = q == H::GROUPS - 1 ? acc[v][u] : *at + acc[v][u];
+                    }
+            }
+            __syncthreads();
+        }
+    }
+    if (g == 0) {
+        float *dst = nch == 1 ? W + (int64_t)a * H::R : Wpart + c * H::R;
+#pragma unroll
+        for (int v = 0; v < PN; ++v)
+#pragma unroll
+            for (int u = 0; u < PN; ++u) {
+                const int i = (ia + u) + H::RA * (ib + v);
+                dst[i] = H::GROUPS > 1 ? acc[v][u] + sums[i] : acc[v][u];
+            }
     }
 }
 
@@ -1518,21 +1645,57 @@ __global__ __launch_bounds__(256) void p2m_slice_sum_kernel(const uint32_t *__re
 
 // ------------------------------------------------------------------------------------
 // L2P, v = L_X^T v2 (Fig. 4 step 3): y_a += sum_i L_i(t_a) V_p[i] for the points a of box p.
-// One block per chunk, one thread per point; V_p and the 1-D basis values sit in LDS.
+// One block per chunk, one thread per point; V_p in LDS (every lane reads the same entry).  The sum is nested over the
+// dimensions, p + p^2 + ... + p^D multiply-adds; the dimensions of at most 81 nodes are unrolled with their basis values in
+// registers, the others are loops that read theirs from LDS.  (One loop over all nodes that multiplied D basis
+// values each: n = 3e5, D = 7, 3 nodes, both depths 1.5 ms.)
 // ------------------------------------------------------------------------------------
-template <int D>
+template <int D, int PN>
+struct L2pShape {
+    static constexpr int inner() {
+        int d = 1;
+        while (d < D && ipow(PN, d + 1) <= 81) ++d;
+        return d;
+    }
+    static constexpr int IN = inner(), OUT = D - IN;   // unrolled and looped dimensions
+};
+// sum over the nodes of dimensions 0 .. d
+template <int PN, int IN, int d>
+__device__ __forceinline__ float l2p_inner(const float (&L)[IN][PN], const float *V) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < PN; ++i) {
+        if constexpr (d == 0) s = fmaf(L[0][i], V[i], s);
+        else s = fmaf(L[d][i], l2p_inner<PN, IN, (d > 0 ? d - 1 : 0)>(L, V + i * ipow(PN, d)), s);
+    }
+    return s;
+}
+// dimensions 0 .. IN - 1 + o, o > 0: wo holds the basis values of the looped dimensions
+template <int PN, int IN, int o>
+__device__ __forceinline__ float l2p_outer(const float (&L)[IN][PN], const float *wo, const float *V) {
+    if constexpr (o == 0) {
+        return l2p_inner<PN, IN, IN - 1>(L, V);
+    } else {
+        float s = 0.f;
+#pragma unroll 1
+        for (int i = 0; i < PN; ++i)
+            s = fmaf(wo[(o - 1) * PN + i], l2p_outer<PN, IN, (o > 0 ? o - 1 : 0)>(L, wo, V + i * ipow(PN, IN + o - 1)), s);
+        return s;
+    }
+}
+template <int D, int PN>
 __global__ __launch_bounds__(P2M_CHUNK) void l2p_kernel(const float *__restrict__ Xs,
                                                         const uint32_t *__restrict__ start,
                                                         const int32_t *__restrict__ cell,
                                                         const uint64_t *__restrict__ far_ptr,
                                                         const uint32_t *__restrict__ chunk_box,
                                                         const uint32_t *__restrict__ chunk_first, int64_t nchunks,
-                                                        int p, int r, CentreArg C, NodeArg N,
-                                                        const float *__restrict__ V, float *__restrict__ ys) {
-    extern __shared__ float lds[];
-    const int DP = D * p, stride = DP + 1;
-    float *Vs = lds;          // [r]
-    float *wts = lds + r;     // [P2M_CHUNK][stride]
+                                                        CentreArg C, NodeArg N, const float *__restrict__ V,
+                                                        float *__restrict__ ys) {
+    constexpr int R = ipow(PN, D), IN = L2pShape<D, PN>::IN, OUT = L2pShape<D, PN>::OUT;
+    constexpr int STRIDE = (OUT * PN) | 1;
+    __shared__ float Vs[R];
+    __shared__ float wts[OUT > 0 ? P2M_CHUNK * STRIDE : 1];
     const int64_t c = block_index();
     if (c >= nchunks) return;
     const uint32_t a = chunk_box[c];
@@ -1540,28 +1703,40 @@ __global__ __launch_bounds__(P2M_CHUNK) void l2p_kernel(const float *__restrict_
     const uint32_t ci = (uint32_t)(c - chunk_first[a]);
     const uint32_t k = start[a] + ci * (uint32_t)P2M_CHUNK + threadIdx.x;
     const bool active = k < start[a + 1];
-    for (int i = threadIdx.x; i < r; i += P2M_CHUNK) Vs[i] = V[(int64_t)a * r + i];
-    float *w = wts + threadIdx.x * stride;
-    if (active) point_weights<D>(Xs + (int64_t)k * D, cell + (int64_t)a * D, C, N, p, w);
+    for (int i = threadIdx.x; i < R; i += P2M_CHUNK) Vs[i] = V[(int64_t)a * R + i];
+    float L[IN][PN];
+    float *w = wts + (OUT > 0 ? threadIdx.x * STRIDE : 0);
+    if (active) {
+#pragma unroll
+        for (int d = 0; d < IN; ++d)
+            dim_weights<PN>(Xs[(int64_t)k * D + d], cell[(int64_t)a * D + d], C.alpha[d], C, N, L[d]);
+#pragma unroll
+        for (int d = IN; d < D; ++d)
+            dim_weights<PN>(Xs[(int64_t)k * D + d], cell[(int64_t)a * D + d], C.alpha[d], C, N, w + (d - IN) * PN);
+    }
     __syncthreads();
     if (!active) return;
-    int dig[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) dig[d] = 0;
-    float acc = 0.f;
-    for (int i = 0; i < r; ++i) {
-        float prod = Vs[i];
-#pragma unroll
-        for (int d = 0; d < D; ++d) prod *= w[d * p + dig[d]];
-        acc += prod;
-        // next multi-index, dimension 0 fastest
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (++dig[d] < p) break;
-            dig[d] = 0;
-        }
+    ys[k] += l2p_outer<PN, IN, OUT>(L, w, Vs);
+}
+
+// f(integral constant of the number of nodes per dimension) for a shape with at most MAX_NODES nodes
+template <int D, class F>
+static void for_nodes(int p, F &&f) {
+    auto at = [&](auto pn) {
+        constexpr int PN = decltype(pn)::value;
+        if constexpr (ipow(PN, D) <= MAX_NODES) f(pn);
+        else fail(F3M_ERR_UNSUPPORTED, "interp_nodes^D exceeds the node cap");
+    };
+    switch (p) {
+        case 2: at(std::integral_constant<int, 2>{}); break;
+        case 3: at(std::integral_constant<int, 3>{}); break;
+        case 4: at(std::integral_constant<int, 4>{}); break;
+        case 5: at(std::integral_constant<int, 5>{}); break;
+        case 6: at(std::integral_constant<int, 6>{}); break;
+        case 7: at(std::integral_constant<int, 7>{}); break;
+        case 8: at(std::integral_constant<int, 8>{}); break;
+        default: fail(F3M_ERR_UNSUPPORTED, "interp_nodes must be in [2,8]");
     }
-    ys[k] += acc;
 }
 
 // ------------------------------------------------------------------------------------
@@ -2688,13 +2863,16 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                                                                   sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS,
                                                                   P.W.p, P.Wpart.p, single_chunks(sv));
         else if (r <= 64)
-            p2m_kernel<D, 64><<<grid_for(sv.nchunks), dim3(64), sh, st>>>(
+            p2m_kernel<D><<<grid_for(sv.nchunks), dim3(64), sh, st>>>(
                 Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, p, r, CS, N,
                 P.W.p, P.Wpart.p);
         else
-            p2m_kernel<D, 256><<<grid_for(sv.nchunks), dim3(256), sh, st>>>(
-                Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, p, r, CS, N,
-                P.W.p, P.Wpart.p);
+            for_nodes<D>(p, [&](auto pn) {
+                constexpr int PN = decltype(pn)::value;
+                if constexpr (ipow(PN, D) > 64)
+                    p2m_halves_kernel<D, PN><<<grid_for(sv.nchunks), dim3(256), 0, st>>>(
+                        Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS, N, P.W.p, P.Wpart.p);
+            });
         F3M_HIP(hipGetLastError());
         if (sv.max_box > P2M_CHUNK)   // some box has several chunks
             reduce_partials(P, sv, r, P.W.p, st);
@@ -2755,7 +2933,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
         if (!on_its_own(l)) continue;
-        const int p = lv.p, r = lv.r;
+        const int p = lv.p;
         const NodeArg N = make_nodes(p);
         hipEvent_t *ev = level_events(l);
         const CentreArg C = make_centre(P, l);          // target grid
@@ -2772,15 +2950,16 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (!(lv.far_implicit && run_m2l_stencil(P, l, P.W.p, P.V.p, st))) kron_m2l(l, P.W.p, P.V.p);
         ev[3] = ev[4] = now = mark();
         {
-            size_t sh = (size_t)(r + P2M_CHUNK * (D * p + 1)) * sizeof(float);
             if (D == 3 && p == 4)
                 l2p34_kernel<<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p,
                                                                       lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C,
                                                                       P.V.p, P.ys.p, P.ys.p, single_chunks(lv));
             else
-                l2p_kernel<D><<<grid_for(lv.nchunks), dim3(P2M_CHUNK), sh, st>>>(
-                    P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, p, r, C, N,
-                    P.V.p, P.ys.p);
+                for_nodes<D>(p, [&](auto pn) {
+                    l2p_kernel<D, decltype(pn)::value><<<grid_for(lv.nchunks), dim3(P2M_CHUNK), 0, st>>>(
+                        P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, N,
+                        P.V.p, P.ys.p);
+                });
             F3M_HIP(hipGetLastError());
         }
         ev[5] = now = mark();
