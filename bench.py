@@ -253,7 +253,8 @@ def main():
     near_depth = int(plan.product_info().near_depth)
     near_interpolated = near_depth > 0
     Lw = near_depth or max([l for l in range(1, L + 1) if level_ms[l][1] > 0 and int(inf.far_pairs[l]) > 0], default=L)
-    pairs = 0 if near_interpolated else int(inf.near_point_pairs)
+    weighted = plan.near_weighted()   # > 0: near pairs between weighted points instead of exact sums
+    pairs = 0 if near_interpolated or weighted else int(inf.near_point_pairs)
     far_points = bool(plan.product_info().far_points[Lw])
     far_L = int(inf.far_pairs[Lw]) + (int(inf.near_pairs[Lw]) if near_interpolated else 0)
     r = inf.nodes_per_box
@@ -392,7 +393,8 @@ def main():
                    "depth": L, "leaf_max": 128, "boxes_leaf": int(inf.nboxes[L]),
                    "near_pairs_leaf": int(inf.near_pairs[L]), "far_pairs_leaf": int(inf.far_pairs[L]),
                    "product_depth": Lw, "near_field": "interpolated at depth %d to within fp32 rounding (truncation bound "
-                   "2^-24 of a kernel value)" % Lw if near_interpolated else "exact sums", "device_bytes": int(inf.device_bytes),
+                   "2^-24 of a kernel value)" % Lw if near_interpolated else "interpolated at depth %d between weighted points "
+                   "(the error there is below 2^-24 of a kernel value)" % weighted if weighted else "exact sums", "device_bytes": int(inf.device_bytes),
                    "eta_smooth": args.eta_smooth, "adaptive_far": bool(args.adaptive_far),
                    "smooth_depth": int(inf.smooth_depth),
                    "arithmetic": "fp32 throughout; the near-field exponents -|x-y|^2/(2 gamma^2) come from one fp16 MFMA on "

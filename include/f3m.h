@@ -295,13 +295,19 @@ f3m_status f3m_plan_info(const f3m_plan_t *plan, f3m_info *out);
 /* How the products of a plan work, where that is not one M2L per depth and exact sums at depth L.  Chosen by
  * f3m_plan; costs nothing to ask for. */
 typedef struct {
-    int32_t near_depth;                        /* 0: the near pairs of depth L are summed exactly.  k > 0: the
+    int32_t near_depth;                        /* 0: the near pairs of depth L are summed exactly (or to within fp32
+                                                  rounding, see f3m_plan_near_weighted).  k > 0: the
                                                   products work down to depth k only and interpolate every pair
                                                   left there (the tree and the lists of f3m_info still end at L) */
     int32_t far_points[F3M_MAX_LEVELS + 1];    /* 1: the far pairs of the depth are interpolated from point to
                                                   point, without node weights (its P2M and L2P times are 0) */
 } f3m_product_info;
 f3m_status f3m_plan_product_info(const f3m_plan_t *plan, f3m_product_info *out);
+
+/* k > 0: the products end at depth k and interpolate its near pairs between points weighted with the Gaussian of their
+ * place in their box, which is off by no more than 2^-24 of a kernel value there (the stage time p2p is that of these
+ * pairs between the boxes).  0: not so, or no plan. */
+int f3m_plan_near_weighted(const f3m_plan_t *plan);
 
 /* perm[k] = caller's index of the k-th point in box order (n entries): the
  * permutation pi of Sec. 4.1; ascending (key, index). */

@@ -298,6 +298,8 @@ f3m_status f3m_plan_product_info(const f3m_plan_t *plan, f3m_product_info *out) 
     return F3M_OK;
 }
 
+int f3m_plan_near_weighted(const f3m_plan_t *plan) { return plan ? plan->near_weighted : 0; }
+
 f3m_status f3m_plan_get_perm(const f3m_plan_t *plan, uint32_t *perm_host) {
     if (!plan || !perm_host) return set_error(F3M_ERR_INVALID_ARG, "null argument");
     return guarded([&] { copy_to_host(perm_host, plan->perm.p, built(plan) ? (size_t)plan->n : 0); });

@@ -1758,12 +1758,24 @@ __device__ inline void lagrange4(float t, float (&L)[4]) {
     L[3] = p01 * d2 * (-1.f / 1.5f);
 }
 
-__device__ inline void weights34(const float *__restrict__ x, const double (&ctr)[3], double inv_half, float (&Lx)[4],
-                                 float (&Ly)[4], float (&Lz)[4]) {
-    lagrange4((float)(((double)x[0] - ctr[0]) * inv_half), Lx);
-    lagrange4((float)(((double)x[1] - ctr[1]) * inv_half), Ly);
-    lagrange4((float)(((double)x[2] - ctr[2]) * inv_half), Lz);
+// returns the squared distance from the box centre in units of (l / 2)^2
+__device__ inline float weights34(const float *__restrict__ x, const double (&ctr)[3], double inv_half, float (&Lx)[4],
+                                  float (&Ly)[4], float (&Lz)[4]) {
+    const float tx = (float)(((double)x[0] - ctr[0]) * inv_half), ty = (float)(((double)x[1] - ctr[1]) * inv_half),
+                tz = (float)(((double)x[2] - ctr[2]) * inv_half);
+    lagrange4(tx, Lx);
+    lagrange4(ty, Ly);
+    lagrange4(tz, Lz);
+    return fmaf(tz, tz, fmaf(ty, ty, tx * tx));
 }
+
+// The weighted near pairs (near_weighted_error in plan.hip) need a second set of node weights, of points times
+// exp(-|u|^2 / 2 gamma^2) = exp2(kw |u|^2 / (l/2)^2): the upper half of the workgroups of a P2M launch makes it.  blocks: workgroups
+// of a half, 0 for the plain node weights only; dW, dpart: from the plain to the weighted arrays.
+struct WeightedArg {
+    int64_t blocks, dW, dpart;
+    float kw;
+};
 
 constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
 constexpr int P2M_NCH = 4;     // chunks per wavefront: the table reads and the first loads of all of them are in
@@ -1774,11 +1786,18 @@ __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs,
                                                    const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
                                                    const uint32_t *__restrict__ chunk_box,
                                                    const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
-                                                   float *__restrict__ W, float *__restrict__ Wpart, int one_chunk) {
+                                                   float *__restrict__ W, float *__restrict__ Wpart, int one_chunk,
+                                                   WeightedArg A) {
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ float tr[64 * TR_STRIDE];
-    const int64_t c0 = block_index() * P2M_NCH;
+    const int64_t bi = block_index();
+    const bool weighted = A.blocks > 0 && bi >= A.blocks;
+    const int64_t c0 = (weighted ? bi - A.blocks : bi) * P2M_NCH;
     if (c0 >= nchunks) return;
+    if (weighted) {
+        W += A.dW;
+        Wpart += A.dpart;
+    }
     const int lane = threadIdx.x;
     // chunk j of this wavefront (a chunk beyond the end repeats the last one and is switched off)
     uint32_t a[P2M_NCH], k0[P2M_NCH], k1[P2M_NCH], nch[P2M_NCH];
@@ -1828,7 +1847,8 @@ __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs,
             float xn[3] = {0.f, 0.f, 0.f}, bn = 0.f;
             if (more) load(j, kb + 64, xn, bn);
             float Lx[4], Ly[4], Lz[4];
-            weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
+            const float u2 = weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
+            if (weighted) bc *= __builtin_amdgcn_exp2f(A.kw * u2);
 #pragma unroll
             for (int i3 = 0; i3 < 4; ++i3) {
                 const float zb = Lz[i3] * bc;
@@ -1882,11 +1902,14 @@ constexpr int P2M_NPAIR = 4;
 __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
                                                         const uint32_t *__restrict__ start,
                                                         const int32_t *__restrict__ cell, int64_t nb, CentreArg C,
-                                                        float *__restrict__ W) {
+                                                        float *__restrict__ W, WeightedArg A) {
     // rows of the upper half are shifted by 32 floats so that the two halves read different banks
     __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE + 32];
-    const int64_t b0 = block_index() * (2 * P2M_NPAIR);
+    const int64_t bi = block_index();
+    const bool weighted = A.blocks > 0 && bi >= A.blocks;
+    const int64_t b0 = (weighted ? bi - A.blocks : bi) * (2 * P2M_NPAIR);
     if (b0 >= nb) return;
+    if (weighted) W += A.dW;
     const int lane = threadIdx.x, half = lane >> 5, t = lane & 31;
     uint32_t k0[P2M_NPAIR], k1[P2M_NPAIR];
     int64_t a[P2M_NPAIR];
@@ -1931,7 +1954,8 @@ __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict_
             float xn[3] = {0.f, 0.f, 0.f}, bn = 0.f;
             if (more) load(j, kb + 32, xn, bn);
             float Lx[4], Ly[4], Lz[4];
-            weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
+            const float u2 = weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
+            if (weighted) bc *= __builtin_amdgcn_exp2f(A.kw * u2);
 #pragma unroll
             for (int i3 = 0; i3 < 4; ++i3) {
                 const float zb = Lz[i3] * bc;
@@ -1975,16 +1999,18 @@ __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict_
 
 constexpr int L2P_NCH = 4;   // chunks per wavefront: their loads are in flight together (a chunk alone is a chain
                              // of dependent loads and the kernel is bound by that latency)
+template <bool WEIGHTED>   // Vw: node potentials of the weighted near pairs, evaluated times exp2(kw |u|^2 / (l/2)^2)
 __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs, const uint32_t *__restrict__ start,
                                                    const int32_t *__restrict__ cell,
                                                    const uint64_t *__restrict__ far_ptr,
                                                    const uint32_t *__restrict__ chunk_box,
                                                    const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
                                                    const float *__restrict__ V, const float *base, float *out,
-                                                   int one_chunk) {
+                                                   int one_chunk, const float *__restrict__ Vw, float kw) {
     // out = base (nullptr: zero) + far field
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ __attribute__((aligned(16))) float vbuf[L2P_NCH][64];
+    __shared__ __attribute__((aligned(16))) float wbuf[WEIGHTED ? L2P_NCH : 1][64];
     const int64_t c0 = block_index() * L2P_NCH;
     if (c0 >= nchunks) return;
     const int lane = threadIdx.x;
@@ -1998,7 +2024,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
         a[j] = one_chunk ? (uint32_t)c : (uint32_t)__builtin_amdgcn_readfirstlane(chunk_box[c]);
     }
     double ctr[L2P_NCH][3];
-    float vrow[L2P_NCH];
+    float vrow[L2P_NCH], wrow[L2P_NCH];
 #pragma unroll
     for (int j = 0; j < L2P_NCH; ++j) {
         const int64_t c = c0 + j < nchunks ? c0 + j : nchunks - 1;
@@ -2012,31 +2038,41 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
 #pragma unroll
         for (int d = 0; d < 3; ++d) ctr[j][d] = C.alpha[d] + ((double)cell[(int64_t)a[j] * 3 + d] + 0.5) * C.edge;
         vrow[j] = V[(int64_t)a[j] * 64 + lane];             // the node potentials of the box, one per lane
+        if constexpr (WEIGHTED) wrow[j] = Vw[(int64_t)a[j] * 64 + lane];
     }
     // The node potentials reach the lanes as LDS broadcasts (every lane reads the same address);
     // as scalar operands they arrive in four dependent batches per box.
 #pragma unroll
-    for (int j = 0; j < L2P_NCH; ++j) vbuf[j][lane] = vrow[j];
+    for (int j = 0; j < L2P_NCH; ++j) {
+        vbuf[j][lane] = vrow[j];
+        if constexpr (WEIGHTED) wbuf[j][lane] = wrow[j];
+    }
     __builtin_amdgcn_wave_barrier();   // one wavefront per block; its LDS operations complete in order
     // one run of 64 points of a chunk: y += sum_i L_i(t) V[i], nested over the dimensions
     auto run = [&](int j, bool live, uint32_t k, const float (&x)[3], float yold) {
         float Lx[4], Ly[4], Lz[4];
-        weights34(x, ctr[j], C.inv_half, Lx, Ly, Lz);
-        float y = 0.f;
+        const float u2 = weights34(x, ctr[j], C.inv_half, Lx, Ly, Lz);
+        auto sum = [&](const float *vb) __attribute__((always_inline)) {
+            float y = 0.f;
 #pragma unroll
-        for (int i3 = 0; i3 < 4; ++i3) {
-            float sy = 0.f;
+            for (int i3 = 0; i3 < 4; ++i3) {
+                float sy = 0.f;
 #pragma unroll
-            for (int i2 = 0; i2 < 4; ++i2) {
-                const float4 v = *reinterpret_cast<const float4 *>(&vbuf[j][4 * i2 + 16 * i3]);
-                float sx = Lx[0] * v.x;
-                sx = fmaf(Lx[1], v.y, sx);
-                sx = fmaf(Lx[2], v.z, sx);
-                sx = fmaf(Lx[3], v.w, sx);
-                sy = fmaf(Ly[i2], sx, sy);
+                for (int i2 = 0; i2 < 4; ++i2) {
+                    const float4 v = *reinterpret_cast<const float4 *>(vb + 4 * i2 + 16 * i3);
+                    float sx = Lx[0] * v.x;
+                    sx = fmaf(Lx[1], v.y, sx);
+                    sx = fmaf(Lx[2], v.z, sx);
+                    sx = fmaf(Lx[3], v.w, sx);
+                    sy = fmaf(Ly[i2], sx, sy);
+                }
+                y = fmaf(Lz[i3], sy, y);
             }
-            y = fmaf(Lz[i3], sy, y);
-        }
+            return y;
+        };
+        float y = sum(vbuf[j]);
+        if constexpr (WEIGHTED) __builtin_amdgcn_sched_barrier(0);   // one set of potentials at a time in registers: 125, not 176
+        if constexpr (WEIGHTED) y = fmaf(__builtin_amdgcn_exp2f(kw * u2), sum(wbuf[WEIGHTED ? j : 0]), y);
         if (live) out[k] = yold + y;
     };
     // Loads are unconditional with the index of a lane beyond the chunk clamped to the chunk's first
@@ -2055,7 +2091,10 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
         yold[j] = base ? base[kk[j]] : 0.f;
     }
 #pragma unroll
-    for (int j = 0; j < L2P_NCH; ++j) run(j, live[j], kk[j], x[j], yold[j]);
+    for (int j = 0; j < L2P_NCH; ++j) {
+        run(j, live[j], kk[j], x[j], yold[j]);
+        if constexpr (WEIGHTED) __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int j = 0; j < L2P_NCH; ++j) {
         for (uint32_t kb = k0[j] + 64; kb < k1[j]; kb += 64) {
@@ -2608,7 +2647,7 @@ void build_far_orders(f3m_plan_s &P, hipStream_t st) {
 void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
-        if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && l > P.near_depth)) continue;
+        if (lv.far_sz == 0 || lv.p == 0 || l > P.last_depth()) continue;
         const int p = lv.p;
         std::vector<double> s(p);
         for (int k = 0; k < p; ++k) s[k] = p > 1 ? std::cos(M_PI * (double)k / (double)(p - 1)) : 0.0;
@@ -2650,14 +2689,14 @@ void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
 
 // ------------------------------------------------------------------------------------
 // partial node weights of the chunks of a box -> W, in one or two stages
-static void reduce_partials(f3m_plan_s &P, f3m_level &lv, int r, float *W, hipStream_t st) {
+static void reduce_partials(f3m_plan_s &P, f3m_level &lv, int r, float *W, hipStream_t st, int64_t dpart = 0) {
     if (lv.nslices > 0) {
         p2m_slice_kernel<<<grid_for(lv.nslices), dim3(256), 0, st>>>(lv.slice_box.p, lv.slice_first.p, lv.chunk_first.p,
-                                                                    lv.nslices, r, P.Wpart.p, P.Wslice.p);
+                                                                    lv.nslices, r, P.Wpart.p + dpart, P.Wslice.p);
         p2m_slice_sum_kernel<<<grid_for(lv.nb), dim3(256), 0, st>>>(lv.slice_first.p, lv.chunk_first.p, lv.nb, r,
                                                                    P.Wslice.p, W);
     } else {
-        p2m_reduce_kernel<<<grid_for(lv.nb), dim3(256), 0, st>>>(lv.chunk_first.p, lv.nb, r, P.Wpart.p, W);
+        p2m_reduce_kernel<<<grid_for(lv.nb), dim3(256), 0, st>>>(lv.chunk_first.p, lv.nb, r, P.Wpart.p + dpart, W);
     }
 }
 
@@ -2708,7 +2747,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     if (box_order) bs_in = b;
     const float *bs = bs_in ? bs_in : P.bs.p;
     // no near field: every pair is interpolated (smooth field, or the products stop above the last depth)
-    const bool no_near = !yn_in && P.rho == 0 && (P.lev[P.L].near_sz == 0 || P.near_depth);
+    const bool no_near = !yn_in && P.rho == 0 && (P.lev[P.L].near_sz == 0 || !P.exact_near());
+    // the plan's second stream has nothing to do where the near pairs are interpolated on the first one
+    const hipStream_t side = P.near_weighted ? nullptr : P.side;
     const float *yn = yn_in ? yn_in : no_near ? nullptr : P.yn.p;
     const int64_t n = P.n;
     const float nc2 = (float)(-1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma));
@@ -2741,10 +2782,10 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     P.t_in = now;
     // The near field goes to the plan's second stream (vector ALU work) and overlaps the
     // far field (matrix-core work) on the caller's stream; with no_overlap it runs in line.
-    hipStream_t sn = P.side ? P.side : st;
-    if (P.side) {
+    hipStream_t sn = side ? side : st;
+    if (side) {
         F3M_HIP(hipEventRecord(P.ev_fork, st));
-        F3M_HIP(hipStreamWaitEvent(P.side, P.ev_fork, 0));
+        F3M_HIP(hipStreamWaitEvent(side, P.ev_fork, 0));
         F3M_HIP(hipEventRecord(P.ev_p2p0, sn));
     }
     // exact sums over a CSR list of box pairs of one depth (target tiles given), into yn
@@ -2816,9 +2857,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         }
     }
     F3M_HIP(hipGetLastError());
-    if (P.side) {
-        F3M_HIP(hipEventRecord(P.ev_p2p1, P.side));
-        F3M_HIP(hipEventRecord(P.ev_join, P.side));
+    if (side) {
+        F3M_HIP(hipEventRecord(P.ev_p2p1, side));
+        F3M_HIP(hipEventRecord(P.ev_join, side));
         P.t_p2p0 = P.ev_p2p0;
         P.t_p2p1 = P.ev_p2p1;
     } else {
@@ -2835,7 +2876,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     // no far pairs, dropped by the adaptive rule (Sec. 4.3), or part of the band of the tree
     auto on_its_own = [&](int l) {
         const f3m_level &lv = P.lev[l];
-        return lv.far_sz > 0 && lv.p > 0 && !(P.near_depth && l > P.near_depth) && !(tree && l >= P.tree_lmin && l <= P.tree_lmax);
+        return lv.far_sz > 0 && lv.p > 0 && l <= P.last_depth() && !(tree && l >= P.tree_lmin && l <= P.tree_lmax);
     };
     // Where the band holds every far depth its one L2P writes the far field of every point: nothing to preset, and in box
     // order it adds the near field and writes the result.
@@ -2857,11 +2898,11 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         size_t sh = (size_t)(FF_TP * D * p + FF_TP) * sizeof(float);
         if (D == 3 && p == 4 && single_chunks(sv))
             p2m34_pair_kernel<<<grid_for(cdiv(sv.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.nb,
-                                                                                        CS, P.W.p);
+                                                                                        CS, P.W.p, WeightedArg{});
         else if (D == 3 && p == 4)
             p2m34_kernel<<<grid_for(cdiv(sv.nchunks, P2M_NCH)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p,
                                                                   sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS,
-                                                                  P.W.p, P.Wpart.p, single_chunks(sv));
+                                                                  P.W.p, P.Wpart.p, single_chunks(sv), WeightedArg{});
         else if (r <= 64)
             p2m_kernel<D><<<grid_for(sv.nchunks), dim3(64), sh, st>>>(
                 Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, p, r, CS, N,
@@ -2951,9 +2992,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         ev[3] = ev[4] = now = mark();
         {
             if (D == 3 && p == 4)
-                l2p34_kernel<<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p,
-                                                                      lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C,
-                                                                      P.V.p, P.ys.p, P.ys.p, single_chunks(lv));
+                l2p34_kernel<false><<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
+                    P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, P.V.p, P.ys.p,
+                    P.ys.p, single_chunks(lv), nullptr, 0.f);
             else
                 for_nodes<D>(p, [&](auto pn) {
                     l2p_kernel<D, decltype(pn)::value><<<grid_for(lv.nchunks), dim3(P2M_CHUNK), 0, st>>>(
@@ -2974,22 +3015,37 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         const int L = P.tree_lmax;
         const int r = 64;
         f3m_level &lf = P.lev[L];
+        // near pairs between weighted points: exp2(kw |u|^2 / (l/2)^2) = exp(-|u|^2 / 2 gamma^2)
+        const bool weighted = P.near_weighted == L;
+        if (P.near_weighted && !weighted) fail(F3M_ERR_HIP, "internal: weighted near pairs outside the last depth of the tree");
+        const double half = 0.5 * (double)P.E / std::ldexp(1.0, L);
+        const float kw = (float)(-1.4426950408889634 * half * half / (2.0 * (double)P.gamma * (double)P.gamma));
         if (!P.src) {
             {
                 hipEvent_t *ev = level_events(L);
                 ev[0] = now;
-                if (single_chunks(lf))
-                    p2m34_pair_kernel<<<grid_for(cdiv(lf.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p,
-                                                                                                lf.nb, make_centre(P, L), lf.Wl.p);
+                const bool pairs = single_chunks(lf);
+                const int64_t blocks = pairs ? cdiv(lf.nb, 2 * P2M_NPAIR) : cdiv(lf.nchunks, P2M_NCH);
+                const WeightedArg A{weighted ? blocks : 0, (lf.nb + 1) * r, lf.nchunks * r, kw};
+                const dim3 grid = grid_for(weighted ? 2 * blocks : blocks);
+                if (pairs)
+                    p2m34_pair_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.nb, make_centre(P, L),
+                                                                 lf.Wl.p, A);
                 else
-                    p2m34_kernel<<<grid_for(cdiv(lf.nchunks, P2M_NCH)), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p,
-                                                                          lf.chunk_first.p, lf.nchunks, make_centre(P, L),
-                                                                          lf.Wl.p, P.Wpart.p, single_chunks(lf));
+                    p2m34_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
+                                                            lf.nchunks, make_centre(P, L), lf.Wl.p, P.Wpart.p, 0, A);
                 F3M_HIP(hipGetLastError());
-                if (lf.max_box > P2M_CHUNK)   // some box has several chunks
+                if (lf.max_box > P2M_CHUNK) {   // some box has several chunks
                     reduce_partials(P, lf, r, lf.Wl.p, st);
+                    if (weighted) reduce_partials(P, lf, r, lf.Wl.p + A.dW, st, A.dpart);
+                }
                 F3M_HIP(hipGetLastError());
                 ev[1] = now = mark();
+            }
+            if (weighted) {   // the near field of this product
+                P.t_p2p0 = now;
+                run_near_weighted(P, lf.Wl.p + (lf.nb + 1) * r, lf.Vl.p + lf.nb * r, st);
+                P.t_p2p1 = now = mark();
             }
             for (int l = L - 1; l >= P.tree_lmin; --l) {
                 f3m_level &lv = P.lev[l], &dn = P.lev[l + 1];
@@ -3030,15 +3086,19 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         {
             hipEvent_t *ev = level_events(L);
             if (P.tree_lmin == L) ev[4] = now;
-            if (P.side && direct_out) {   // the near field may be what is waited for: not part of the downward pass
+            if (side && direct_out) {   // the near field may be what is waited for: not part of the downward pass
                 P.t_wait0 = mark();
                 F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
                 P.t_wait1 = mark();
             }
             const float *base = direct_out ? yn : one_l2p ? nullptr : P.ys.p;
-            l2p34_kernel<<<grid_for(cdiv(lf.nchunks, L2P_NCH)), dim3(64), 0, st>>>(P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p,
-                                                                  lf.chunk_first.p, lf.nchunks, make_centre(P, L),
-                                                                  lf.Vl.p, base, direct_out ? y : P.ys.p, single_chunks(lf));
+            auto l2p = [&](auto kern) {
+                kern<<<grid_for(cdiv(lf.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
+                    P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks, make_centre(P, L), lf.Vl.p,
+                    base, direct_out ? y : P.ys.p, single_chunks(lf), weighted ? lf.Vl.p + lf.nb * r : nullptr, kw);
+            };
+            if (weighted) l2p(l2p34_kernel<true>);
+            else l2p(l2p34_kernel<false>);
             F3M_HIP(hipGetLastError());
             ev[5] = now = mark();
         }
@@ -3048,7 +3108,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
             ev[4] = ev[5] = now;
         }
     }
-    if (P.side && !direct_out) {
+    if (side && !direct_out) {
         F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));
         now = mark();
     }
@@ -3083,7 +3143,7 @@ void run_kmvm_multi(f3m_plan_s &P, const float *B, int64_t ldb, float *Y, int64_
     const double gl = 1.4426950408889634 / (2.0 * (double)P.gamma * (double)P.gamma) * CL.edge * CL.edge;
     // the conditions under which the single product uses the plain D = 3 Gram kernel for its near field
     const bool fused = m > 1 && P.D == 3 && gl * 3.0 <= 6.0 && gl > 1e-30 && !P.force_all_near && P.T <= 1024 &&
-                       !(P.src && P.L == 0) && P.rho == 0 && leaf.near_sz > 0 && !P.near_depth && P.ntiles >= 8192;
+                       !(P.src && P.L == 0) && P.rho == 0 && leaf.near_sz > 0 && P.exact_near() && P.ntiles >= 8192;
     if (!fused) {
         for (int j = 0; j < m; ++j) run_kmvm(P, B + (int64_t)j * ldb, Y + (int64_t)j * ldy, st);
         return;

@@ -683,10 +683,146 @@ __global__ __launch_bounds__(768) void m2l_stencil_quad_kernel(const uint32_t *_
 
 constexpr int64_t M2L_QUAD_PARENTS = 1024;
 
+// ------------------------------------------------------------------------------------
+// Near pairs between weighted points (near_weighted_error in plan.hip): V_t = sum over the 27 boxes q around t of
+// G'_{o_z} x G'_{o_y} x G'_{o_x} W'_q with G'_o[i][j] = exp((l/2)^2 / gamma^2 (s_i s_j + 2 o s_i - 2 o s_j - 2 o^2)), o = -1, 0, 1.
+// G'_{-o} is the transpose of G'_o, and G'_o[i][j] = G'_o[3-j][3-i]: 16 different numbers.  The eight children of a parent share
+// their line and plane sums on the inner 4 x 4 x 4 places of its candidate grid, by the scheme of
+// m2l_stencil_quad_kernel: eight wavefronts, one per plane cy = 1 .. 4 and x parity of the targets.  1e7 points, 32768
+// parents: 67 us (exact sums over these pairs: 1560 us), with the second half of the P2M (117 -> 256 us) and the L2P (81 -> 115).
+// ------------------------------------------------------------------------------------
+__host__ __device__ constexpr int near_factor_index(int o, int i, int j) {
+    if (o < 0) return near_factor_index(-o, j, i);
+    const bool far_i = i == 0 || i == 3, far_j = j == 0 || j == 3;   // |s| = 1, else 1/2
+    if (o == 0) return (far_i && far_j ? 0 : far_i || far_j ? 1 : 2) + ((i < 2) != (j < 2) ? 3 : 0);
+    const int a = i + j <= 3 ? i : 3 - j, b = i + j <= 3 ? j : 3 - i;
+    return 6 + (a == 0 ? b : a == 1 ? 4 + b : a == 2 ? 7 + b : 9);
+}
+template <int O>
+__device__ __forceinline__ void near_apply(float (&out)[4], const float (&in)[4], const float (&E)[16]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = fmaf(E[near_factor_index(O, i, j)], in[j], out[i]);
+}
+
+template <int TX>
+__device__ __forceinline__ void near_plane_sums(const uint32_t (*__restrict__ rank)[16], int plane, int lane, uint32_t zero_row,
+                                                const float *__restrict__ W, const float (&E)[16], float *pl) {
+    // lane = iy + 4 (parent) + 16 iz; places TX .. TX + 2 of the four along x
+    const uint32_t *cand = rank[(lane >> 2) & 3];
+    const float *Wl = W + 4 * ((lane & 3) + 4 * (lane >> 4));
+    float u[4][3][4];   // every row of the plane that is needed, all loads in flight together
+#pragma unroll
+    for (int cz = 0; cz < 4; ++cz)
+#pragma unroll
+        for (int cx = 0; cx < 3; ++cx) {
+            const float4 f = *reinterpret_cast<const float4 *>(Wl + (int64_t)min(cand[4 * cz + TX + cx], zero_row) * 64);
+            u[cz][cx][0] = f.x;
+            u[cz][cx][1] = f.y;
+            u[cz][cx][2] = f.z;
+            u[cz][cx][3] = f.w;
+        }
+    float p0[4] = {0.f, 0.f, 0.f, 0.f}, p1[4] = {0.f, 0.f, 0.f, 0.f};   // plane sums of the z parities
+    auto line = [&](auto CZ) __attribute__((always_inline)) {
+        constexpr int cz = decltype(CZ)::value;
+        float l[4] = {0.f, 0.f, 0.f, 0.f};
+        near_apply<-1>(l, u[cz][0], E);
+        near_apply<0>(l, u[cz][1], E);
+        near_apply<1>(l, u[cz][2], E);
+        fibre_swap(l);
+        if constexpr (cz <= 2) near_apply<cz - 1>(p0, l, E);
+        if constexpr (cz >= 1) near_apply<cz - 2>(p1, l, E);
+    };
+    line(std::integral_constant<int, 0>{});
+    line(std::integral_constant<int, 1>{});
+    line(std::integral_constant<int, 2>{});
+    line(std::integral_constant<int, 3>{});
+    // now lane = iy + 4 (parent) + 16 ix; entry (ix, iy, iz) goes to place iy + 4 ix + 16 iz
+    float *dst = pl + (plane * 4 + TX) * (ST_PAR * PL_STRIDE) + ((lane >> 2) & 3) * PL_STRIDE + (lane & 3) + 4 * (lane >> 4);
+#pragma unroll
+    for (int iz = 0; iz < 4; ++iz) {
+        dst[16 * iz] = p0[iz];
+        dst[2 * ST_PAR * PL_STRIDE + 16 * iz] = p1[iz];
+    }
+}
+
+__global__ __launch_bounds__(512) void near_weighted_kernel(const uint32_t *__restrict__ cand_tab,
+                                                            const uint32_t *__restrict__ child_tab, int64_t nparents,
+                                                            int64_t per_xcd, const float *__restrict__ tab,
+                                                            uint32_t zero_row, const float *__restrict__ W,
+                                                            float *__restrict__ V) {
+    __shared__ __attribute__((aligned(16))) float pl[4 * 4 * ST_PAR * PL_STRIDE];   // [plane][tx + 2 tz][parent]
+    __shared__ float es[16];
+    __shared__ uint32_t ranks[4][ST_PAR][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t bi = block_index2();
+    const int64_t p0 = ((bi & 7) * per_xcd + (bi >> 3)) * ST_PAR;
+    if ((bi >> 3) >= per_xcd || p0 >= nparents) return;
+    if (tid < 16) es[tid] = tab[tid];
+    if (tid >= 256) {   // the inner places; a parent behind the last one repeats it, and nothing of it is stored
+        const int e = tid - 256, q = e >> 6, cx = e & 3, cy = (e >> 2) & 3, cz = (e >> 4) & 3;
+        ranks[cy][q][cx + 4 * cz] = cand_tab[min(p0 + q, nparents - 1) * ST_CAND + (cx + 1) + 6 * (cy + 1) + 36 * (cz + 1)];
+    }
+    __syncthreads();
+    float E[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) E[k] = es[k];
+    if (w < 4) near_plane_sums<0>(ranks[w], w, lane, zero_row, W, E, pl);
+    else near_plane_sums<1>(ranks[w - 4], w - 4, lane, zero_row, W, E, pl);
+    __syncthreads();
+    // ---- the child of parity w of the four parents, where it exists: lane = ix + 4 iz + 16 (parent)
+    const int64_t pb = p0 + (lane >> 4);
+    const uint32_t t = pb < nparents ? child_tab[pb * 8 + w] : ~0u;
+    if (__ballot(t != ~0u) == 0ull) return;
+    const int ty = (w >> 1) & 1;
+    const float *src = pl + (4 * ty + (w & 1) + 2 * (w >> 2)) * (ST_PAR * PL_STRIDE) + (lane >> 4) * PL_STRIDE + 4 * (lane & 15);
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    auto plane = [&](auto o) __attribute__((always_inline)) {   // planes ty, ty + 1, ty + 2 of the four
+        constexpr int O = decltype(o)::value;
+        const float4 f = *reinterpret_cast<const float4 *>(src + (O + 1) * 4 * (ST_PAR * PL_STRIDE));
+        const float in[4] = {f.x, f.y, f.z, f.w};
+        near_apply<O>(acc, in, E);
+    };
+    plane(std::integral_constant<int, -1>{});
+    plane(std::integral_constant<int, 0>{});
+    plane(std::integral_constant<int, 1>{});
+    if (t != ~0u) {
+        float *out = V + (int64_t)t * 64 + (lane & 3) + 16 * ((lane >> 2) & 3);
+#pragma unroll
+        for (int iy = 0; iy < 4; ++iy) out[4 * iy] = acc[iy];
+    }
+}
+
+void upload_near_table(f3m_plan_s &P, hipStream_t st) {
+    const double s[4] = {1.0, 0.5, -0.5, -1.0};
+    const double half = 0.5 * (double)P.E / (double)(1ull << P.near_weighted);
+    const double c = half * half / ((double)P.gamma * (double)P.gamma);
+    std::vector<float> t(16);
+    for (int o = 0; o <= 1; ++o)
+        for (int i = 0; i < 4; ++i)
+            for (int j = 0; j < 4; ++j)
+                t[near_factor_index(o, i, j)] = (float)std::exp(c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o)));
+    P.near_tab.alloc(16, &P.bytes);
+    F3M_HIP(hipMemcpyAsync(P.near_tab.p, t.data(), 16 * sizeof(float), hipMemcpyHostToDevice, st));
+    P.host_tabs.push_back(std::move(t));   // stays alive until the plan has been waited for
+}
+
+// W: weighted node weights of depth near_weighted with a row of zeros behind them
+void run_near_weighted(f3m_plan_s &P, const float *W, float *V, hipStream_t st) {
+    f3m_level &lv = P.lev[P.near_weighted], &up = P.lev[P.near_weighted - 1];
+    const int64_t per_xcd = cdiv(cdiv(up.nb, ST_PAR), 8);
+    near_weighted_kernel<<<grid2(per_xcd * 8), dim3(512), 0, st>>>(lv.st_cand.p, lv.st_child.p, up.nb, per_xcd, P.near_tab.p,
+                                                                  (uint32_t)lv.nb, W, V);
+    F3M_HIP(hipGetLastError());
+}
+
 // candidate and child tables of a depth whose M2L runs on the candidate grid without a small field
 // the tables of a depth, preset to "none"; false: the depth does not use them
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st) {
-    if (!m2l_stencil_applies(P) || level < 1 || P.rho != 0 || (P.near_depth && level > P.near_depth)) return false;
+    // (while the depths are built their last one for the products, P.near_weighted, is not yet known)
+    if (!m2l_stencil_applies(P) || level < 1 || P.rho != 0 || (P.near_depth && level > P.near_depth) ||
+        (P.near_weighted && level > P.near_weighted)) return false;
     f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
     if (!lv.far_implicit || lv.far_sz == 0 || lv.p == 0) return false;
     lv.st_cand.alloc((size_t)up.nb * ST_CAND, &P.bytes);

@@ -51,7 +51,8 @@ struct f3m_level {
     f3m::DevBuf<float> gtab;
     int gtab_omax = 0;
     // node weights / node potentials kept per depth when they are passed between depths
-    f3m::DevBuf<float> Wl, Vl;          // [nb*64]
+    f3m::DevBuf<float> Wl, Vl;          // [(nb + 1) * 64], [nb * 64]; at depth near_weighted the same again behind
+                                        // them for the weighted near pairs
 };
 
 // Tables of the three-pass permutation between the caller's order and the box order of one point set
@@ -144,6 +145,11 @@ struct f3m_plan_s {
     }
     int near_depth = 0;                 // > 0: the products work down to this depth only, whose adjacent pairs are
                                         // interpolated too, to within fp32 rounding (near_interp_error)
+    int near_weighted = 0;              // > 0: the products end at this depth, whose near pairs are interpolated between
+                                        // weighted points, to within fp32 rounding (near_weighted_error)
+    bool exact_near() const { return near_depth == 0 && near_weighted == 0; }
+    int last_depth() const { return near_depth ? near_depth : near_weighted ? near_weighted : L; }   // of the products
+    f3m::DevBuf<float> near_tab;        // [16] factors of the weighted near pairs (near_factor_index)
     int tree_lmin = 0, tree_lmax = 0;   // tree_lmin > 0: node weights/potentials are passed between depths
                                         // tree_lmin..tree_lmax (D = 3, 4 nodes/dim); other depths work
                                         // straight from the points
@@ -184,6 +190,7 @@ bool smooth_rule(double E, int depth, int D, double gamma, double eta_smooth);  
 int adaptive_nodes(double E, int depth, double gamma, int p);                   // Sec. 4.3 node rule (0: dropped)
 
 double near_interp_error(double E, int depth, double gamma);                    // D = 3, 4 nodes per dimension
+double near_weighted_error(double E, int depth, double gamma);
 
 // plan.hip
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
@@ -229,6 +236,8 @@ void run_far_points(f3m_plan_s &P, int level, const float *bs, float *ys, int om
 bool m2l_stencil_applies(const f3m_plan_s &P);   // D = 3, 4 nodes per dimension, far ratio 2
 void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);   // after the lists of the depth exist
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables
+void upload_near_table(f3m_plan_s &P, hipStream_t st);                 // factors of the weighted near pairs
+void run_near_weighted(f3m_plan_s &P, const float *W, float *V, hipStream_t st);
 bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStream_t st, bool zero_row = false);  // false: does not apply
 
 }  // namespace f3m

@@ -1167,6 +1167,9 @@ static void divide_finish(const SetRef &S, int l, const uint64_t *words) {
     if ((int64_t)words[1] != S.lev[l - 1].nb) fail(F3M_ERR_HIP, "internal: parent count mismatch");
 }
 
+// Weighted near pairs end at the first depth that allows it where the last one has this many boxes at least.
+constexpr int64_t WEIGHTED_MIN_BOXES = 8192;
+
 template <int D>
 static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st) {
     const int64_t n = P.n;
@@ -1252,7 +1255,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     // per depth: after the division, after the lists
     P.plan_events.resize(2 * (size_t)(cap + 1), nullptr);
     uint64_t *words = scope_words();
-    int l = 0;
+    int l = 0, weighted = 0;
     for (;; ++l) {
         f3m_level &lv = P.lev[l];
         for (size_t k = 0; k < sets.size(); ++k) divide_set<D>(P, sets[k], l, part, words + HW_SET + 2 * k, st);
@@ -1311,9 +1314,10 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
                 // unit of fp32 (kernel values are close to 1 there), is the last one the products need: all the pairs
                 // left there go through the M2L, and the tree below it only defines the lists that are reported.  Measured at n = 1e9,
                 // lengthscale 1 (depth 5 of 8): 314 -> 82 ms for plan and product, the error against the oracle unchanged.
-                if (P.near_depth == 0 && l >= 2 && lv.p == 4 && P.rho == 0 && !P.adaptive_far && !(P.eta_smooth > 0.f) &&
-                    near_interp_error((double)P.E, l, (double)P.gamma) <= 0x1p-24)
-                    P.near_depth = l;
+                if (P.near_depth == 0 && l >= 2 && lv.p == 4 && P.rho == 0 && !P.adaptive_far && !(P.eta_smooth > 0.f)) {
+                    if (near_interp_error((double)P.E, l, (double)P.gamma) <= 0x1p-24) P.near_depth = l;
+                    else if (weighted == 0 && near_weighted_error((double)P.E, l, (double)P.gamma) <= 0x1p-24) weighted = l;
+                }
             } else if (tf > 0 && far_points_allowed(P, l)) {
                 lv.far_points = far_points_pays(P, l, point_pairs(up.start.p, up.start.p, up.near_ptr.p, up.near_col.p, up.nb, st));
                 lv.far_col.alloc(lv.far_points ? 0 : (size_t)tf, tally);
@@ -1340,6 +1344,17 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         if (!(lv.near_sz > 0 && lv.max_box > P.leaf_max && sv.max_box > P.leaf_max && l < cap)) break;
     }
     P.L = l;
+    // The tree is too coarse for the plain interpolation of near pairs, but not for that between weighted points: near pairs
+    // are interpolated at the first depth that allows it -- or, where the last depth has few boxes, at the last one, which
+    // costs nothing more (a few workgroups per depth).  Product of 1e7 points, lengthscale 0.1, depth 6 of 6: 2.36 -> 1.04 ms;
+    // four columns of 3e6 points, lengthscale 0.3, depth 5 of 6: 3.36 -> 1.14 ms; of 2e4 points, lengthscale 1, depth 3
+    // of 3: 84 -> 71 us.
+    if (P.near_depth == 0 && weighted > 0)
+        P.near_weighted = P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
+    for (int k = P.last_depth() + 1; k <= P.L; ++k) {   // not needed: the products end above
+        P.lev[k].st_cand.release();
+        P.lev[k].st_child.release();
+    }
 
     // ---- work splits and workspaces
     F3M_HIP(hipEventRecord(ea, st));
@@ -1350,7 +1365,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     // (with 4 nodes per dimension in 3-D; the M2L of a depth in the band is the candidate-grid one where
     // that applies, else the one that works from the far list: two point sets, other far ratios)
     auto in_band = [&](int k) {
-        return D == 3 && k >= 2 && P.lev[k].far_sz > 0 && P.lev[k].p == 4 && !(P.near_depth && k > P.near_depth);
+        return D == 3 && k >= 2 && P.lev[k].far_sz > 0 && P.lev[k].p == 4 && k <= P.last_depth();
     };
     for (int k = P.L; k >= 2 && P.tree_lmax == 0; --k)
         if (in_band(k)) P.tree_lmax = k;
@@ -1360,13 +1375,14 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         upload_transfer(P, st);
     }
     upload_kron_tables(P, st);
+    if (P.near_weighted) upload_near_table(P, st);
     build_far_orders(P, st);
     for (int k = 1; k <= P.L; ++k) build_stencil_tables(P, k, st);
     ItemLists items(tally, st);
     int64_t max_w = 0, max_v = 0;
     for (int k = 1; k <= P.L; ++k) {
         f3m_level &lv = P.lev[k];
-        if (lv.far_sz == 0 || lv.p == 0 || (P.near_depth && k > P.near_depth)) continue;   // nothing to interpolate, or dropped
+        if (lv.far_sz == 0 || lv.p == 0 || k > P.last_depth()) continue;   // nothing to interpolate, or dropped
         if (lv.far_points) {
             far_points_prepare(P, k, st);
             const f3m_level &up = P.lev[k - 1];
@@ -1379,10 +1395,12 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             // Node potentials are passed down the targets' tree.  One point set: node weights are passed up
             // the same tree, and carry one row of zeros behind the last box (what the candidate-grid M2L reads
             // for an absent candidate).  Two point sets: the node weights of every depth come from the points.
-            lv.Vl.alloc((size_t)lv.nb * lv.r, tally);
+            const size_t twice = k == P.near_weighted ? 2 : 1;
+            lv.Vl.alloc(twice * (size_t)lv.nb * lv.r, tally);
             if (!P.src) {
-                lv.Wl.alloc((size_t)(lv.nb + 1) * lv.r, tally);
-                F3M_HIP(hipMemsetAsync(lv.Wl.p + (size_t)lv.nb * lv.r, 0, (size_t)lv.r * sizeof(float), st));
+                lv.Wl.alloc(twice * (size_t)(lv.nb + 1) * lv.r, tally);
+                for (size_t h = 1; h <= twice; ++h)
+                    F3M_HIP(hipMemsetAsync(lv.Wl.p + (h * (size_t)(lv.nb + 1) - 1) * lv.r, 0, (size_t)lv.r * sizeof(float), st));
                 if (k < P.tree_lmax) continue;   // only the last depth of the band needs chunks
             }
         }
@@ -1408,7 +1426,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         if (!tree || P.src) max_w = std::max(max_w, sv.nb * (int64_t)lv.r);
         if (!tree) max_v = std::max(max_v, lv.nb * (int64_t)lv.r);
     }
-    if (P.near_depth == 0) {
+    if (P.exact_near()) {
         const f3m_level &lf = P.lev[P.L];
         // Few boxes: rows are long, and the near field splits every tile over several wavefronts; an overflow
         // tile would leave its whole row to one wavefront, so there are none (every run is a tile of its own).
@@ -1426,10 +1444,10 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     int64_t max_part = 0, max_slice = 0;
     for (int k = 1; k <= P.L; ++k) {
         const f3m_level &sv = P.slev(k);
-        max_part = std::max(max_part, sv.nchunks * (int64_t)P.lev[k].r);
+        max_part = std::max(max_part, (k == P.near_weighted ? 2 : 1) * sv.nchunks * (int64_t)P.lev[k].r);
         max_slice = std::max(max_slice, sv.nslices * (int64_t)P.lev[k].r);
     }
-    if (P.near_depth == 0) {
+    if (P.exact_near()) {
         const f3m_level &lf = P.lev[P.L];
         const uint32_t ts = lf.nb < 8192 ? 0u : (uint32_t)overflow_targets(D);
         // tiles worked in pairs (the rows must come from the plain far rule: the kernel tells the shared near
@@ -1447,7 +1465,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     }
     {
         // partial sums of a near field whose tiles are split over several wavefronts (few targets, long rows)
-        const int nsplit = P.near_depth == 0 && P.lev[P.L].near_sz > 0 ? p2p_nsplit(P, P.L, P.ntiles) : 1;
+        const int nsplit = P.exact_near() && P.lev[P.L].near_sz > 0 ? p2p_nsplit(P, P.L, P.ntiles) : 1;
         if (nsplit > 1) P.p2p_part.alloc((size_t)nsplit * (size_t)n, tally);
     }
     if (P.route || (P.src && P.src->route)) {
@@ -1551,6 +1569,20 @@ bool smooth_rule(double E, int depth, int D, double gamma, double eta_smooth) {
 double near_interp_error(double E, int depth, double gamma) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (2.0 * gamma * gamma), L = 5.0 / 3.0;
     return q * q * (12.0 / 24.0) * 0.25 / 16.0 * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
+}
+
+// The same for points that carry the Gaussian of their own place in the box.  With x = c + u and y = c' + w, D = c' - c,
+//   exp(-|x - y|^2 / 2 gamma^2) = e(u) e(w) F(u, w),  e(u) = exp(-u^2 / 2 gamma^2),
+//   F(u, w) = exp((u w + u D - w D - D^2 / 2) / gamma^2) per dimension,
+// only F is interpolated: its fourth derivative is ((u - D) / gamma^2)^4 F, at most (1.5 l / gamma^2)^4 F for adjacent boxes
+// (|u| <= l / 2, |D| <= l), times (l / 2)^4, a quarter (the node polynomial) over 4!: (0.75 l^2 / gamma^2)^4 / 96 for one
+// interpolation.  e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and
+// the node values of F go without e: three dimensions of either point, at most exp(6 l^2 / 8 gamma^2)), and the six
+// interpolations make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.
+double near_weighted_error(double E, int depth, double gamma) {
+    const double l = E / std::ldexp(1.0, depth), q = l * l / (gamma * gamma), L = 5.0 / 3.0;
+    const double one = 0.75 * q, e1 = one * one * one * one / 96.0;
+    return e1 * std::exp(0.75 * q) * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
 }
 
 // Adaptive far-field rule of Sec. 4.3 on q = l^2 / (2 gamma^2): min(p, 3) nodes per dimension if

@@ -100,6 +100,7 @@ def lib():
         L.f3m_last_error.restype = ctypes.c_char_p
         L.f3m_plan_info.argtypes = [vp, ctypes.POINTER(Info)]
         L.f3m_plan_product_info.argtypes = [vp, ctypes.POINTER(ProductInfo)]
+        L.f3m_plan_near_weighted.argtypes = [vp]
         L.f3m_plan_get_perm.argtypes = [vp, vp]
         L.f3m_plan_get_point_keys.argtypes = [vp, vp]
         L.f3m_plan_get_boxes.argtypes = [vp, ci, vp, vp]
@@ -110,7 +111,7 @@ def lib():
                      "f3m_plan_get_perm", "f3m_plan_get_point_keys", "f3m_plan_get_boxes", "f3m_plan_get_list",
                      "f3m_stage_times", "f3m_level_times", "f3m_plan_xy", "direct_kmvm_xy", "direct_kmvm_xy_rows_f64",
                      "f3m_plan_source_info", "f3m_plan_get_source_perm", "f3m_plan_get_source_boxes",
-                     "direct_kmvm_rows_f64_static", "f3m_plan_product_info"):
+                     "direct_kmvm_rows_f64_static", "f3m_plan_product_info", "f3m_plan_near_weighted"):
             getattr(L, name).restype = ci
         _lib = L
     return _lib
@@ -234,6 +235,10 @@ class Plan:
         out = ProductInfo()
         _check(lib().f3m_plan_product_info(self._h, ctypes.byref(out)))
         return out
+
+    def near_weighted(self):
+        """f3m_plan_near_weighted: the depth whose near pairs are interpolated between weighted points, or 0"""
+        return int(lib().f3m_plan_near_weighted(self._h))
 
     def perm(self):
         out = np.empty(self.n, dtype=np.uint32)
