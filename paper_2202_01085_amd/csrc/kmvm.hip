@@ -2109,6 +2109,172 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
     }
 }
 
+// P2M and L2P of boxes with thousands of points: a wavefront per run of up to P2M_LONG points of one box.  The kernels above end
+// every 256 points with a sum over the lanes, or start with the 64 potentials in LDS; here that is 2 % of the work.
+// The loads of four rounds are in flight.  WEIGHTED: both sets of node weights / node potentials (the
+// weighted near pairs) from one reading of the points.
+constexpr int LONG_AHEAD = 4;
+template <bool WEIGHTED>
+__global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
+                                                        const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
+                                                        const uint32_t *__restrict__ chunk_box,
+                                                        const uint32_t *__restrict__ chunk_first, int64_t nchunks,
+                                                        CentreArg C, float *__restrict__ W, float *__restrict__ Wpart,
+                                                        int64_t dW, int64_t dpart, float kw) {
+    constexpr int NS = WEIGHTED ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE];
+    const int64_t c = block_index();
+    if (c >= nchunks) return;
+    const int lane = threadIdx.x;
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(chunk_box[c]);
+    const uint32_t c0 = chunk_first[a], c1 = chunk_first[a + 1];
+    const uint32_t k0 = start[a] + (uint32_t)(c - c0) * (uint32_t)P2M_LONG;
+    const uint32_t k1 = min(k0 + (uint32_t)P2M_LONG, start[a + 1]);
+    double ctr[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ctr[d] = C.alpha[d] + ((double)cell[(int64_t)a * 3 + d] + 0.5) * C.edge;
+    float x[LONG_AHEAD][3], bv[LONG_AHEAD];
+    // unconditional loads, the index behind the end clamped to the last point and its weight zero
+    auto load = [&](int s, uint32_t kb) __attribute__((always_inline)) {
+        const uint32_t k = kb + (uint32_t)lane, kc = min(k, k1 - 1u);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[s][d] = Xs[(int64_t)kc * 3 + d];
+        const float b = bs[kc];
+        bv[s] = k < k1 ? b : 0.f;
+    };
+#pragma unroll
+    for (int s = 0; s < LONG_AHEAD; ++s) load(s, k0 + 64u * s);
+    float acc[NS][64];
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int q = 0; q < 64; ++q) acc[h][q] = 0.f;
+    for (uint32_t kb = k0; kb < k1; kb += 64u * LONG_AHEAD) {
+#pragma unroll
+        for (int s = 0; s < LONG_AHEAD; ++s) {
+            float Lx[4], Ly[4], Lz[4];
+            const float u2 = weights34(x[s], ctr, C.inv_half, Lx, Ly, Lz);
+            const float b = bv[s];
+            load(s, kb + 64u * (s + LONG_AHEAD));
+            float xy[16];
+#pragma unroll
+            for (int i2 = 0; i2 < 4; ++i2)
+#pragma unroll
+                for (int i1 = 0; i1 < 4; ++i1) xy[i1 + 4 * i2] = Lx[i1] * Ly[i2];
+#pragma unroll
+            for (int h = 0; h < NS; ++h) {
+                const float bh = h ? b * __builtin_amdgcn_exp2f(kw * u2) : b;
+#pragma unroll
+                for (int i3 = 0; i3 < 4; ++i3) {
+                    const float zb = Lz[i3] * bh;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[h][q + 16 * i3] = fmaf(xy[q], zb, acc[h][q + 16 * i3]);
+                }
+            }
+        }
+    }
+    // sum over the lanes, 32 nodes at a time, as in p2m34_kernel
+    const int i = lane & 31, part = lane >> 5;
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        float *dst = c1 - c0 == 1 ? W + h * dW + (int64_t)a * 64 : Wpart + h * dpart + c * 64;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+                *reinterpret_cast<float4 *>(&tr[lane * TR_STRIDE + 4 * g]) = make_float4(
+                    acc[h][32 * q + 4 * g], acc[h][32 * q + 4 * g + 1], acc[h][32 * q + 4 * g + 2], acc[h][32 * q + 4 * g + 3]);
+            __syncthreads();
+            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+            for (int row = 0; row < 32; row += 4) {
+                s0 += tr[(32 * part + row + 0) * TR_STRIDE + i];
+                s1 += tr[(32 * part + row + 1) * TR_STRIDE + i];
+                s2 += tr[(32 * part + row + 2) * TR_STRIDE + i];
+                s3 += tr[(32 * part + row + 3) * TR_STRIDE + i];
+            }
+            float t = (s0 + s1) + (s2 + s3);
+            t += __shfl_xor(t, 32, 64);
+            if (part == 0) dst[32 * q + i] = t;
+        }
+    }
+}
+
+// out = base (nullptr: zero) + far field; far_ptr as in l2p34_kernel
+template <bool WEIGHTED>
+__global__ __launch_bounds__(64) void l2p34_long_kernel(const float *__restrict__ Xs, const uint32_t *__restrict__ start,
+                                                        const int32_t *__restrict__ cell,
+                                                        const uint64_t *__restrict__ far_ptr,
+                                                        const uint32_t *__restrict__ chunk_box,
+                                                        const uint32_t *__restrict__ chunk_first, int64_t nchunks,
+                                                        CentreArg C, const float *__restrict__ V, const float *base,
+                                                        float *out, const float *__restrict__ Vw, float kw) {
+    constexpr int NS = WEIGHTED ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float vb[NS][64];
+    const int64_t c = block_index();
+    if (c >= nchunks) return;
+    const int lane = threadIdx.x;
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(chunk_box[c]);
+    if (far_ptr && far_ptr[a + 1] == far_ptr[a]) return;
+    const uint32_t k0 = start[a] + (uint32_t)(c - chunk_first[a]) * (uint32_t)P2M_LONG;
+    const uint32_t k1 = min(k0 + (uint32_t)P2M_LONG, start[a + 1]);
+    double ctr[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ctr[d] = C.alpha[d] + ((double)cell[(int64_t)a * 3 + d] + 0.5) * C.edge;
+    vb[0][lane] = V[(int64_t)a * 64 + lane];
+    if constexpr (WEIGHTED) vb[NS - 1][lane] = Vw[(int64_t)a * 64 + lane];
+    __syncthreads();
+    // the potentials of the box in registers of every lane (multiply-adds on registers alone issue fastest)
+    float v[NS][64];
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int q = 0; q < 64; ++q) {
+            v[h][q] = vb[h][q];
+            asm volatile("" : "+v"(v[h][q]));
+        }
+    float x[LONG_AHEAD][3], old[LONG_AHEAD];
+    auto load = [&](int s, uint32_t kb) __attribute__((always_inline)) {
+        const uint32_t kc = min(kb + (uint32_t)lane, k1 - 1u);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[s][d] = Xs[(int64_t)kc * 3 + d];
+        old[s] = base ? base[kc] : 0.f;
+    };
+#pragma unroll
+    for (int s = 0; s < LONG_AHEAD; ++s) load(s, k0 + 64u * s);
+    for (uint32_t kb = k0; kb < k1; kb += 64u * LONG_AHEAD) {
+#pragma unroll
+        for (int s = 0; s < LONG_AHEAD; ++s) {
+            float Lx[4], Ly[4], Lz[4];
+            const float u2 = weights34(x[s], ctr, C.inv_half, Lx, Ly, Lz);
+            const float yold = old[s];
+            // (base may be out: the entry loaded here is stored by a later round of this lane only)
+            load(s, kb + 64u * (s + LONG_AHEAD));
+            float y[NS];
+#pragma unroll
+            for (int h = 0; h < NS; ++h) {
+                y[h] = 0.f;
+#pragma unroll
+                for (int i3 = 0; i3 < 4; ++i3) {
+                    float sy = 0.f;
+#pragma unroll
+                    for (int i2 = 0; i2 < 4; ++i2) {
+                        float sx = Lx[0] * v[h][4 * i2 + 16 * i3];
+#pragma unroll
+                        for (int i1 = 1; i1 < 4; ++i1) sx = fmaf(Lx[i1], v[h][i1 + 4 * i2 + 16 * i3], sx);
+                        sy = fmaf(Ly[i2], sx, sy);
+                    }
+                    y[h] = fmaf(Lz[i3], sy, y[h]);
+                }
+            }
+            if constexpr (WEIGHTED) y[0] = fmaf(__builtin_amdgcn_exp2f(kw * u2), y[NS - 1], y[0]);
+            const uint32_t k = kb + 64u * s + (uint32_t)lane;
+            if (k < k1) out[k] = yold + y[0];
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------
 // Node weights and node potentials between depths (D = 3, 4 nodes per dimension).
 // The basis functions of a parent box are polynomials of degree 3 per coordinate, and the
@@ -2702,6 +2868,8 @@ static void reduce_partials(f3m_plan_s &P, f3m_level &lv, int r, float *W, hipSt
 
 // every box of the depth is exactly one chunk of the P2M / L2P work split (chunk index = box rank)
 static int single_chunks(const f3m_level &lv) { return lv.max_box <= P2M_CHUNK && lv.nchunks == lv.nb ? 1 : 0; }
+// the runs of the depth are long ones (D = 3, 4 nodes per dimension)
+static bool long_chunks(const f3m_level &lv) { return lv.chunk > P2M_CHUNK; }
 
 // g = log2(e) l^2 / (2 gamma^2) of a depth: c l^2 bounds the magnitude of the expanded exponent terms in
 // box-local coordinates (|x'|^2 + |y'|^2 <= 7.5 D/3 l^2)
@@ -2896,7 +3064,11 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         const NodeArg N = make_nodes(p);
         const CentreArg CS = make_centre(P, l, true);   // source grid
         size_t sh = (size_t)(FF_TP * D * p + FF_TP) * sizeof(float);
-        if (D == 3 && p == 4 && single_chunks(sv))
+        if (D == 3 && p == 4 && long_chunks(sv))
+            p2m34_long_kernel<false><<<grid_for(sv.nchunks), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p,
+                                                                               sv.chunk_first.p, sv.nchunks, CS, P.W.p, P.Wpart.p,
+                                                                               0, 0, 0.f);
+        else if (D == 3 && p == 4 && single_chunks(sv))
             p2m34_pair_kernel<<<grid_for(cdiv(sv.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.nb,
                                                                                         CS, P.W.p, WeightedArg{});
         else if (D == 3 && p == 4)
@@ -2915,7 +3087,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                         Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS, N, P.W.p, P.Wpart.p);
             });
         F3M_HIP(hipGetLastError());
-        if (sv.max_box > P2M_CHUNK)   // some box has several chunks
+        if (sv.max_box > sv.chunk)   // some box has several chunks
             reduce_partials(P, sv, r, P.W.p, st);
         F3M_HIP(hipGetLastError());
     };
@@ -2991,7 +3163,11 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (!(lv.far_implicit && run_m2l_stencil(P, l, P.W.p, P.V.p, st))) kron_m2l(l, P.W.p, P.V.p);
         ev[3] = ev[4] = now = mark();
         {
-            if (D == 3 && p == 4)
+            if (D == 3 && p == 4 && long_chunks(lv))
+                l2p34_long_kernel<false><<<grid_for(lv.nchunks), dim3(64), 0, st>>>(
+                    P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, P.V.p, P.ys.p,
+                    P.ys.p, nullptr, 0.f);
+            else if (D == 3 && p == 4)
                 l2p34_kernel<false><<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
                     P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, P.V.p, P.ys.p,
                     P.ys.p, single_chunks(lv), nullptr, 0.f);
@@ -3028,14 +3204,22 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 const int64_t blocks = pairs ? cdiv(lf.nb, 2 * P2M_NPAIR) : cdiv(lf.nchunks, P2M_NCH);
                 const WeightedArg A{weighted ? blocks : 0, (lf.nb + 1) * r, lf.nchunks * r, kw};
                 const dim3 grid = grid_for(weighted ? 2 * blocks : blocks);
-                if (pairs)
+                auto p2m_long = [&](auto kern) {
+                    kern<<<grid_for(lf.nchunks), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
+                                                                    lf.nchunks, make_centre(P, L), lf.Wl.p, P.Wpart.p, A.dW,
+                                                                    A.dpart, kw);
+                };
+                if (long_chunks(lf)) {
+                    if (weighted) p2m_long(p2m34_long_kernel<true>);
+                    else p2m_long(p2m34_long_kernel<false>);
+                } else if (pairs)
                     p2m34_pair_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.nb, make_centre(P, L),
                                                                  lf.Wl.p, A);
                 else
                     p2m34_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
                                                             lf.nchunks, make_centre(P, L), lf.Wl.p, P.Wpart.p, 0, A);
                 F3M_HIP(hipGetLastError());
-                if (lf.max_box > P2M_CHUNK) {   // some box has several chunks
+                if (lf.max_box > lf.chunk) {   // some box has several chunks
                     reduce_partials(P, lf, r, lf.Wl.p, st);
                     if (weighted) reduce_partials(P, lf, r, lf.Wl.p + A.dW, st, A.dpart);
                 }
@@ -3097,8 +3281,18 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                     P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks, make_centre(P, L), lf.Vl.p,
                     base, direct_out ? y : P.ys.p, single_chunks(lf), weighted ? lf.Vl.p + lf.nb * r : nullptr, kw);
             };
-            if (weighted) l2p(l2p34_kernel<true>);
-            else l2p(l2p34_kernel<false>);
+            auto l2p_long = [&](auto kern) {
+                kern<<<grid_for(lf.nchunks), dim3(64), 0, st>>>(
+                    P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks, make_centre(P, L), lf.Vl.p,
+                    base, direct_out ? y : P.ys.p, weighted ? lf.Vl.p + lf.nb * r : nullptr, kw);
+            };
+            if (long_chunks(lf)) {
+                if (weighted) l2p_long(l2p34_long_kernel<true>);
+                else l2p_long(l2p34_long_kernel<false>);
+            } else {
+                if (weighted) l2p(l2p34_kernel<true>);
+                else l2p(l2p34_kernel<false>);
+            }
             F3M_HIP(hipGetLastError());
             ev[5] = now = mark();
         }

@@ -25,6 +25,7 @@ struct f3m_level {
     f3m::DevBuf<uint32_t> sm_tile_box, sm_tile_first;
     // P2M work split: a chunk is a run of at most P2M_CHUNK points of one box
     int64_t nchunks = 0;
+    int chunk = 256;                    // points of a chunk: P2M_CHUNK, or P2M_LONG where boxes are large
     f3m::DevBuf<uint32_t> chunk_box;    // [nchunks]
     f3m::DevBuf<uint32_t> chunk_first;  // [nb+1] first chunk of each box
     // boxes with very many chunks (few, huge boxes): a slice is a run of at most P2M_SLICE chunks of one
@@ -178,6 +179,7 @@ struct f3m_plan_s {
 namespace f3m {
 
 constexpr int P2M_CHUNK = 256;
+constexpr int P2M_LONG = 2048;   // points of a chunk where boxes hold thousands (3-D, 4 nodes per dimension)
 constexpr int P2M_SLICE = 512;   // chunks per slice of the two-stage sum of partial node weights
 // largest last run of a leaf box that is treated as an overflow tile (near field with the sources on the lanes):
 // beyond about 10 targets a half-filled 64-wide tile is the cheaper of the two (measured at n = 1e9)
