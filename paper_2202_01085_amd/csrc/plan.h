@@ -61,6 +61,8 @@ struct f3m_level {
 // digit and where the tile's run of each digit lies in the next order.
 struct f3m_route {
     int64_t n = 0, ntiles = 0;
+    bool grouped = false;   // one pass: the points grouped by the boxes of one depth, in each of them in the caller's order
+                            // (slot1, dstart1 and gofs1 of 512 digits a tile; tiles of the caller's order)
     int s2 = 0, B1 = 1, B2 = 1;
     f3m::DevBuf<uint16_t> slot1, slot2, off3;      // [n] each
     f3m::DevBuf<uint32_t> dstart1, dstart2;        // [ntiles][257]
@@ -100,6 +102,8 @@ struct f3m_plan_s {
 
     f3m::DevBuf<uint32_t> keys;   // [n] keys at depth Lq, box order
     f3m::DevBuf<uint32_t> perm;   // [n]
+    // "Box order" of the products is that of perm, except where the points are only grouped by the boxes of depth
+    // last_depth() (route->grouped): the boxes of that depth and above have the same intervals in both.
     f3m::DevBuf<float> Xs;        // [n*D] coordinates in box order, row-major
     f3m::DevBuf<float> bs, ys;    // [n] right-hand side / far-field result in box order
     f3m::DevBuf<float> yn;        // [n] near-field result in box order
@@ -199,6 +203,9 @@ void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st); 
 void compute_far_point_pairs(f3m_plan_s &P);   // near_point_pairs and lev[].far_point_pairs, once (synchronises)
 // route.hip: permutations of large vectors as three streaming passes with tables built once per plan
 void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, hipStream_t st);
+constexpr int ROUTE_GROUP_BOXES = 512;
+void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift, const uint32_t *box_keys, int64_t nb,
+                       int64_t *tally, hipStream_t st);
 void route_scatter(const f3m_route &R, const float *in, const float *in2, float *out, float *tmp_a, float *tmp_b,
                    hipStream_t st);                                   // out[perm[k]] = in[k] (+ in2[k])
 void route_gather(const f3m_route &R, const float *in, float *out, float *tmp_a, float *tmp_b, hipStream_t st);

@@ -306,17 +306,18 @@ __global__ __launch_bounds__(RS_NT, 4) void rs_scatter_kernel(const uint32_t *__
     }
 }
 
-// sorts (keys_a, index) by the low `bits` bits; returns true if the result is in the b buffers
-static bool radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint32_t *vals_b, int64_t n, int bits,
-                       hipStream_t st) {
+// sorts (keys_a, index) by the low `bits` bits; returns true if the result is in the b buffers.  keys_c (or null): takes the
+// place of keys_a from the second pass on, whose input then stays as it was (bits > 8).
+static bool radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint32_t *vals_b, uint32_t *keys_c, int64_t n,
+                       int bits, hipStream_t st) {
     int64_t nblk = cdiv(n, RS_TILE);
     DevBuf<uint32_t> hist;
     hist.alloc((size_t)nblk * 256);
     bool in_b = false, first = true;
     for (int shift = 0; shift < bits; shift += 8) {
-        const uint32_t *kin = in_b ? keys_b : keys_a;
+        const uint32_t *kin = in_b ? keys_b : first || !keys_c ? keys_a : keys_c;
         const uint32_t *vin = first ? nullptr : (in_b ? vals_b : vals_a);
-        uint32_t *kout = in_b ? keys_a : keys_b;
+        uint32_t *kout = in_b ? (keys_c ? keys_c : keys_a) : keys_b;
         uint32_t *vout = in_b ? vals_a : vals_b;
         rs_hist_kernel<<<dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(RS_NT), 0, st>>>(kin, n, shift, hist.p, nblk);
         F3M_HIP(hipGetLastError());
@@ -1201,9 +1202,19 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         F3M_HIP(hipGetLastError());
     }
     F3M_HIP(hipEventRecord(P.ev[1], st));
+    // Points whose products end at a depth of few boxes are only grouped by them (below), for which the keys are needed in the
+    // caller's order.  The depth, if the tree gets that far: the smooth one, or that of the weighted near pairs.
+    bool may_group = false;
+    if (D == 3 && !P.src && n >= P.route_min_n && P.rho == 0 && !P.force_all_near && P.E > 0.f)
+        for (int l = 1; l <= 3 && !may_group; ++l)
+            may_group = smooth_rule((double)P.E, l, D, (double)P.gamma, (double)P.eta_smooth) ||
+                        (l >= 2 && m2l_stencil_applies(P) && !P.adaptive_far && !(P.eta_smooth > 0.f) &&
+                         near_weighted_error((double)P.E, l, (double)P.gamma) <= 0x1p-24);
+    DevBuf<uint32_t> keys_in;   // ... in the caller's order (may_group)
     int bits_sorted = 0;
     for (const SetRef &S : sets) {
         DevBuf<uint32_t> keys_b, perm_b;
+        if (may_group) keys_in.alloc((size_t)S.n + RS_TILE);
         keys_b.alloc((size_t)S.n + RS_TILE);
         perm_b.alloc((size_t)S.n + RS_TILE);
         int bits = P.E > 0.f ? D * P.Lq : 0;
@@ -1213,15 +1224,19 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             iota_kernel<<<dim3((unsigned)cdiv(S.n, 256)), dim3(256), 0, st>>>(S.perm->p, S.n);
             in_b = false;
         } else {
-            in_b = radix_sort(S.keys->p, S.perm->p, keys_b.p, perm_b.p, S.n, bits, st);
+            in_b = radix_sort(S.keys->p, S.perm->p, keys_b.p, perm_b.p, keys_in.p, S.n, bits, st);
         }
         if (in_b) {
             std::swap(S.keys->p, keys_b.p);
             std::swap(S.perm->p, perm_b.p);
+            if (keys_in.p) std::swap(keys_in.p, keys_b.p);   // keys_in: the input of the sort
+        } else if (keys_in.p) {
+            std::swap(S.keys->p, keys_in.p);
         }
     }
     F3M_HIP(hipEventRecord(P.ev[2], st));
-    for (size_t k = 0; k < sets.size(); ++k) {
+    // the points into box order, once the depth that the products end at is known
+    auto order_points = [&](size_t k) {
         const SetRef &S = sets[k];
         // 64 zero points of padding after the last point: kernels may read whole 32-point blocks
         S.Xs->alloc(((size_t)S.n + PAD_POINTS) * D, tally);
@@ -1229,20 +1244,23 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         // A large set goes through the three-pass permutation, whose tables also serve every product
         // (route.hip); its points follow the same way when they have three coordinates.
         std::unique_ptr<f3m_route> &route = k ? P.src->route : P.route;
-        if (S.n >= P.route_min_n && bits_sorted > 0) {
+        const int last = P.last_depth();
+        if (may_group && P.lev[last].nb <= ROUTE_GROUP_BOXES && (P.lev[P.L].near_sz == 0 || !P.exact_near())) {
+            route.reset(new f3m_route());
+            route_group_build(*route, keys_in.p, S.n, D * (P.Lq - last), P.lev[last].key.p, P.lev[last].nb, tally, st);
+        } else if (S.n >= P.route_min_n && bits_sorted > 0) {
             route.reset(new f3m_route());
             route_build(*route, S.perm->p, S.n, tally, st);
         }
         if (route && D == 3) {
             DevBuf<float> tmp;
-            tmp.alloc((size_t)S.n * 3);
+            if (!route->grouped) tmp.alloc((size_t)S.n * 3);
             route_gather_rows3(*route, S.X, S.Xs->p, tmp.p, st);
         } else {
             gather_rows_kernel<D><<<dim3((unsigned)cdiv(S.n, 256)), dim3(256), 0, st>>>(S.X, S.perm->p, S.n, S.Xs->p);
             F3M_HIP(hipGetLastError());
         }
-    }
-    F3M_HIP(hipEventRecord(P.ev[3], st));
+    };
 
     // ---- Algorithm 1 loop: divide, new interactions, partition
     int cap = P.Lq;
@@ -1349,12 +1367,20 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     // costs nothing more (a few workgroups per depth).  Product of 1e7 points, lengthscale 0.1, depth 6 of 6: 2.36 -> 1.04 ms;
     // four columns of 3e6 points, lengthscale 0.3, depth 5 of 6: 3.36 -> 1.14 ms; of 2e4 points, lengthscale 1, depth 3
     // of 3: 84 -> 71 us.
+    // Also instead of the plain interpolation two or three depths further down, where that makes the boxes so few that the
+    // points need only be grouped by them: one pass each way instead of three (n = 1e9, lengthscale 1, depth 3 and not 5: 77.6 -> 60.6 ms for plan and
+    // product).
+    const bool group = may_group && weighted > 0 && P.lev[weighted].nb <= ROUTE_GROUP_BOXES;
+    if (group && P.near_depth > 0 && P.lev[P.near_depth].nb > ROUTE_GROUP_BOXES) P.near_depth = 0;
     if (P.near_depth == 0 && weighted > 0)
-        P.near_weighted = P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
+        P.near_weighted = group ? weighted : P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
     for (int k = P.last_depth() + 1; k <= P.L; ++k) {   // not needed: the products end above
         P.lev[k].st_cand.release();
         P.lev[k].st_child.release();
     }
+    F3M_HIP(hipEventRecord(P.ev[3], st));
+    for (size_t k = 0; k < sets.size(); ++k) order_points(k);
+    keys_in.release();
 
     // ---- work splits and workspaces
     F3M_HIP(hipEventRecord(ea, st));
@@ -1471,7 +1497,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         const int nsplit = P.exact_near() && P.lev[P.L].near_sz > 0 ? p2p_nsplit(P, P.L, P.ntiles) : 1;
         if (nsplit > 1) P.p2p_part.alloc((size_t)nsplit * (size_t)n, tally);
     }
-    if (P.route || (P.src && P.src->route)) {
+    if ((P.route && !P.route->grouped) || (P.src && P.src->route)) {
         const size_t m = (size_t)std::max<int64_t>(P.route ? n : 0, (P.src && P.src->route) ? P.src->n : (P.route ? n : 0));
         P.route_a.alloc(m, tally);
         P.route_b.alloc(m, tally);
@@ -1492,11 +1518,11 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     float ms = 0.f;
     F3M_HIP(hipEventElapsedTime(&P.times.bbox_keys, P.ev[0], P.ev[1]));
     F3M_HIP(hipEventElapsedTime(&P.times.sort, P.ev[1], P.ev[2]));
-    F3M_HIP(hipEventElapsedTime(&P.times.gather, P.ev[2], P.ev[3]));
+    F3M_HIP(hipEventElapsedTime(&P.times.gather, P.ev[3], ea));
     P.host_tabs.clear();
     P.times.boxes = P.times.lists = 0.f;
     for (int k = 0; k <= P.L; ++k) {
-        const hipEvent_t before = k ? P.plan_events[2 * (size_t)k - 1] : P.ev[3];
+        const hipEvent_t before = k ? P.plan_events[2 * (size_t)k - 1] : P.ev[2];
         const hipEvent_t mid = P.plan_events[2 * (size_t)k], after = P.plan_events[2 * (size_t)k + 1];
         F3M_HIP(hipEventElapsedTime(&ms, before, mid));
         P.times.boxes += ms;

@@ -15,6 +15,10 @@
 // and the places (the position of a value in the LDS copy of its tile, 16 bits per value and pass) depend on
 // perm only: they are computed once per plan by route_build, so a pass moves data and does nothing else.
 // The gather direction (caller's order -> box order) runs the same three passes backwards with the same tables.
+//
+// Where the products need the points by the boxes of a coarse depth only (at most 512 of them), ONE pass does: a tile of T
+// consecutive caller indices is dealt to the boxes, in which the points keep the caller's order (route_group_build).
+// n = 1e9, 512 boxes: tables 5.8 -> 3.1 ms (with the counts), points 18.7 -> 7.0, right-hand side in 6.2 -> 2.4, result out 6.6 -> 2.2.
 #include "plan.h"
 
 namespace f3m {
@@ -24,6 +28,15 @@ constexpr int RT_TILE = 1 << RT_BITS;    // values per tile and per window
 constexpr int RT_NT = 1024;              // threads of a workgroup: one tile
 constexpr int RT_IPT = RT_TILE / RT_NT;  // 32 values per thread
 constexpr int RT_NW = RT_NT / 64;        // 16 wavefronts
+
+struct RouteCountIn {
+    const uint32_t *p;
+    __device__ uint64_t operator()(int64_t i) const { return p[i]; }
+};
+struct RouteCountOut {
+    uint32_t *p;
+    __device__ void operator()(int64_t i, uint64_t ex, uint64_t) const { p[i] = (uint32_t)ex; }
+};
 
 struct RouteLevel {
     int shift;        // digit of a destination index: (i >> shift) & mask
@@ -204,16 +217,18 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
 // the passes.  A source or destination with several components per value (the rows of X) is addressed as
 // base[(index) * stride + component]; the orders between the passes hold one array per component.
 // ------------------------------------------------------------------------------------
-// digit whose run of places [ds[b], ds[b+1]) holds place q (ds ascending, ds[256] = values of the tile)
+// digit whose run of places [ds[b], ds[b+1]) holds place q (ds ascending, ds[NB] = values of the tile)
+template <int NB>
 __device__ inline int route_digit_of(const uint32_t *ds, uint32_t q) {
     int b = 0;
 #pragma unroll
-    for (int step = 128; step >= 1; step >>= 1)
+    for (int step = NB / 2; step >= 1; step >>= 1)
         if (ds[b + step] <= q) b += step;
     return b;
 }
 
-// pass 1 or 2 forwards: tile of `in` (tile order, in2 added if given) -> runs of `out`
+// pass 1 or 2 forwards: tile of `in` (tile order, in2 added if given) -> runs of `out`; NB: digits of the tables
+template <int NB>
 __global__ __launch_bounds__(RT_NT) void route_deal_kernel(const float *__restrict__ in, const float *__restrict__ in2,
                                                            float *__restrict__ out, const uint16_t *__restrict__ slot,
                                                            const uint32_t *__restrict__ dstart_tab,
@@ -221,13 +236,13 @@ __global__ __launch_bounds__(RT_NT) void route_deal_kernel(const float *__restri
     const int64_t tb = route_tile(n);
     if (tb < 0) return;
     __shared__ float stage[RT_TILE];
-    __shared__ uint32_t ds[257], go[256];
+    __shared__ uint32_t ds[NB + 1], go[NB];
     const int tid = threadIdx.x;
     const int64_t tile0 = tb * RT_TILE;
     const int64_t left = n - tile0;
     const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
-    if (tid <= 256) ds[tid] = dstart_tab[tb * 257 + tid];
-    if (tid < 256) go[tid] = gofs_tab[tb * 256 + tid];
+    if (tid <= NB) ds[tid] = dstart_tab[tb * (NB + 1) + tid];
+    if (tid < NB) go[tid] = gofs_tab[tb * NB + tid];
     uint16_t sl[RT_IPT];
     float v[RT_IPT];
 #pragma unroll
@@ -252,13 +267,13 @@ __global__ __launch_bounds__(RT_NT) void route_deal_kernel(const float *__restri
 #pragma unroll
     for (int r = 0; r < RT_IPT; ++r) {
         const uint32_t q = (uint32_t)(r * RT_NT + tid);
-        if ((int)q < cnt) out[go[route_digit_of(ds, q)] + q] = stage[q];
+        if ((int)q < cnt) out[go[route_digit_of<NB>(ds, q)] + q] = stage[q];
     }
 }
 
 // pass 2 or 1 backwards: runs of `in` -> tile of `out` (tile order); NC components, one array each on the
 // input side (in + c * in_stride); on the output side one array each (ROWS == false) or rows of NC values
-template <int NC, bool ROWS>
+template <int NC, bool ROWS, int NB>
 __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__restrict__ in, int64_t in_stride,
                                                               float *__restrict__ out, int64_t out_stride,
                                                               const uint16_t *__restrict__ slot,
@@ -267,13 +282,13 @@ __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__res
     const int64_t tb = route_tile(n);
     if (tb < 0) return;
     __shared__ float stage[RT_TILE];
-    __shared__ uint32_t ds[257], go[256];
+    __shared__ uint32_t ds[NB + 1], go[NB];
     const int tid = threadIdx.x;
     const int64_t tile0 = tb * RT_TILE;
     const int64_t left = n - tile0;
     const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
-    if (tid <= 256) ds[tid] = dstart_tab[tb * 257 + tid];
-    if (tid < 256) go[tid] = gofs_tab[tb * 256 + tid];
+    if (tid <= NB) ds[tid] = dstart_tab[tb * (NB + 1) + tid];
+    if (tid < NB) go[tid] = gofs_tab[tb * NB + tid];
     uint32_t sl[RT_IPT / 2];   // two places per register
 #pragma unroll
     for (int r = 0; r < RT_IPT; r += 2) {
@@ -294,7 +309,7 @@ __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__res
 #pragma unroll
             for (int r = 0; r < FLY; ++r) {
                 const uint32_t q = (uint32_t)((h + r) * RT_NT + tid);
-                t[r] = (int)q < cnt ? src[go[route_digit_of(ds, q)] + q] : 0.f;
+                t[r] = (int)q < cnt ? src[go[route_digit_of<NB>(ds, q)] + q] : 0.f;
             }
 #pragma unroll
             for (int r = 0; r < FLY; ++r) stage[(h + r) * RT_NT + tid] = t[r];
@@ -405,6 +420,198 @@ __global__ __launch_bounds__(RT_NT) void route_pick_kernel(const float *__restri
 }
 
 // ------------------------------------------------------------------------------------
+// One pass: points grouped by the boxes of one depth.  Digit of a point = rank of its box (lut[key >> shift]); inside a box the
+// points keep the caller's order, tile by tile, so the order depends on nothing but the points.
+// ------------------------------------------------------------------------------------
+constexpr int RG_NB = ROUTE_GROUP_BOXES;
+static_assert(RG_NB <= RT_NT / 2, "a thread per digit and one more");
+
+// rank of a box by its key; places of unoccupied boxes are not read
+__global__ __launch_bounds__(256) void route_lut_kernel(const uint32_t *__restrict__ key, int64_t nb, uint16_t *__restrict__ lut) {
+    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (a < nb) lut[key[a]] = (uint16_t)a;
+}
+
+// points of every box in a tile: hist[digit][tile]
+__global__ __launch_bounds__(RT_NT) void route_group_count_kernel(const uint32_t *__restrict__ keys, int64_t n, int shift,
+                                                                  const uint16_t *__restrict__ lut_tab, int nb,
+                                                                  int64_t ntiles, uint32_t *__restrict__ hist) {
+    const int64_t tb = route_tile(n);
+    if (tb < 0) return;
+    __shared__ uint32_t cnt[RG_NB];
+    __shared__ uint16_t lut[RG_NB];
+    const int tid = threadIdx.x;
+    if (tid < RG_NB) {
+        cnt[tid] = 0;
+        lut[tid] = lut_tab[tid];
+    }
+    __syncthreads();
+    const int64_t tile0 = tb * RT_TILE;
+#pragma unroll
+    for (int h = 0; h < RT_IPT; h += 16) {
+        uint32_t key[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t i = tile0 + (h + r) * RT_NT + tid;
+            key[r] = i < n ? keys[i] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (tile0 + (h + r) * RT_NT + tid < n) atomicAdd(&cnt[lut[key[r] >> shift]], 1u);
+    }
+    __syncthreads();
+    if (tid < nb) hist[(int64_t)tid * ntiles + tb] = cnt[tid];
+}
+
+// places of the values of a tile in its LDS copy (as route_rank_kernel finds them), and the tables of the tile; first:
+// the scanned counts, i.e. the position of the tile's first value of each digit
+__global__ __launch_bounds__(RT_NT) void route_group_rank_kernel(const uint32_t *__restrict__ keys, int64_t n, int shift,
+                                                                 const uint16_t *__restrict__ lut_tab, int nb,
+                                                                 int64_t ntiles, const uint32_t *__restrict__ first,
+                                                                 uint16_t *__restrict__ slot, uint32_t *__restrict__ dstart_out,
+                                                                 uint32_t *__restrict__ gofs_out) {
+    const int64_t tb = route_tile(n);
+    if (tb < 0) return;
+    __shared__ uint32_t wcnt[RT_NW][RG_NB];   // per wave: values of each digit seen so far; later the wave's offset
+    __shared__ uint64_t wmask[RT_NW][RG_NB];  // per wave: the lanes that hold each digit in the current round
+    __shared__ uint32_t dstart[RG_NB + 1];
+    __shared__ uint16_t lut[RG_NB];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid < RG_NB) {
+#pragma unroll
+        for (int k = 0; k < RT_NW; ++k) {
+            wcnt[k][tid] = 0;
+            wmask[k][tid] = 0ull;
+        }
+        lut[tid] = lut_tab[tid];
+    }
+    __syncthreads();
+    const uint64_t mybit = 1ull << lane;
+    const int64_t tile0 = tb * RT_TILE, base = tile0 + (int64_t)w * (RT_IPT * 64);
+    uint32_t rk[RT_IPT / 2], dig[RT_IPT / 2];   // rank within (wave, digit), below 2048, and the digit: two per register
+#pragma unroll
+    for (int r = 0; r < RT_IPT / 2; ++r) rk[r] = dig[r] = 0u;
+#pragma unroll
+    for (int h = 0; h < RT_IPT; h += 8) {   // eight rounds at a time: their loads are in flight together
+        uint32_t key[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int64_t i = base + (h + r) * 64 + lane;
+            key[r] = i < n ? keys[i] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const bool valid = base + (h + r) * 64 + lane < n;
+            // (see route_rank_kernel: the lanes with the same digit find each other through LDS)
+            if (valid) {
+                const uint32_t digit = lut[key[r] >> shift];
+                dig[(h + r) / 2] |= digit << (16 * ((h + r) & 1));
+                atomicOr(reinterpret_cast<unsigned long long *>(&wmask[w][digit]), (unsigned long long)mybit);
+                __builtin_amdgcn_wave_barrier();
+                const uint64_t peers = wmask[w][digit];
+                const uint32_t cnt = wcnt[w][digit];
+                const uint32_t before =
+                    __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+                rk[(h + r) / 2] |= (cnt + before) << (16 * ((h + r) & 1));
+                __builtin_amdgcn_wave_barrier();
+                if (before == 0) {
+                    wcnt[w][digit] = cnt + (uint32_t)__popcll(peers);
+                    wmask[w][digit] = 0ull;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    if (tid < RG_NB) {   // the waves' counts become the waves' offsets; the totals go to dstart
+        uint32_t run = 0;
+#pragma unroll
+        for (int k = 0; k < RT_NW; ++k) {
+            const uint32_t c = wcnt[k][tid];
+            wcnt[k][tid] = run;
+            run += c;
+        }
+        dstart[tid] = run;
+    }
+    __syncthreads();
+    if (w == 0) {   // exclusive prefix sum of the totals
+        constexpr int PER = RG_NB / 64;
+        uint32_t v[PER], s = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) { v[k] = dstart[lane * PER + k]; s += v[k]; }
+        uint32_t ex = wave_incl_scan_u32(s) - s;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) { dstart[lane * PER + k] = ex; ex += v[k]; }
+        if (lane == 63) dstart[RG_NB] = ex;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RT_IPT; ++r) {
+        const int64_t i = base + r * 64 + lane;
+        if (i < n) {
+            const uint32_t digit = (dig[r / 2] >> (16 * (r & 1))) & 0xFFFFu;
+            slot[i] = (uint16_t)(dstart[digit] + wcnt[w][digit] + ((rk[r / 2] >> (16 * (r & 1))) & 0xFFFFu));
+        }
+    }
+    if (tid <= RG_NB) dstart_out[tb * (RG_NB + 1) + tid] = dstart[tid];
+    if (tid < RG_NB) gofs_out[tb * RG_NB + tid] = (tid < nb ? first[(int64_t)tid * ntiles + tb] : 0u) - dstart[tid];
+}
+
+// rows of three coordinates: tile of `in` (caller's order) -> runs of `out`.  A thread holds its 32 rows; the places of the
+// tile are filled a quarter at a time (96 KB of LDS), and a quarter leaves as runs of whole rows.
+__global__ __launch_bounds__(RT_NT) void route_group_rows3_kernel(const float *__restrict__ in, float *__restrict__ out,
+                                                                  const uint16_t *__restrict__ slot,
+                                                                  const uint32_t *__restrict__ dstart_tab,
+                                                                  const uint32_t *__restrict__ gofs_tab, int64_t n) {
+    const int64_t tb = route_tile(n);
+    if (tb < 0) return;
+    constexpr int QUARTER = RT_TILE / 4;
+    __shared__ float stage[QUARTER * 3];
+    __shared__ uint32_t ds[RG_NB + 1], go[RG_NB];
+    const int tid = threadIdx.x;
+    const int64_t tile0 = tb * RT_TILE;
+    const int64_t left = n - tile0;
+    const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
+    if (tid <= RG_NB) ds[tid] = dstart_tab[tb * (RG_NB + 1) + tid];
+    if (tid < RG_NB) go[tid] = gofs_tab[tb * RG_NB + tid];
+    struct Row { float v[3]; };
+    const Row *rin = reinterpret_cast<const Row *>(in);
+    Row *rout = reinterpret_cast<Row *>(out);
+    Row row[RT_IPT];
+    uint32_t sl[RT_IPT / 2];   // two places per register
+#pragma unroll
+    for (int r = 0; r < RT_IPT; ++r) {
+        const int e = r * RT_NT + tid;
+        row[r] = rin[tile0 + (e < cnt ? e : 0)];
+        const uint32_t p = slot[tile0 + (e < cnt ? e : 0)];
+        sl[r / 2] = (r & 1) ? (sl[r / 2] | (p << 16)) : p;
+    }
+#pragma unroll 1
+    for (int h = 0; h < 4; ++h) {
+        __syncthreads();   // the places of the last quarter have been read
+#pragma unroll
+        for (int r = 0; r < RT_IPT; ++r) {
+            const uint32_t at = ((sl[r / 2] >> (16 * (r & 1))) & 0xFFFFu) - (uint32_t)(h * QUARTER);
+            if (at < (uint32_t)QUARTER && r * RT_NT + tid < cnt) {
+                stage[3 * at] = row[r].v[0];
+                stage[3 * at + 1] = row[r].v[1];
+                stage[3 * at + 2] = row[r].v[2];
+            }
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int r = 0; r < QUARTER / RT_NT; ++r) {
+            const uint32_t p = (uint32_t)(r * RT_NT + tid), q = (uint32_t)(h * QUARTER) + p;
+            if ((int)q < cnt) {
+                const Row t = {{stage[3 * p], stage[3 * p + 1], stage[3 * p + 2]}};
+                rout[go[route_digit_of<RG_NB>(ds, q)] + q] = t;
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------
 static RouteLevel route_level(const f3m_route &R, int pass) {
     RouteLevel L{};
     L.second = pass == 2;
@@ -460,12 +667,45 @@ void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, 
     }
 }
 
+// Tables of the one pass that groups the points by the nb boxes of a depth: keys of the points in the caller's order,
+// box of a point = key >> shift, one of box_keys (ascending).
+void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift, const uint32_t *box_keys, int64_t nb,
+                       int64_t *tally, hipStream_t st) {
+    if (nb < 1 || nb > RG_NB) fail(F3M_ERR_HIP, "internal: too many boxes for the one-pass grouping");
+    R.n = n;
+    R.ntiles = cdiv(n, RT_TILE);
+    R.grouped = true;
+    R.slot1.alloc((size_t)n, tally);
+    R.dstart1.alloc((size_t)R.ntiles * (RG_NB + 1), tally);
+    R.gofs1.alloc((size_t)R.ntiles * RG_NB, tally);
+    DevBuf<uint16_t> lut;
+    lut.alloc(RG_NB);
+    F3M_HIP(hipMemsetAsync(lut.p, 0, RG_NB * sizeof(uint16_t), st));
+    route_lut_kernel<<<dim3((unsigned)cdiv(nb, 256)), dim3(256), 0, st>>>(box_keys, nb, lut.p);
+    DevBuf<uint32_t> hist;
+    hist.alloc((size_t)nb * (size_t)R.ntiles);
+    const unsigned grid = route_grid(R.ntiles);
+    route_group_count_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(keys, n, shift, lut.p, (int)nb, R.ntiles, hist.p);
+    F3M_HIP(hipGetLastError());
+    exclusive_scan(RouteCountIn{hist.p}, nb * R.ntiles, RouteCountOut{hist.p}, nullptr, st);
+    route_group_rank_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(keys, n, shift, lut.p, (int)nb, R.ntiles, hist.p, R.slot1.p,
+                                                               R.dstart1.p, R.gofs1.p);
+    F3M_HIP(hipGetLastError());
+}
+
 // out[perm[k]] = in[k] (+ in2[k]); tmp_a, tmp_b: n floats each
 void route_scatter(const f3m_route &R, const float *in, const float *in2, float *out, float *tmp_a, float *tmp_b,
                    hipStream_t st) {
     const unsigned grid = route_grid(R.ntiles);
-    route_deal_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(in, in2, tmp_a, R.slot1.p, R.dstart1.p, R.gofs1.p, R.B1, R.n);
-    route_deal_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, nullptr, tmp_b, R.slot2.p, R.dstart2.p, R.gofs2.p, R.B2,
+    if (R.grouped) {
+        if (in2) fail(F3M_ERR_HIP, "internal: grouped points have no exact near field");
+        route_collect_kernel<1, false, RG_NB><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, 0, out, 0, R.slot1.p, R.dstart1.p,
+                                                                                 R.gofs1.p, 0, R.n);
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    route_deal_kernel<256><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, in2, tmp_a, R.slot1.p, R.dstart1.p, R.gofs1.p, R.B1, R.n);
+    route_deal_kernel<256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, nullptr, tmp_b, R.slot2.p, R.dstart2.p, R.gofs2.p, R.B2,
                                                          R.n);
     route_place_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, out, R.off3.p, R.n);
     F3M_HIP(hipGetLastError());
@@ -474,10 +714,15 @@ void route_scatter(const f3m_route &R, const float *in, const float *in2, float 
 // out[k] = in[perm[k]]; tmp_a, tmp_b: n floats each
 void route_gather(const f3m_route &R, const float *in, float *out, float *tmp_a, float *tmp_b, hipStream_t st) {
     const unsigned grid = route_grid(R.ntiles);
+    if (R.grouped) {
+        route_deal_kernel<RG_NB><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, nullptr, out, R.slot1.p, R.dstart1.p, R.gofs1.p, 0, R.n);
+        F3M_HIP(hipGetLastError());
+        return;
+    }
     route_pick_kernel<1><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, tmp_a, 0, R.off3.p, R.n);
-    route_collect_kernel<1, false><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, 0, tmp_b, 0, R.slot2.p, R.dstart2.p,
+    route_collect_kernel<1, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, 0, tmp_b, 0, R.slot2.p, R.dstart2.p,
                                                                       R.gofs2.p, R.B2, R.n);
-    route_collect_kernel<1, false><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, 0, out, 0, R.slot1.p, R.dstart1.p,
+    route_collect_kernel<1, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, 0, out, 0, R.slot1.p, R.dstart1.p,
                                                                       R.gofs1.p, R.B1, R.n);
     F3M_HIP(hipGetLastError());
 }
@@ -486,10 +731,15 @@ void route_gather(const f3m_route &R, const float *in, float *out, float *tmp_a,
 // three component arrays of order p2; tmp: 3 n floats.
 void route_gather_rows3(const f3m_route &R, const float *in, float *out, float *tmp, hipStream_t st) {
     const unsigned grid = route_grid(R.ntiles);
+    if (R.grouped) {
+        route_group_rows3_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(in, out, R.slot1.p, R.dstart1.p, R.gofs1.p, R.n);
+        F3M_HIP(hipGetLastError());
+        return;
+    }
     route_pick_kernel<3><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, out, R.n, R.off3.p, R.n);
-    route_collect_kernel<3, false><<<dim3(grid), dim3(RT_NT), 0, st>>>(out, R.n, tmp, R.n, R.slot2.p, R.dstart2.p,
+    route_collect_kernel<3, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(out, R.n, tmp, R.n, R.slot2.p, R.dstart2.p,
                                                                       R.gofs2.p, R.B2, R.n);
-    route_collect_kernel<3, true><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp, R.n, out, 0, R.slot1.p, R.dstart1.p,
+    route_collect_kernel<3, true, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp, R.n, out, 0, R.slot1.p, R.dstart1.p,
                                                                      R.gofs1.p, R.B1, R.n);
     F3M_HIP(hipGetLastError());
 }

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(CG_NT) void cg_init_kernel(const float *__restrict_
                                                         float *__restrict__ p, int64_t n, double *__restrict__ part) {
     double s = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * CG_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * CG_NT) {
-        const float v = b[perm[i]];
+        const float v = b[perm ? perm[i] : (uint32_t)i];
         x[i] = 0.f;
         r[i] = v;
         p[i] = v;
@@ -139,7 +139,10 @@ void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter,
         F3M_HIP(hipMemcpyAsync(h, scal.p, sizeof(h), hipMemcpyDeviceToHost, st));
         F3M_HIP(hipStreamSynchronize(st));
     };
-    cg_init_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(b, P.perm.p, xs.p, r.p, p.p, n, part.p);
+    // grouped points are not in the order of perm
+    const bool grouped = P.route && P.route->grouped;
+    if (grouped) route_gather(*P.route, b, q.p, nullptr, nullptr, st);
+    cg_init_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(grouped ? q.p : b, grouped ? nullptr : P.perm.p, xs.p, r.p, p.p, n, part.p);
     cg_reduce_kernel<<<dim3(1), dim3(CG_NT), 0, st>>>(part.p, blocks, scal.p, 0);
     F3M_HIP(hipGetLastError());
     fetch();
@@ -169,7 +172,8 @@ void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter,
         F3M_HIP(hipGetLastError());
     }
     if (iters_host) *iters_host = it;
-    cg_unpermute_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(xs.p, P.perm.p, n, x);
+    if (grouped) route_scatter(*P.route, xs.p, nullptr, x, nullptr, nullptr, st);
+    else cg_unpermute_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(xs.p, P.perm.p, n, x);
     F3M_HIP(hipGetLastError());
     F3M_HIP(hipStreamSynchronize(st));   // the work vectors are released on return
 }
