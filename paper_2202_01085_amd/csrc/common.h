@@ -54,6 +54,23 @@ private:
 constexpr int HOST_WORDS = 512;
 uint64_t *scope_words();   // of the thread's open scope of a stream
 
+// events of the current device, from a list of at most EVENTS_MAX that plans have given back (a plan makes some fifty: creating and
+// destroying them took 70 us of a plan and product of 1e5 points)
+hipEvent_t event_get();
+void event_put(hipEvent_t e, int device) noexcept;
+
+// p[0 .. n) = value for up to two arrays, and zeros in many short ones, by a kernel each (a hipMemsetAsync costs the host three
+// times as much as a launch)
+void fill_words(uint32_t *p, int64_t n, uint32_t *q, int64_t m, uint32_t value, hipStream_t st);
+struct ZeroList {
+    static constexpr int MAX = 48;
+    float *p[MAX];
+    uint32_t n[MAX];
+    int count = 0;
+    void add(float *at, size_t words);
+    void run(hipStream_t st);   // and forgets them
+};
+
 // A device allocation that releases itself; the byte count is added to *tally if given.
 template <class T>
 struct DevBuf {

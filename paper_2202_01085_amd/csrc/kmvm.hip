@@ -2307,13 +2307,6 @@ static TransferArg make_transfer() {
     return T;
 }
 
-void upload_transfer(f3m_plan_s &P, hipStream_t st) {
-    const TransferArg T = make_transfer();
-    P.transfer.alloc(32, &P.bytes);
-    P.host_tabs.emplace_back(&T.t[0][0][0], &T.t[0][0][0] + 32);
-    F3M_HIP(hipMemcpyAsync(P.transfer.p, P.host_tabs.back().data(), 32 * sizeof(float), hipMemcpyHostToDevice, st));
-}
-
 // Both transfers run one wavefront per PARENT with lane = node (ix + 4 iy + 16 iz) and apply the
 // three 4 x 4 factors one dimension at a time, 4 multiply-adds each: the other three entries of a
 // fibre sit in the lane's quad (x: DPP quad permutations), in its row of 16 lanes (y: DPP row
@@ -2809,8 +2802,29 @@ void build_far_orders(f3m_plan_s &P, hipStream_t st) {
     }
 }
 
-// per depth with far pairs: the 1-D factor matrices of the node-to-node kernel matrix, built in fp64
-void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
+// up to TAB_ARG floats to the device as an argument of a launch: a copy from pageable memory takes the host 20 us
+constexpr int TAB_ARG = 960;
+struct TabArg { float v[TAB_ARG]; };
+__global__ __launch_bounds__(256) void put_table_kernel(float *__restrict__ dst, int n, TabArg A) {
+    for (int i = threadIdx.x; i < n; i += 256) dst[i] = A.v[i];
+}
+
+// per depth with far pairs: the 1-D factor matrices of the node-to-node kernel matrix, built in fp64; the factors of the weighted
+// near pairs and the parent's basis at a child's nodes
+void upload_tables(f3m_plan_s &P, hipStream_t st) {
+    std::vector<float> &g = P.host_tabs;
+    g.clear();
+    std::vector<std::pair<float **, size_t>> places;   // where the address of a table goes, and its offset
+    auto table = [&](float **at, size_t count) {
+        places.emplace_back(at, g.size());
+        g.resize(g.size() + count);
+        return &g[places.back().second];
+    };
+    if (P.tree_lmin > 0) {
+        const TransferArg T = make_transfer();
+        std::copy(&T.t[0][0][0], &T.t[0][0][0] + 32, table(&P.transfer.p, 32));
+    }
+    if (P.near_weighted) near_table(P, table(&P.near_tab.p, 16));
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
         if (lv.far_sz == 0 || lv.p == 0 || l > P.last_depth()) continue;
@@ -2837,18 +2851,29 @@ void upload_kron_tables(f3m_plan_s &P, hipStream_t st) {
         }
         double u[F3M_MAX_DIM];
         P.grid_shift(l, u);
-        std::vector<float> g((size_t)ndim * S.no * p * p);
+        float *G = table(&lv.gtab.p, (size_t)ndim * S.no * p * p);
         for (int d = 0; d < ndim; ++d)
             for (int k = 0; k < S.no; ++k)
                 for (int i = 0; i < p; ++i)
                     for (int j = 0; j < p; ++j) {
                         // source node minus target node in half box edges: 2 (o + u) + s_j - s_i
                         const double t = 2.0 * ((double)(S.omin[d] + k) + u[d]) + s[j] - s[i];
-                        g[(((size_t)d * S.no + k) * p + i) * p + j] = (float)std::exp(-c * t * t);
+                        G[(((size_t)d * S.no + k) * p + i) * p + j] = (float)std::exp(-c * t * t);
                     }
-        lv.gtab.alloc(g.size(), &P.bytes);
-        F3M_HIP(hipMemcpyAsync(lv.gtab.p, g.data(), g.size() * sizeof(float), hipMemcpyHostToDevice, st));
-        P.host_tabs.push_back(std::move(g));   // stays alive until the plan has been waited for
+    }
+    if (g.empty()) return;
+    P.tables.alloc(g.size(), &P.bytes);
+    for (auto &t : places) *t.first = P.tables.p + t.second;
+    if (g.size() <= 8 * TAB_ARG) {
+        for (size_t at = 0; at < g.size(); at += TAB_ARG) {
+            TabArg A;
+            const int count = (int)std::min<size_t>(TAB_ARG, g.size() - at);
+            std::copy(g.data() + at, g.data() + at + count, A.v);
+            put_table_kernel<<<dim3(1), dim3(256), 0, st>>>(P.tables.p + at, count, A);
+        }
+        F3M_HIP(hipGetLastError());
+    } else {   // (the host copy stays until the plan has been waited for)
+        F3M_HIP(hipMemcpyAsync(P.tables.p, g.data(), g.size() * sizeof(float), hipMemcpyHostToDevice, st));
     }
 }
 
@@ -2928,9 +2953,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     auto mark = [&] {
         if (nmarks == P.marks.size()) {   // (an event that cannot be made leaves the list as it is)
             P.marks.reserve(nmarks + 1);
-            hipEvent_t e = nullptr;
-            F3M_HIP(hipEventCreate(&e));
-            P.marks.push_back(e);
+            P.marks.push_back(event_get());
         }
         F3M_HIP(hipEventRecord(P.marks[nmarks], st));
         return P.marks[nmarks++];
@@ -3346,7 +3369,7 @@ void run_kmvm_multi(f3m_plan_s &P, const float *B, int64_t ldb, float *Y, int64_
     if (!P.multi_bs.p) {
         P.multi_bs.alloc(4 * bs_stride, &P.bytes);
         P.multi_yn.alloc(4 * (size_t)n, &P.bytes);
-        F3M_HIP(hipMemsetAsync(P.multi_bs.p, 0, 4 * bs_stride * sizeof(float), st));   // the padding stays zero
+        fill_words((uint32_t *)P.multi_bs.p, (int64_t)(4 * bs_stride), nullptr, 0, 0u, st);   // the padding stays zero
     }
     for (int j0 = 0; j0 < m; j0 += 4) {
         const int mb = std::min(4, m - j0);

@@ -794,18 +794,14 @@ __global__ __launch_bounds__(512) void near_weighted_kernel(const uint32_t *__re
     }
 }
 
-void upload_near_table(f3m_plan_s &P, hipStream_t st) {
+void near_table(const f3m_plan_s &P, float *t) {
     const double s[4] = {1.0, 0.5, -0.5, -1.0};
     const double half = 0.5 * (double)P.E / (double)(1ull << P.near_weighted);
     const double c = half * half / ((double)P.gamma * (double)P.gamma);
-    std::vector<float> t(16);
     for (int o = 0; o <= 1; ++o)
         for (int i = 0; i < 4; ++i)
             for (int j = 0; j < 4; ++j)
                 t[near_factor_index(o, i, j)] = (float)std::exp(c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o)));
-    P.near_tab.alloc(16, &P.bytes);
-    F3M_HIP(hipMemcpyAsync(P.near_tab.p, t.data(), 16 * sizeof(float), hipMemcpyHostToDevice, st));
-    P.host_tabs.push_back(std::move(t));   // stays alive until the plan has been waited for
 }
 
 // W: weighted node weights of depth near_weighted with a row of zeros behind them
@@ -827,8 +823,7 @@ bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st) {
     if (!lv.far_implicit || lv.far_sz == 0 || lv.p == 0) return false;
     lv.st_cand.alloc((size_t)up.nb * ST_CAND, &P.bytes);
     lv.st_child.alloc((size_t)up.nb * 8, &P.bytes);
-    F3M_HIP(hipMemsetAsync(lv.st_cand.p, 0xFF, (size_t)up.nb * ST_CAND * sizeof(uint32_t), st));
-    F3M_HIP(hipMemsetAsync(lv.st_child.p, 0xFF, (size_t)up.nb * 8 * sizeof(uint32_t), st));
+    fill_words(lv.st_cand.p, up.nb * ST_CAND, lv.st_child.p, up.nb * 8, ~0u, st);
     return true;
 }
 

@@ -49,7 +49,7 @@ struct f3m_level {
     int p = 0, r = 0;
     bool smooth = false;
     // 1-D factors of the node-to-node kernel matrix, [2*omax+1][p][p]
-    f3m::DevBuf<float> gtab;
+    struct { float *p = nullptr; } gtab;   // (part of the plan's tables)
     int gtab_omax = 0;
     // node weights / node potentials kept per depth when they are passed between depths
     f3m::DevBuf<float> Wl, Vl;          // [(nb + 1) * 64], [nb * 64]; at depth near_weighted the same again behind
@@ -154,11 +154,12 @@ struct f3m_plan_s {
                                         // weighted points, to within fp32 rounding (near_weighted_error)
     bool exact_near() const { return near_depth == 0 && near_weighted == 0; }
     int last_depth() const { return near_depth ? near_depth : near_weighted ? near_weighted : L; }   // of the products
-    f3m::DevBuf<float> near_tab;        // [16] factors of the weighted near pairs (near_factor_index)
+    struct { float *p = nullptr; } near_tab;   // [16] factors of the weighted near pairs (near_factor_index)
     int tree_lmin = 0, tree_lmax = 0;   // tree_lmin > 0: node weights/potentials are passed between depths
                                         // tree_lmin..tree_lmax (D = 3, 4 nodes/dim); other depths work
                                         // straight from the points
-    f3m::DevBuf<float> transfer;        // [2][4][4] parent basis at the child's nodes
+    struct { float *p = nullptr; } transfer;   // [2][4][4] parent basis at the child's nodes
+    f3m::DevBuf<float> tables;          // gtab of every depth, near_tab and transfer
     // large n: both permutations of a product run as three streaming passes (route.hip); the two work
     // vectors hold max(n, sources) floats each
     int64_t route_min_n = 0;                    // the passes are used from this many points on
@@ -168,7 +169,7 @@ struct f3m_plan_s {
 
     hipEvent_t ev[16] = {nullptr};
     std::vector<hipEvent_t> plan_events;  // two per depth while the plan is built
-    std::vector<std::vector<float>> host_tabs;   // tables on their way to the device, until the plan is complete
+    std::vector<float> host_tabs;       // the tables on their way to the device, until the plan is complete
     // Times of a product: an event at every boundary between its stages, in order (marks); the others name them.
     // far_events: 6 per depth, around the far-field kernels of that depth.  t_wait0 .. t_wait1 (if not null): a wait for
     // the near field inside the downward pass of depth tree_lmax.
@@ -229,8 +230,7 @@ void run_direct_rows_f64(const float *X, const float *Y, int64_t ny, int D, floa
 // the same with the partial sums in a static device array: no allocation, no wait (m <= 16384)
 void run_direct_rows_f64_static(const float *X, int64_t n, int D, float gamma, const float *b, const int64_t *rows,
                                 int64_t m, double *y64, hipStream_t st);
-void upload_transfer(f3m_plan_s &P, hipStream_t st);            // parent-basis-at-child-nodes table
-void upload_kron_tables(f3m_plan_s &P, hipStream_t st);         // per-dimension kernel factors of every far depth
+void upload_tables(f3m_plan_s &P, hipStream_t st);              // kernel factors of every far depth, parent basis at child nodes
 void build_far_orders(f3m_plan_s &P, hipStream_t st);           // far rows in row-major cell order for the grouped M2L
 // solve.hip: conjugate gradients for (K + lambda I) x = b on a one-set plan (synchronises)
 void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter, float tol, int *iters_host,
@@ -245,7 +245,7 @@ void run_far_points(f3m_plan_s &P, int level, const float *bs, float *ys, int om
 bool m2l_stencil_applies(const f3m_plan_s &P);   // D = 3, 4 nodes per dimension, far ratio 2
 void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);   // after the lists of the depth exist
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables
-void upload_near_table(f3m_plan_s &P, hipStream_t st);                 // factors of the weighted near pairs
+void near_table(const f3m_plan_s &P, float *t);                        // 16 factors of the weighted near pairs
 void run_near_weighted(f3m_plan_s &P, const float *W, float *V, hipStream_t st);
 bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStream_t st, bool zero_row = false);  // false: does not apply
 

@@ -8,14 +8,10 @@
 #include "plan.h"
 
 f3m_plan_s::~f3m_plan_s() {
-    for (auto &e : ev)
-        if (e) (void)hipEventDestroy(e);
-    for (auto &e : plan_events)
-        if (e) (void)hipEventDestroy(e);
-    for (auto &e : marks)
-        if (e) (void)hipEventDestroy(e);
-    for (hipEvent_t e : {ev_fork, ev_join, ev_p2p0, ev_p2p1})
-        if (e) (void)hipEventDestroy(e);
+    for (auto &e : ev) f3m::event_put(e, device);
+    for (auto &e : plan_events) f3m::event_put(e, device);
+    for (auto &e : marks) f3m::event_put(e, device);
+    for (hipEvent_t e : {ev_fork, ev_join, ev_p2p0, ev_p2p1}) f3m::event_put(e, device);
     if (side) (void)hipStreamDestroy(side);
 }
 
@@ -34,7 +30,7 @@ constexpr int BBOX_NT = 256;
 
 template <int D>
 __global__ __launch_bounds__(BBOX_NT) void bbox_kernel(const float *__restrict__ X, int64_t n,
-                                                       float *__restrict__ part, int *__restrict__ nonfinite) {
+                                                       float *__restrict__ part) {
     float mn[D], mx[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) { mn[d] = INFINITY; mx[d] = -INFINITY; }
@@ -68,10 +64,27 @@ __global__ __launch_bounds__(BBOX_NT) void bbox_kernel(const float *__restrict__
         int d = threadIdx.x;
         float a = smn[0][d], b = smx[0][d];
         for (int k = 1; k < BBOX_NT / 64; ++k) { a = fminf(a, smn[k][d]); b = fmaxf(b, smx[k][d]); }
-        part[(int64_t)blockIdx.x * 2 * D + d] = a;
-        part[(int64_t)blockIdx.x * 2 * D + D + d] = b;
+        part[(int64_t)blockIdx.x * (2 * D + 1) + d] = a;
+        part[(int64_t)blockIdx.x * (2 * D + 1) + D + d] = b;
     }
-    if (threadIdx.x == 0 && sbad) atomicOr(nonfinite, 1);
+    if (threadIdx.x == 0) part[(int64_t)blockIdx.x * (2 * D + 1) + 2 * D] = sbad ? 1.f : 0.f;
+}
+// the same over the blocks, to words of the host: minima, maxima, whether a value is not finite (one wavefront per word)
+__global__ __launch_bounds__(1024) void bbox_final_kernel(const float *__restrict__ part, int nblocks, int D,
+                                                          uint64_t *__restrict__ words) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, m = 2 * D + 1;
+    if (w >= m) return;
+    float v = w < D ? INFINITY : -INFINITY;
+    for (int k = lane; k < nblocks; k += 64) {
+        const float p = part[(int64_t)k * m + w];
+        v = w < D ? fminf(v, p) : fmaxf(v, p);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const float o = __shfl_xor(v, off, 64);
+        v = w < D ? fminf(v, o) : fmaxf(v, o);
+    }
+    if (lane == 0) words[w] = __float_as_uint(v);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1070,25 +1083,24 @@ struct SetRef {
 template <int D>
 static float set_bounds(const SetRef &S, const char *name, hipStream_t st) {
     DevBuf<float> part;
-    DevBuf<int> bad;
-    part.alloc((size_t)BBOX_BLOCKS * 2 * D);
-    bad.alloc(1);
-    F3M_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), st));
-    bbox_kernel<D><<<dim3(BBOX_BLOCKS), dim3(BBOX_NT), 0, st>>>(S.X, S.n, part.p, bad.p);
+    part.alloc((size_t)BBOX_BLOCKS * (2 * D + 1));
+    // (a set that needs fewer blocks leaves no empty ones behind)
+    const int blocks = (int)std::min<int64_t>(BBOX_BLOCKS, cdiv(S.n, BBOX_NT));
+    uint64_t *words = scope_words();
+    bbox_kernel<D><<<dim3(blocks), dim3(BBOX_NT), 0, st>>>(S.X, S.n, part.p);
+    bbox_final_kernel<<<dim3(1), dim3(1024), 0, st>>>(part.p, blocks, D, words);
     F3M_HIP(hipGetLastError());
-    std::vector<float> hp((size_t)BBOX_BLOCKS * 2 * D);
-    int hbad = 0;
-    F3M_HIP(hipMemcpyAsync(hp.data(), part.p, hp.size() * sizeof(float), hipMemcpyDeviceToHost, st));
-    F3M_HIP(hipMemcpyAsync(&hbad, bad.p, sizeof(int), hipMemcpyDeviceToHost, st));
     F3M_HIP(hipStreamSynchronize(st));
-    if (hbad) fail(F3M_ERR_NONFINITE, std::string(name) + " holds a NaN or an infinity");
+    auto value = [&](int k) {
+        const uint32_t u = (uint32_t)words[k];
+        float f;
+        std::memcpy(&f, &u, sizeof(f));
+        return f;
+    };
+    if (value(2 * D) != 0.f) fail(F3M_ERR_NONFINITE, std::string(name) + " holds a NaN or an infinity");
     float E = 0.f;
     for (int d = 0; d < D; ++d) {
-        float mn = INFINITY, mx = -INFINITY;
-        for (int k = 0; k < BBOX_BLOCKS; ++k) {
-            mn = std::min(mn, hp[(size_t)k * 2 * D + d]);
-            mx = std::max(mx, hp[(size_t)k * 2 * D + D + d]);
-        }
+        const float mn = value(d), mx = value(D + d);
         volatile float ext = mx - mn;  // one fp32 subtraction
         if (ext > E) E = ext;
         S.alpha[d] = mn;
@@ -1175,7 +1187,7 @@ template <int D>
 static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st) {
     const int64_t n = P.n;
     int64_t *tally = &P.bytes;
-    for (int k = 0; k < 8; ++k) F3M_HIP(hipEventCreate(&P.ev[k]));
+    for (int k = 0; k < 6; ++k) P.ev[k] = event_get();
     F3M_HIP(hipEventRecord(P.ev[0], st));
     // the set(s) to partition: the targets, and the sources when they are another set
     std::vector<SetRef> sets;
@@ -1235,12 +1247,13 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         }
     }
     F3M_HIP(hipEventRecord(P.ev[2], st));
+    ZeroList zeros;   // cleared when the plan is otherwise complete
     // the points into box order, once the depth that the products end at is known
     auto order_points = [&](size_t k) {
         const SetRef &S = sets[k];
         // 64 zero points of padding after the last point: kernels may read whole 32-point blocks
         S.Xs->alloc(((size_t)S.n + PAD_POINTS) * D, tally);
-        F3M_HIP(hipMemsetAsync(S.Xs->p + (size_t)S.n * D, 0, (size_t)PAD_POINTS * D * sizeof(float), st));
+        zeros.add(S.Xs->p + (size_t)S.n * D, (size_t)PAD_POINTS * D);
         // A large set goes through the three-pass permutation, whose tables also serve every product
         // (route.hip); its points follow the same way when they have three coordinates.
         std::unique_ptr<f3m_route> &route = k ? P.src->route : P.route;
@@ -1278,7 +1291,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         f3m_level &lv = P.lev[l];
         for (size_t k = 0; k < sets.size(); ++k) divide_set<D>(P, sets[k], l, part, words + HW_SET + 2 * k, st);
         const f3m_level &sv = P.slev(l);
-        for (int k = 0; k < 2; ++k) F3M_HIP(hipEventCreate(&P.plan_events[2 * (size_t)l + k]));
+        for (int k = 0; k < 2; ++k) P.plan_events[2 * (size_t)l + k] = event_get();
         F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l], st));
 
         // new interactions + partition
@@ -1398,10 +1411,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     if (P.tree_lmax > 0) {
         P.tree_lmin = P.tree_lmax;
         while (in_band(P.tree_lmin - 1)) --P.tree_lmin;
-        upload_transfer(P, st);
     }
-    upload_kron_tables(P, st);
-    if (P.near_weighted) upload_near_table(P, st);
+    upload_tables(P, st);
     build_far_orders(P, st);
     for (int k = 1; k <= P.L; ++k) build_stencil_tables(P, k, st);
     ItemLists items(tally, st);
@@ -1426,7 +1437,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             if (!P.src) {
                 lv.Wl.alloc(twice * (size_t)(lv.nb + 1) * lv.r, tally);
                 for (size_t h = 1; h <= twice; ++h)
-                    F3M_HIP(hipMemsetAsync(lv.Wl.p + (h * (size_t)(lv.nb + 1) - 1) * lv.r, 0, (size_t)lv.r * sizeof(float), st));
+                    zeros.add(lv.Wl.p + (h * (size_t)(lv.nb + 1) - 1) * lv.r, (size_t)lv.r);
                 if (k < P.tree_lmax) continue;   // only the last depth of the band needs chunks
             }
         }
@@ -1442,7 +1453,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             // may overlap in a small part of the sources' cube only).
             DevBuf<uint32_t> used;
             used.alloc((size_t)sv.nb);
-            F3M_HIP(hipMemsetAsync(used.p, 0, (size_t)sv.nb * sizeof(uint32_t), st));
+            fill_words(used.p, sv.nb, nullptr, 0, 0u, st);
             mark_cols_kernel<<<dim3((unsigned)std::min<int64_t>(cdiv(lv.far_sz, 256), 1 << 20)), dim3(256), 0, st>>>(
                 lv.far_col.p, lv.far_sz, used.p);
             F3M_HIP(hipGetLastError());
@@ -1503,11 +1514,13 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         P.route_b.alloc(m, tally);
     }
     P.bs.alloc((size_t)P.ns() + PAD_POINTS, tally);
-    F3M_HIP(hipMemsetAsync(P.bs.p + P.ns(), 0, (size_t)PAD_POINTS * sizeof(float), st));
+    zeros.add(P.bs.p + P.ns(), PAD_POINTS);
+    zeros.run(st);
     P.ys.alloc((size_t)n, tally);
     P.yn.alloc((size_t)n, tally);
     if (!P.no_overlap) F3M_HIP(hipStreamCreateWithFlags(&P.side, hipStreamNonBlocking));
-    for (hipEvent_t *e : {&P.ev_fork, &P.ev_join, &P.ev_p2p0, &P.ev_p2p1}) F3M_HIP(hipEventCreate(e));
+    if (P.side)
+        for (hipEvent_t *e : {&P.ev_fork, &P.ev_join, &P.ev_p2p0, &P.ev_p2p1}) *e = event_get();
     P.W.alloc((size_t)max_w, tally);
     P.V.alloc((size_t)max_v, tally);
     P.Wpart.alloc((size_t)max_part, tally);

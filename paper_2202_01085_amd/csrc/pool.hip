@@ -21,7 +21,9 @@ struct Pool {
     std::multimap<std::pair<int, size_t>, void *> blocks;   // (device, class size) -> free block
     size_t held = 0;                                          // bytes of the free blocks
     std::vector<void *> words;                                // free arrays of scope_words (one per plan built at once)
+    std::vector<std::pair<int, hipEvent_t>> events;           // (device, event)
 };
+constexpr size_t EVENTS_MAX = 4096;
 
 // the open scope of a thread
 struct Scope {
@@ -127,6 +129,71 @@ uint64_t *scope_words() {
     return (uint64_t *)S.words;
 }
 
+hipEvent_t event_get() {
+    int dev = 0;
+    F3M_HIP(hipGetDevice(&dev));
+    {
+        Pool &P = pool();
+        std::lock_guard<std::mutex> lock(P.m);
+        for (size_t k = P.events.size(); k-- > 0;)
+            if (P.events[k].first == dev) {
+                const hipEvent_t e = P.events[k].second;
+                P.events.erase(P.events.begin() + (std::ptrdiff_t)k);
+                return e;
+            }
+    }
+    hipEvent_t e = nullptr;
+    F3M_HIP(hipEventCreate(&e));
+    return e;
+}
+
+void event_put(hipEvent_t e, int device) noexcept {
+    if (!e) return;
+    try {
+        Pool &P = pool();
+        std::lock_guard<std::mutex> lock(P.m);
+        if (P.events.size() < EVENTS_MAX) {
+            P.events.emplace_back(device, e);
+            return;
+        }
+    } catch (...) {   // no room for the list
+    }
+    (void)hipEventDestroy(e);
+}
+
+namespace {
+__global__ __launch_bounds__(256) void fill_words_kernel(uint32_t *__restrict__ p, int64_t n, uint32_t *__restrict__ q,
+                                                         int64_t m, uint32_t value) {
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n + m; i += step) {
+        if (i < n) p[i] = value;
+        else q[i - n] = value;
+    }
+}
+__global__ __launch_bounds__(256) void zero_list_kernel(ZeroList L) {
+    for (uint32_t i = threadIdx.x; i < L.n[blockIdx.x]; i += 256) L.p[blockIdx.x][i] = 0.f;
+}
+}  // namespace
+
+void fill_words(uint32_t *p, int64_t n, uint32_t *q, int64_t m, uint32_t value, hipStream_t st) {
+    if (n + m <= 0) return;
+    const int64_t blocks = cdiv(n + m, 256 * 8);
+    fill_words_kernel<<<dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st>>>(p, n, q, m, value);
+    F3M_HIP(hipGetLastError());
+}
+
+void ZeroList::add(float *at, size_t words) {
+    if (count == MAX) fail(F3M_ERR_HIP, "internal: too many arrays to clear at once");
+    p[count] = at;
+    n[count++] = (uint32_t)words;
+}
+
+void ZeroList::run(hipStream_t st) {
+    if (count > 0) zero_list_kernel<<<dim3((unsigned)count), dim3(256), 0, st>>>(*this);
+    F3M_HIP(hipGetLastError());
+    count = 0;
+}
+
 void *pool_alloc(size_t bytes) {
     const size_t cs = class_size(bytes);
     int dev = 0;
@@ -190,6 +257,8 @@ size_t pool_trim() {
     std::lock_guard<std::mutex> lock(P.m);
     for (void *w : P.words) (void)hipHostFree(w);
     P.words.clear();
+    for (auto &e : P.events) (void)hipEventDestroy(e.second);
+    P.events.clear();
     return trim_locked(P, 0);
 }
 

@@ -680,7 +680,7 @@ void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift,
     R.gofs1.alloc((size_t)R.ntiles * RG_NB, tally);
     DevBuf<uint16_t> lut;
     lut.alloc(RG_NB);
-    F3M_HIP(hipMemsetAsync(lut.p, 0, RG_NB * sizeof(uint16_t), st));
+    fill_words((uint32_t *)lut.p, RG_NB / 2, nullptr, 0, 0u, st);
     route_lut_kernel<<<dim3((unsigned)cdiv(nb, 256)), dim3(256), 0, st>>>(box_keys, nb, lut.p);
     DevBuf<uint32_t> hist;
     hist.alloc((size_t)nb * (size_t)R.ntiles);

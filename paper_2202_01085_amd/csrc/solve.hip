@@ -128,12 +128,11 @@ void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter,
     xs.alloc((size_t)n);
     r.alloc((size_t)n);
     p.alloc((size_t)n + PAD_POINTS);
-    F3M_HIP(hipMemsetAsync(p.p + n, 0, PAD_POINTS * sizeof(float), st));
     q.alloc((size_t)n);
     const int blocks = (int)std::min<int64_t>(CG_BLOCKS, cdiv(n, CG_NT));
     part.alloc((size_t)blocks);
     scal.alloc(S_COUNT);
-    F3M_HIP(hipMemsetAsync(scal.p, 0, S_COUNT * sizeof(double), st));
+    fill_words((uint32_t *)(p.p + n), PAD_POINTS, (uint32_t *)scal.p, 2 * S_COUNT, 0u, st);
     double h[S_COUNT];
     auto fetch = [&] {
         F3M_HIP(hipMemcpyAsync(h, scal.p, sizeof(h), hipMemcpyDeviceToHost, st));
