@@ -897,6 +897,23 @@ struct PtrOut {
         if (i == n - 1) p[n] = ex + v;
     }
 };
+// the same for two lists whose totals are below 2^32, in the halves of one number
+struct PairIn {
+    const uint32_t *a, *b;
+    __device__ uint64_t operator()(int64_t i) const { return (uint64_t)a[i] | ((uint64_t)b[i] << 32); }
+};
+struct PairOut {
+    uint64_t *p, *q;
+    int64_t n;
+    __device__ void operator()(int64_t i, uint64_t ex, uint64_t v) const {
+        p[i] = ex & 0xFFFFFFFFull;
+        q[i] = ex >> 32;
+        if (i == n - 1) {
+            p[n] = (ex + v) & 0xFFFFFFFFull;
+            q[n] = (ex + v) >> 32;
+        }
+    }
+};
 struct FirstOut {
     uint32_t *p;
     int64_t n;
@@ -1180,6 +1197,227 @@ static void divide_finish(const SetRef &S, int l, const uint64_t *words) {
     if ((int64_t)words[1] != S.lev[l - 1].nb) fail(F3M_ERR_HIP, "internal: parent count mismatch");
 }
 
+// The box tables of ALL depths from the sorted keys at once, for sets of up to BULK_MAX points.  A point is the head of a box at
+// depth l iff its key differs from the one before it in the bits of depths <= l, so one number per point, the first
+// depth at which it is a head, gives every table: counts per block and depth, a scan of them, and one pass that
+// writes start, key, parent, cell and child ranges.  Depth by depth it was six launches and two waits each, and small sets are
+// bound by those (plan and product of 1e5 points in 2-D 1.16 -> 1.00 ms, of 1e6 normal points 2.07 -> 1.82).
+constexpr int64_t BULK_MAX = (int64_t)1 << 24;
+constexpr int BULK_LEVELS = F3M_MAX_LEVELS + 1;
+constexpr int BULK_TILE = 2048;   // 256 threads with eight keys each
+
+// first depth at which two keys differ (Lq + 1: equal)
+template <int D>
+__device__ inline int first_depth(uint32_t a, uint32_t b, int Lq) {
+    const uint32_t x = a ^ b;
+    return x ? Lq - (31 - __clz((int)x)) / D : Lq + 1;
+}
+
+// heads of the eight points from base on: first depths, Lq + 2 behind the end
+template <int D>
+__device__ inline void head_depths(const uint32_t *__restrict__ keys, int64_t base, int64_t n, int Lq, uint32_t (&k)[9], int (&h)[8]) {
+    // (whole tiles may be read: the keys carry slack)
+    const uint4 *p = reinterpret_cast<const uint4 *>(keys + base);
+    const uint4 a = p[0], b = p[1];
+    k[0] = base > 0 ? keys[base - 1] : 0u;
+    k[1] = a.x; k[2] = a.y; k[3] = a.z; k[4] = a.w; k[5] = b.x; k[6] = b.y; k[7] = b.z; k[8] = b.w;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) h[j] = base + j >= n ? Lq + 2 : base + j == 0 ? 0 : first_depth<D>(k[j], k[j + 1], Lq);
+}
+
+// counts[l][block]: heads of depth l in the block; *depth: the first depth whose boxes all hold at most zeta points (a box
+// of depth l holds more iff some point and the one zeta places further on agree in the bits of depth l)
+template <int D>
+__global__ __launch_bounds__(256) void levels_count_kernel(const uint32_t *__restrict__ keys, int64_t n, int Lq, int zeta,
+                                                           int nlevels, int64_t nblk, uint32_t *__restrict__ counts,
+                                                           uint32_t *__restrict__ depth) {
+    __shared__ uint32_t wsum[4][BULK_LEVELS];
+    __shared__ uint32_t wdeep[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t base = (int64_t)blockIdx.x * BULK_TILE + (int64_t)tid * 8;
+    uint32_t k[9];
+    int h[8];
+    head_depths<D>(keys, base, n, Lq, k, h);
+    uint32_t deep = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (base + j + zeta < n) deep = max(deep, (uint32_t)first_depth<D>(k[j + 1], keys[base + j + zeta], Lq));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) deep = max(deep, (uint32_t)__shfl_xor((int)deep, off, 64));
+    for (int l = 0; l < nlevels; ++l) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c += (uint32_t)__popcll(__ballot(h[j] <= l));
+        if (lane == 0) wsum[w][l] = c;
+    }
+    if (lane == 0) wdeep[w] = deep;
+    __syncthreads();
+    if (tid < nlevels) counts[(int64_t)tid * nblk + blockIdx.x] = wsum[0][tid] + wsum[1][tid] + wsum[2][tid] + wsum[3][tid];
+    if (tid == 64) {
+        const uint32_t d = max(max(wdeep[0], wdeep[1]), max(wdeep[2], wdeep[3]));
+        if (d) atomicMax(depth, d);
+    }
+}
+
+// counts of a depth -> positions of its blocks (a workgroup per depth); totals and the depth to words of the host
+__global__ __launch_bounds__(1024) void levels_scan_kernel(uint32_t *__restrict__ counts, int64_t nblk,
+                                                           const uint32_t *__restrict__ depth, uint64_t *__restrict__ words) {
+    __shared__ uint32_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l = blockIdx.x;
+    uint32_t *c = counts + (int64_t)l * nblk;
+    uint32_t carry = 0;
+    for (int64_t r = 0; r < nblk; r += 1024) {
+        const uint32_t v = r + tid < nblk ? c[r + tid] : 0u;
+        const uint32_t incl = wave_incl_scan_u32(v);
+        __syncthreads();   // the last round has read wsum
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            before += q < w ? wsum[q] : 0u;
+            carry += wsum[q];
+        }
+        if (r + tid < nblk) c[r + tid] = before + incl - v;
+    }
+    if (tid == 0) {
+        words[l] = carry;
+        if (l == 0) words[BULK_LEVELS] = *depth;
+    }
+}
+
+struct LevelTables {
+    uint32_t *start[BULK_LEVELS], *key[BULK_LEVELS], *parent[BULK_LEVELS], *cstart[BULK_LEVELS];
+    int32_t *cell[BULK_LEVELS];
+    uint32_t nb[BULK_LEVELS];
+};
+// depths 1 .. L (the root is written by root_kernel)
+template <int D>
+__global__ __launch_bounds__(256) void levels_apply_kernel(const uint32_t *__restrict__ keys, int64_t n, int Lq, int L,
+                                                           int64_t nblk, const uint32_t *__restrict__ counts, LevelTables T) {
+    __shared__ uint32_t wsum[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t base = (int64_t)blockIdx.x * BULK_TILE + (int64_t)tid * 8;
+    uint32_t k[9];
+    int h[8];
+    head_depths<D>(keys, base, n, Lq, k, h);
+    uint32_t up[8];   // rank of the box of every point, one depth up
+#pragma unroll
+    for (int j = 0; j < 8; ++j) up[j] = 0u;
+    for (int l = 1; l <= L; ++l) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c += h[j] <= l ? 1u : 0u;
+        const uint32_t incl = wave_incl_scan_u32(c);
+        if (lane == 63) wsum[l & 1][w] = incl;
+        __syncthreads();   // (two arrays in turn: one barrier per depth)
+        uint32_t r = counts[(int64_t)l * nblk + blockIdx.x] + incl - c;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) r += q < w ? wsum[l & 1][q] : 0u;
+        const int shift = D * (Lq - l);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (h[j] <= l) {
+                const uint32_t key = (uint32_t)((uint64_t)k[j + 1] >> shift);
+                T.start[l][r] = (uint32_t)(base + j);
+                T.key[l][r] = key;
+                T.parent[l][r] = up[j];
+                if (h[j] < l) T.cstart[l - 1][up[j]] = r;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    int32_t cc = 0;
+                    for (int b = 0; b < l; ++b) cc |= (int32_t)((key >> (b * D + d)) & 1u) << b;
+                    T.cell[l][(int64_t)r * D + d] = cc;
+                }
+                ++r;
+            }
+            up[j] = r - 1u;   // (wraps for the points before the first head of the block's first box only if none precedes:
+                              // point 0 is a head of every depth)
+            if (base + j == n - 1) {
+                T.start[l][T.nb[l]] = (uint32_t)n;
+                T.cstart[l - 1][T.nb[l - 1]] = T.nb[l];
+            }
+        }
+    }
+}
+
+// largest box of every depth 1 .. L: gridDim.y depths, a maximum per block; then to words of the host
+__global__ __launch_bounds__(256) void levels_max_kernel(LevelTables T, uint32_t *__restrict__ largest) {
+    const int l = 1 + (int)blockIdx.y;
+    uint32_t m = 0;
+    for (uint32_t a = blockIdx.x * 256u + threadIdx.x; a < T.nb[l]; a += gridDim.x * 256u) m = max(m, T.start[l][a + 1] - T.start[l][a]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+    if ((threadIdx.x & 63) == 0 && m) atomicMax(&largest[l], m);
+}
+__global__ __launch_bounds__(64) void levels_max_words_kernel(const uint32_t *__restrict__ largest, int L, uint64_t *__restrict__ words) {
+    if ((int)threadIdx.x <= L) words[threadIdx.x] = largest[threadIdx.x];
+}
+
+// words of the host that the tables of set k report in: boxes of every depth and the last depth, later the largest boxes
+inline uint64_t *bulk_words(size_t k) { return scope_words() + 64 + 64 * k; }
+
+// depths of the tree (first step, ends with a wait) and its tables (second step) for all sets; returns the depth where the
+// largest box of one of the sets is at most zeta, or cap
+template <int D>
+static int bulk_divide(f3m_plan_s &P, const std::vector<SetRef> &sets, int cap, hipStream_t st) {
+    int64_t *tally = &P.bytes;
+    DevBuf<uint32_t> counts[2], depth;
+    depth.alloc(2 + 2 * BULK_LEVELS);   // per set: the depth; the largest boxes
+    fill_words(depth.p, 2 + 2 * BULK_LEVELS, nullptr, 0, 0u, st);
+    for (size_t k = 0; k < sets.size(); ++k) {
+        const int64_t n = sets[k].n, nblk = cdiv(n, BULK_TILE);
+        counts[k].alloc((size_t)(cap + 1) * (size_t)nblk);
+        levels_count_kernel<D><<<dim3((unsigned)nblk), dim3(256), 0, st>>>(sets[k].keys->p, n, P.Lq, P.leaf_max, cap + 1, nblk,
+                                                                          counts[k].p, depth.p + k);
+        levels_scan_kernel<<<dim3((unsigned)cap + 1), dim3(1024), 0, st>>>(counts[k].p, nblk, depth.p + k, bulk_words(k));
+    }
+    F3M_HIP(hipGetLastError());
+    F3M_HIP(hipStreamSynchronize(st));
+    int L = cap;
+    for (size_t k = 0; k < sets.size(); ++k) L = std::min(L, (int)bulk_words(k)[BULK_LEVELS]);
+    // the loop over the depths ends at the smooth depth at the latest (Sec. 4.3)
+    for (int l = 1; l < L; ++l)
+        if (!P.force_all_near && smooth_rule((double)P.E, l, D, (double)P.gamma, (double)P.eta_smooth)) L = l;
+    for (size_t k = 0; k < sets.size(); ++k) {
+        const SetRef &S = sets[k];
+        const int64_t nblk = cdiv(S.n, BULK_TILE);
+        LevelTables T{};
+        for (int l = 0; l <= L; ++l) {
+            f3m_level &lv = S.lev[l];
+            lv.nb = l ? (int64_t)bulk_words(k)[l] : 1;
+            lv.max_box = S.n;   // (of the root; the others: bulk_finish)
+            lv.key.alloc((size_t)lv.nb, tally);
+            lv.start.alloc((size_t)lv.nb + 1, tally);
+            lv.parent.alloc((size_t)lv.nb, tally);
+            lv.cell.alloc((size_t)lv.nb * D, tally);
+            if (l < L) lv.cstart.alloc((size_t)lv.nb + 1, tally);
+            T.start[l] = lv.start.p;
+            T.key[l] = lv.key.p;
+            T.parent[l] = lv.parent.p;
+            T.cstart[l] = lv.cstart.p;
+            T.cell[l] = lv.cell.p;
+            T.nb[l] = (uint32_t)lv.nb;
+        }
+        root_kernel<<<1, 1, 0, st>>>((uint32_t)S.n, D, T.key[0], T.start[0], T.parent[0], T.cell[0]);
+        if (L >= 1) {
+            uint32_t *largest = depth.p + 2 + k * BULK_LEVELS;
+            levels_apply_kernel<D><<<dim3((unsigned)nblk), dim3(256), 0, st>>>(S.keys->p, S.n, P.Lq, L, nblk, counts[k].p, T);
+            const unsigned gx = (unsigned)std::min<int64_t>(64, cdiv(S.lev[L].nb, 256));
+            levels_max_kernel<<<dim3(gx, (unsigned)L), dim3(256), 0, st>>>(T, largest);
+            levels_max_words_kernel<<<dim3(1), dim3(64), 0, st>>>(largest, L, bulk_words(k));
+        }
+        F3M_HIP(hipGetLastError());
+    }
+    return L;
+}
+
+// after a wait for the stream
+static void bulk_finish(const std::vector<SetRef> &sets, int L) {
+    for (size_t k = 0; k < sets.size(); ++k)
+        for (int l = 1; l <= L; ++l) sets[k].lev[l].max_box = (int64_t)bulk_words(k)[l];
+}
+
 // Weighted near pairs end at the first depth that allows it where the last one has this many boxes at least.
 constexpr int64_t WEIGHTED_MIN_BOXES = 8192;
 
@@ -1287,9 +1525,12 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     P.plan_events.resize(2 * (size_t)(cap + 1), nullptr);
     uint64_t *words = scope_words();
     int l = 0, weighted = 0;
+    bool bulk = cap > 0;
+    for (const SetRef &S : sets) bulk = bulk && S.n <= BULK_MAX;
+    const int bulk_depth = bulk ? bulk_divide<D>(P, sets, cap, st) : 0;
     for (;; ++l) {
         f3m_level &lv = P.lev[l];
-        for (size_t k = 0; k < sets.size(); ++k) divide_set<D>(P, sets[k], l, part, words + HW_SET + 2 * k, st);
+        for (size_t k = 0; k < sets.size() && !bulk; ++k) divide_set<D>(P, sets[k], l, part, words + HW_SET + 2 * k, st);
         const f3m_level &sv = P.slev(l);
         for (int k = 0; k < 2; ++k) P.plan_events[2 * (size_t)l + k] = event_get();
         F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l], st));
@@ -1319,15 +1560,23 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             A.cnt_small = cs.p;
             launch_lists<D>(0, P, l, A, lists_by_parent(A, D), st);
             words[HW_SMALL] = 0;
-            exclusive_scan(U32In{cn.p}, lv.nb, PtrOut{lv.near_ptr.p, lv.nb}, words + HW_NEAR, st);
-            exclusive_scan(U32In{cf.p}, lv.nb, PtrOut{lv.far_ptr.p, lv.nb}, words + HW_FAR, st);
+            // up to three dimensions with a far ratio of at most 2 a box has at most 216 candidates: both scans in one
+            const bool both = D <= 3 && P.T <= 4 && P.rho == 0 && !P.src && !P.force_all_near && lv.nb < ((int64_t)1 << 24);
+            if (both) {
+                exclusive_scan(PairIn{cn.p, cf.p}, lv.nb, PairOut{lv.near_ptr.p, lv.far_ptr.p, lv.nb}, words + HW_NEAR, st);
+            } else {
+                exclusive_scan(U32In{cn.p}, lv.nb, PtrOut{lv.near_ptr.p, lv.nb}, words + HW_NEAR, st);
+                exclusive_scan(U32In{cf.p}, lv.nb, PtrOut{lv.far_ptr.p, lv.nb}, words + HW_FAR, st);
+            }
             if (P.rho > 0) {
                 lv.small_ptr.alloc((size_t)lv.nb + 1, tally);
                 exclusive_scan(U32In{cs.p}, lv.nb, PtrOut{lv.small_ptr.p, lv.nb}, words + HW_SMALL, st);
             }
             F3M_HIP(hipStreamSynchronize(st));
-            for (size_t k = 0; k < sets.size(); ++k) divide_finish(sets[k], l, words + HW_SET + 2 * k);
-            const uint64_t tn = words[HW_NEAR], tf = words[HW_FAR], ts = words[HW_SMALL];
+            if (bulk && l == 1) bulk_finish(sets, bulk_depth);
+            for (size_t k = 0; k < sets.size() && !bulk; ++k) divide_finish(sets[k], l, words + HW_SET + 2 * k);
+            const uint64_t tn = both ? words[HW_NEAR] & 0xFFFFFFFFull : words[HW_NEAR];
+            const uint64_t tf = both ? words[HW_NEAR] >> 32 : words[HW_FAR], ts = words[HW_SMALL];
             if (P.rho > 0) lv.small_col.alloc((size_t)ts, tally);
             lv.near_sz = (int64_t)tn;
             lv.far_sz = (int64_t)tf;
@@ -1373,6 +1622,17 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         F3M_HIP(hipEventRecord(P.plan_events[2 * (size_t)l + 1], st));
         // while interactions remain and the largest box of either tree is above zeta (Algorithm 1)
         if (!(lv.near_sz > 0 && lv.max_box > P.leaf_max && sv.max_box > P.leaf_max && l < cap)) break;
+        if (bulk && l >= bulk_depth) fail(F3M_ERR_HIP, "internal: the tables end above the last depth");
+    }
+    // (small fields may have left no interactions above the last depth that has tables; they are not part of the plan)
+    for (const SetRef &S : sets) {
+        for (int k = l + 1; k <= bulk_depth; ++k) {
+            f3m_level &lv = S.lev[k];
+            for (DevBuf<uint32_t> *t : {&lv.key, &lv.start, &lv.parent, &lv.cstart}) t->release();
+            lv.cell.release();
+            lv.nb = lv.max_box = 0;
+        }
+        if (bulk_depth > l) S.lev[l].cstart.release();
     }
     P.L = l;
     // The tree is too coarse for the plain interpolation of near pairs, but not for that between weighted points: near pairs
