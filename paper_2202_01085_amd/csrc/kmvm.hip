@@ -1770,11 +1770,11 @@ __device__ inline float weights34(const float *__restrict__ x, const double (&ct
 }
 
 // The weighted near pairs (near_weighted_error in plan.hip) need a second set of node weights, of points times
-// exp(-|u|^2 / 2 gamma^2) = exp2(kw |u|^2 / (l/2)^2): the upper half of the workgroups of a P2M launch makes it.  blocks: workgroups
-// of a half, 0 for the plain node weights only; dW, dpart: from the plain to the weighted arrays.
+// exp(-|u|^2 / 2 gamma^2) = exp2(kw |u|^2 / (l/2)^2): the workgroups of a P2M launch from `blocks` on make it (none, the upper
+// half, or all of them); dW, dpart: from the plain to the weighted arrays.
 struct WeightedArg {
-    int64_t blocks, dW, dpart;
-    float kw;
+    int64_t blocks = INT64_MAX, dW = 0, dpart = 0;
+    float kw = 0.f;
 };
 
 constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
@@ -1791,7 +1791,7 @@ __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs,
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ float tr[64 * TR_STRIDE];
     const int64_t bi = block_index();
-    const bool weighted = A.blocks > 0 && bi >= A.blocks;
+    const bool weighted = bi >= A.blocks;
     const int64_t c0 = (weighted ? bi - A.blocks : bi) * P2M_NCH;
     if (c0 >= nchunks) return;
     if (weighted) {
@@ -1906,7 +1906,7 @@ __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict_
     // rows of the upper half are shifted by 32 floats so that the two halves read different banks
     __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE + 32];
     const int64_t bi = block_index();
-    const bool weighted = A.blocks > 0 && bi >= A.blocks;
+    const bool weighted = bi >= A.blocks;
     const int64_t b0 = (weighted ? bi - A.blocks : bi) * (2 * P2M_NPAIR);
     if (b0 >= nb) return;
     if (weighted) W += A.dW;
@@ -2824,7 +2824,7 @@ void upload_tables(f3m_plan_s &P, hipStream_t st) {
         const TransferArg T = make_transfer();
         std::copy(&T.t[0][0][0], &T.t[0][0][0] + 32, table(&P.transfer.p, 32));
     }
-    if (P.near_weighted) near_table(P, table(&P.near_tab.p, 16));
+    if (P.near_weighted && !P.src) near_table(P, table(&P.near_tab.p, 16));
     for (int l = 1; l <= P.L; ++l) {
         f3m_level &lv = P.lev[l];
         if (lv.far_sz == 0 || lv.p == 0 || l > P.last_depth()) continue;
@@ -2860,6 +2860,16 @@ void upload_tables(f3m_plan_s &P, hipStream_t st) {
                         const double t = 2.0 * ((double)(S.omin[d] + k) + u[d]) + s[j] - s[i];
                         G[(((size_t)d * S.no + k) * p + i) * p + j] = (float)std::exp(-c * t * t);
                     }
+        if (P.src && l == P.near_weighted) {   // the factor F of near_weighted_error, for the same offsets
+            float *Gn = table(&P.near_tab.p, (size_t)ndim * S.no * p * p);
+            for (int d = 0; d < ndim; ++d)
+                for (int k = 0; k < S.no; ++k)
+                    for (int i = 0; i < p; ++i)
+                        for (int j = 0; j < p; ++j) {
+                            const double o = (double)(S.omin[d] + k) + u[d];
+                            Gn[(((size_t)d * S.no + k) * p + i) * p + j] = (float)std::exp(2.0 * c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o)));
+                        }
+        }
     }
     if (g.empty()) return;
     P.tables.alloc(g.size(), &P.bytes);
@@ -3115,7 +3125,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         F3M_HIP(hipGetLastError());
     };
     // M2L of a depth from its far list, factor by factor; rows of V whose far row is empty are left alone
-    auto kron_m2l = [&](int l, const float *W, float *V) {
+    auto kron_m2l = [&](int l, const float *W, float *V, bool near_rows = false) {
         f3m_level &lv = P.lev[l];
         f3m_level &sv = P.slev(l);
         const int p = lv.p, r = lv.r;
@@ -3124,8 +3134,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         if (nfib <= 32) {   // several far pairs per wavefront
             const size_t sh = (size_t)((64 / nfib) * r + D * KS.no * p * p) * sizeof(float);
             auto launch = [&](auto kern) {
-                kern<<<grid_for(lv.nb), dim3(64), sh, st>>>(lv.cell.p, sv.cell.p, lv.far_ptr.p, lv.far_col.p, lv.nb, D, r,
-                                                            lv.gtab.p, KS, W, V);
+                kern<<<grid_for(lv.nb), dim3(64), sh, st>>>(
+                    lv.cell.p, sv.cell.p, near_rows ? lv.near_ptr.p : lv.far_ptr.p, near_rows ? lv.near_col.p : lv.far_col.p, lv.nb,
+                    D, r, near_rows ? P.near_tab.p : lv.gtab.p, KS, W, V);
             };
             switch (p) {
                 case 2: launch(m2l_kron_small_kernel<2>); break;
@@ -3225,7 +3236,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 ev[0] = now;
                 const bool pairs = single_chunks(lf);
                 const int64_t blocks = pairs ? cdiv(lf.nb, 2 * P2M_NPAIR) : cdiv(lf.nchunks, P2M_NCH);
-                const WeightedArg A{weighted ? blocks : 0, (lf.nb + 1) * r, lf.nchunks * r, kw};
+                const WeightedArg A{weighted ? blocks : INT64_MAX, (lf.nb + 1) * r, lf.nchunks * r, kw};
                 const dim3 grid = grid_for(weighted ? 2 * blocks : blocks);
                 auto p2m_long = [&](auto kern) {
                     kern<<<grid_for(lf.nchunks), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
@@ -3249,7 +3260,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 F3M_HIP(hipGetLastError());
                 ev[1] = now = mark();
             }
-            if (weighted) {   // the near field of this product
+            if (weighted) {   // the near field of this product (two sets: below)
                 P.t_p2p0 = now;
                 run_near_weighted(P, lf.Wl.p + (lf.nb + 1) * r, lf.Vl.p + lf.nb * r, st);
                 P.t_p2p1 = now = mark();
@@ -3281,6 +3292,24 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 kron_m2l(l, P.src ? P.W.p : lv.Wl.p, lv.Vl.p);
             }
             ev[3] = now = mark();
+        }
+        if (weighted && P.src) {   // the near field of this product
+            P.t_p2p0 = now;
+            f3m_level &ns = P.near_src;
+            if (ns.nchunks > 0) {
+                WeightedArg A;
+                A.blocks = 0;
+                A.kw = kw;
+                p2m34_kernel<<<grid_for(cdiv(ns.nchunks, P2M_NCH)), dim3(64), 0, st>>>(
+                    Ys, bs, P.slev(L).start.p, P.slev(L).cell.p, ns.chunk_box.p, ns.chunk_first.p, ns.nchunks,
+                    make_centre(P, L, true), ns.Wl.p, P.Wpart.p, 0, A);
+                F3M_HIP(hipGetLastError());
+                if (ns.max_box > ns.chunk) reduce_partials(P, ns, r, ns.Wl.p, st);
+            }
+            float *Vn = lf.Vl.p + lf.nb * r;
+            zero_kernel<<<dim3((unsigned)cdiv(lf.nb * (int64_t)r, 256)), dim3(256), 0, st>>>(Vn, lf.nb * (int64_t)r);
+            kron_m2l(L, ns.Wl.p, Vn, true);
+            P.t_p2p1 = now = mark();
         }
         for (int l = P.tree_lmin + 1; l <= L; ++l) {
             f3m_level &lv = P.lev[l], &up = P.lev[l - 1];

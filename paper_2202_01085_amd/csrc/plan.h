@@ -154,7 +154,10 @@ struct f3m_plan_s {
                                         // weighted points, to within fp32 rounding (near_weighted_error)
     bool exact_near() const { return near_depth == 0 && near_weighted == 0; }
     int last_depth() const { return near_depth ? near_depth : near_weighted ? near_weighted : L; }   // of the products
-    struct { float *p = nullptr; } near_tab;   // [16] factors of the weighted near pairs (near_factor_index)
+    struct { float *p = nullptr; } near_tab;   // factors of the weighted near pairs: 16 (near_factor_index), or for two sets
+                                               // [D][offsets][p][p] like gtab
+    f3m_level near_src;                        // two sets: the sources' boxes of depth near_weighted that occur in a near row
+                                               // (nb, chunk and slice lists), and their weighted node weights (Wl)
     int tree_lmin = 0, tree_lmax = 0;   // tree_lmin > 0: node weights/potentials are passed between depths
                                         // tree_lmin..tree_lmax (D = 3, 4 nodes/dim); other depths work
                                         // straight from the points
@@ -197,7 +200,7 @@ bool smooth_rule(double E, int depth, int D, double gamma, double eta_smooth);  
 int adaptive_nodes(double E, int depth, double gamma, int p);                   // Sec. 4.3 node rule (0: dropped)
 
 double near_interp_error(double E, int depth, double gamma);                    // D = 3, 4 nodes per dimension
-double near_weighted_error(double E, int depth, double gamma);
+double near_weighted_error(double E, int depth, double gamma, double reach = 1.0);
 
 // plan.hip
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)

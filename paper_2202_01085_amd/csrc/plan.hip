@@ -1604,6 +1604,11 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             } else {
                 lv.far_col.alloc((size_t)tf, tally);
             }
+            // two sets: near pairs between weighted points from the first depth on that allows it, as for one set
+            if (P.src && weighted == 0 && D == 3 && l >= 2 && tf > 0 && lv.p == 4 && P.rho == 0 && !P.force_all_near &&
+                !P.adaptive_far && !(P.eta_smooth > 0.f) && P.theta <= 4.f &&
+                near_weighted_error((double)P.E, l, (double)P.gamma, (double)P.theta) <= 0x1p-24)
+                weighted = l;
             A.near_ptr = lv.near_ptr.p;
             A.far_ptr = lv.far_ptr.p;
             A.small_ptr = lv.small_ptr.p;
@@ -1646,7 +1651,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     const bool group = may_group && weighted > 0 && P.lev[weighted].nb <= ROUTE_GROUP_BOXES;
     if (group && P.near_depth > 0 && P.lev[P.near_depth].nb > ROUTE_GROUP_BOXES) P.near_depth = 0;
     if (P.near_depth == 0 && weighted > 0)
-        P.near_weighted = group ? weighted : P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
+        P.near_weighted = group || P.src ? weighted : P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
     for (int k = P.last_depth() + 1; k <= P.L; ++k) {   // not needed: the products end above
         P.lev[k].st_cand.release();
         P.lev[k].st_child.release();
@@ -1703,7 +1708,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         }
         // Large boxes: long runs.  From 2048 points a box on: below, most runs would be short ones, and a wavefront per run
         // leaves the chip idle (n = 1e9, 32768 boxes: P2M 5.39 -> 3.66 ms, L2P 5.43 -> 3.63).
-        if (D == 3 && lv.p == 4 && !P.src && n / lv.nb >= P2M_LONG) lv.chunk = P2M_LONG;
+        if (D == 3 && lv.p == 4 && n / lv.nb >= P2M_LONG) lv.chunk = P2M_LONG;
+        if (D == 3 && lv.p == 4 && P.src && P.ns() / sv.nb >= P2M_LONG) sv.chunk = P2M_LONG;
         // runs of points for the L2P (targets: in the band only its last depth) and the P2M (sources: the
         // same runs for one point set)
         if (!tree || k == P.tree_lmax)
@@ -1717,7 +1723,21 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
             mark_cols_kernel<<<dim3((unsigned)std::min<int64_t>(cdiv(lv.far_sz, 256), 1 << 20)), dim3(256), 0, st>>>(
                 lv.far_col.p, lv.far_sz, used.p);
             F3M_HIP(hipGetLastError());
-            items.chunks(sv.start.p, sv.nb, P2M_CHUNK, sv.chunk_first, sv.chunk_box, sv.nchunks, nullptr, used.p);
+            items.chunks(sv.start.p, sv.nb, (uint32_t)sv.chunk, sv.chunk_first, sv.chunk_box, sv.nchunks, nullptr, used.p);
+            if (k == P.near_weighted) {   // the same for the near rows
+                f3m_level &ns = P.near_src;
+                ns.nb = sv.nb;
+                ns.max_box = sv.max_box;
+                used.alloc((size_t)sv.nb);
+                fill_words(used.p, sv.nb, nullptr, 0, 0u, st);
+                mark_cols_kernel<<<dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(lv.near_sz, 256), 1 << 20))), dim3(256), 0, st>>>(
+                    lv.near_col.p, lv.near_sz, used.p);
+                F3M_HIP(hipGetLastError());
+                items.chunks(sv.start.p, sv.nb, P2M_CHUNK, ns.chunk_first, ns.chunk_box, ns.nchunks, nullptr, used.p);
+                if (ns.max_box > (int64_t)ns.chunk * P2M_SLICE * 2)
+                    items.chunks(ns.chunk_first.p, ns.nb, P2M_SLICE, ns.slice_first, ns.slice_box, ns.nslices);
+                ns.Wl.alloc((size_t)ns.nb * lv.r, tally);
+            }
         }
         if (sv.max_box > (int64_t)sv.chunk * P2M_SLICE * 2) {
             // a box with more than a thousand chunks: its partial node weights are summed in two stages
@@ -1746,6 +1766,10 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         const f3m_level &sv = P.slev(k);
         max_part = std::max(max_part, (k == P.near_weighted ? 2 : 1) * sv.nchunks * (int64_t)P.lev[k].r);
         max_slice = std::max(max_slice, sv.nslices * (int64_t)P.lev[k].r);
+    }
+    if (P.near_weighted && P.src) {
+        max_part = std::max(max_part, P.near_src.nchunks * (int64_t)P.lev[P.near_weighted].r);
+        max_slice = std::max(max_slice, P.near_src.nslices * (int64_t)P.lev[P.near_weighted].r);
     }
     if (P.exact_near()) {
         const f3m_level &lf = P.lev[P.L];
@@ -1878,12 +1902,13 @@ double near_interp_error(double E, int depth, double gamma) {
 //   F(u, w) = exp((u w + u D - w D - D^2 / 2) / gamma^2) per dimension,
 // only F is interpolated: its fourth derivative is ((u - D) / gamma^2)^4 F, at most (1.5 l / gamma^2)^4 F for adjacent boxes
 // (|u| <= l / 2, |D| <= l), times (l / 2)^4, a quarter (the node polynomial) over 4!: (0.75 l^2 / gamma^2)^4 / 96 for one
-// interpolation.  e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and
+// interpolation.  (reach: the largest |D| / l of a near pair, 1 for one point set.  The grids of two sets are shifted against
+// each other, and |D| goes up to the far ratio: 1.25 instead of 0.75 with ratio 2, 2^-24 at l = 0.128 gamma.)  e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and
 // the node values of F go without e: three dimensions of either point, at most exp(6 l^2 / 8 gamma^2)), and the six
 // interpolations make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.
-double near_weighted_error(double E, int depth, double gamma) {
+double near_weighted_error(double E, int depth, double gamma, double reach) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (gamma * gamma), L = 5.0 / 3.0;
-    const double one = 0.75 * q, e1 = one * one * one * one / 96.0;
+    const double one = 0.5 * (reach + 0.5) * q, e1 = one * one * one * one / 96.0;
     return e1 * std::exp(0.75 * q) * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
 }
 
