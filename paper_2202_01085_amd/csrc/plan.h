@@ -61,6 +61,8 @@ struct f3m_level {
 // digit and where the tile's run of each digit lies in the next order.
 struct f3m_route {
     int64_t n = 0, ntiles = 0;
+    int ipt = 32;           // values of a tile and of a window: 1024 ipt (two: 8, 20 or 28)
+    bool two = false;       // two passes: tiles dealt to the windows directly (512 digits a tile)
     bool grouped = false;   // one pass: the points grouped by the boxes of one depth, in each of them in the caller's order
                             // (slot1, dstart1 and gofs1 of 512 digits a tile; tiles of the caller's order)
     int s2 = 0, B1 = 1, B2 = 1;
@@ -206,7 +208,8 @@ double near_weighted_error(double E, int depth, double gamma, double reach = 1.0
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
 void compute_far_point_pairs(f3m_plan_s &P);   // near_point_pairs and lev[].far_point_pairs, once (synchronises)
 // route.hip: permutations of large vectors as three streaming passes with tables built once per plan
-void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, hipStream_t st);
+bool route_two_passes(int64_t n);   // sizes below those of the three passes for which two pay
+void route_build(f3m_route &R, const uint32_t *perm, int64_t n, bool two, int64_t *tally, hipStream_t st);
 constexpr int ROUTE_GROUP_BOXES = 512;
 void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift, const uint32_t *box_keys, int64_t nb,
                        int64_t *tally, hipStream_t st);

@@ -1255,7 +1255,7 @@ __global__ __launch_bounds__(256) void levels_count_kernel(const uint32_t *__res
     if (tid < nlevels) counts[(int64_t)tid * nblk + blockIdx.x] = wsum[0][tid] + wsum[1][tid] + wsum[2][tid] + wsum[3][tid];
     if (tid == 64) {
         const uint32_t d = max(max(wdeep[0], wdeep[1]), max(wdeep[2], wdeep[3]));
-        if (d) atomicMax(depth, d);
+        if (d > *(volatile uint32_t *)depth) atomicMax(depth, d);   // (thousands of blocks, few of which raise it)
     }
 }
 
@@ -1499,9 +1499,9 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         if (may_group && P.lev[last].nb <= ROUTE_GROUP_BOXES && (P.lev[P.L].near_sz == 0 || !P.exact_near())) {
             route.reset(new f3m_route());
             route_group_build(*route, keys_in.p, S.n, D * (P.Lq - last), P.lev[last].key.p, P.lev[last].nb, tally, st);
-        } else if (S.n >= P.route_min_n && bits_sorted > 0) {
+        } else if ((S.n >= P.route_min_n || route_two_passes(S.n)) && bits_sorted > 0) {
             route.reset(new f3m_route());
-            route_build(*route, S.perm->p, S.n, tally, st);
+            route_build(*route, S.perm->p, S.n, S.n < P.route_min_n, tally, st);
         }
         if (route && D == 3) {
             DevBuf<float> tmp;

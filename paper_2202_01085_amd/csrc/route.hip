@@ -16,6 +16,8 @@
 // perm only: they are computed once per plan by route_build, so a pass moves data and does nothing else.
 // The gather direction (caller's order -> box order) runs the same three passes backwards with the same tables.
 //
+// Up to 512 windows (smaller tiles and windows, 2^21 to 2^24 points) pass 1 deals to the windows directly: two passes.
+//
 // Where the products need the points by the boxes of a coarse depth only (at most 512 of them), ONE pass does: a tile of T
 // consecutive caller indices is dealt to the boxes, in which the points keep the caller's order (route_group_build).
 // n = 1e9, 512 boxes: tables 5.8 -> 3.1 ms (with the counts), points 18.7 -> 7.0, right-hand side in 6.2 -> 2.4, result out 6.6 -> 2.2.
@@ -24,10 +26,13 @@
 namespace f3m {
 
 constexpr int RT_BITS = 15;
-constexpr int RT_TILE = 1 << RT_BITS;    // values per tile and per window
+constexpr int RT_TILE = 1 << RT_BITS;    // values per tile and per window of the three passes and of the grouping
 constexpr int RT_NT = 1024;              // threads of a workgroup: one tile
 constexpr int RT_IPT = RT_TILE / RT_NT;  // 32 values per thread
 constexpr int RT_NW = RT_NT / 64;        // 16 wavefronts
+// The kernels take the values per thread as a template parameter IPT: 32, or for two passes 20 (two workgroups of 80 KB share a
+// compute unit, and 10 million points are one round of them), 8 or 28.
+constexpr int RT_NB2 = 512;              // digits of two passes and of the grouping
 
 struct RouteCountIn {
     const uint32_t *p;
@@ -51,8 +56,10 @@ struct RouteLevel {
 // contiguous range of tiles, so that the runs which neighbouring tiles write to (or read from) the same bucket
 // meet in one L2 as whole lines.  The grid holds a whole number of rounds over the dies (route_grid); a
 // workgroup beyond the last tile returns at once.
+template <int IPT>
 __device__ inline int64_t route_tile(int64_t n) {
-    const int64_t ntiles = (n + RT_TILE - 1) / RT_TILE, per_die = (ntiles + 7) >> 3;
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t ntiles = (n + TILE - 1) / TILE, per_die = (ntiles + 7) >> 3;
     const int64_t t = (int64_t)(blockIdx.x & 7u) * per_die + (int64_t)(blockIdx.x >> 3);
     return t < ntiles ? t : -1;
 }
@@ -74,23 +81,28 @@ __global__ __launch_bounds__(256) void route_cursor_init_kernel(uint32_t *__rest
 // digits ascending, inside a digit in tile order), the destinations moved along to the next order, and the
 // tile's tables (first place of each digit; global position of the tile's first value of each digit, minus
 // that place).  Tile order = (wavefront, round, lane); ranking against per-wave LDS counters.
+template <int IPT, int NB, bool TWO>   // TWO: digit = window of the destination
 __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__restrict__ dest_in, int64_t n, RouteLevel R,
                                                            uint32_t *__restrict__ cursor,
                                                            uint16_t *__restrict__ slot, uint32_t *__restrict__ dest_out,
                                                            uint16_t *__restrict__ off_out,
                                                            uint32_t *__restrict__ dstart_out,
                                                            uint32_t *__restrict__ gofs_out) {
-    const int64_t tb = route_tile(n);
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t tb = route_tile<IPT>(n);
     if (tb < 0) return;
-    __shared__ uint32_t wcnt[RT_NW][256];   // per wave: values of each digit seen so far; later the wave's offset
-    __shared__ uint32_t dstart[257];        // first place of each digit
-    __shared__ uint32_t gbase[256];         // global position of the tile's first value of each digit
-    __shared__ __attribute__((aligned(8))) uint32_t skey[RT_TILE];
+    constexpr int SKEY = TILE > 2 * RT_NW * NB ? TILE : 2 * RT_NW * NB;
+    __shared__ uint32_t wcnt[RT_NW][NB];   // per wave: values of each digit seen so far; later the wave's offset
+    __shared__ uint32_t dstart[NB + 1];        // first place of each digit
+    __shared__ uint32_t gbase[NB];         // global position of the tile's first value of each digit
+    __shared__ __attribute__((aligned(8))) uint32_t skey[SKEY];
     // per wave, while the values are ranked (skey is not in use yet): the lanes that hold each digit in the current round
-    uint64_t (*wmask)[256] = reinterpret_cast<uint64_t (*)[256]>(skey);
-    static_assert(sizeof(uint64_t) * RT_NW * 256 <= sizeof(uint32_t) * RT_TILE, "the lane masks must fit the tile buffer");
+    uint64_t (*wmask)[NB] = reinterpret_cast<uint64_t (*)[NB]>(skey);
+    auto digit_of = [&](uint32_t dest) __attribute__((always_inline)) -> uint32_t {
+        return TWO ? dest / (uint32_t)TILE : (dest >> R.shift) & R.mask;
+    };
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid < 256) {
+    if (tid < NB) {
 #pragma unroll
         for (int k = 0; k < RT_NW; ++k) {
             wcnt[k][tid] = 0;
@@ -99,24 +111,25 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
     }
     __syncthreads();
     const uint64_t mybit = 1ull << lane;
-    const int64_t tile0 = tb * RT_TILE;
-    const int64_t base = tile0 + (int64_t)w * (RT_IPT * 64);
-    uint32_t rk[RT_IPT / 2];   // rank within (wave, digit), below 2048: two per register
+    const int64_t tile0 = tb * TILE;
+    const int64_t base = tile0 + (int64_t)w * (IPT * 64);
+    constexpr int CH = IPT % 8 == 0 ? 8 : 4;
+    uint32_t rk[IPT / 2];   // rank within (wave, digit), below 2048: two per register
 #pragma unroll
-    for (int r = 0; r < RT_IPT / 2; ++r) rk[r] = 0u;
+    for (int r = 0; r < IPT / 2; ++r) rk[r] = 0u;
 #pragma unroll
-    for (int h = 0; h < RT_IPT; h += 8) {   // eight rounds at a time: their loads are in flight together
-        uint32_t key[8];
+    for (int h = 0; h < IPT; h += CH) {   // CH rounds at a time: their loads are in flight together
+        uint32_t key[CH];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < CH; ++r) {
             const int64_t i = base + (h + r) * 64 + lane;
             key[r] = i < n ? dest_in[i] : 0u;
         }
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < CH; ++r) {
             const int64_t i = base + (h + r) * 64 + lane;
             const bool valid = i < n;
-            const uint32_t digit = (key[r] >> R.shift) & R.mask;
+            const uint32_t digit = digit_of(key[r]);
             // The lanes of the round with the same digit find each other through LDS: every lane ORs its own
             // bit into the 64-bit word of its digit (an atomic OR: the result does not depend on the order),
             // reads the word back and counts the bits below its own; the first lane of each group adds the
@@ -142,7 +155,7 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
     }
     __syncthreads();
     // per digit: the waves' counts become the waves' offsets; the totals go to dstart
-    if (tid < 256) {
+    if (tid < NB) {
         uint32_t run = 0;
 #pragma unroll
         for (int k = 0; k < RT_NW; ++k) {
@@ -153,19 +166,20 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
         dstart[tid] = run;
     }
     __syncthreads();
-    if (w == 0) {   // exclusive prefix sum of the 256 totals: four digits per lane
-        uint32_t v[4], s = 0;
+    if (w == 0) {   // exclusive prefix sum of the totals
+        constexpr int PER = NB / 64;
+        uint32_t v[PER], s = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { v[k] = dstart[lane * 4 + k]; s += v[k]; }
+        for (int k = 0; k < PER; ++k) { v[k] = dstart[lane * PER + k]; s += v[k]; }
         uint32_t ex = wave_incl_scan_u32(s) - s;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { dstart[lane * 4 + k] = ex; ex += v[k]; }
-        if (lane == 63) dstart[256] = ex;
+        for (int k = 0; k < PER; ++k) { dstart[lane * PER + k] = ex; ex += v[k]; }
+        if (lane == 63) dstart[NB] = ex;
     }
     __syncthreads();
     // the runs of this tile: digit b takes the next dstart[b + 1] - dstart[b] positions of its bucket (pass 1)
     // or of its window inside the bucket of this tile (pass 2)
-    if (tid < 256) {
+    if (tid < NB) {
         uint32_t g = 0;
         if (tid < R.B) {
             const uint32_t count = dstart[tid + 1] - dstart[tid];
@@ -175,18 +189,18 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
         gbase[tid] = g;
     }
 #pragma unroll
-    for (int h = 0; h < RT_IPT; h += 8) {
-        uint32_t key[8];   // read again: keeping the first copy would not fit the registers
+    for (int h = 0; h < IPT; h += CH) {
+        uint32_t key[CH];   // read again: keeping the first copy would not fit the registers
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < CH; ++r) {
             const int64_t i = base + (h + r) * 64 + lane;
             key[r] = i < n ? dest_in[i] : 0u;
         }
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < CH; ++r) {
             const int64_t i = base + (h + r) * 64 + lane;
             if (i < n) {
-                const uint32_t digit = (key[r] >> R.shift) & R.mask;
+                const uint32_t digit = digit_of(key[r]);
                 const uint32_t pos = dstart[digit] + wcnt[w][digit] + ((rk[(h + r) / 2] >> (16 * ((h + r) & 1))) & 0xFFFFu);
                 skey[pos] = key[r];
                 slot[i] = (uint16_t)pos;
@@ -196,21 +210,21 @@ __global__ __launch_bounds__(RT_NT) void route_rank_kernel(const uint32_t *__res
     }
     __syncthreads();
     const int64_t left = n - tile0;
-    const int cntile = (int)(left < RT_TILE ? left : RT_TILE);
+    const int cntile = (int)(left < TILE ? left : TILE);
 #pragma unroll 4
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const int pos = r * RT_NT + tid;
         if (pos < cntile) {
             const uint32_t k = skey[pos];
-            const uint32_t digit = (k >> R.shift) & R.mask;
+            const uint32_t digit = digit_of(k);
             const uint32_t g = gbase[digit] + ((uint32_t)pos - dstart[digit]);
             // the last pass needs no more than the place inside the window
-            if (off_out) off_out[g] = (uint16_t)(k & (RT_TILE - 1));
+            if (off_out) off_out[g] = (uint16_t)(TWO ? k - digit * (uint32_t)TILE : k & (RT_TILE - 1));
             else dest_out[g] = k;
         }
     }
-    if (tid <= 256) dstart_out[tb * 257 + tid] = dstart[tid];
-    if (tid < 256) gofs_out[tb * 256 + tid] = gbase[tid] - dstart[tid];
+    if (tid <= NB) dstart_out[tb * (NB + 1) + tid] = dstart[tid];
+    if (tid < NB) gofs_out[tb * NB + tid] = gbase[tid] - dstart[tid];
 }
 
 // ------------------------------------------------------------------------------------
@@ -228,44 +242,45 @@ __device__ inline int route_digit_of(const uint32_t *ds, uint32_t q) {
 }
 
 // pass 1 or 2 forwards: tile of `in` (tile order, in2 added if given) -> runs of `out`; NB: digits of the tables
-template <int NB>
+template <int NB, int IPT>
 __global__ __launch_bounds__(RT_NT) void route_deal_kernel(const float *__restrict__ in, const float *__restrict__ in2,
                                                            float *__restrict__ out, const uint16_t *__restrict__ slot,
                                                            const uint32_t *__restrict__ dstart_tab,
                                                            const uint32_t *__restrict__ gofs_tab, int B, int64_t n) {
-    const int64_t tb = route_tile(n);
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t tb = route_tile<IPT>(n);
     if (tb < 0) return;
-    __shared__ float stage[RT_TILE];
+    __shared__ float stage[TILE];
     __shared__ uint32_t ds[NB + 1], go[NB];
     const int tid = threadIdx.x;
-    const int64_t tile0 = tb * RT_TILE;
+    const int64_t tile0 = tb * TILE;
     const int64_t left = n - tile0;
-    const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
+    const int cnt = (int)(left < TILE ? left : TILE);
     if (tid <= NB) ds[tid] = dstart_tab[tb * (NB + 1) + tid];
     if (tid < NB) go[tid] = gofs_tab[tb * NB + tid];
-    uint16_t sl[RT_IPT];
-    float v[RT_IPT];
+    uint16_t sl[IPT];
+    float v[IPT];
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const int e = r * RT_NT + tid;
         sl[r] = e < cnt ? slot[tile0 + e] : (uint16_t)0;
         v[r] = e < cnt ? in[tile0 + e] : 0.f;
     }
     if (in2) {
 #pragma unroll
-        for (int r = 0; r < RT_IPT; ++r) {
+        for (int r = 0; r < IPT; ++r) {
             const int e = r * RT_NT + tid;
             if (e < cnt) v[r] += in2[tile0 + e];
         }
     }
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r)
+    for (int r = 0; r < IPT; ++r)
         if (r * RT_NT + tid < cnt) stage[sl[r]] = v[r];
     __syncthreads();
     // a thread per place: consecutive places of a run go to consecutive addresses, and all the stores of a
     // thread are independent (a wavefront per run would wait for one short run after the other)
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const uint32_t q = (uint32_t)(r * RT_NT + tid);
         if ((int)q < cnt) out[go[route_digit_of<NB>(ds, q)] + q] = stage[q];
     }
@@ -273,38 +288,39 @@ __global__ __launch_bounds__(RT_NT) void route_deal_kernel(const float *__restri
 
 // pass 2 or 1 backwards: runs of `in` -> tile of `out` (tile order); NC components, one array each on the
 // input side (in + c * in_stride); on the output side one array each (ROWS == false) or rows of NC values
-template <int NC, bool ROWS, int NB>
+template <int NC, bool ROWS, int NB, int IPT>
 __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__restrict__ in, int64_t in_stride,
                                                               float *__restrict__ out, int64_t out_stride,
                                                               const uint16_t *__restrict__ slot,
                                                               const uint32_t *__restrict__ dstart_tab,
                                                               const uint32_t *__restrict__ gofs_tab, int B, int64_t n) {
-    const int64_t tb = route_tile(n);
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t tb = route_tile<IPT>(n);
     if (tb < 0) return;
-    __shared__ float stage[RT_TILE];
+    __shared__ float stage[TILE];
     __shared__ uint32_t ds[NB + 1], go[NB];
     const int tid = threadIdx.x;
-    const int64_t tile0 = tb * RT_TILE;
+    const int64_t tile0 = tb * TILE;
     const int64_t left = n - tile0;
-    const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
+    const int cnt = (int)(left < TILE ? left : TILE);
     if (tid <= NB) ds[tid] = dstart_tab[tb * (NB + 1) + tid];
     if (tid < NB) go[tid] = gofs_tab[tb * NB + tid];
-    uint32_t sl[RT_IPT / 2];   // two places per register
+    uint32_t sl[IPT / 2];   // two places per register
 #pragma unroll
-    for (int r = 0; r < RT_IPT; r += 2) {
+    for (int r = 0; r < IPT; r += 2) {
         const int e0 = r * RT_NT + tid, e1 = e0 + RT_NT;
         const uint32_t a = e0 < cnt ? slot[tile0 + e0] : 0u, b = e1 < cnt ? slot[tile0 + e1] : 0u;
         sl[r / 2] = a | (b << 16);
     }
     __syncthreads();
-    float v[ROWS ? NC : 1][RT_IPT];
+    float v[ROWS ? NC : 1][IPT];
     // a thread per place (see route_deal_kernel): place q comes from go[digit of q] + q in the order before
-    constexpr int FLY = ROWS ? 8 : 16;   // loads in flight per thread (the row variant is short of registers)
+    constexpr int FLY = IPT % 8 ? 4 : ROWS || IPT % 16 ? 8 : 16;   // loads in flight per thread (the row variant is short of registers)
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const float *src = in + (int64_t)c * in_stride;
 #pragma unroll
-        for (int h = 0; h < RT_IPT; h += FLY) {
+        for (int h = 0; h < IPT; h += FLY) {
             float t[FLY];
 #pragma unroll
             for (int r = 0; r < FLY; ++r) {
@@ -316,11 +332,11 @@ __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__res
         }
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < RT_IPT; ++r) v[ROWS ? c : 0][r] = stage[(sl[r / 2] >> (16 * (r & 1))) & 0xFFFFu];
+        for (int r = 0; r < IPT; ++r) v[ROWS ? c : 0][r] = stage[(sl[r / 2] >> (16 * (r & 1))) & 0xFFFFu];
         if (!ROWS) {
             float *dst = out + (int64_t)c * out_stride;
 #pragma unroll
-            for (int r = 0; r < RT_IPT; ++r) {
+            for (int r = 0; r < IPT; ++r) {
                 const int e = r * RT_NT + tid;
                 if (e < cnt) dst[tile0 + e] = v[0][r];
             }
@@ -332,7 +348,7 @@ __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__res
         struct Row { float v[NC]; };
         Row *rows = reinterpret_cast<Row *>(out);
 #pragma unroll
-        for (int r = 0; r < RT_IPT; ++r) {
+        for (int r = 0; r < IPT; ++r) {
             const int e = r * RT_NT + tid;
             if (e < cnt) {
                 Row t;
@@ -345,29 +361,31 @@ __global__ __launch_bounds__(RT_NT) void route_collect_kernel(const float *__res
 }
 
 // pass 3 forwards: the values of a window, each to its place inside the window
+template <int IPT>
 __global__ __launch_bounds__(RT_NT) void route_place_kernel(const float *__restrict__ in, float *__restrict__ out,
                                                             const uint16_t *__restrict__ off, int64_t n) {
-    const int64_t tb = route_tile(n);
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t tb = route_tile<IPT>(n);
     if (tb < 0) return;
-    __shared__ float stage[RT_TILE];
+    __shared__ float stage[TILE];
     const int tid = threadIdx.x;
-    const int64_t win0 = tb * RT_TILE;
+    const int64_t win0 = tb * TILE;
     const int64_t left = n - win0;
-    const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
-    uint16_t o[RT_IPT];
-    float v[RT_IPT];
+    const int cnt = (int)(left < TILE ? left : TILE);
+    uint16_t o[IPT];
+    float v[IPT];
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const int e = r * RT_NT + tid;
         o[r] = e < cnt ? off[win0 + e] : (uint16_t)0;
         v[r] = e < cnt ? in[win0 + e] : 0.f;
     }
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r)
+    for (int r = 0; r < IPT; ++r)
         if (r * RT_NT + tid < cnt) stage[o[r]] = v[r];
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const int e = r * RT_NT + tid;
         if (e < cnt) out[win0 + e] = stage[e];
     }
@@ -376,41 +394,43 @@ __global__ __launch_bounds__(RT_NT) void route_place_kernel(const float *__restr
 // pass 3 backwards: a window of the caller's array (NC values per row, row-major) -> order p2, one array per
 // component.  A thread reads its rows once, whole (the window of a point set is not read again per coordinate),
 // and passes them through the LDS copy one coordinate at a time.
-template <int NC>
+template <int NC, int IPT>
 __global__ __launch_bounds__(RT_NT) void route_pick_kernel(const float *__restrict__ in, float *__restrict__ out,
                                                            int64_t out_stride, const uint16_t *__restrict__ off,
                                                            int64_t n) {
-    const int64_t tb = route_tile(n);
+    constexpr int TILE = RT_NT * IPT;
+    const int64_t tb = route_tile<IPT>(n);
     if (tb < 0) return;
-    __shared__ float stage[RT_TILE];
+    __shared__ float stage[TILE];
     const int tid = threadIdx.x;
-    const int64_t win0 = tb * RT_TILE;
+    const int64_t win0 = tb * TILE;
     const int64_t left = n - win0;
-    const int cnt = (int)(left < RT_TILE ? left : RT_TILE);
+    const int cnt = (int)(left < TILE ? left : TILE);
+    constexpr int FLY = IPT % 8 ? 4 : 8;   // loads in flight per thread
     struct Row { float v[NC]; };
-    Row row[RT_IPT];
+    Row row[IPT];
     const Row *rows = reinterpret_cast<const Row *>(in);
 #pragma unroll
-    for (int r = 0; r < RT_IPT; ++r) {
+    for (int r = 0; r < IPT; ++r) {
         const int e = r * RT_NT + tid;
         row[r] = rows[win0 + (e < cnt ? e : 0)];
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
 #pragma unroll
-        for (int r = 0; r < RT_IPT; ++r) stage[r * RT_NT + tid] = row[r].v[c];
+        for (int r = 0; r < IPT; ++r) stage[r * RT_NT + tid] = row[r].v[c];
         __syncthreads();
         float *dst = out + (int64_t)c * out_stride;
 #pragma unroll
-        for (int h = 0; h < RT_IPT; h += 8) {
-            uint32_t o[8];
+        for (int h = 0; h < IPT; h += FLY) {
+            uint32_t o[FLY];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
+            for (int r = 0; r < FLY; ++r) {
                 const int e = (h + r) * RT_NT + tid;
                 o[r] = e < cnt ? off[win0 + e] : 0u;
             }
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
+            for (int r = 0; r < FLY; ++r) {
                 const int e = (h + r) * RT_NT + tid;
                 if (e < cnt) dst[win0 + e] = stage[o[r]];
             }
@@ -424,6 +444,7 @@ __global__ __launch_bounds__(RT_NT) void route_pick_kernel(const float *__restri
 // points keep the caller's order, tile by tile, so the order depends on nothing but the points.
 // ------------------------------------------------------------------------------------
 constexpr int RG_NB = ROUTE_GROUP_BOXES;
+static_assert(RG_NB == RT_NB2, "tables of 512 digits");
 static_assert(RG_NB <= RT_NT / 2, "a thread per digit and one more");
 
 // rank of a box by its key; places of unoccupied boxes are not read
@@ -436,7 +457,7 @@ __global__ __launch_bounds__(256) void route_lut_kernel(const uint32_t *__restri
 __global__ __launch_bounds__(RT_NT) void route_group_count_kernel(const uint32_t *__restrict__ keys, int64_t n, int shift,
                                                                   const uint16_t *__restrict__ lut_tab, int nb,
                                                                   int64_t ntiles, uint32_t *__restrict__ hist) {
-    const int64_t tb = route_tile(n);
+    const int64_t tb = route_tile<RT_IPT>(n);
     if (tb < 0) return;
     __shared__ uint32_t cnt[RG_NB];
     __shared__ uint16_t lut[RG_NB];
@@ -470,7 +491,7 @@ __global__ __launch_bounds__(RT_NT) void route_group_rank_kernel(const uint32_t 
                                                                  int64_t ntiles, const uint32_t *__restrict__ first,
                                                                  uint16_t *__restrict__ slot, uint32_t *__restrict__ dstart_out,
                                                                  uint32_t *__restrict__ gofs_out) {
-    const int64_t tb = route_tile(n);
+    const int64_t tb = route_tile<RT_IPT>(n);
     if (tb < 0) return;
     __shared__ uint32_t wcnt[RT_NW][RG_NB];   // per wave: values of each digit seen so far; later the wave's offset
     __shared__ uint64_t wmask[RT_NW][RG_NB];  // per wave: the lanes that hold each digit in the current round
@@ -564,7 +585,7 @@ __global__ __launch_bounds__(RT_NT) void route_group_rows3_kernel(const float *_
                                                                   const uint16_t *__restrict__ slot,
                                                                   const uint32_t *__restrict__ dstart_tab,
                                                                   const uint32_t *__restrict__ gofs_tab, int64_t n) {
-    const int64_t tb = route_tile(n);
+    const int64_t tb = route_tile<RT_IPT>(n);
     if (tb < 0) return;
     constexpr int QUARTER = RT_TILE / 4;
     __shared__ float stage[QUARTER * 3];
@@ -629,9 +650,45 @@ static RouteLevel route_level(const f3m_route &R, int pass) {
     return L;
 }
 
+// Two passes win over the plain gather and scatter from 2^21 points on: 1e7 points, right-hand side in 179 -> 50 us, result
+// out 135 -> 51, points 213 -> 148 for tables of 51 us; 3e6 points, 39 -> 17 and 38 -> 18.  (Three passes at 1e7: 305 tiles of 32768
+// on 256 compute units, a second round that is nearly empty.)
+bool route_two_passes(int64_t n) { return n >= ((int64_t)1 << 21) && n <= (int64_t)RT_NB2 * RT_NT * 28; }
+
+template <class F>
+static void for_ipt(int ipt, F &&f) {
+    if (ipt == 8) f(std::integral_constant<int, 8>{});
+    else if (ipt == 20) f(std::integral_constant<int, 20>{});
+    else f(std::integral_constant<int, 28>{});
+}
+
 // Tables of the three passes for the permutation perm (n entries, box order -> caller's index).
-void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, hipStream_t st) {
+void route_build(f3m_route &R, const uint32_t *perm, int64_t n, bool two, int64_t *tally, hipStream_t st) {
     R.n = n;
+    if (two) {
+        R.two = true;
+        R.ipt = n <= (int64_t)RT_NB2 * RT_NT * 8 ? 8 : n <= (int64_t)RT_NB2 * RT_NT * 20 ? 20 : 28;
+        const int tile = RT_NT * R.ipt;
+        R.ntiles = cdiv(n, tile);
+        R.B1 = (int)R.ntiles;
+        if (R.ntiles > RT_NB2) fail(F3M_ERR_UNSUPPORTED, "too many points for the two-pass permutation");
+        R.slot1.alloc((size_t)n, tally);
+        R.off3.alloc((size_t)n, tally);
+        R.dstart1.alloc((size_t)R.ntiles * (RT_NB2 + 1), tally);
+        R.gofs1.alloc((size_t)R.ntiles * RT_NB2, tally);
+        DevBuf<uint32_t> cursor;
+        cursor.alloc((size_t)R.ntiles);
+        route_cursor_init_kernel<<<dim3((unsigned)cdiv(R.ntiles, 256)), dim3(256), 0, st>>>(cursor.p, R.ntiles, (uint32_t)tile);
+        RouteLevel L{};
+        L.ntiles = R.ntiles;
+        L.B = R.B1;
+        for_ipt(R.ipt, [&](auto ipt) {
+            route_rank_kernel<decltype(ipt)::value, RT_NB2, true><<<dim3(route_grid(R.ntiles)), dim3(RT_NT), 0, st>>>(
+                perm, n, L, cursor.p, R.slot1.p, nullptr, R.off3.p, R.dstart1.p, R.gofs1.p);
+        });
+        F3M_HIP(hipGetLastError());
+        return;
+    }
     R.ntiles = cdiv(n, RT_TILE);
     int wbits = 0;
     while (((int64_t)1 << wbits) < R.ntiles) ++wbits;
@@ -658,7 +715,7 @@ void route_build(f3m_route &R, const uint32_t *perm, int64_t n, int64_t *tally, 
         const int64_t ncur = pass == 1 ? R.B1 : nwin;
         route_cursor_init_kernel<<<dim3((unsigned)cdiv(ncur, 256)), dim3(256), 0, st>>>(
             cursor.p, ncur, pass == 1 ? (uint32_t)R.B2 * (uint32_t)RT_TILE : (uint32_t)RT_TILE);
-        route_rank_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(din, n, L, cursor.p, pass == 1 ? R.slot1.p : R.slot2.p,
+        route_rank_kernel<RT_IPT, 256, false><<<dim3(grid), dim3(RT_NT), 0, st>>>(din, n, L, cursor.p, pass == 1 ? R.slot1.p : R.slot2.p,
                                                              pass == 1 ? dest1.p : nullptr,
                                                              pass == 1 ? nullptr : R.off3.p,
                                                              pass == 1 ? R.dstart1.p : R.dstart2.p,
@@ -699,15 +756,24 @@ void route_scatter(const f3m_route &R, const float *in, const float *in2, float 
     const unsigned grid = route_grid(R.ntiles);
     if (R.grouped) {
         if (in2) fail(F3M_ERR_HIP, "internal: grouped points have no exact near field");
-        route_collect_kernel<1, false, RG_NB><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, 0, out, 0, R.slot1.p, R.dstart1.p,
+        route_collect_kernel<1, false, RG_NB, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, 0, out, 0, R.slot1.p, R.dstart1.p,
                                                                                  R.gofs1.p, 0, R.n);
         F3M_HIP(hipGetLastError());
         return;
     }
-    route_deal_kernel<256><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, in2, tmp_a, R.slot1.p, R.dstart1.p, R.gofs1.p, R.B1, R.n);
-    route_deal_kernel<256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, nullptr, tmp_b, R.slot2.p, R.dstart2.p, R.gofs2.p, R.B2,
+    if (R.two) {
+        for_ipt(R.ipt, [&](auto ipt) {
+            constexpr int IPT = decltype(ipt)::value;
+            route_deal_kernel<RT_NB2, IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, in2, tmp_a, R.slot1.p, R.dstart1.p, R.gofs1.p, R.B1, R.n);
+            route_place_kernel<IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, out, R.off3.p, R.n);
+        });
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    route_deal_kernel<256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, in2, tmp_a, R.slot1.p, R.dstart1.p, R.gofs1.p, R.B1, R.n);
+    route_deal_kernel<256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, nullptr, tmp_b, R.slot2.p, R.dstart2.p, R.gofs2.p, R.B2,
                                                          R.n);
-    route_place_kernel<<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, out, R.off3.p, R.n);
+    route_place_kernel<RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, out, R.off3.p, R.n);
     F3M_HIP(hipGetLastError());
 }
 
@@ -715,14 +781,24 @@ void route_scatter(const f3m_route &R, const float *in, const float *in2, float 
 void route_gather(const f3m_route &R, const float *in, float *out, float *tmp_a, float *tmp_b, hipStream_t st) {
     const unsigned grid = route_grid(R.ntiles);
     if (R.grouped) {
-        route_deal_kernel<RG_NB><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, nullptr, out, R.slot1.p, R.dstart1.p, R.gofs1.p, 0, R.n);
+        route_deal_kernel<RG_NB, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, nullptr, out, R.slot1.p, R.dstart1.p, R.gofs1.p, 0, R.n);
         F3M_HIP(hipGetLastError());
         return;
     }
-    route_pick_kernel<1><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, tmp_a, 0, R.off3.p, R.n);
-    route_collect_kernel<1, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, 0, tmp_b, 0, R.slot2.p, R.dstart2.p,
+    if (R.two) {
+        for_ipt(R.ipt, [&](auto ipt) {
+            constexpr int IPT = decltype(ipt)::value;
+            route_pick_kernel<1, IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, tmp_a, 0, R.off3.p, R.n);
+            route_collect_kernel<1, false, RT_NB2, IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, 0, out, 0, R.slot1.p, R.dstart1.p,
+                                                                                         R.gofs1.p, R.B1, R.n);
+        });
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    route_pick_kernel<1, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, tmp_a, 0, R.off3.p, R.n);
+    route_collect_kernel<1, false, 256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_a, 0, tmp_b, 0, R.slot2.p, R.dstart2.p,
                                                                       R.gofs2.p, R.B2, R.n);
-    route_collect_kernel<1, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, 0, out, 0, R.slot1.p, R.dstart1.p,
+    route_collect_kernel<1, false, 256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp_b, 0, out, 0, R.slot1.p, R.dstart1.p,
                                                                       R.gofs1.p, R.B1, R.n);
     F3M_HIP(hipGetLastError());
 }
@@ -736,10 +812,20 @@ void route_gather_rows3(const f3m_route &R, const float *in, float *out, float *
         F3M_HIP(hipGetLastError());
         return;
     }
-    route_pick_kernel<3><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, out, R.n, R.off3.p, R.n);
-    route_collect_kernel<3, false, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(out, R.n, tmp, R.n, R.slot2.p, R.dstart2.p,
+    if (R.two) {
+        for_ipt(R.ipt, [&](auto ipt) {
+            constexpr int IPT = decltype(ipt)::value;
+            route_pick_kernel<3, IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, tmp, R.n, R.off3.p, R.n);
+            route_collect_kernel<3, true, RT_NB2, IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp, R.n, out, 0, R.slot1.p, R.dstart1.p,
+                                                                                        R.gofs1.p, R.B1, R.n);
+        });
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    route_pick_kernel<3, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(in, out, R.n, R.off3.p, R.n);
+    route_collect_kernel<3, false, 256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(out, R.n, tmp, R.n, R.slot2.p, R.dstart2.p,
                                                                       R.gofs2.p, R.B2, R.n);
-    route_collect_kernel<3, true, 256><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp, R.n, out, 0, R.slot1.p, R.dstart1.p,
+    route_collect_kernel<3, true, 256, RT_IPT><<<dim3(grid), dim3(RT_NT), 0, st>>>(tmp, R.n, out, 0, R.slot1.p, R.dstart1.p,
                                                                      R.gofs1.p, R.B1, R.n);
     F3M_HIP(hipGetLastError());
 }
