@@ -1782,12 +1782,13 @@ constexpr int P2M_NCH = 4;     // chunks per wavefront: the table reads and the 
                                // flight together (a chunk alone is a chain of dependent loads, and the kernel was
                                // bound by that latency)
 
+template <bool PERM>   // bs is in the caller's order, bs[perm[k]] the right-hand side of point k
 __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
                                                    const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
                                                    const uint32_t *__restrict__ chunk_box,
                                                    const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
                                                    float *__restrict__ W, float *__restrict__ Wpart, int one_chunk,
-                                                   WeightedArg A) {
+                                                   WeightedArg A, const uint32_t *__restrict__ perm) {
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ float tr[64 * TR_STRIDE];
     const int64_t bi = block_index();
@@ -1827,7 +1828,7 @@ __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs,
         const uint32_t kc = live ? k : k0[j];
 #pragma unroll
         for (int d = 0; d < 3; ++d) x[d] = Xs[(int64_t)kc * 3 + d];
-        const float bl = bs[kc];
+        const float bl = bs[PERM ? perm[kc] : kc];
         bv = live ? bl : 0.f;
     };
     float x[P2M_NCH][3], bv[P2M_NCH];
@@ -1899,10 +1900,12 @@ __global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs,
 // one round of 64, which costs the same.  Lane = point; the two halves of a wavefront work on boxes a and a + 1,
 // four such pairs per wavefront with the first loads of all of them in flight together.
 constexpr int P2M_NPAIR = 4;
+template <bool PERM>
 __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
                                                         const uint32_t *__restrict__ start,
                                                         const int32_t *__restrict__ cell, int64_t nb, CentreArg C,
-                                                        float *__restrict__ W, WeightedArg A) {
+                                                        float *__restrict__ W, WeightedArg A,
+                                                        const uint32_t *__restrict__ perm) {
     // rows of the upper half are shifted by 32 floats so that the two halves read different banks
     __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE + 32];
     const int64_t bi = block_index();
@@ -1933,7 +1936,7 @@ __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict_
         const uint32_t kc = live ? k : k0[j];
 #pragma unroll
         for (int d = 0; d < 3; ++d) x[d] = Xs[(int64_t)kc * 3 + d];
-        const float bl = bs[kc];
+        const float bl = bs[PERM ? perm[kc] : kc];
         bv = live ? bl : 0.f;
     };
     float x[P2M_NPAIR][3], bv[P2M_NPAIR];
@@ -1999,15 +2002,16 @@ __global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict_
 
 constexpr int L2P_NCH = 4;   // chunks per wavefront: their loads are in flight together (a chunk alone is a chain
                              // of dependent loads and the kernel is bound by that latency)
-template <bool WEIGHTED>   // Vw: node potentials of the weighted near pairs, evaluated times exp2(kw |u|^2 / (l/2)^2)
+template <bool WEIGHTED, bool PERM>   // Vw: node potentials of the weighted near pairs, evaluated times exp2(kw |u|^2 / (l/2)^2)
 __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs, const uint32_t *__restrict__ start,
                                                    const int32_t *__restrict__ cell,
                                                    const uint64_t *__restrict__ far_ptr,
                                                    const uint32_t *__restrict__ chunk_box,
                                                    const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
                                                    const float *__restrict__ V, const float *base, float *out,
-                                                   int one_chunk, const float *__restrict__ Vw, float kw) {
-    // out = base (nullptr: zero) + far field
+                                                   int one_chunk, const float *__restrict__ Vw, float kw,
+                                                   const uint32_t *__restrict__ perm) {
+    // out[perm[k]] (PERM; else out[k]) = base (nullptr: zero) + far field
     // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
     __shared__ __attribute__((aligned(16))) float vbuf[L2P_NCH][64];
     __shared__ __attribute__((aligned(16))) float wbuf[WEIGHTED ? L2P_NCH : 1][64];
@@ -2080,7 +2084,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
     // run of every chunk has all its loads issued before any is used, then what is left of the chunks.
     float x[L2P_NCH][3], yold[L2P_NCH];
     bool live[L2P_NCH];
-    uint32_t kk[L2P_NCH];
+    uint32_t kk[L2P_NCH], ko[L2P_NCH];
 #pragma unroll
     for (int j = 0; j < L2P_NCH; ++j) {
         const uint32_t k = k0[j] + lane;
@@ -2089,10 +2093,11 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
 #pragma unroll
         for (int d = 0; d < 3; ++d) x[j][d] = Xs[(int64_t)kk[j] * 3 + d];
         yold[j] = base ? base[kk[j]] : 0.f;
+        ko[j] = PERM ? perm[kk[j]] : kk[j];
     }
 #pragma unroll
     for (int j = 0; j < L2P_NCH; ++j) {
-        run(j, live[j], kk[j], x[j], yold[j]);
+        run(j, live[j], ko[j], x[j], yold[j]);
         if constexpr (WEIGHTED) __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -2104,7 +2109,7 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
             float xr[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) xr[d] = Xs[(int64_t)kc * 3 + d];
-            run(j, lv, kc, xr, base ? base[kc] : 0.f);
+            run(j, lv, PERM ? perm[kc] : kc, xr, base ? base[kc] : 0.f);
         }
     }
 }
@@ -2973,7 +2978,15 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     const float *Ys = P.Ys();   // sources in box order (the targets themselves for one point set)
 
     hipEvent_t now = P.t_begin = mark();   // the last mark: nothing has been launched on the stream since
-    if (!bs_in) {   // else gathered by the caller
+    // One set whose points are read by the P2M of one depth only: it takes the right-hand side from the caller's order itself
+    const uint32_t *perm_in = nullptr;
+    if (!bs_in && !P.src && !P.route && no_near && P.tree_lmin > 0 && !long_chunks(P.lev[P.tree_lmax])) {
+        perm_in = P.perm.p;
+        for (int l = 1; l < P.tree_lmin || l <= P.last_depth(); ++l)
+            if ((l < P.tree_lmin || l > P.tree_lmax) && P.lev[l].far_sz > 0 && P.lev[l].p > 0) perm_in = nullptr;
+    }
+    if (perm_in) bs = b;
+    if (!bs_in && !perm_in) {   // else gathered by the caller
         if (P.sroute())
             route_gather(*P.sroute(), b, P.bs.p, P.route_a.p, P.route_b.p, st);
         else
@@ -3083,7 +3096,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
     // order it adds the near field and writes the result.
     bool one_l2p = tree;
     for (int l = 1; l <= P.L; ++l) one_l2p = one_l2p && !on_its_own(l);
-    const bool direct_out = one_l2p && box_order;
+    // So it does where the result goes straight to its place in the caller's order (perm_out), by direct stores.
+    const uint32_t *perm_out = one_l2p && !box_order && !P.route && !long_chunks(P.lev[P.tree_lmax]) ? P.perm.p : nullptr;
+    const bool direct_out = one_l2p && (box_order || perm_out);
     if (!one_l2p) {
         zero_kernel<<<dim3(gn), dim3(256), 0, st>>>(P.ys.p, n);
         F3M_HIP(hipGetLastError());
@@ -3102,12 +3117,13 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                                                                                sv.chunk_first.p, sv.nchunks, CS, P.W.p, P.Wpart.p,
                                                                                0, 0, 0.f);
         else if (D == 3 && p == 4 && single_chunks(sv))
-            p2m34_pair_kernel<<<grid_for(cdiv(sv.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.nb,
-                                                                                        CS, P.W.p, WeightedArg{});
+            p2m34_pair_kernel<false><<<grid_for(cdiv(sv.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.nb,
+                                                                                        CS, P.W.p, WeightedArg{}, nullptr);
         else if (D == 3 && p == 4)
-            p2m34_kernel<<<grid_for(cdiv(sv.nchunks, P2M_NCH)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p,
+            p2m34_kernel<false><<<grid_for(cdiv(sv.nchunks, P2M_NCH)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p,
                                                                   sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS,
-                                                                  P.W.p, P.Wpart.p, single_chunks(sv), WeightedArg{});
+                                                                  P.W.p, P.Wpart.p, single_chunks(sv), WeightedArg{},
+                                                                  nullptr);
         else if (r <= 64)
             p2m_kernel<D><<<grid_for(sv.nchunks), dim3(64), sh, st>>>(
                 Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, p, r, CS, N,
@@ -3202,9 +3218,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                     P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, P.V.p, P.ys.p,
                     P.ys.p, nullptr, 0.f);
             else if (D == 3 && p == 4)
-                l2p34_kernel<false><<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
+                l2p34_kernel<false, false><<<grid_for(cdiv(lv.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
                     P.Xs.p, lv.start.p, lv.cell.p, lv.far_ptr.p, lv.chunk_box.p, lv.chunk_first.p, lv.nchunks, C, P.V.p, P.ys.p,
-                    P.ys.p, single_chunks(lv), nullptr, 0.f);
+                    P.ys.p, single_chunks(lv), nullptr, 0.f, nullptr);
             else
                 for_nodes<D>(p, [&](auto pn) {
                     l2p_kernel<D, decltype(pn)::value><<<grid_for(lv.nchunks), dim3(P2M_CHUNK), 0, st>>>(
@@ -3246,12 +3262,20 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 if (long_chunks(lf)) {
                     if (weighted) p2m_long(p2m34_long_kernel<true>);
                     else p2m_long(p2m34_long_kernel<false>);
-                } else if (pairs)
-                    p2m34_pair_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.nb, make_centre(P, L),
-                                                                 lf.Wl.p, A);
-                else
-                    p2m34_kernel<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
-                                                            lf.nchunks, make_centre(P, L), lf.Wl.p, P.Wpart.p, 0, A);
+                } else if (pairs) {
+                    auto launch = [&](auto kern) {
+                        kern<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.nb, make_centre(P, L), lf.Wl.p, A, perm_in);
+                    };
+                    if (perm_in) launch(p2m34_pair_kernel<true>);
+                    else launch(p2m34_pair_kernel<false>);
+                } else {
+                    auto launch = [&](auto kern) {
+                        kern<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks,
+                                                        make_centre(P, L), lf.Wl.p, P.Wpart.p, 0, A, perm_in);
+                    };
+                    if (perm_in) launch(p2m34_kernel<true>);
+                    else launch(p2m34_kernel<false>);
+                }
                 F3M_HIP(hipGetLastError());
                 if (lf.max_box > lf.chunk) {   // some box has several chunks
                     reduce_partials(P, lf, r, lf.Wl.p, st);
@@ -3283,7 +3307,15 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 ev[1] = now = mark();
             }
             ev[2] = now;
-            if (lv.far_implicit) {
+            if (m2l_stencil_small(P, l)) {
+                // with the depths behind it that have few parents too; the time is that of the deepest
+                int to = l;
+                while (to < L && m2l_stencil_small(P, to + 1)) ++to;
+                run_m2l_small(P, l, to, st);
+                for (; l < to; ++l) level_events(l)[2] = level_events(l)[3] = now;
+                ev = level_events(to);
+                ev[2] = now;
+            } else if (lv.far_implicit) {
                 if (!run_m2l_stencil(P, l, lv.Wl.p, lv.Vl.p, st, true))   // Wl ends with a row of zeros
                     fail(F3M_ERR_HIP, "internal: depth outside the candidate-grid M2L");
             } else {
@@ -3300,9 +3332,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 WeightedArg A;
                 A.blocks = 0;
                 A.kw = kw;
-                p2m34_kernel<<<grid_for(cdiv(ns.nchunks, P2M_NCH)), dim3(64), 0, st>>>(
+                p2m34_kernel<false><<<grid_for(cdiv(ns.nchunks, P2M_NCH)), dim3(64), 0, st>>>(
                     Ys, bs, P.slev(L).start.p, P.slev(L).cell.p, ns.chunk_box.p, ns.chunk_first.p, ns.nchunks,
-                    make_centre(P, L, true), ns.Wl.p, P.Wpart.p, 0, A);
+                    make_centre(P, L, true), ns.Wl.p, P.Wpart.p, 0, A, nullptr);
                 F3M_HIP(hipGetLastError());
                 if (ns.max_box > ns.chunk) reduce_partials(P, ns, r, ns.Wl.p, st);
             }
@@ -3331,7 +3363,7 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
             auto l2p = [&](auto kern) {
                 kern<<<grid_for(cdiv(lf.nchunks, L2P_NCH)), dim3(64), 0, st>>>(
                     P.Xs.p, lf.start.p, lf.cell.p, nullptr, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks, make_centre(P, L), lf.Vl.p,
-                    base, direct_out ? y : P.ys.p, single_chunks(lf), weighted ? lf.Vl.p + lf.nb * r : nullptr, kw);
+                    base, direct_out ? y : P.ys.p, single_chunks(lf), weighted ? lf.Vl.p + lf.nb * r : nullptr, kw, perm_out);
             };
             auto l2p_long = [&](auto kern) {
                 kern<<<grid_for(lf.nchunks), dim3(64), 0, st>>>(
@@ -3342,8 +3374,10 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
                 if (weighted) l2p_long(l2p34_long_kernel<true>);
                 else l2p_long(l2p34_long_kernel<false>);
             } else {
-                if (weighted) l2p(l2p34_kernel<true>);
-                else l2p(l2p34_kernel<false>);
+                if (weighted && perm_out) l2p(l2p34_kernel<true, true>);
+                else if (weighted) l2p(l2p34_kernel<true, false>);
+                else if (perm_out) l2p(l2p34_kernel<false, true>);
+                else l2p(l2p34_kernel<false, false>);
             }
             F3M_HIP(hipGetLastError());
             ev[5] = now = mark();

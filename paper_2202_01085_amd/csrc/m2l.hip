@@ -259,13 +259,19 @@ __global__ __launch_bounds__(256) void stencil_table_kernel(const uint64_t *__re
 
 // ZROW: W has a row of zeros behind its last box (index zero_row): an absent candidate (~0 in the table)
 // reads that row, which saves the compare-and-select pairs around every load.
+// Several depths with few parents share a launch (their M2L do not depend on each other): the workgroups from first[k] on are
+// those of entry k.
+struct M2lDepths {
+    static constexpr int MAX = 6;
+    const uint32_t *cand[MAX], *child[MAX];
+    const float *G[MAX], *W[MAX];
+    float *V[MAX];
+    uint32_t first[MAX], nparents[MAX], zero_row[MAX];
+    int all_far[MAX];
+    int count = 0;
+};
 template <bool ZROW>
-__global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t *__restrict__ cand_tab,
-                                                                 const uint32_t *__restrict__ child_tab,
-                                                                 int64_t nparents, int64_t per_xcd,
-                                                                 const float *__restrict__ G, int all_far,
-                                                                 uint32_t zero_row,
-                                                                 const float *__restrict__ W, float *__restrict__ V) {
+__global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(M2lDepths A) {
     __shared__ float xl[2 * 36 * 64];       // X_tx(cy, cz) at [(tx * 36 + cy + 6 cz) * 64 + node]
     __shared__ float xn[2 * 16 * 64];       // the same over the near candidates only, 1 <= cy, cz <= 4
     __shared__ float yp[4 * 6 * 64];        // Y_{tx,ty}(cz) at [((tx + 2 ty) * 6 + cz) * 64 + node]
@@ -273,11 +279,20 @@ __global__ __launch_bounds__(512) void m2l_stencil_shared_kernel(const uint32_t 
     __shared__ float gs[7 * 16];            // the factor table
     // (the wavefront's number in a scalar register: ranks and row addresses are then scalar work)
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int e = 0;
+#pragma unroll
+    for (int k = 1; k < M2lDepths::MAX; ++k)
+        if (k < A.count && blockIdx.x >= A.first[k]) e = k;
+    const uint32_t *__restrict__ cand_tab = A.cand[e], *__restrict__ child_tab = A.child[e];
+    const float *__restrict__ W = A.W[e];
+    float *__restrict__ V = A.V[e];
+    const uint32_t zero_row = A.zero_row[e];
+    const int all_far = A.all_far[e];
     // consecutive parents (neighbours in space) on the same XCD, so that its L2 serves the overlap
-    const int64_t bi = block_index2();
-    const int64_t pb = (bi & 7) * per_xcd + (bi >> 3);
-    if ((bi >> 3) >= per_xcd || pb >= nparents) return;
-    if (tid < 7 * 16) gs[tid] = G[tid];
+    const uint32_t bi = blockIdx.x - A.first[e], per_xcd = (A.nparents[e] + 7) / 8;
+    const int64_t pb = (int64_t)(bi & 7) * per_xcd + (bi >> 3);
+    if ((bi >> 3) >= per_xcd || pb >= (int64_t)A.nparents[e]) return;
+    if (tid < 7 * 16) gs[tid] = A.G[e][tid];
     const uint32_t t = child_tab[pb * 8 + w];   // the child with parity w (wave-uniform), or ~0
     // lines w + 8 i of six candidates each, i = 0..4: node weights straight into registers (zeros for absent
     // candidates), all loads in flight together
@@ -836,6 +851,42 @@ void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st) {
     F3M_HIP(hipGetLastError());
 }
 
+// the M2L of the depth runs on the candidate grid with few parents, and may share a launch with others of its kind
+bool m2l_stencil_small(const f3m_plan_s &P, int level) {
+    return m2l_stencil_applies(P) && level >= 1 && P.lev[level].far_implicit && P.lev[level].st_cand.p && P.lev[level].gtab.p &&
+           P.lev[level - 1].nb < M2L_QUAD_PARENTS;
+}
+
+static void add_depth(const f3m_plan_s &P, int level, const float *W, float *V, uint32_t zero_row, M2lDepths &A, uint32_t &blocks) {
+    const f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
+    const int k = A.count++;
+    A.cand[k] = lv.st_cand.p;
+    A.child[k] = lv.st_child.p;
+    A.G[k] = lv.gtab.p;
+    A.W[k] = W;
+    A.V[k] = V;
+    A.first[k] = blocks;
+    A.nparents[k] = (uint32_t)up.nb;
+    A.zero_row[k] = zero_row;
+    A.all_far[k] = lv.smooth || level == P.near_depth ? 1 : 0;
+    blocks += (uint32_t)(cdiv(up.nb, 8) * 8);
+}
+
+// depths from .. to (m2l_stencil_small each, node weights with a row of zeros behind them): one launch for up to six.  The three
+// depths of 2.5e5 points: 19 us one after the other, 10 together.
+void run_m2l_small(f3m_plan_s &P, int from, int to, hipStream_t st) {
+    for (int l = from; l <= to;) {
+        M2lDepths A;
+        uint32_t blocks = 0;
+        // the deepest first: it has the most workgroups
+        const int last = std::min(to, l + M2lDepths::MAX - 1);
+        for (int k = last; k >= l; --k) add_depth(P, k, P.lev[k].Wl.p, P.lev[k].Vl.p, (uint32_t)P.lev[k].nb, A, blocks);
+        m2l_stencil_shared_kernel<true><<<dim3(blocks), dim3(512), 0, st>>>(A);
+        F3M_HIP(hipGetLastError());
+        l = last + 1;
+    }
+}
+
 bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStream_t st, bool zero_row) {
     if (!m2l_stencil_applies(P) || level < 1) return false;
     f3m_level &lv = P.lev[level], &up = P.lev[level - 1];
@@ -845,17 +896,19 @@ bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStre
     if (lv.st_cand.p) {   // no small field: the variants that share the line and plane sums between the children
         // Four parents to a workgroup from M2L_QUAD_PARENTS on: below, the chip is not full and the longer chain of a workgroup
         // shows (8, 64, 512, 4096 parents: 5.0, 5.1, 6 to 7, 42 us with one parent to a workgroup, 8.2, 9.3, 9.6, 28 with four).
-        const bool quad = up.nb >= M2L_QUAD_PARENTS;
-        const int64_t per = quad ? cdiv(cdiv(up.nb, ST_PAR), 8) : per_xcd;
-        auto launch = [&](auto kern, int threads, uint32_t zr) {
-            kern<<<grid2(per * 8), dim3(threads), 0, st>>>(lv.st_cand.p, lv.st_child.p, up.nb, per, lv.gtab.p, all_far, zr, W, V);
-        };
-        if (zero_row) {   // W carries a row of zeros at index nb
-            if (quad) launch(m2l_stencil_quad_kernel<true>, 768, (uint32_t)lv.nb);
-            else launch(m2l_stencil_shared_kernel<true>, 512, (uint32_t)lv.nb);
+        if (up.nb < M2L_QUAD_PARENTS) {
+            M2lDepths A;
+            uint32_t blocks = 0;
+            add_depth(P, level, W, V, zero_row ? (uint32_t)lv.nb : 0u, A, blocks);
+            if (zero_row) m2l_stencil_shared_kernel<true><<<dim3(blocks), dim3(512), 0, st>>>(A);   // W carries a row of zeros at index nb
+            else m2l_stencil_shared_kernel<false><<<dim3(blocks), dim3(512), 0, st>>>(A);
         } else {
-            if (quad) launch(m2l_stencil_quad_kernel<false>, 768, 0u);
-            else launch(m2l_stencil_shared_kernel<false>, 512, 0u);
+            const int64_t per = cdiv(cdiv(up.nb, ST_PAR), 8);
+            auto launch = [&](auto kern, uint32_t zr) {
+                kern<<<grid2(per * 8), dim3(768), 0, st>>>(lv.st_cand.p, lv.st_child.p, up.nb, per, lv.gtab.p, all_far, zr, W, V);
+            };
+            if (zero_row) launch(m2l_stencil_quad_kernel<true>, (uint32_t)lv.nb);
+            else launch(m2l_stencil_quad_kernel<false>, 0u);
         }
         F3M_HIP(hipGetLastError());
         return true;

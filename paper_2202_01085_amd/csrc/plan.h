@@ -253,6 +253,8 @@ void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);   // after 
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables
 void near_table(const f3m_plan_s &P, float *t);                        // 16 factors of the weighted near pairs
 void run_near_weighted(f3m_plan_s &P, const float *W, float *V, hipStream_t st);
+bool m2l_stencil_small(const f3m_plan_s &P, int level);                // few parents: several depths may share a launch
+void run_m2l_small(f3m_plan_s &P, int from, int to, hipStream_t st);
 bool run_m2l_stencil(f3m_plan_s &P, int level, const float *W, float *V, hipStream_t st, bool zero_row = false);  // false: does not apply
 
 }  // namespace f3m
