@@ -1770,234 +1770,232 @@ __device__ inline float weights34(const float *__restrict__ x, const double (&ct
 }
 
 // The weighted near pairs (near_weighted_error in plan.hip) need a second set of node weights, of points times
-// exp(-|u|^2 / 2 gamma^2) = exp2(kw |u|^2 / (l/2)^2): the workgroups of a P2M launch from `blocks` on make it (none, the upper
-// half, or all of them); dW, dpart: from the plain to the weighted arrays.
+// exp(-|u|^2 / 2 gamma^2) = exp2(kw |u|^2 / (l/2)^2): made together with the plain one (NS = 2 below; dW, dpart: from the plain
+// to the weighted arrays), or alone (only).
 struct WeightedArg {
-    int64_t blocks = INT64_MAX, dW = 0, dpart = 0;
+    int64_t dW = 0, dpart = 0;
     float kw = 0.f;
+    bool only = false;
 };
 
-constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
-constexpr int P2M_NCH = 4;     // chunks per wavefront: the table reads and the first loads of all of them are in
-                               // flight together (a chunk alone is a chain of dependent loads, and the kernel was
-                               // bound by that latency)
+// P2M on the matrix cores: v_mfma_f32_4x4x1 multiplies 16 independent columns of 4 by rows of 4 in fp32.  A quad of lanes is
+// one of the 16 and takes one point at a time; its lane i evaluates L_i alone, the three coordinates and the weight
+// of the point are made once per point (lane = point) and reach the quad as DPP broadcasts.  With A = L_x L_y[j] (j = 0 .. 3)
+// and B = L_z b the node sums of the quad's points stay in 16 registers a lane for each set of weights (v[set][i2][i1], lane
+// 4 quad + i3), and are summed over the quads once per box.  What bounds it: vector issue, some 24 instructions
+// for 16 points and both sets (the 64-accumulator form, lane = point, took 130 for one lane's point and a sum of 64 x 64 values through
+// LDS for each set).
+typedef float f4v __attribute__((ext_vector_type(4)));
+template <int NS> struct P2mSums { f4v v[NS][4]; };
+struct QuadNode { float a, b, c, w; };   // L_i(t) = (t - a) (t - b) (t - c) w, multiplied in the order of lagrange4
 
-template <bool PERM>   // bs is in the caller's order, bs[perm[k]] the right-hand side of point k
-__global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
-                                                   const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
-                                                   const uint32_t *__restrict__ chunk_box,
-                                                   const uint32_t *__restrict__ chunk_first, int64_t nchunks, CentreArg C,
-                                                   float *__restrict__ W, float *__restrict__ Wpart, int one_chunk,
-                                                   WeightedArg A, const uint32_t *__restrict__ perm) {
-    // one_chunk: every box is a single chunk (chunk index = box rank): two dependent table reads less
-    __shared__ float tr[64 * TR_STRIDE];
-    const int64_t bi = block_index();
-    const bool weighted = bi >= A.blocks;
-    const int64_t c0 = (weighted ? bi - A.blocks : bi) * P2M_NCH;
-    if (c0 >= nchunks) return;
-    if (weighted) {
-        W += A.dW;
-        Wpart += A.dpart;
-    }
-    const int lane = threadIdx.x;
-    // chunk j of this wavefront (a chunk beyond the end repeats the last one and is switched off)
-    uint32_t a[P2M_NCH], k0[P2M_NCH], k1[P2M_NCH], nch[P2M_NCH];
-    int64_t cj[P2M_NCH];
-    bool on[P2M_NCH];
+__device__ inline QuadNode quad_node(int i) {
+    return {i == 0 ? 0.5f : i == 1 ? 1.f : i == 2 ? -1.f : -0.5f, i < 2 ? -0.5f : 1.f, i < 2 ? -1.f : 0.5f,
+            i == 0 ? 1.f / 1.5f : i == 1 ? -1.f / 0.75f : i == 2 ? 1.f / 0.75f : -1.f / 1.5f};
+}
+
+template <int CTRL, int BANKS> __device__ inline float dpp_into(float old, float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v), CTRL, 0xF,
+                                                                 BANKS, true));
+}
+template <int R> __device__ inline float quad_bcast(float v) { return dpp_into<R * 0x55, 0xF>(0.f, v); }
+
+// the points in lane R of every quad
+template <int NS, int R>
+__device__ inline void p2m34_step(P2mSums<NS> &S, const QuadNode &N, float tx, float ty, float tz, float b, float be) {
+    auto basis = [&](float t) __attribute__((always_inline)) { return (t - N.a) * ((t - N.b) * (t - N.c)) * N.w; };
+    const float Lx = basis(quad_bcast<R>(tx)), Ly = basis(quad_bcast<R>(ty)), Lz = basis(quad_bcast<R>(tz));
+    const float A[4] = {Lx * quad_bcast<0>(Ly), Lx * quad_bcast<1>(Ly), Lx * quad_bcast<2>(Ly), Lx * quad_bcast<3>(Ly)};
+    const float B = Lz * quad_bcast<R>(b);
 #pragma unroll
-    for (int j = 0; j < P2M_NCH; ++j) {
-        cj[j] = c0 + j < nchunks ? c0 + j : nchunks - 1;
-        on[j] = c0 + j < nchunks;
-        a[j] = one_chunk ? (uint32_t)cj[j] : (uint32_t)__builtin_amdgcn_readfirstlane(chunk_box[cj[j]]);
-    }
-    double ctr[P2M_NCH][3];
+    for (int j = 0; j < 4; ++j) S.v[0][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[j], B, S.v[0][j], 0, 0, 0);
+    if constexpr (NS == 2) {
+        const float Be = Lz * quad_bcast<R>(be);
 #pragma unroll
-    for (int j = 0; j < P2M_NCH; ++j) {
-        const uint32_t ci = one_chunk ? 0u : (uint32_t)(cj[j] - chunk_first[a[j]]);
-        nch[j] = one_chunk ? 1u : chunk_first[a[j] + 1] - chunk_first[a[j]];
-        k0[j] = start[a[j]] + ci * (uint32_t)P2M_CHUNK;     // a point of the box: always a valid index
-        k1[j] = min(k0[j] + (uint32_t)P2M_CHUNK, start[a[j] + 1]);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) ctr[j][d] = C.alpha[d] + ((double)cell[(int64_t)a[j] * 3 + d] + 0.5) * C.edge;
-    }
-    // Loads are unconditional, the index of a lane beyond the chunk clamped to the chunk's first point
-    // and its weight set to zero (a branch around them would make every load wait on its own).
-    auto load = [&](int j, uint32_t kb, float (&x)[3], float &bv) {
-        const uint32_t k = kb + lane;
-        const bool live = k < k1[j];
-        const uint32_t kc = live ? k : k0[j];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) x[d] = Xs[(int64_t)kc * 3 + d];
-        const float bl = bs[PERM ? perm[kc] : kc];
-        bv = live ? bl : 0.f;
-    };
-    float x[P2M_NCH][3], bv[P2M_NCH];
-#pragma unroll
-    for (int j = 0; j < P2M_NCH; ++j) load(j, k0[j], x[j], bv[j]);
-    const int i = lane & 31, part = lane >> 5;
-#pragma unroll
-    for (int j = 0; j < P2M_NCH; ++j) {
-        if (!on[j]) continue;   // wave-uniform
-        float acc[64];
-#pragma unroll
-        for (int q = 0; q < 64; ++q) acc[q] = 0.f;
-        float xc[3] = {x[j][0], x[j][1], x[j][2]}, bc = bv[j];
-        for (uint32_t kb = k0[j];;) {
-            // the next run of the chunk (boxes above 64 points) is loaded while this one is added
-            const bool more = kb + 64 < k1[j];
-            float xn[3] = {0.f, 0.f, 0.f}, bn = 0.f;
-            if (more) load(j, kb + 64, xn, bn);
-            float Lx[4], Ly[4], Lz[4];
-            const float u2 = weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
-            if (weighted) bc *= __builtin_amdgcn_exp2f(A.kw * u2);
-#pragma unroll
-            for (int i3 = 0; i3 < 4; ++i3) {
-                const float zb = Lz[i3] * bc;
-#pragma unroll
-                for (int i2 = 0; i2 < 4; ++i2) {
-                    const float yz = Ly[i2] * zb;
-#pragma unroll
-                    for (int i1 = 0; i1 < 4; ++i1) acc[i1 + 4 * i2 + 16 * i3] = fmaf(Lx[i1], yz, acc[i1 + 4 * i2 + 16 * i3]);
-                }
-            }
-            if (!more) break;
-            kb += 64;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xc[d] = xn[d];
-            bc = bn;
-        }
-        // sum over lanes, 32 nodes at a time (half the LDS, twice the resident wavefronts): lane l
-        // writes its row; lane (i, part) adds rows 32 part .. 32 part + 31 of column i, and the two
-        // parts meet through one shuffle
-        float *dst = nch[j] == 1 ? W + (int64_t)a[j] * 64 : Wpart + cj[j] * 64;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            __syncthreads();   // the sums of the previous half (or chunk) have been read
-#pragma unroll
-            for (int g = 0; g < 8; ++g)
-                *reinterpret_cast<float4 *>(&tr[lane * TR_STRIDE + 4 * g]) =
-                    make_float4(acc[32 * q + 4 * g], acc[32 * q + 4 * g + 1], acc[32 * q + 4 * g + 2], acc[32 * q + 4 * g + 3]);
-            __syncthreads();
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-            for (int row = 0; row < 32; row += 4) {
-                s0 += tr[(32 * part + row + 0) * TR_STRIDE + i];
-                s1 += tr[(32 * part + row + 1) * TR_STRIDE + i];
-                s2 += tr[(32 * part + row + 2) * TR_STRIDE + i];
-                s3 += tr[(32 * part + row + 3) * TR_STRIDE + i];
-            }
-            float t = (s0 + s1) + (s2 + s3);
-            t += __shfl_xor(t, 32, 64);
-            if (part == 0) dst[32 * q + i] = t;
-        }
+        for (int j = 0; j < 4; ++j) S.v[NS - 1][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[j], Be, S.v[NS - 1][j], 0, 0, 0);
     }
 }
 
-// P2M where every box is one chunk (no box above P2M_CHUNK points): a box per HALF wavefront.  The kernel is
-// bound by its instruction stream, and a third of that stream is the sum of the 64 accumulators over the lanes;
-// with 32 lanes per box that sum covers two boxes at once (per pass of 32 accumulators a lane adds 32 rows
-// instead of 32 rows of one box out of 64), and a box of some 60 points takes two rounds of 32 lanes instead of
-// one round of 64, which costs the same.  Lane = point; the two halves of a wavefront work on boxes a and a + 1,
-// four such pairs per wavefront with the first loads of all of them in flight together.
-constexpr int P2M_NPAIR = 4;
-template <bool PERM>
-__global__ __launch_bounds__(64) void p2m34_pair_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
-                                                        const uint32_t *__restrict__ start,
-                                                        const int32_t *__restrict__ cell, int64_t nb, CentreArg C,
-                                                        float *__restrict__ W, WeightedArg A,
-                                                        const uint32_t *__restrict__ perm) {
-    // rows of the upper half are shifted by 32 floats so that the two halves read different banks
-    __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE + 32];
-    const int64_t bi = block_index();
-    const bool weighted = bi >= A.blocks;
-    const int64_t b0 = (weighted ? bi - A.blocks : bi) * (2 * P2M_NPAIR);
-    if (b0 >= nb) return;
-    if (weighted) W += A.dW;
-    const int lane = threadIdx.x, half = lane >> 5, t = lane & 31;
-    uint32_t k0[P2M_NPAIR], k1[P2M_NPAIR];
-    int64_t a[P2M_NPAIR];
-    bool on[P2M_NPAIR];
-    double ctr[P2M_NPAIR][3];
-#pragma unroll
-    for (int j = 0; j < P2M_NPAIR; ++j) {
-        a[j] = b0 + 2 * j + half;
-        on[j] = a[j] < nb;
-        const int64_t ac = on[j] ? a[j] : nb - 1;
-        k0[j] = start[ac];
-        k1[j] = on[j] ? start[ac + 1] : k0[j];   // a box beyond the end has no points
-#pragma unroll
-        for (int d = 0; d < 3; ++d) ctr[j][d] = C.alpha[d] + ((double)cell[ac * 3 + d] + 0.5) * C.edge;
+// the point that a lane loads: point number i of a run of 64 (HALF: of each half's run of 32) sits in lane i / 16 (i / 8) of quad
+// i % 16 (i % 8 of the half), so that a short run needs few steps
+template <bool HALF> __device__ inline uint32_t p2m34_point(int lane) {
+    return HALF ? 8u * (lane & 3) + ((lane & 31) >> 2) : 16u * (lane & 3) + (lane >> 2);
+}
+
+// a run of points, `left` of them or more to come (the same in every lane); points behind the end have b = 0
+template <int NS, bool HALF>
+__device__ inline void p2m34_run(P2mSums<NS> &S, const QuadNode &N, const float (&x)[3], float b, const double (&ctr)[3],
+                                 double inv_half, float kw, bool only, int left) {
+    constexpr int PER = HALF ? 8 : 16;
+    const float tx = (float)(((double)x[0] - ctr[0]) * inv_half), ty = (float)(((double)x[1] - ctr[1]) * inv_half),
+                tz = (float)(((double)x[2] - ctr[2]) * inv_half);
+    float be = 0.f;
+    if (NS == 2 || only) {
+        const float e = __builtin_amdgcn_exp2f(kw * fmaf(tz, tz, fmaf(ty, ty, tx * tx)));
+        if (NS == 2) be = b * e;
+        else b *= e;
     }
-    // Loads are unconditional, the index of a lane beyond the box clamped to the box's first point and its
-    // weight set to zero (a branch around them would make every load wait on its own).
-    auto load = [&](int j, uint32_t kb, float (&x)[3], float &bv) __attribute__((always_inline)) {
-        const uint32_t k = kb + (uint32_t)t;
-        const bool live = k < k1[j];
-        const uint32_t kc = live ? k : k0[j];
+    p2m34_step<NS, 0>(S, N, tx, ty, tz, b, be);
+    if (left > PER) p2m34_step<NS, 1>(S, N, tx, ty, tz, b, be);
+    if (left > 2 * PER) p2m34_step<NS, 2>(S, N, tx, ty, tz, b, be);
+    if (left > 3 * PER) p2m34_step<NS, 3>(S, N, tx, ty, tz, b, be);
+}
+
+// sums over the quads of the wavefront (HALF: of each half) to dst (the plain set) and dst + dset: every exchange between lanes
+// halves the registers as long as there are some to share out (set, then i2), 16 bytes (i1) a lane at the end
+template <int NS, bool HALF> __device__ inline void p2m34_store(const P2mSums<NS> &S, int lane, float *dst, int64_t dset, bool on) {
+    auto add32 = [](f4v a, f4v b) __attribute__((always_inline)) {   // lanes 0-31: a, 32-63: b
+        f4v r;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) x[d] = Xs[(int64_t)kc * 3 + d];
-        const float bl = bs[PERM ? perm[kc] : kc];
-        bv = live ? bl : 0.f;
+        for (int m = 0; m < 4; ++m) {
+            const float am = a[m], bm = b[m];
+            const auto w = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, am), __builtin_bit_cast(uint32_t, bm), false,
+                                                            false);
+            r[m] = __builtin_bit_cast(float, (uint32_t)w[0]) + __builtin_bit_cast(float, (uint32_t)w[1]);
+        }
+        return r;
     };
-    float x[P2M_NPAIR][3], bv[P2M_NPAIR];
+    auto add16 = [](f4v a, f4v b) __attribute__((always_inline)) {   // even rows of 16 lanes: a, odd rows: b
+        f4v r;
 #pragma unroll
-    for (int j = 0; j < P2M_NPAIR; ++j) load(j, k0[j], x[j], bv[j]);
-    const int rowbase = lane * TR_STRIDE + half * 32;
-#pragma unroll
-    for (int j = 0; j < P2M_NPAIR; ++j) {
-        if (b0 + 2 * j >= nb) break;   // wave-uniform: neither box of the pair exists
-        float acc[64];
-#pragma unroll
-        for (int q = 0; q < 64; ++q) acc[q] = 0.f;
-        float xc[3] = {x[j][0], x[j][1], x[j][2]}, bc = bv[j];
-        for (uint32_t kb = k0[j];;) {
-            // the next round (a box above 32 points) is loaded while this one is added; the wavefront goes on
-            // while either half has points left
-            const bool more = __ballot(kb + 32 < k1[j]) != 0ull;
-            float xn[3] = {0.f, 0.f, 0.f}, bn = 0.f;
-            if (more) load(j, kb + 32, xn, bn);
-            float Lx[4], Ly[4], Lz[4];
-            const float u2 = weights34(xc, ctr[j], C.inv_half, Lx, Ly, Lz);
-            if (weighted) bc *= __builtin_amdgcn_exp2f(A.kw * u2);
-#pragma unroll
-            for (int i3 = 0; i3 < 4; ++i3) {
-                const float zb = Lz[i3] * bc;
-#pragma unroll
-                for (int i2 = 0; i2 < 4; ++i2) {
-                    const float yz = Ly[i2] * zb;
-#pragma unroll
-                    for (int i1 = 0; i1 < 4; ++i1) acc[i1 + 4 * i2 + 16 * i3] = fmaf(Lx[i1], yz, acc[i1 + 4 * i2 + 16 * i3]);
-                }
-            }
-            if (!more) break;
-            kb += 32;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xc[d] = xn[d];
-            bc = bn;
+        for (int m = 0; m < 4; ++m) {
+            const float am = a[m], bm = b[m];
+            const auto w = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, am), __builtin_bit_cast(uint32_t, bm), false,
+                                                            false);
+            r[m] = __builtin_bit_cast(float, (uint32_t)w[0]) + __builtin_bit_cast(float, (uint32_t)w[1]);
         }
-        // sum over the 32 lanes of each half, 32 nodes at a time: lane l writes its row; lane t of a half adds
-        // the 32 rows of its half in column t
-        float *dst = W + a[j] * 64;
+        return r;
+    };
+    auto add8 = [](f4v a, f4v b) __attribute__((always_inline)) {    // lanes 0-7 of a row: a, 8-15: b
+        f4v r;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            __syncthreads();   // the sums of the previous pass (or pair) have been read
+        for (int m = 0; m < 4; ++m) r[m] = dpp_into<0x128, 0xC>(a[m], b[m]) + dpp_into<0x128, 0x3>(b[m], a[m]);
+        return r;
+    };
+    auto add4 = [](f4v a, f4v b) __attribute__((always_inline)) {    // even quads of a row: a, odd quads: b
+        f4v r;
 #pragma unroll
-            for (int g = 0; g < 8; ++g)
-                *reinterpret_cast<float4 *>(&tr[rowbase + 4 * g]) =
-                    make_float4(acc[32 * q + 4 * g], acc[32 * q + 4 * g + 1], acc[32 * q + 4 * g + 2], acc[32 * q + 4 * g + 3]);
-            __syncthreads();
-            const float *col = tr + (32 * half) * TR_STRIDE + half * 32 + t;
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+        for (int m = 0; m < 4; ++m) r[m] = dpp_into<0x114, 0xA>(a[m], b[m]) + dpp_into<0x104, 0x5>(b[m], a[m]);
+        return r;
+    };
+    auto fold8 = [](f4v a) __attribute__((always_inline)) {          // lanes 0-7 of a row: a
 #pragma unroll
-            for (int row = 0; row < 32; row += 4) {
-                s0 += col[(row + 0) * TR_STRIDE];
-                s1 += col[(row + 1) * TR_STRIDE];
-                s2 += col[(row + 2) * TR_STRIDE];
-                s3 += col[(row + 3) * TR_STRIDE];
-            }
-            if (on[j]) dst[32 * q + t] = (s0 + s1) + (s2 + s3);
+        for (int m = 0; m < 4; ++m) a[m] += dpp_into<0x108, 0xF>(0.f, a[m]);
+        return a;
+    };
+    auto fold4 = [](f4v a) __attribute__((always_inline)) {          // even quads: a (with lane 4 and more to the right)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[m] += dpp_into<0x104, 0xF>(0.f, a[m]);
+        return a;
+    };
+    const auto &v = S.v;
+    const int i3 = lane & 3, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1, b5 = lane >> 5;
+    f4v r;
+    int i2, set = 0;
+    if constexpr (HALF && NS == 2) {
+        const f4v e = add8(add16(v[0][0], v[1][0]), add16(v[0][2], v[1][2])), o = add8(add16(v[0][1], v[1][1]), add16(v[0][3], v[1][3]));
+        r = add4(e, o);
+        i2 = 2 * b3 + b2;
+        set = b4;
+    } else if constexpr (HALF) {
+        r = fold4(add8(add16(v[0][0], v[0][2]), add16(v[0][1], v[0][3])));
+        i2 = 2 * b4 + b3;
+        on = on && b2 == 0;
+    } else if constexpr (NS == 2) {
+        r = fold4(add8(add16(add32(v[0][0], v[1][0]), add32(v[0][2], v[1][2])), add16(add32(v[0][1], v[1][1]), add32(v[0][3], v[1][3]))));
+        i2 = 2 * b4 + b3;
+        set = b5;
+        on = on && b2 == 0;
+    } else {
+        r = fold4(fold8(add16(add32(v[0][0], v[0][2]), add32(v[0][1], v[0][3]))));
+        i2 = 2 * b5 + b4;
+        on = on && b2 == 0 && b3 == 0;
+    }
+    if (on) *reinterpret_cast<f4v *>(dst + set * dset + 16 * i3 + 4 * i2) = r;
+}
+
+template <int NS> __device__ inline void p2m34_zero(P2mSums<NS> &S) {
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) S.v[h][j] = f4v{0.f, 0.f, 0.f, 0.f};
+}
+
+// A wavefront per run of up to P2M_CHUNK points of one box (of the chunk list), or, where every box is one run (PAIR), a box
+// per HALF wavefront: its sum over the quads covers two boxes at once, and a box of some 40 points fills five steps of 8 instead
+// of three of 16.  The loads of two rounds are in flight; they are masked where they are used, and the last rounds load nothing, since a
+// branch around a load, or a select right behind it, makes the compiler wait for it there.
+// Both sets of 1e7 points in 262144 boxes 100 us (256 by the 64-accumulator form), of 3e6 points in 32768 boxes 27.7 (48), the plain
+// set of 2.5e5 points in 4096 boxes 4.2 (9.4).  One pair of boxes to a wavefront: with the loads of four pairs in flight 113,
+// 31, 7.5.
+template <int NS, bool PERM, bool PAIR>   // PERM: bs is in the caller's order, bs[perm[k]] the right-hand side of point k
+__global__ __launch_bounds__(64) void p2m34_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
+                                                   const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
+                                                   const uint32_t *__restrict__ chunk_box,
+                                                   const uint32_t *__restrict__ chunk_first, int64_t count, CentreArg C,
+                                                   float *__restrict__ W, float *__restrict__ Wpart, WeightedArg A,
+                                                   const uint32_t *__restrict__ perm) {
+    constexpr int RUN = PAIR ? 32 : 64, AHEAD = 2;
+    const int64_t cb = block_index() * (PAIR ? 2 : 1);
+    if (cb >= count) return;
+    const int lane = threadIdx.x;
+    const uint32_t pt = p2m34_point<PAIR>(lane);
+    const int64_t c = PAIR ? cb + (lane >> 5) : cb;
+    const bool on = c < count;   // PAIR: a box beyond the end repeats the last one, without points
+    int64_t a;
+    uint32_t k0, k1;
+    bool whole = true;
+    if constexpr (PAIR) {
+        a = on ? c : count - 1;
+        k0 = start[a];
+        const uint32_t e = start[a + 1];
+        k1 = on ? e : k0;
+    } else {
+        a = (uint32_t)__builtin_amdgcn_readfirstlane(chunk_box[c]);
+        const uint32_t c0 = chunk_first[a];
+        whole = chunk_first[a + 1] - c0 == 1;
+        k0 = start[a] + (uint32_t)(c - c0) * (uint32_t)P2M_CHUNK;
+        k1 = min(k0 + (uint32_t)P2M_CHUNK, start[a + 1]);
+    }
+    double ctr[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ctr[d] = C.alpha[d] + ((double)cell[a * 3 + d] + 0.5) * C.edge;
+    float x[AHEAD][3], bv[AHEAD];
+    auto load = [&](int s, uint32_t kb) __attribute__((always_inline)) {   // behind the end: the first point, a valid index
+        const uint32_t k = kb + pt, kc = k < k1 ? k : k0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[s][d] = Xs[(int64_t)kc * 3 + d];
+        bv[s] = bs[PERM ? perm[kc] : kc];
+    };
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) load(s, k0 + (uint32_t)(RUN * s));
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {   // else the first loads and the loop's become one, at its top and waited for there
+        asm volatile("" : "+v"(bv[s]));
+#pragma unroll
+        for (int d = 0; d < 3; ++d) asm volatile("" : "+v"(x[s][d]));
+    }
+    const QuadNode N = quad_node(lane & 3);
+    P2mSums<NS> S;
+    p2m34_zero(S);
+    const int nj = (int)(k1 - k0);   // the wavefront goes on while either half has points left
+    int left = PAIR ? max(__builtin_amdgcn_readlane(nj, 0), __builtin_amdgcn_readlane(nj, 32)) : __builtin_amdgcn_readfirstlane(nj);
+    uint32_t kb = k0;
+    for (; left > RUN * AHEAD; left -= RUN * AHEAD, kb += (uint32_t)(RUN * AHEAD)) {
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            const float xc[3] = {x[s][0], x[s][1], x[s][2]}, b = kb + (uint32_t)(RUN * s) + pt < k1 ? bv[s] : 0.f;
+            load(s, kb + (uint32_t)(RUN * (s + AHEAD)));
+            p2m34_run<NS, PAIR>(S, N, xc, b, ctr, C.inv_half, A.kw, A.only, RUN);
         }
     }
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {
+        if (left > RUN * s)
+            p2m34_run<NS, PAIR>(S, N, x[s], kb + (uint32_t)(RUN * s) + pt < k1 ? bv[s] : 0.f, ctr, C.inv_half, A.kw, A.only, left - RUN * s);
+    }
+    if (whole) p2m34_store<NS, PAIR>(S, lane, W + a * 64, A.dW, on);
+    else p2m34_store<NS, PAIR>(S, lane, Wpart + c * 64, A.dpart, true);
 }
 
 constexpr int L2P_NCH = 4;   // chunks per wavefront: their loads are in flight together (a chunk alone is a chain
@@ -2114,10 +2112,13 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
     }
 }
 
-// P2M and L2P of boxes with thousands of points: a wavefront per run of up to P2M_LONG points of one box.  The kernels above end
-// every 256 points with a sum over the lanes, or start with the 64 potentials in LDS; here that is 2 % of the work.
-// The loads of four rounds are in flight.  WEIGHTED: both sets of node weights / node potentials (the
-// weighted near pairs) from one reading of the points.
+// P2M and L2P of boxes with thousands of points: a wavefront per run of up to P2M_LONG points of one box.  L2P above starts every
+// 256 points with the 64 potentials in LDS; here that is 2 % of the work.  P2M above has few registers to sum over the lanes, and
+// pays with every factor evaluated four times; with a lane per point and 64 sums in it the sum over the lanes is 2 % of the
+// work here, and the multiply-adds cost less than the products of both (1e9 points, two sets: 6.0 ms, on the matrix cores 6.6;
+// 1e8 points, one set: 0.37, 0.52).  The loads of four rounds are in flight.  WEIGHTED: both sets of node weights / node
+// potentials (the weighted near pairs) from one reading of the points.
+constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
 constexpr int LONG_AHEAD = 4;
 template <bool WEIGHTED>
 __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
@@ -2125,7 +2126,7 @@ __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict_
                                                         const uint32_t *__restrict__ chunk_box,
                                                         const uint32_t *__restrict__ chunk_first, int64_t nchunks,
                                                         CentreArg C, float *__restrict__ W, float *__restrict__ Wpart,
-                                                        int64_t dW, int64_t dpart, float kw) {
+                                                        WeightedArg A) {
     constexpr int NS = WEIGHTED ? 2 : 1;
     __shared__ __attribute__((aligned(16))) float tr[64 * TR_STRIDE];
     const int64_t c = block_index();
@@ -2168,7 +2169,7 @@ __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict_
                 for (int i1 = 0; i1 < 4; ++i1) xy[i1 + 4 * i2] = Lx[i1] * Ly[i2];
 #pragma unroll
             for (int h = 0; h < NS; ++h) {
-                const float bh = h ? b * __builtin_amdgcn_exp2f(kw * u2) : b;
+                const float bh = h ? b * __builtin_amdgcn_exp2f(A.kw * u2) : b;
 #pragma unroll
                 for (int i3 = 0; i3 < 4; ++i3) {
                     const float zb = Lz[i3] * bh;
@@ -2178,11 +2179,11 @@ __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict_
             }
         }
     }
-    // sum over the lanes, 32 nodes at a time, as in p2m34_kernel
+    // sum over the lanes, 32 nodes at a time: a lane writes its row, lane (i, part) adds rows 32 part .. 32 part + 31 of column i
     const int i = lane & 31, part = lane >> 5;
 #pragma unroll
     for (int h = 0; h < NS; ++h) {
-        float *dst = c1 - c0 == 1 ? W + h * dW + (int64_t)a * 64 : Wpart + h * dpart + c * 64;
+        float *dst = c1 - c0 == 1 ? W + h * A.dW + (int64_t)a * 64 : Wpart + h * A.dpart + c * 64;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             __syncthreads();
@@ -2911,6 +2912,29 @@ static int single_chunks(const f3m_level &lv) { return lv.max_box <= P2M_CHUNK &
 // the runs of the depth are long ones (D = 3, 4 nodes per dimension)
 static bool long_chunks(const f3m_level &lv) { return lv.chunk > P2M_CHUNK; }
 
+// P2M of the runs of lv (3-D, 4 nodes): NS = 2 both sets of node weights, else one.  chunk_box and its like from `list`, boxes of lv.
+template <int NS>
+static void p2m34(const f3m_plan_s &P, const f3m_level &lv, const f3m_level &list, const float *X, const float *b, const CentreArg &C,
+                  float *W, const WeightedArg &A, const uint32_t *perm, hipStream_t st) {
+    const bool pairs = &lv == &list && single_chunks(lv);
+    const int64_t count = pairs ? lv.nb : list.nchunks;
+    if (long_chunks(list)) {
+        p2m34_long_kernel<(NS > 1)><<<grid_for(count), dim3(64), 0, st>>>(X, b, lv.start.p, lv.cell.p, list.chunk_box.p, list.chunk_first.p,
+                                                                         count, C, W, P.Wpart.p, A);
+        F3M_HIP(hipGetLastError());
+        return;
+    }
+    auto run = [&](auto kern) {
+        kern<<<grid_for(pairs ? cdiv(count, 2) : count), dim3(64), 0, st>>>(X, b, lv.start.p, lv.cell.p, list.chunk_box.p, list.chunk_first.p,
+                                                                            count, C, W, P.Wpart.p, A, perm);
+        F3M_HIP(hipGetLastError());
+    };
+    if (pairs && perm) run(p2m34_kernel<NS, true, true>);
+    else if (pairs) run(p2m34_kernel<NS, false, true>);
+    else if (perm) run(p2m34_kernel<NS, true, false>);
+    else run(p2m34_kernel<NS, false, false>);
+}
+
 // g = log2(e) l^2 / (2 gamma^2) of a depth: c l^2 bounds the magnitude of the expanded exponent terms in
 // box-local coordinates (|x'|^2 + |y'|^2 <= 7.5 D/3 l^2)
 static double gram_exponent_scale(const f3m_plan_s &P, int l) {
@@ -3112,18 +3136,8 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         const NodeArg N = make_nodes(p);
         const CentreArg CS = make_centre(P, l, true);   // source grid
         size_t sh = (size_t)(FF_TP * D * p + FF_TP) * sizeof(float);
-        if (D == 3 && p == 4 && long_chunks(sv))
-            p2m34_long_kernel<false><<<grid_for(sv.nchunks), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p,
-                                                                               sv.chunk_first.p, sv.nchunks, CS, P.W.p, P.Wpart.p,
-                                                                               0, 0, 0.f);
-        else if (D == 3 && p == 4 && single_chunks(sv))
-            p2m34_pair_kernel<false><<<grid_for(cdiv(sv.nb, 2 * P2M_NPAIR)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p, sv.nb,
-                                                                                        CS, P.W.p, WeightedArg{}, nullptr);
-        else if (D == 3 && p == 4)
-            p2m34_kernel<false><<<grid_for(cdiv(sv.nchunks, P2M_NCH)), dim3(64), 0, st>>>(Ys, bs, sv.start.p, sv.cell.p,
-                                                                  sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, CS,
-                                                                  P.W.p, P.Wpart.p, single_chunks(sv), WeightedArg{},
-                                                                  nullptr);
+        if (D == 3 && p == 4)
+            p2m34<1>(P, sv, sv, Ys, bs, CS, P.W.p, WeightedArg{}, nullptr, st);
         else if (r <= 64)
             p2m_kernel<D><<<grid_for(sv.nchunks), dim3(64), sh, st>>>(
                 Ys, bs, sv.start.p, sv.cell.p, sv.chunk_box.p, sv.chunk_first.p, sv.nchunks, p, r, CS, N,
@@ -3250,33 +3264,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
             {
                 hipEvent_t *ev = level_events(L);
                 ev[0] = now;
-                const bool pairs = single_chunks(lf);
-                const int64_t blocks = pairs ? cdiv(lf.nb, 2 * P2M_NPAIR) : cdiv(lf.nchunks, P2M_NCH);
-                const WeightedArg A{weighted ? blocks : INT64_MAX, (lf.nb + 1) * r, lf.nchunks * r, kw};
-                const dim3 grid = grid_for(weighted ? 2 * blocks : blocks);
-                auto p2m_long = [&](auto kern) {
-                    kern<<<grid_for(lf.nchunks), dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p,
-                                                                    lf.nchunks, make_centre(P, L), lf.Wl.p, P.Wpart.p, A.dW,
-                                                                    A.dpart, kw);
-                };
-                if (long_chunks(lf)) {
-                    if (weighted) p2m_long(p2m34_long_kernel<true>);
-                    else p2m_long(p2m34_long_kernel<false>);
-                } else if (pairs) {
-                    auto launch = [&](auto kern) {
-                        kern<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.nb, make_centre(P, L), lf.Wl.p, A, perm_in);
-                    };
-                    if (perm_in) launch(p2m34_pair_kernel<true>);
-                    else launch(p2m34_pair_kernel<false>);
-                } else {
-                    auto launch = [&](auto kern) {
-                        kern<<<grid, dim3(64), 0, st>>>(P.Xs.p, bs, lf.start.p, lf.cell.p, lf.chunk_box.p, lf.chunk_first.p, lf.nchunks,
-                                                        make_centre(P, L), lf.Wl.p, P.Wpart.p, 0, A, perm_in);
-                    };
-                    if (perm_in) launch(p2m34_kernel<true>);
-                    else launch(p2m34_kernel<false>);
-                }
-                F3M_HIP(hipGetLastError());
+                const WeightedArg A{(lf.nb + 1) * r, lf.nchunks * r, kw, false};
+                if (weighted) p2m34<2>(P, lf, lf, P.Xs.p, bs, make_centre(P, L), lf.Wl.p, A, perm_in, st);
+                else p2m34<1>(P, lf, lf, P.Xs.p, bs, make_centre(P, L), lf.Wl.p, A, perm_in, st);
                 if (lf.max_box > lf.chunk) {   // some box has several chunks
                     reduce_partials(P, lf, r, lf.Wl.p, st);
                     if (weighted) reduce_partials(P, lf, r, lf.Wl.p + A.dW, st, A.dpart);
@@ -3330,12 +3320,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
             f3m_level &ns = P.near_src;
             if (ns.nchunks > 0) {
                 WeightedArg A;
-                A.blocks = 0;
                 A.kw = kw;
-                p2m34_kernel<false><<<grid_for(cdiv(ns.nchunks, P2M_NCH)), dim3(64), 0, st>>>(
-                    Ys, bs, P.slev(L).start.p, P.slev(L).cell.p, ns.chunk_box.p, ns.chunk_first.p, ns.nchunks,
-                    make_centre(P, L, true), ns.Wl.p, P.Wpart.p, 0, A, nullptr);
-                F3M_HIP(hipGetLastError());
+                A.only = true;
+                p2m34<1>(P, P.slev(L), ns, Ys, bs, make_centre(P, L, true), ns.Wl.p, A, nullptr, st);
                 if (ns.max_box > ns.chunk) reduce_partials(P, ns, r, ns.Wl.p, st);
             }
             float *Vn = lf.Vl.p + lf.nb * r;
