@@ -145,9 +145,15 @@ __global__ __launch_bounds__(256) void keys_kernel(const float *__restrict__ X, 
 // result is deterministic (ascending key, then ascending original index).
 // ------------------------------------------------------------------------------------
 constexpr int RS_NT = 256;
-constexpr int RS_IPT = 32;
-constexpr int RS_TILE = RS_NT * RS_IPT;
+// Keys of a thread.  A tile of 32 x 256 keys writes runs of 32 keys to a digit, which large n need; with few keys its tiles leave compute
+// units idle, and a workgroup takes 21 us alone, a chain of 32 rounds.  Below 2^20 keys tiles of 8 x 256: a scatter pass
+// of 1e5 keys 21 -> 7.5 us, of 1e6 23.5 -> 11.6.  Plans of 1.5e6 and 2e6 points take the same time with either, of 6e6 929 us
+// with the large tiles and 971 with the small ones.
+constexpr int RS_IPT_MANY = 32, RS_IPT_FEW = 8;
+constexpr int64_t RS_FEW = 1 << 20;
+constexpr int RS_SLACK = RS_NT * RS_IPT_MANY;   // keys that may be read behind the last one
 
+template <int RS_IPT>
 __global__ __launch_bounds__(RS_NT) void rs_hist_kernel(const uint32_t *__restrict__ keys, int64_t n, int shift,
                                                         uint32_t *__restrict__ hist, int64_t nblk) {
     __shared__ uint32_t h[256];
@@ -159,6 +165,7 @@ __global__ __launch_bounds__(RS_NT) void rs_hist_kernel(const uint32_t *__restri
     __syncthreads();
     // all loads first, four keys each, without a bounds test (the key buffers carry a tile of slack behind the
     // last key); what lies behind the end is left out of the counts
+    constexpr int RS_TILE = RS_NT * RS_IPT;
     const int64_t base = tile * RS_TILE;
     const int64_t left = n - base;
     const int cntile = (int)(left < RS_TILE ? left : RS_TILE);
@@ -188,17 +195,17 @@ struct U32Out {
 };
 
 // Stable scatter of one tile of RS_TILE keys.  Tile order = (wave, round, lane): every wave
-// ranks its own 32 rounds of 64 keys with a private LDS counter array, with no block barrier
+// ranks its own RS_IPT rounds of 64 keys with a private LDS counter array, with no block barrier
 // inside the loop; then the tile is put in digit order in LDS and written out so that
 // consecutive threads write consecutive addresses of a digit run.  The buffers must be readable
 // for a whole tile behind the last key.
-template <bool FIRST>   // FIRST: the values are the positions themselves (vals_in is not read)
+template <bool FIRST, int RS_IPT>   // FIRST: the values are the positions themselves (vals_in is not read)
 __global__ __launch_bounds__(RS_NT, 4) void rs_scatter_kernel(const uint32_t *__restrict__ keys_in,
                                                            const uint32_t *__restrict__ vals_in,
                                                            uint32_t *__restrict__ keys_out,
                                                            uint32_t *__restrict__ vals_out, int64_t n, int shift,
                                                            const uint32_t *__restrict__ offs, int64_t nblk) {
-    constexpr int NW = RS_NT / 64;
+    constexpr int NW = RS_NT / 64, RS_TILE = RS_NT * RS_IPT;
     __shared__ uint32_t wcnt[NW][256];      // per wave: keys of each digit seen so far
     __shared__ uint32_t dstart[256];        // first tile-local position of each digit
     __shared__ uint32_t gbase[256];         // global position of the tile's first key of each digit
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(RS_NT, 4) void rs_scatter_kernel(const uint32_t *__
     __syncthreads();
     const int64_t base = tile * RS_TILE + (int64_t)w * (RS_IPT * 64);
     // Registers are what bounds the number of resident workgroups: ranks and positions are kept as 16-bit
-    // halves (a tile has 8192 places; 0xFFFF = out of range), the digits of the written keys as bytes.
+    // halves (a tile has at most 8192 places; 0xFFFF = out of range), the digits of the written keys as bytes.
     uint32_t key[RS_IPT], val[RS_IPT], rk[RS_IPT / 2];
     const int64_t left = n - tile * RS_TILE;
     const int cntile = (int)(left < RS_TILE ? left : RS_TILE);   // keys of this tile (the last one may be short)
@@ -269,7 +276,7 @@ __global__ __launch_bounds__(RS_NT, 4) void rs_scatter_kernel(const uint32_t *__
         dstart[tid] = ex;
     }
     __syncthreads();
-    // keys and values pass through the same 32 KB of LDS one after the other
+    // keys and values pass through the same LDS (32 KB) one after the other
 #pragma unroll
     for (int r = 0; r < RS_IPT; ++r) {
         const uint32_t rank = (rk[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
@@ -323,7 +330,9 @@ __global__ __launch_bounds__(RS_NT, 4) void rs_scatter_kernel(const uint32_t *__
 // place of keys_a from the second pass on, whose input then stays as it was (bits > 8).
 static bool radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint32_t *vals_b, uint32_t *keys_c, int64_t n,
                        int bits, hipStream_t st) {
-    int64_t nblk = cdiv(n, RS_TILE);
+    const bool few = n < RS_FEW;
+    const int64_t nblk = cdiv(n, RS_NT * (few ? RS_IPT_FEW : RS_IPT_MANY));
+    const dim3 grid((unsigned)((nblk + 7) / 8 * 8));   // a whole number of rounds over the dies
     DevBuf<uint32_t> hist;
     hist.alloc((size_t)nblk * 256);
     bool in_b = false, first = true;
@@ -332,14 +341,15 @@ static bool radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uin
         const uint32_t *vin = first ? nullptr : (in_b ? vals_b : vals_a);
         uint32_t *kout = in_b ? (keys_c ? keys_c : keys_a) : keys_b;
         uint32_t *vout = in_b ? vals_a : vals_b;
-        rs_hist_kernel<<<dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(RS_NT), 0, st>>>(kin, n, shift, hist.p, nblk);
+        if (few) rs_hist_kernel<RS_IPT_FEW><<<grid, dim3(RS_NT), 0, st>>>(kin, n, shift, hist.p, nblk);
+        else rs_hist_kernel<RS_IPT_MANY><<<grid, dim3(RS_NT), 0, st>>>(kin, n, shift, hist.p, nblk);
         F3M_HIP(hipGetLastError());
         exclusive_scan(U32In{hist.p}, nblk * 256, U32Out{hist.p}, nullptr, st);
-        const unsigned grid = (unsigned)((nblk + 7) / 8 * 8);   // a whole number of rounds over the dies
-        if (first)
-            rs_scatter_kernel<true><<<dim3(grid), dim3(RS_NT), 0, st>>>(kin, vin, kout, vout, n, shift, hist.p, nblk);
-        else
-            rs_scatter_kernel<false><<<dim3(grid), dim3(RS_NT), 0, st>>>(kin, vin, kout, vout, n, shift, hist.p, nblk);
+        auto scatter = [&](auto kern) { kern<<<grid, dim3(RS_NT), 0, st>>>(kin, vin, kout, vout, n, shift, hist.p, nblk); };
+        if (few && first) scatter(rs_scatter_kernel<true, RS_IPT_FEW>);
+        else if (few) scatter(rs_scatter_kernel<false, RS_IPT_FEW>);
+        else if (first) scatter(rs_scatter_kernel<true, RS_IPT_MANY>);
+        else scatter(rs_scatter_kernel<false, RS_IPT_MANY>);
         F3M_HIP(hipGetLastError());
         in_b = !in_b;
         first = false;
@@ -1444,8 +1454,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     // ---- keys, sort, gather
     for (const SetRef &S : sets) {
         // (one tile of slack behind the keys and the indices: the sort reads whole tiles)
-        S.keys->alloc((size_t)S.n + RS_TILE, tally);
-        S.perm->alloc((size_t)S.n + RS_TILE, tally);
+        S.keys->alloc((size_t)S.n + RS_SLACK, tally);
+        S.perm->alloc((size_t)S.n + RS_SLACK, tally);
         AlphaArg aa;
         for (int d = 0; d < F3M_MAX_DIM; ++d) aa.a[d] = S.alpha[d];
         keys_kernel<D><<<dim3((unsigned)cdiv(S.n, 256)), dim3(256), 0, st>>>(S.X, S.n, aa, P.scale, P.Lq, S.keys->p);
@@ -1464,9 +1474,9 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     int bits_sorted = 0;
     for (const SetRef &S : sets) {
         DevBuf<uint32_t> keys_b, perm_b;
-        if (may_group) keys_in.alloc((size_t)S.n + RS_TILE);
-        keys_b.alloc((size_t)S.n + RS_TILE);
-        perm_b.alloc((size_t)S.n + RS_TILE);
+        if (may_group) keys_in.alloc((size_t)S.n + RS_SLACK);
+        keys_b.alloc((size_t)S.n + RS_SLACK);
+        perm_b.alloc((size_t)S.n + RS_SLACK);
         int bits = P.E > 0.f ? D * P.Lq : 0;
         bits_sorted = bits;
         bool in_b;
