@@ -1913,9 +1913,10 @@ double near_interp_error(double E, int depth, double gamma) {
 // only F is interpolated: its fourth derivative is ((u - D) / gamma^2)^4 F, at most (1.5 l / gamma^2)^4 F for adjacent boxes
 // (|u| <= l / 2, |D| <= l), times (l / 2)^4, a quarter (the node polynomial) over 4!: (0.75 l^2 / gamma^2)^4 / 96 for one
 // interpolation.  (reach: the largest |D| / l of a near pair, 1 for one point set.  The grids of two sets are shifted against
-// each other, and |D| goes up to the far ratio: 1.25 instead of 0.75 with ratio 2, 2^-24 at l = 0.128 gamma.)  e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and
-// the node values of F go without e: three dimensions of either point, at most exp(6 l^2 / 8 gamma^2)), and the six
-// interpolations make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.
+// each other, and |D| goes up to the far ratio: 1.25 instead of 0.75 with ratio 2, 2^-24 at l = 0.128 gamma.)
+// e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and the node values of F
+// go without e: three dimensions of either point, at most exp(6 l^2 / 8 gamma^2)), and the six interpolations
+// make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.
 double near_weighted_error(double E, int depth, double gamma, double reach) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (gamma * gamma), L = 5.0 / 3.0;
     const double one = 0.5 * (reach + 0.5) * q, e1 = one * one * one * one / 96.0;
