@@ -1740,14 +1740,11 @@ static void for_nodes(int p, F &&f) {
 }
 
 // ------------------------------------------------------------------------------------
-// P2M and L2P for D = 3 with 4 nodes per dimension (r = 64 = one wavefront): one wave per
-// chunk, one lane per POINT.  The nodes are {1, 1/2, -1/2, -1}; the product-form basis of one
+// P2M and L2P for D = 3 with 4 nodes per dimension (r = 64).  The nodes are {1, 1/2, -1/2, -1}; the product-form basis of one
 // coordinate costs 4 subtractions and 10 multiplications.
-//   P2M: every lane keeps all 64 node sums of its own points in registers (64 FMAs per point
-//        after 20 multiplications for the partial products), and the 64 x 64 lane-by-node
-//        array is summed over lanes once per chunk through LDS (lane i ends up with node i).
-//   L2P: V of the box is wave-uniform (scalar operands); the tensor contraction is nested:
-//        64 + 16 + 4 FMAs per point.
+//   P2M: a quad of lanes per point, the 64 products on the matrix cores (p2m34_kernel); runs of thousands of points
+//        of one box: lane = point, the 64 node sums in its registers (p2m34_long_kernel).
+//   L2P: lane = point, the tensor contraction nested: 64 + 16 + 4 FMAs per point and set of potentials.
 // ------------------------------------------------------------------------------------
 __device__ inline void lagrange4(float t, float (&L)[4]) {
     const float d0 = t - 1.f, d1 = t - 0.5f, d2 = t + 0.5f, d3 = t + 1.f;

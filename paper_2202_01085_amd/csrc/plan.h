@@ -80,7 +80,7 @@ struct f3m_source {
     float alpha[F3M_MAX_DIM] = {0};
     f3m::DevBuf<uint32_t> keys, perm;   // [n]
     f3m::DevBuf<float> Xs;              // [n*D] coordinates in box order, padded
-    std::unique_ptr<f3m_route> route;   // large sets: the right-hand side comes into box order in three passes
+    std::unique_ptr<f3m_route> route;   // large sets: the right-hand side comes into box order in streaming passes
     f3m_level lev[F3M_MAX_LEVELS + 1];  // box tables and P2M work splits only (no lists)
 };
 
