@@ -203,6 +203,8 @@ int adaptive_nodes(double E, int depth, double gamma, int p);                   
 
 double near_interp_error(double E, int depth, double gamma);                    // D = 3, 4 nodes per dimension
 double near_weighted_error(double E, int depth, double gamma, double reach = 1.0);
+void product_depths(int L, int64_t leaf_boxes, bool leaf_far, bool leaf_near, bool two_sets, bool may_group, int weighted,
+                    int *near_depth, int *near_weighted, bool *grouped);
 
 // plan.hip
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
@@ -210,8 +212,9 @@ void compute_far_point_pairs(f3m_plan_s &P);   // near_point_pairs and lev[].far
 // route.hip: permutations of large vectors as three streaming passes with tables built once per plan
 bool route_two_passes(int64_t n);   // sizes below those of the three passes for which two pay
 void route_build(f3m_route &R, const uint32_t *perm, int64_t n, bool two, int64_t *tally, hipStream_t st);
-constexpr int ROUTE_GROUP_BOXES = 512;
-void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift, const uint32_t *box_keys, int64_t nb,
+// points are grouped by the boxes of a depth of at most this (3-D): its tables have a place for every cell, occupied or not
+constexpr int ROUTE_GROUP_DEPTH = 3, ROUTE_GROUP_BOXES = 1 << (3 * ROUTE_GROUP_DEPTH);
+void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int Lq, int depth, const uint32_t *box_keys, int64_t nb,
                        int64_t *tally, hipStream_t st);
 void route_scatter(const f3m_route &R, const float *in, const float *in2, float *out, float *tmp_a, float *tmp_b,
                    hipStream_t st);                                   // out[perm[k]] = in[k] (+ in2[k])

@@ -1428,9 +1428,6 @@ static void bulk_finish(const std::vector<SetRef> &sets, int L) {
         for (int l = 1; l <= L; ++l) sets[k].lev[l].max_box = (int64_t)bulk_words(k)[l];
 }
 
-// Weighted near pairs end at the first depth that allows it where the last one has this many boxes at least.
-constexpr int64_t WEIGHTED_MIN_BOXES = 8192;
-
 template <int D>
 static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st) {
     const int64_t n = P.n;
@@ -1466,7 +1463,7 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     // caller's order.  The depth, if the tree gets that far: the smooth one, or that of the weighted near pairs.
     bool may_group = false;
     if (D == 3 && !P.src && n >= P.route_min_n && P.rho == 0 && !P.force_all_near && P.E > 0.f)
-        for (int l = 1; l <= 3 && !may_group; ++l)
+        for (int l = 1; l <= ROUTE_GROUP_DEPTH && !may_group; ++l)
             may_group = smooth_rule((double)P.E, l, D, (double)P.gamma, (double)P.eta_smooth) ||
                         (l >= 2 && m2l_stencil_applies(P) && !P.adaptive_far && !(P.eta_smooth > 0.f) &&
                          near_weighted_error((double)P.E, l, (double)P.gamma) <= 0x1p-24);
@@ -1496,7 +1493,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
     }
     F3M_HIP(hipEventRecord(P.ev[2], st));
     ZeroList zeros;   // cleared when the plan is otherwise complete
-    // the points into box order, once the depth that the products end at is known
+    bool grouped = false;   // the points are only grouped by the boxes of the last depth of the products
+    // the points into box order, once that depth is known
     auto order_points = [&](size_t k) {
         const SetRef &S = sets[k];
         // 64 zero points of padding after the last point: kernels may read whole 32-point blocks
@@ -1506,9 +1504,9 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         // (route.hip); its points follow the same way when they have three coordinates.
         std::unique_ptr<f3m_route> &route = k ? P.src->route : P.route;
         const int last = P.last_depth();
-        if (may_group && P.lev[last].nb <= ROUTE_GROUP_BOXES && (P.lev[P.L].near_sz == 0 || !P.exact_near())) {
+        if (grouped) {
             route.reset(new f3m_route());
-            route_group_build(*route, keys_in.p, S.n, D * (P.Lq - last), P.lev[last].key.p, P.lev[last].nb, tally, st);
+            route_group_build(*route, keys_in.p, S.n, P.Lq, last, P.lev[last].key.p, P.lev[last].nb, tally, st);
         } else if ((S.n >= P.route_min_n || route_two_passes(S.n)) && bits_sorted > 0) {
             route.reset(new f3m_route());
             route_build(*route, S.perm->p, S.n, S.n < P.route_min_n, tally, st);
@@ -1650,18 +1648,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         if (bulk_depth > l) S.lev[l].cstart.release();
     }
     P.L = l;
-    // The tree is too coarse for the plain interpolation of near pairs, but not for that between weighted points: near pairs
-    // are interpolated at the first depth that allows it -- or, where the last depth has few boxes, at the last one, which
-    // costs nothing more (a few workgroups per depth).  Product of 1e7 points, lengthscale 0.1, depth 6 of 6: 2.36 -> 1.04 ms;
-    // four columns of 3e6 points, lengthscale 0.3, depth 5 of 6: 3.36 -> 1.14 ms; of 2e4 points, lengthscale 1, depth 3
-    // of 3: 84 -> 71 us.
-    // Also instead of the plain interpolation two or three depths further down, where that makes the boxes so few that the
-    // points need only be grouped by them: one pass each way instead of three (n = 1e9, lengthscale 1, depth 3 and not 5: 77.6 -> 60.6 ms for plan and
-    // product).
-    const bool group = may_group && weighted > 0 && P.lev[weighted].nb <= ROUTE_GROUP_BOXES;
-    if (group && P.near_depth > 0 && P.lev[P.near_depth].nb > ROUTE_GROUP_BOXES) P.near_depth = 0;
-    if (P.near_depth == 0 && weighted > 0)
-        P.near_weighted = group || P.src ? weighted : P.lev[l].nb < WEIGHTED_MIN_BOXES && P.lev[l].far_sz > 0 ? l : weighted;
+    product_depths(P.L, P.lev[l].nb, P.lev[l].far_sz > 0, P.lev[l].near_sz > 0, P.src != nullptr, may_group, weighted,
+                   &P.near_depth, &P.near_weighted, &grouped);
     for (int k = P.last_depth() + 1; k <= P.L; ++k) {   // not needed: the products end above
         P.lev[k].st_cand.release();
         P.lev[k].st_child.release();
@@ -1921,6 +1909,34 @@ double near_weighted_error(double E, int depth, double gamma, double reach) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (gamma * gamma), L = 5.0 / 3.0;
     const double one = 0.5 * (reach + 0.5) * q, e1 = one * one * one * one / 96.0;
     return e1 * std::exp(0.75 * q) * (std::pow(L, 6.0) - 1.0) / (L - 1.0);
+}
+
+// Weighted near pairs end at the first depth that allows it where the last one has this many boxes at least.
+constexpr int64_t WEIGHTED_MIN_BOXES = 8192;
+
+// The depth that the products end at, and whether the points need only be grouped by its boxes.  L: the last depth of the tree,
+// with leaf_boxes boxes and, or not, far and near pairs; near_depth, weighted: the first depths at which the near pairs may be
+// interpolated as they are and between weighted points (0: none; weighted comes first); may_group: the points may be grouped by the
+// boxes of a depth of at most ROUTE_GROUP_DEPTH.
+//
+// The tree is too coarse for the plain interpolation of near pairs, but not for that between weighted points: near pairs
+// are interpolated at the first depth that allows it -- or, where the last depth has few boxes, at the last one, which
+// costs nothing more (a few workgroups per depth).  Product of 1e7 points, lengthscale 0.1, depth 6 of 6: 2.36 -> 1.04 ms;
+// four columns of 3e6 points, lengthscale 0.3, depth 5 of 6: 3.36 -> 1.14 ms; of 2e4 points, lengthscale 1, depth 3
+// of 3: 84 -> 71 us.
+// Also instead of the plain interpolation two or three depths further down, where that makes the depth so coarse that the
+// points need only be grouped by its boxes: one pass each way instead of three (n = 1e9, lengthscale 1, depth 3 and not 5: 77.6 -> 60.6 ms
+// for plan and product).  What counts is the depth, not how many of its boxes hold points: points on a line or in a
+// plane, or a few clusters, have few boxes at deep depths, whose keys go beyond the tables of the grouping.
+void product_depths(int L, int64_t leaf_boxes, bool leaf_far, bool leaf_near, bool two_sets, bool may_group, int weighted,
+                    int *near_depth, int *near_weighted, bool *grouped) {
+    const bool group = may_group && weighted > 0 && weighted <= ROUTE_GROUP_DEPTH;
+    if (group && *near_depth > ROUTE_GROUP_DEPTH) *near_depth = 0;
+    *near_weighted = 0;
+    if (*near_depth == 0 && weighted > 0)
+        *near_weighted = group || two_sets ? weighted : leaf_boxes < WEIGHTED_MIN_BOXES && leaf_far ? L : weighted;
+    const int last = *near_depth ? *near_depth : *near_weighted ? *near_weighted : L;
+    *grouped = may_group && last <= ROUTE_GROUP_DEPTH && (!leaf_near || *near_depth || *near_weighted);
 }
 
 // Adaptive far-field rule of Sec. 4.3 on q = l^2 / (2 gamma^2): min(p, 3) nodes per dimension if

@@ -440,7 +440,8 @@ __global__ __launch_bounds__(RT_NT) void route_pick_kernel(const float *__restri
 }
 
 // ------------------------------------------------------------------------------------
-// One pass: points grouped by the boxes of one depth.  Digit of a point = rank of its box (lut[key >> shift]); inside a box the
+// One pass: points grouped by the boxes of one depth.  Digit of a point = rank of its box (lut[key >> shift], with
+// key >> shift below RG_NB: depth 3 at most); inside a box the
 // points keep the caller's order, tile by tile, so the order depends on nothing but the points.
 // ------------------------------------------------------------------------------------
 constexpr int RG_NB = ROUTE_GROUP_BOXES;
@@ -724,11 +725,14 @@ void route_build(f3m_route &R, const uint32_t *perm, int64_t n, bool two, int64_
     }
 }
 
-// Tables of the one pass that groups the points by the nb boxes of a depth: keys of the points in the caller's order,
-// box of a point = key >> shift, one of box_keys (ascending).
-void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int shift, const uint32_t *box_keys, int64_t nb,
+// Tables of the one pass that groups the points by the nb boxes of a depth (3-D): keys of the points, of depth Lq, in the caller's
+// order; the key of a point's box is one of box_keys (ascending).
+void route_group_build(f3m_route &R, const uint32_t *keys, int64_t n, int Lq, int depth, const uint32_t *box_keys, int64_t nb,
                        int64_t *tally, hipStream_t st) {
-    if (nb < 1 || nb > RG_NB) fail(F3M_ERR_HIP, "internal: too many boxes for the one-pass grouping");
+    // The table of ranks is read at the keys of the boxes: few OCCUPIED boxes of a deeper depth do not fit it.
+    if (depth < 0 || depth > ROUTE_GROUP_DEPTH || depth > Lq || nb < 1 || nb > RG_NB)
+        fail(F3M_ERR_HIP, "internal: too many boxes for the one-pass grouping");
+    const int shift = 3 * (Lq - depth);
     R.n = n;
     R.ntiles = cdiv(n, RT_TILE);
     R.grouped = true;

@@ -69,3 +69,39 @@ def test_grouped_points(n, dist, gamma, zeta, more):
         assert torch.equal(got, y)
     plan.close()
     ref.close()
+
+
+def thin_points(name, n):
+    """Point sets with few occupied boxes at deep depths: the keys there go beyond the 512 cells of depth 3."""
+    rng = np.random.default_rng(343)
+    X = rng.random((n, 3))
+    if name == "line":
+        X[:, 1] = X[:, 2] = X[:, 0]
+    elif name == "plane":
+        X[:, 2] = 0.25
+    elif name == "outliers":        # one cluster and two points far away: no far pairs at the depths down to the cluster
+        X = 0.45 + 0.08 * X
+        X[0], X[1] = 0.0, 1.0
+    else:                           # tight clusters in corners
+        X = 0.02 * X + np.array([[0.0, 0.0, 0.0], [0.9, 0.9, 0.9], [0.0, 0.0, 0.9]])[rng.integers(0, 3, n)]
+    return torch.from_numpy(X.astype(np.float32))
+
+
+@pytest.mark.parametrize("name", ["line", "plane", "outliers", "corners"])
+@pytest.mark.parametrize("gamma", [0.5, 0.8, 1.0, 2.0, 3.0, 8.0])
+def test_few_boxes_of_a_deep_depth(name, gamma):
+    n = 9_000
+    say("thin points %s gamma=%g" % (name, gamma))
+    X, b = thin_points(name, n), inputs.rhs_normal(n, 344)
+    ref = f3m.Plan(X.to(DEV), gamma, 4, 2.0, leaf_max=8, route_min_points=n + 1)
+    plan = f3m.Plan(X.to(DEV), gamma, 4, 2.0, leaf_max=8, route_min_points=1)
+    say("  depth %d, products end at: plain %d, weighted %d" % (plan.info().depth, plan.product_info().near_depth, plan.near_weighted()))
+    T = oracle.Tree(X.numpy(), theta=2.0, zeta=8)
+    want = T.apply(b.numpy(), float(np.float32(gamma)), 4)
+    y = plan.kmvm(b.to(DEV))
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy(), want, TOL_F3M, "vs CPU F3M")
+    assert_close(ref.kmvm(b.to(DEV)).cpu().numpy(), want, TOL_F3M, "the ungrouped plan")
+    assert np.array_equal(plan.perm(), ref.perm())
+    plan.close()
+    ref.close()
