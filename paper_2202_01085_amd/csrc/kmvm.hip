@@ -2870,7 +2870,8 @@ void upload_tables(f3m_plan_s &P, hipStream_t st) {
                     for (int i = 0; i < p; ++i)
                         for (int j = 0; j < p; ++j) {
                             const double o = (double)(S.omin[d] + k) + u[d];
-                            Gn[(((size_t)d * S.no + k) * p + i) * p + j] = (float)std::exp(2.0 * c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o)));
+                            Gn[(((size_t)d * S.no + k) * p + i) * p + j] =
+                                (float)(basis_scale() * std::exp(2.0 * c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o))));
                         }
         }
     }

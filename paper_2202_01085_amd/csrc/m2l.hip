@@ -816,7 +816,7 @@ void near_table(const f3m_plan_s &P, float *t) {
     for (int o = 0; o <= 1; ++o)
         for (int i = 0; i < 4; ++i)
             for (int j = 0; j < 4; ++j)
-                t[near_factor_index(o, i, j)] = (float)std::exp(c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o)));
+                t[near_factor_index(o, i, j)] = (float)(basis_scale() * std::exp(c * (s[i] * s[j] + 2.0 * o * (s[i] - s[j] - o))));
 }
 
 // W: weighted node weights of depth near_weighted with a row of zeros behind them

@@ -254,6 +254,13 @@ void run_far_points(f3m_plan_s &P, int level, const float *bs, float *ys, int om
 bool m2l_stencil_applies(const f3m_plan_s &P);   // D = 3, 4 nodes per dimension, far ratio 2
 void build_stencil_tables(f3m_plan_s &P, int level, hipStream_t st);   // after the lists of the depth exist
 bool stencil_tables_alloc(f3m_plan_s &P, int level, hipStream_t st);   // false: the depth has no such tables
+// The basis of 4 nodes is evaluated with the weights 2/3 and 4/3 rounded to fp32, both 3e-8 too large, so a product of P2M and L2P is
+// 1.8e-7 too large in 3-D whatever the points.  This is what takes it out of a factor of one dimension: the interpolated near pairs
+// replace exact sums, which have no such bias.
+inline double basis_scale() {
+    const double w = 1.5 * (double)(1.f / 1.5f);
+    return 1.0 / (w * w);
+}
 void near_table(const f3m_plan_s &P, float *t);                        // 16 factors of the weighted near pairs
 void run_near_weighted(f3m_plan_s &P, const float *W, float *V, hipStream_t st);
 bool m2l_stencil_small(const f3m_plan_s &P, int level);                // few parents: several depths may share a launch

@@ -76,3 +76,24 @@ def test_weighted_near_field_of_one_large_box():
     # all weights positive and every kernel value above 0.5: the error is that of the far pairs, boxes of edge 1/4 and less
     assert_close(y[rows].cpu().numpy(), want, TOL_F3M, "vs exact rows")
     plan.close()
+
+
+@pytest.mark.parametrize("two", [False, True])
+def test_no_bias_against_exact_near_sums(two):
+    """Positive weights, so that rounding in one direction shows: the mean difference from the same products with exact near
+    sums (which the small field of one point a pair, i.e. of none, asks for).  The fp32 basis is 3e-8 too large in each of the six
+    applications, 1.8e-7, of which the near pairs, a quarter of the sum here, would pass on 4e-8; what remains are the roundings of the
+    table's factors, some 2e-8 in any direction for one lengthscale, and less over five."""
+    n = 3_000
+    X, b = inputs.points_uniform(n, 3, 31, device=DEV), inputs.rhs_normal(n, 32, device=DEV).abs()
+    more = dict(Y=inputs.points_uniform(n, 3, 33, device=DEV)) if two else {}
+    mean = []
+    for gamma in (2.0, 2.15, 2.3, 3.0, 4.0):
+        plan, exact = f3m.Plan(X, gamma, 4, 2.0, **more), f3m.Plan(X, gamma, 4, 2.0, small_field=1, **more)
+        assert plan.near_weighted() == plan.info().depth == exact.info().depth == 2 and exact.near_weighted() == 0
+        y, y_exact = plan.kmvm(b).double(), exact.kmvm(b).double()
+        mean.append(float(((y - y_exact) / y_exact).mean()))
+        plan.close()
+        exact.close()
+    say("  mean differences " + " ".join("%.1e" % m for m in mean))
+    assert abs(sum(mean) / len(mean)) <= 2e-8
