@@ -2117,6 +2117,11 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
 // potentials (the weighted near pairs) from one reading of the points.
 constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
 constexpr int LONG_AHEAD = 4;
+// Points of a run whose node sums stay in fp32: 16 to a lane, then fp64.  With all 2048 points of a run in fp32, over the lanes too,
+// sums that cancel were off by three times as much as with runs of 256 points (4.8e-9 of the norm of the weights,
+// 1.5e-9; now 1.2e-9).  It costs nothing that shows: 1e9 points 61.7 and 62.1 ms, runs of one side differ by 2.3 %.
+constexpr int LONG_FP32 = 1024;
+static_assert(LONG_FP32 % (64 * LONG_AHEAD) == 0, "whole rounds of loads");
 template <bool WEIGHTED>
 __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict__ Xs, const float *__restrict__ bs,
                                                         const uint32_t *__restrict__ start, const int32_t *__restrict__ cell,
@@ -2147,59 +2152,70 @@ __global__ __launch_bounds__(64) void p2m34_long_kernel(const float *__restrict_
     };
 #pragma unroll
     for (int s = 0; s < LONG_AHEAD; ++s) load(s, k0 + 64u * s);
-    float acc[NS][64];
+    // sums over the lanes so far: node 32 q + i in lanes i and 32 + i, half of the rows each
+    const int i = lane & 31, part = lane >> 5;
+    double sum[NS][2];
 #pragma unroll
-    for (int h = 0; h < NS; ++h)
+    for (int h = 0; h < NS; ++h) sum[h][0] = sum[h][1] = 0.0;
+    uint32_t kb = k0;
+    do {
+        float acc[NS][64];
 #pragma unroll
-        for (int q = 0; q < 64; ++q) acc[h][q] = 0.f;
-    for (uint32_t kb = k0; kb < k1; kb += 64u * LONG_AHEAD) {
+        for (int h = 0; h < NS; ++h)
 #pragma unroll
-        for (int s = 0; s < LONG_AHEAD; ++s) {
-            float Lx[4], Ly[4], Lz[4];
-            const float u2 = weights34(x[s], ctr, C.inv_half, Lx, Ly, Lz);
-            const float b = bv[s];
-            load(s, kb + 64u * (s + LONG_AHEAD));
-            float xy[16];
+            for (int q = 0; q < 64; ++q) acc[h][q] = 0.f;
+        const uint32_t ke = min(kb + (uint32_t)LONG_FP32, k1);
+        for (; kb < ke; kb += 64u * LONG_AHEAD) {
 #pragma unroll
-            for (int i2 = 0; i2 < 4; ++i2)
+            for (int s = 0; s < LONG_AHEAD; ++s) {
+                float Lx[4], Ly[4], Lz[4];
+                const float u2 = weights34(x[s], ctr, C.inv_half, Lx, Ly, Lz);
+                const float b = bv[s];
+                load(s, kb + 64u * (s + LONG_AHEAD));
+                float xy[16];
 #pragma unroll
-                for (int i1 = 0; i1 < 4; ++i1) xy[i1 + 4 * i2] = Lx[i1] * Ly[i2];
+                for (int i2 = 0; i2 < 4; ++i2)
 #pragma unroll
-            for (int h = 0; h < NS; ++h) {
-                const float bh = h ? b * __builtin_amdgcn_exp2f(A.kw * u2) : b;
+                    for (int i1 = 0; i1 < 4; ++i1) xy[i1 + 4 * i2] = Lx[i1] * Ly[i2];
 #pragma unroll
-                for (int i3 = 0; i3 < 4; ++i3) {
-                    const float zb = Lz[i3] * bh;
+                for (int h = 0; h < NS; ++h) {
+                    const float bh = h ? b * __builtin_amdgcn_exp2f(A.kw * u2) : b;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) acc[h][q + 16 * i3] = fmaf(xy[q], zb, acc[h][q + 16 * i3]);
+                    for (int i3 = 0; i3 < 4; ++i3) {
+                        const float zb = Lz[i3] * bh;
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) acc[h][q + 16 * i3] = fmaf(xy[q], zb, acc[h][q + 16 * i3]);
+                    }
                 }
             }
         }
-    }
-    // sum over the lanes, 32 nodes at a time: a lane writes its row, lane (i, part) adds rows 32 part .. 32 part + 31 of column i
-    const int i = lane & 31, part = lane >> 5;
+        // sum over the lanes, 32 nodes at a time: a lane writes its row, lane (i, part) adds rows 32 part .. 32 part + 31 of column i
+#pragma unroll
+        for (int h = 0; h < NS; ++h)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                __syncthreads();
+#pragma unroll
+                for (int g = 0; g < 8; ++g)
+                    *reinterpret_cast<float4 *>(&tr[lane * TR_STRIDE + 4 * g]) = make_float4(
+                        acc[h][32 * q + 4 * g], acc[h][32 * q + 4 * g + 1], acc[h][32 * q + 4 * g + 2], acc[h][32 * q + 4 * g + 3]);
+                __syncthreads();
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int row = 0; row < 32; row += 2) {
+                    s0 += (double)tr[(32 * part + row) * TR_STRIDE + i];
+                    s1 += (double)tr[(32 * part + row + 1) * TR_STRIDE + i];
+                }
+                sum[h][q] += s0 + s1;
+            }
+    } while (kb < k1);
 #pragma unroll
     for (int h = 0; h < NS; ++h) {
         float *dst = c1 - c0 == 1 ? W + h * A.dW + (int64_t)a * 64 : Wpart + h * A.dpart + c * 64;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            __syncthreads();
-#pragma unroll
-            for (int g = 0; g < 8; ++g)
-                *reinterpret_cast<float4 *>(&tr[lane * TR_STRIDE + 4 * g]) = make_float4(
-                    acc[h][32 * q + 4 * g], acc[h][32 * q + 4 * g + 1], acc[h][32 * q + 4 * g + 2], acc[h][32 * q + 4 * g + 3]);
-            __syncthreads();
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-            for (int row = 0; row < 32; row += 4) {
-                s0 += tr[(32 * part + row + 0) * TR_STRIDE + i];
-                s1 += tr[(32 * part + row + 1) * TR_STRIDE + i];
-                s2 += tr[(32 * part + row + 2) * TR_STRIDE + i];
-                s3 += tr[(32 * part + row + 3) * TR_STRIDE + i];
-            }
-            float t = (s0 + s1) + (s2 + s3);
-            t += __shfl_xor(t, 32, 64);
-            if (part == 0) dst[32 * q + i] = t;
+            const double t = sum[h][q] + __shfl_xor(sum[h][q], 32, 64);
+            if (part == 0) dst[32 * q + i] = (float)t;
         }
     }
 }
