@@ -74,11 +74,17 @@ typedef struct {
                                summed directly (exactly) at that depth, whatever its distance, and is not
                                divided further.  0 (default) = off; the paper suggests rho = 2 * nodes per
                                box. */
-    int32_t route_min_points; /* a point set with at least this many points moves b, y and its own coordinates
-                               between the caller's order and the box order in three streaming passes through
-                               LDS instead of one random gather or scatter (same values, bit for bit); 0 =
-                               library default (2^24: below it the caches hold the vectors).  A smaller value
-                               lets tests reach that path on small inputs. */
+    int32_t route_min_points; /* how b, y and the coordinates of a point set move between the caller's order and the
+                               box order: in streaming passes through LDS, or in one random gather or scatter.
+                               0 = library default: two passes from 2^21 to 14 680 064 points, three from 2^24
+                               on, else directly.  A value > 0: three passes for sets of at least that many
+                               points, below it directly (so a value above the size switches the passes off, a
+                               small one lets tests reach them on small inputs).  Same values, bit for bit,
+                               with one exception: where the default or the value calls for three passes, one
+                               3-D set whose products end at depth 3 or above is only grouped by the boxes of
+                               that depth, in one pass; near pairs are then interpolated there, and sums are
+                               made in another order.  Tables and work vectors take 12 bytes a point with
+                               two passes, 14 with three, 2 when grouped. */
 } f3m_options;
 
 typedef struct {

@@ -105,7 +105,8 @@ static f3m_status make_plan(const float *X, int64_t n, const float *Y, int64_t n
         P->eta_smooth = opt ? opt->eta_smooth : 0.f;
         P->adaptive_far = opt ? (opt->adaptive_far != 0) : 0;
         P->rho = opt ? opt->small_field : 0;
-        P->route_min_n = (opt && opt->route_min_points > 0) ? opt->route_min_points : ((int64_t)1 << 24);
+        P->route_given = opt && opt->route_min_points > 0;
+        P->route_min_n = P->route_given ? opt->route_min_points : ((int64_t)1 << 24);
         F3M_HIP(hipGetDevice(&P->device));
         if (two_sets) {
             P->src.reset(new f3m_source());

@@ -56,7 +56,7 @@ struct f3m_level {
                                         // them for the weighted near pairs
 };
 
-// Tables of the three-pass permutation between the caller's order and the box order of one point set
+// Tables of the permutation in one, two or three passes between the caller's order and the box order of one point set
 // (route.hip): per pass the place of every value in the LDS copy of its tile, per tile the first place of each
 // digit and where the tile's run of each digit lies in the next order.
 struct f3m_route {
@@ -165,9 +165,10 @@ struct f3m_plan_s {
                                         // straight from the points
     struct { float *p = nullptr; } transfer;   // [2][4][4] parent basis at the child's nodes
     f3m::DevBuf<float> tables;          // gtab of every depth, near_tab and transfer
-    // large n: both permutations of a product run as three streaming passes (route.hip); the two work
+    // large n: both permutations of a product run as streaming passes (route.hip); the two work
     // vectors hold max(n, sources) floats each
-    int64_t route_min_n = 0;                    // the passes are used from this many points on
+    int64_t route_min_n = 0;                    // three passes (one: grouped) are used from this many points on
+    bool route_given = false;                   // the caller named that number: below it no two passes either
     std::unique_ptr<f3m_route> route;           // of the targets (and of the sources of a one-set plan)
     f3m::DevBuf<float> route_a, route_b;
     const f3m_route *sroute() const { return src ? src->route.get() : route.get(); }
@@ -209,7 +210,7 @@ void product_depths(int L, int64_t leaf_boxes, bool leaf_far, bool leaf_near, bo
 // plan.hip
 void build_plan(f3m_plan_s &P, const float *X, const float *Y, hipStream_t st);   // Y == nullptr: one set (P.src set otherwise)
 void compute_far_point_pairs(f3m_plan_s &P);   // near_point_pairs and lev[].far_point_pairs, once (synchronises)
-// route.hip: permutations of large vectors as three streaming passes with tables built once per plan
+// route.hip: permutations of large vectors as streaming passes with tables built once per plan
 bool route_two_passes(int64_t n);   // sizes below those of the three passes for which two pay
 void route_build(f3m_route &R, const uint32_t *perm, int64_t n, bool two, int64_t *tally, hipStream_t st);
 // points are grouped by the boxes of a depth of at most this (3-D): its tables have a place for every cell, occupied or not

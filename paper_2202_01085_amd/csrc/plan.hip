@@ -1500,14 +1500,14 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         // 64 zero points of padding after the last point: kernels may read whole 32-point blocks
         S.Xs->alloc(((size_t)S.n + PAD_POINTS) * D, tally);
         zeros.add(S.Xs->p + (size_t)S.n * D, (size_t)PAD_POINTS * D);
-        // A large set goes through the three-pass permutation, whose tables also serve every product
+        // A large set goes through the permutation in streaming passes, whose tables also serve every product
         // (route.hip); its points follow the same way when they have three coordinates.
         std::unique_ptr<f3m_route> &route = k ? P.src->route : P.route;
         const int last = P.last_depth();
         if (grouped) {
             route.reset(new f3m_route());
             route_group_build(*route, keys_in.p, S.n, P.Lq, last, P.lev[last].key.p, P.lev[last].nb, tally, st);
-        } else if ((S.n >= P.route_min_n || route_two_passes(S.n)) && bits_sorted > 0) {
+        } else if ((S.n >= P.route_min_n || (!P.route_given && route_two_passes(S.n))) && bits_sorted > 0) {
             route.reset(new f3m_route());
             route_build(*route, S.perm->p, S.n, S.n < P.route_min_n, tally, st);
         }

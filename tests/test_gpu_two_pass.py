@@ -1,5 +1,5 @@
-"""The two-pass permutation (2^21 points and more) moves data and nothing else: the bits of the plan that gathers and scatters
-directly (the option route_min_points above the size, which leaves sizes below 2^21 and above 28 * 2^19 to the direct way)."""
+"""The two-pass permutation (the default from 2^21 to 512 x 28 x 1024 points) moves data and nothing else: the bits of the plan that
+gathers and scatters directly (the option route_min_points above the size) and of the one that takes three passes (below it)."""
 import pytest
 import torch
 
@@ -11,25 +11,33 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# 8192 to a tile: the smallest, a last tile of one, full; 20480; 28672 and the largest.  Every point its own weight, and a
-# kernel so narrow that a product is the right-hand side itself up to near neighbours: a misplaced value shows.
+DIRECT = 2 ** 31 - 1      # as route_min_points: no passes at any size
+
+
+# 8192 values to a tile: the smallest, a last tile of one, full; 20480; 28672 and the largest.  The kernel couples neighbours, so
+# a value, a point or a result in another's place changes the sums.
 @pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1, 512 * 8192, 512 * 8192 + 1, 10_000_000, 512 * 20480 + 1, 512 * 28672])
-def test_two_passes_put_every_value_in_its_place(n):
+def test_two_passes_equal_the_direct_way_at_every_tile(n):
     say("two passes n=%d" % n)
     X = inputs.points_uniform(n, 3, 371, device=DEV)
     b = inputs.rhs_normal(n, 372, device=DEV)
-    plan = f3m.Plan(X, 1e-6, 4, 2.0)
-    y = plan.kmvm(b)
-    # neighbours closer than a few 1e-6 are rare: all but a few rows are the right-hand side bit for bit
-    same = (y == b).sum().item()
-    assert same >= n - 2_000
-    y2 = plan.kmvm(-b)
-    assert torch.equal(y2, -y)
-    plan.close()
+    y = {}
+    for min_points in (0, DIRECT):
+        plan = f3m.Plan(X, 0.02, 4, 2.0, route_min_points=min_points)
+        y[min_points] = plan.kmvm(b)
+        tables = plan.info().device_bytes
+        plan.close()
+        if min_points:
+            assert with_passes - tables >= 12 * n       # the other plan has the tables and work vectors of two passes
+        with_passes = tables
+    assert torch.equal(y[0], y[DIRECT])
+    rows = inputs.sample_rows(n, 200, 373).to(DEV)
+    want = f3m.direct_kmvm_rows_f64(X, b, 0.02, rows)
+    assert float((y[0][rows] - want).norm() / want.norm()) <= 1e-2       # the error of 4 nodes; a wrong place gives 1
 
 
-def test_two_passes_equal_the_direct_way():
-    """The same points with the two passes and as the targets of a plan whose sources go the direct way."""
+def test_two_passes_equal_three():
+    """Targets, sources, one set, several right-hand sides and the solver."""
     n, m = 2_200_001, 50_000
     X = inputs.points_uniform(n, 3, 373, device=DEV)
     Y = X[:: n // m][:m].contiguous()
