@@ -4,15 +4,17 @@
 // Textbook Hestenes-Stiefel recurrences from x_0 = 0.  Vectors are fp32 in HBM; every inner product
 // is accumulated in fp64 in a fixed order (grid-stride partial sums, which every block of the next pass adds up for
 // itself), and the step lengths stay on the device, so an iteration costs one f3m_kmvm and three fused vector passes
-// (48 n bytes).  The host reads the residual of an iteration from its own memory while the next one runs; the device stops by itself (a
-// flag that keeps x from changing).  With a pass for every sum and a copy and a wait in every iteration, ten iterations of
-// 2.5e5 points took 2.14 ms, now 1.81.
+// (48 n bytes).  The host reads the residual of an iteration from its own memory while the next one runs, as long as the tolerance is far
+// (cg_loop.h); should an iteration have been launched that was not needed, the device stops by itself (a flag that keeps x from changing)
+// and the solve ends after that iteration's product.  With a pass for every sum and a copy and a wait in every iteration, ten
+// iterations of 2.5e5 points took 2.14 ms, now 1.81.
 // The solve works in the plan's box order: b is permuted once on the way in and x once on the
 // way out (inner products do not depend on the order), so the products inside the loop skip
 // both permutations of f3m_kmvm.
 #include <cmath>
 #include <vector>
 
+#include "cg_loop.h"
 #include "plan.h"
 
 namespace f3m {
@@ -169,32 +171,32 @@ void run_cg(f3m_plan_s &P, float lambda, const float *b, float *x, int max_iter,
     } ev(P.device);
     for (hipEvent_t &e : ev.e) e = event_get();
     auto slot = [&](int k) { return words + W_SLOT + W_PER * (k % W_SLOTS); };
-    // the result of iteration `it`: true if it was the last
-    auto look = [&] {
-        F3M_HIP(hipEventSynchronize(ev.e[it % W_SLOTS]));
-        const double rs = slot(it)[0], pq = slot(it)[1];
-        const bool last = slot(it)[2] != 0.0;
-        ++it;
+    // the result of iteration k: true if it was the last
+    auto look = [&](int k, double *residual) {
+        F3M_HIP(hipEventSynchronize(ev.e[k % W_SLOTS]));
+        const double rs = slot(k)[0], pq = slot(k)[1];
+        const bool last = slot(k)[2] != 0.0;
+        it = k + 1;
         if (!(pq > 0.0) || !std::isfinite(rs)) {
             if (iters_host) *iters_host = it;
             fail(F3M_ERR_BREAKDOWN,
                  "conjugate gradients broke down: p.(K + lambda I)p is not positive (the approximate operator is not "
                  "positive definite along a search direction; raise lambda or the accuracy of the plan)");
         }
+        *residual = std::sqrt(rs);
         if (history_host) history_host[it] = (float)(std::sqrt(rs) / nb);
         return last;
     };
-    bool ended = !(nb > 0.0);
-    for (int k = 0; k < max_iter && !ended; ++k) {   // k: iterations launched; the host looks at one while the next runs
+    const double limit = (double)tol * nb;
+    auto launch = [&](int k) {
         run_kmvm(P, p.p, q.p, st, true);
         cg_shift_dot_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(p.p, q.p, lambda, n, part.p);
         cg_update_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(xs.p, r.p, p.p, q.p, scal.p, k & 1, part.p, n, part2.p);
-        cg_direction_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(p.p, r.p, scal.p, k & 1, part2.p, (double)tol * nb, n, slot(k));
+        cg_direction_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(p.p, r.p, scal.p, k & 1, part2.p, limit, n, slot(k));
         F3M_HIP(hipGetLastError());
         F3M_HIP(hipEventRecord(ev.e[k % W_SLOTS], st));
-        if (k > 0) ended = look();
-        if (k + 1 == max_iter && !ended) (void)look();
-    }
+    };
+    cg_iterate(nb > 0.0 ? max_iter : 0, nb, limit, launch, look);
     if (iters_host) *iters_host = it;
     if (grouped) route_scatter(*P.route, xs.p, nullptr, x, nullptr, nullptr, st);
     else cg_unpermute_kernel<<<dim3(blocks), dim3(CG_NT), 0, st>>>(xs.p, P.perm.p, n, x);
