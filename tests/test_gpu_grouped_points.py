@@ -71,6 +71,24 @@ def test_grouped_points(n, dist, gamma, zeta, more):
     ref.close()
 
 
+def test_solve_to_a_tolerance_on_grouped_points():
+    """The tree goes deeper than the depth the points are grouped by; the solver's vectors are in the grouped order."""
+    n, gamma, lam = 40_000, 1.0, 4_000.0
+    X, b = points("uniform", n).to(DEV), inputs.rhs_normal(n, 345, device=DEV)
+    plan = f3m.Plan(X, gamma, 4, 2.0, leaf_max=16, route_min_points=1)
+    ref = f3m.Plan(X, gamma, 4, 2.0, leaf_max=16, route_min_points=n + 1)
+    assert 0 < plan.near_weighted() <= 3 < plan.info().depth
+    (x, it, h), (x_ref, it_ref, h_ref) = (p.cg_solve(b, lam, tol=1e-4, max_iter=200) for p in (plan, ref))
+    say("  %d and %d iterations" % (it, it_ref))
+    assert it < 200 and abs(it - it_ref) <= 1 and h[-1] <= 1e-4 and (h[:-1] > 1e-4).all() and len(h) == it + 1
+    # both solve their system to 1e-4 of |b|, and the smallest eigenvalue is lam
+    assert float((x - x_ref).norm()) <= 2e-4 * float(b.norm()) / lam
+    res = plan.kmvm(x) + lam * x - b
+    assert float(res.norm() / b.norm()) <= 1.1e-4
+    plan.close()
+    ref.close()
+
+
 def thin_points(name, n):
     """Point sets with few occupied boxes at deep depths: the keys there go beyond the 512 cells of depth 3."""
     rng = np.random.default_rng(343)
