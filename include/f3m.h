@@ -107,7 +107,7 @@ typedef struct {
                                                   near_point_pairs they add up to n*n */
     int64_t near_point_pairs;                  /* sum of |p||q| over the near pairs of depth L: the point pairs
                                                   a product sums exactly, unless it interpolates them
-                                                  (f3m_product_info.near_depth > 0) */
+                                                  (f3m_product_info.near_depth or f3m_plan_near_weighted > 0) */
     int64_t device_bytes;                      /* device memory held by the plan */
     int32_t smooth_depth;                      /* depth whose adjacent pairs are interpolated (smooth
                                                   field), -1 if none */
@@ -160,7 +160,9 @@ f3m_status f3m_plan_ex(const float *X, int64_t n, int D, float lengthscale, int 
  *   Wide kernels: in 3-D with 4 nodes per dimension, one point set, eta = 2 and none of the options of
  *   Sec. 4.2 and 4.3, the product ends at the first depth >= 2 whose adjacent pairs too are interpolated to
  *   within 2^-24 (the rounding unit of fp32; boxes with an edge of at most 0.0316 lengthscales), and has no
- *   exact sums then.  f3m_plan_product_info reports that depth.
+ *   exact sums then.  f3m_plan_product_info reports that depth.  Narrower ones, and two point sets with
+ *   eta <= 4: where a depth >= 2 allows it (edges of at most 0.166 lengthscales, 0.128 for two sets with eta = 2)
+ *   the near pairs are interpolated between weighted points, see f3m_plan_near_weighted.
  *   b, y   device fp32[n], caller's order; y is overwritten; they must not overlap.
  *   Asynchronous on `stream`: the call only enqueues kernels, it allocates nothing and never waits for
  *   the device (every workspace was sized by f3m_plan); one call in flight per plan (the plan holds the

@@ -3355,6 +3355,9 @@ static void run_kmvm_d(f3m_plan_s &P, const float *b, float *y, hipStream_t st, 
         {
             hipEvent_t *ev = level_events(L);
             if (P.tree_lmin == L) ev[4] = now;
+            // The L2P adds the near field, so it waits for it; without that it would overlap, and a pass would add and scatter (product of
+            // 1e6 points, exact near field on the second stream: 270 us, 277 with the pass; 2e6 normal 1080 and 1109; below 1e4 points the
+            // two differ by less than 2 %).
             if (side && direct_out) {   // the near field may be what is waited for: not part of the downward pass
                 P.t_wait0 = mark();
                 F3M_HIP(hipStreamWaitEvent(st, P.ev_join, 0));

@@ -1904,7 +1904,9 @@ double near_interp_error(double E, int depth, double gamma) {
 // each other, and |D| goes up to the far ratio: 1.25 instead of 0.75 with ratio 2, 2^-24 at l = 0.128 gamma.)
 // e(u) e(w) F is at most exp(l^2 / 8 gamma^2) between the nodes (F is taken at another w than e, and the node values of F
 // go without e: three dimensions of either point, at most exp(6 l^2 / 8 gamma^2)), and the six interpolations
-// make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.
+// make it 1 + L + ... + L^5 times that.  2^-24 at l = 0.166 gamma.  That is the worst sum of six worst errors: there the largest
+// error of a pair is 5e-9 and the root of the mean square 9e-10, a sixtieth of fp32 rounding; the sum over the near boxes of
+// evenly spread points with equal weights is off by 5e-10 of itself.
 double near_weighted_error(double E, int depth, double gamma, double reach) {
     const double l = E / std::ldexp(1.0, depth), q = l * l / (gamma * gamma), L = 5.0 / 3.0;
     const double one = 0.5 * (reach + 0.5) * q, e1 = one * one * one * one / 96.0;

@@ -583,8 +583,10 @@ __global__ __launch_bounds__(RT_NT) void route_group_rank_kernel(const uint32_t 
     if (tid < RG_NB) gofs_out[tb * RG_NB + tid] = (tid < nb ? first[(int64_t)tid * ntiles + tb] : 0u) - dstart[tid];
 }
 
-// rows of three coordinates: tile of `in` (caller's order) -> runs of `out`.  A thread holds its 32 rows; the places of the
-// tile are filled a quarter at a time (96 KB of LDS), and a quarter leaves as runs of whole rows.
+// rows of three coordinates: tile of `in` (caller's order) -> runs of `out`.  A thread reads its 32 rows once; the places of the
+// tile are filled a quarter at a time (96 KB of LDS), and a quarter leaves as runs of whole rows.  The rows and their places are 112 numbers
+// a thread, and a workgroup of 1024 threads has 128 registers for each: 21 do not fit, go to scratch memory once and come back in every
+// quarter.  n = 1e9: 39 GB moved where rows and places are 26, 7.4 ms.
 __global__ __launch_bounds__(RT_NT) void route_group_rows3_kernel(const float *__restrict__ in, float *__restrict__ out,
                                                                   const uint16_t *__restrict__ slot,
                                                                   const uint32_t *__restrict__ dstart_tab,

@@ -52,3 +52,24 @@ def test_bound_covers_the_interpolation_error(bound, depth, ratio, reach):
 def test_where_the_bound_reaches_fp32_rounding(bound):
     assert bound(1.0, 3, 0.125 / 0.165, 1.0) <= 2.0 ** -24 < bound(1.0, 3, 0.125 / 0.167, 1.0)
     assert bound(1.0, 3, 0.125 / 0.128, 2.0) <= 2.0 ** -24 < bound(1.0, 3, 0.125 / 0.1295, 2.0)
+
+
+def test_error_at_the_limit_is_far_below_rounding():
+    """Where the bound has just reached 2^-24 the error itself (fp64): single pairs, and the sum over the 27 near boxes of
+    evenly spread points with weights of one sign, where errors of one sign would add up."""
+    c = (0.5 * 0.166) ** 2
+    t = np.linspace(-1.0, 1.0, 81)
+    L, e = basis(t), np.exp(-0.5 * c * t * t)
+    exact, inter = {}, {}
+    for o in (-1, 0, 1):
+        f = np.exp(c * (NODES[:, None] * NODES[None, :] + 2.0 * o * (NODES[:, None] - NODES[None, :] - o)))
+        exact[o] = np.exp(-0.5 * c * (t[:, None] - t[None, :] - 2.0 * o) ** 2)
+        inter[o] = e[:, None] * (L @ f @ L.T) * e[None, :]
+    rng = np.random.default_rng(6)
+    i, j = rng.integers(0, t.size, (2, 3, 100_000))
+    err = np.array([np.prod([inter[o[d]][i[d], j[d]] for d in range(3)], axis=0)
+                    - np.prod([exact[o[d]][i[d], j[d]] for d in range(3)], axis=0) for o in np.ndindex(3, 3, 3) for o in [np.array(o) - 1]])
+    assert np.abs(err).max() <= 2.0 ** -24 / 8 and np.sqrt((err ** 2).mean()) <= 2.0 ** -24 / 50
+    s, a = (sum(m[o].mean(axis=1) for o in m) for m in (exact, inter))
+    rel = np.einsum("i,j,k->ijk", a, a, a) / np.einsum("i,j,k->ijk", s, s, s) - 1.0
+    assert np.abs(rel).max() <= 2.0 ** -24 / 30
