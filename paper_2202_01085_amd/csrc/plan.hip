@@ -1459,8 +1459,8 @@ static void build_plan_d(f3m_plan_s &P, const float *X, const float *Y, hipStrea
         F3M_HIP(hipGetLastError());
     }
     F3M_HIP(hipEventRecord(P.ev[1], st));
-    // Points whose products end at a depth of few boxes are only grouped by them (below), for which the keys are needed in the
-    // caller's order.  The depth, if the tree gets that far: the smooth one, or that of the weighted near pairs.
+    // Points whose products end at a depth of at most ROUTE_GROUP_DEPTH are only grouped by its boxes (below), for which the keys are
+    // needed in the caller's order.  The depth, if the tree gets that far: the smooth one, or that of the weighted near pairs.
     bool may_group = false;
     if (D == 3 && !P.src && n >= P.route_min_n && P.rho == 0 && !P.force_all_near && P.E > 0.f)
         for (int l = 1; l <= ROUTE_GROUP_DEPTH && !may_group; ++l)

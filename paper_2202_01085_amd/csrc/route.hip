@@ -21,7 +21,7 @@
 // passes.  From there to 2^24 points a set goes the direct way (at 1.6e7 points three passes take 220 us off a product and add
 // 100 to 160 us to the plan).
 //
-// Where the products need the points by the boxes of a coarse depth only (at most 512 of them), ONE pass does: a tile of T
+// Where the products need the points by the boxes of a coarse depth only (at most 512 cells), ONE pass does: a tile of T
 // consecutive caller indices is dealt to the boxes, in which the points keep the caller's order (route_group_build).
 // n = 1e9, 512 boxes: tables 5.8 -> 3.1 ms (with the counts), points 18.7 -> 7.0, right-hand side in 6.2 -> 2.4, result out 6.6 -> 2.2.
 #include "plan.h"
