@@ -2111,15 +2111,15 @@ __global__ __launch_bounds__(64) void l2p34_kernel(const float *__restrict__ Xs,
 
 // P2M and L2P of boxes with thousands of points: a wavefront per run of up to P2M_LONG points of one box.  L2P above starts every
 // 256 points with the 64 potentials in LDS; here that is 2 % of the work.  P2M above has few registers to sum over the lanes, and
-// pays with every factor evaluated four times; with a lane per point and 64 sums in it the sum over the lanes is 2 % of the
-// work here, and the multiply-adds cost less than the products of both (1e9 points, two sets: 6.0 ms, on the matrix cores 6.6;
-// 1e8 points, one set: 0.37, 0.52).  The loads of four rounds are in flight.  WEIGHTED: both sets of node weights / node
+// pays with every factor evaluated four times; with a lane per point and 64 sums in it the sum over the lanes is a few percent of the
+// work here, and the multiply-adds cost less than the products of both (two sets of 1e9 points with fp32 sums over a run: 6.0 ms, on
+// the matrix cores 6.6; 1e8 points, one set: 0.37, 0.52).  The loads of four rounds are in flight.  WEIGHTED: both sets of node weights / node
 // potentials (the weighted near pairs) from one reading of the points.
 constexpr int TR_STRIDE = 36;  // floats per lane row in the LDS transpose of 32 accumulators (16-byte aligned, bank-shifted)
 constexpr int LONG_AHEAD = 4;
 // Points of a run whose node sums stay in fp32: 16 to a lane, then fp64.  With all 2048 points of a run in fp32, over the lanes too,
 // sums that cancel were off by three times as much as with runs of 256 points (4.8e-9 of the norm of the weights,
-// 1.5e-9; now 1.2e-9).  It costs nothing that shows: 1e9 points 61.7 and 62.1 ms, runs of one side differ by 2.3 %.
+// 1.5e-9; now 1.2e-9).  1e9 points, both sets of weights: 6.28 -> 6.64 ms; 1e8 points, one set, 0.37 as before.
 constexpr int LONG_FP32 = 1024;
 static_assert(LONG_FP32 % (64 * LONG_AHEAD) == 0, "whole rounds of loads");
 template <bool WEIGHTED>
